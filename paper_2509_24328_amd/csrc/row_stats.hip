@@ -85,27 +85,21 @@ __device__ __forceinline__ void sweep_online_pair(const void* ra, const void* rb
     acc_a.add1(WARP ? cut_below(za, cut_a) : za, La);
     acc_b.add1(WARP ? cut_below(zb, cut_b) : zb, Lb);
   };
-  if (aligned16(ra) && aligned16(rb)) {
-    const u32x4* pa = reinterpret_cast<const u32x4*>(ra);
-    const u32x4* pb = reinterpret_cast<const u32x4*>(rb);
-    const int nvec = V / EPV;
-    int i = tid;
-    for (; i + nt < nvec; i += 2 * nt) {
-      const u32x4 a0 = pa[i], b0 = pb[i], a1 = pa[i + nt], b1 = pb[i + nt];
-      add_vec(a0, acc_a, La, cut_a);
-      add_vec(b0, acc_b, Lb, cut_b);
-      add_vec(a1, acc_a, La, cut_a);
-      add_vec(b1, acc_b, Lb, cut_b);
-    }
-    for (; i < nvec; i += nt) {
-      const u32x4 a0 = pa[i], b0 = pb[i];
-      add_vec(a0, acc_a, La, cut_a);
-      add_vec(b0, acc_b, Lb, cut_b);
-    }
-    for (int v = nvec * EPV + tid; v < V; v += nt) add_one(v);
-  } else {
-    for (int v = tid; v < V; v += nt) add_one(v);
+  const int nvec = V / EPV;
+  int i = tid;
+  for (; i + nt < nvec; i += 2 * nt) {
+    const u32x4 a0 = load_vec(ra, i), b0 = load_vec(rb, i), a1 = load_vec(ra, i + nt), b1 = load_vec(rb, i + nt);
+    add_vec(a0, acc_a, La, cut_a);
+    add_vec(b0, acc_b, Lb, cut_b);
+    add_vec(a1, acc_a, La, cut_a);
+    add_vec(b1, acc_b, Lb, cut_b);
   }
+  for (; i < nvec; i += nt) {
+    const u32x4 a0 = load_vec(ra, i), b0 = load_vec(rb, i);
+    add_vec(a0, acc_a, La, cut_a);
+    add_vec(b0, acc_b, Lb, cut_b);
+  }
+  for (int v = nvec * EPV + tid; v < V; v += nt) add_one(v);
 }
 
 // Sweep-2 arithmetic for one vocabulary entry (see row_stats_kernel for the

@@ -262,14 +262,14 @@ struct Top4 {
 
 constexpr int kTagSteps = 1 << 16;   // vector steps per lane that fit the 16-bit tag
 
-// Sweep 1 for rows made of whole, aligned vectors: the online (max, sum-exp) of
-// sweep_online plus the lane's four largest vector maxima with their positions.
+// Sweep 1: the online (max, sum-exp) of sweep_online plus the lane's four largest vector
+// maxima with their positions.  The entries past the last whole vector only go into the sums:
+// they are looked at one by one when the list is built.
 template <int DT>
 __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online& acc, Top4& top, const float L) {
   constexpr int EPV = Elem<DT>::per_vec;
   const int tid = threadIdx.x;
   constexpr int nt = kWarpThreads;
-  const u32x4* p = reinterpret_cast<const u32x4*>(row);
   const int nvec = V / EPV;
   auto add_vec = [&](const u32x4& q, int i) {
     float f[EPV];
@@ -283,11 +283,12 @@ __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online
   };
   int i = tid;
   for (; i + 3 * nt < nvec; i += 4 * nt) {
-    const u32x4 q0 = __builtin_nontemporal_load(p + i), q1 = __builtin_nontemporal_load(p + i + nt),
-                q2 = __builtin_nontemporal_load(p + i + 2 * nt), q3 = __builtin_nontemporal_load(p + i + 3 * nt);
+    const u32x4 q0 = load_vec_nt(row, i), q1 = load_vec_nt(row, i + nt), q2 = load_vec_nt(row, i + 2 * nt),
+                q3 = load_vec_nt(row, i + 3 * nt);
     add_vec(q0, i); add_vec(q1, i + nt); add_vec(q2, i + 2 * nt); add_vec(q3, i + 3 * nt);
   }
-  for (; i < nvec; i += nt) add_vec(__builtin_nontemporal_load(p + i), i);
+  for (; i < nvec; i += nt) add_vec(load_vec_nt(row, i), i);
+  for (int v = nvec * EPV + tid; v < V; v += nt) acc.add1(load_elem<DT>(row, v), L);
 }
 
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
@@ -370,8 +371,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   Online acc[1];
   acc[0].init();
   Top4 top;
-  const bool tagged = aligned16(row) && V % Elem<DT>::per_vec == 0 &&
-                      V / Elem<DT>::per_vec <= kTagSteps * kWarpThreads;
+  const bool tagged = V / Elem<DT>::per_vec <= kTagSteps * kWarpThreads;
   if (tagged) sweep_online_top4<DT>(row, V, acc[0], top, lt);
   else sweep_online<DT, false, false>(row, V, 0, 1, acc[0], lt);
   MS merged[1];
@@ -627,7 +627,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   if (tid == 0) { sh.n_cand = 0; sh.near_tie = 0; sh.settled = 0; sh.n_keep = -1; sh.out_done = 0; }
   __syncthreads();
 
-  // ---- attempt 1 (tagged rows): only the lanes' largest vectors are read again.
+  // ---- attempt 1: only the lanes' largest vectors are read again.
   // A lane whose fourth-largest vector may reach tau may hide a fifth one that
   // does: such a lane (rare) walks all of its vectors again instead.
   if (tagged && V > kCand && (!use_k || top_k <= kWarpThreads)) {
@@ -656,19 +656,19 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     const uint32_t tau_key = sh.tau_key;
     if (tau > -INFINITY) {
       constexpr int EPV = Elem<DT>::per_vec;
-      const u32x4* p = reinterpret_cast<const u32x4*>(row);
-      auto list_vector = [&](uint32_t vec) {
-        float f[EPV];
-        unpack<DT>(p[vec], f);
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-          if (f[e] >= tau && f[e] > -INFINITY) {
-            const int at = atomicAdd(&sh.n_cand, 1);
-            if (at < kCand)
-              sh.key[at] = ((uint64_t)okey(f[e]) << 32) | (uint64_t)(0xFFFFFFFFu - (vec * EPV + (uint32_t)e));
-          }
+      auto list_entry = [&](float f, uint32_t v) {
+        if (f >= tau && f > -INFINITY) {
+          const int at = atomicAdd(&sh.n_cand, 1);
+          if (at < kCand) sh.key[at] = ((uint64_t)okey(f) << 32) | (uint64_t)(0xFFFFFFFFu - v);
         }
       };
+      auto list_vector = [&](uint32_t vec) {
+        float f[EPV];
+        unpack<DT>(load_vec(row, (int)vec), f);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) list_entry(f[e], vec * EPV + (uint32_t)e);
+      };
+      for (int v = V / EPV * EPV + tid; v < V; v += kWarpThreads) list_entry(load_elem<DT>(row, v), (uint32_t)v);
       if (top.k4 >= tau_key) {
         for (uint32_t vec = (uint32_t)tid; vec < (uint32_t)(V / EPV); vec += kWarpThreads) list_vector(vec);
       } else {
