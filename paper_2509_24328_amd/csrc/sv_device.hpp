@@ -169,24 +169,55 @@ struct MS {
 
 __device__ __forceinline__ float ref_of(float m, const float L = kL32) { return fmaxf(m * L, kRefFloor); }
 
-__device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __shfl_xor(lo, mask, kWave);
-  hi = __shfl_xor(hi, mask, kWave);
-  return __hiloint2double(hi, lo);
+// ---------------------------------------------------------------------------
+// Wavefront reductions and scans on the DPP lane network: a step is a register move inside the
+// vector ALU (rows of 16 lanes shifted by 1, 2, 4, 8, then lane 15 of a row and lane 31 handed to
+// the rows above), where a shuffle is a trip through the LDS crossbar.  All 64 lanes must be active.
+// ---------------------------------------------------------------------------
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_f64(double v) {      // v + (v of the lane that CTRL names, else 0)
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max_f32(float v) {
+  const int o = __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false);
+  return fmaxf(v, __int_as_float(o));
+}
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+// Inclusive prefix sum over the lanes.
+__device__ __forceinline__ double wave_scan_f64(double v) {
+  v = dpp_add_f64<kDppShr1, 0xf>(v);
+  v = dpp_add_f64<kDppShr2, 0xf>(v);
+  v = dpp_add_f64<kDppShr4, 0xf>(v);
+  v = dpp_add_f64<kDppShr8, 0xf>(v);
+  v = dpp_add_f64<kDppBcast15, 0xa>(v);
+  return dpp_add_f64<kDppBcast31, 0xc>(v);
+}
+
+// Value of one lane (a constant or wavefront-uniform index) in every lane.
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ float lane_f32(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
 __device__ __forceinline__ float wave_max_f32(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  return v;
+  v = dpp_max_f32<kDppShr1, 0xf>(v);
+  v = dpp_max_f32<kDppShr2, 0xf>(v);
+  v = dpp_max_f32<kDppShr4, 0xf>(v);
+  v = dpp_max_f32<kDppShr8, 0xf>(v);
+  v = dpp_max_f32<kDppBcast15, 0xa>(v);
+  v = dpp_max_f32<kDppBcast31, 0xc>(v);
+  return lane_f32(v, kWave - 1);
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += shfl_xor_f64(v, off);
-  return v;
-}
+__device__ __forceinline__ double wave_sum_f64(double v) { return lane_f64(wave_scan_f64(v), kWave - 1); }
 
 // Scratch for the workgroup reductions below (up to 16 waves).
 struct BlockScratch {

@@ -12,7 +12,8 @@ namespace sv {
 
 struct Plan;
 
-constexpr int kChunk = 8192;          // vocabulary entries per sampling chunk
+constexpr int kChunk = 8192;          // vocabulary entries per workgroup of the sampling stage's mass pass
+constexpr int kGranule = 4096;        // vocabulary entries per stored mass
 constexpr size_t kWsAlign = 256;
 constexpr int kMaxSplit = 8;          // a row may be swept by up to 8 workgroups
 // SV_FLAG_NEAR_CDF_EDGE: the sampling threshold lies within kCdfEdgeRel * W + kCdfEdgeAbs of an
@@ -30,7 +31,8 @@ inline int elem_bytes(int dtype) { return dtype == SV_F32 ? 4 : (dtype == SV_BF1
 
 inline bool is_aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-inline int n_chunks(int V) { return (V + kChunk - 1) / kChunk; }
+__host__ __device__ inline int n_chunks(int V) { return (V + kChunk - 1) / kChunk; }
+__host__ __device__ inline int n_granules(int V) { return (V + kGranule - 1) / kGranule; }
 
 // What sv_row_stats leaves in the workspace for sv_verify_sample_chained: which
 // call wrote the draft normalisers that follow it.
@@ -50,8 +52,7 @@ struct VerifyWs {
   float* m_d;         // [B*k*kMaxSplit]
   float* zx_t;        // [B*k] target logit of the drafted token
   float* zx_d;        // [B*k] draft logit of the drafted token
-  double* mass_r;     // [B*C] residual mass of each chunk of the sampling row
-  double* mass_t;     // [B*C] target mass of each chunk of the sampling row
+  double* mass;       // [B*n_granules] mass of each granule of the sampling row (residual or target)
   Plan* plan;          // [B] per-sequence sampling plan (verify_sample.hip)
   // written by sv_row_stats, read by sv_verify_sample_chained
   ChainHeader* chain;  // [1]
@@ -67,7 +68,7 @@ inline VerifyWs carve_verify_ws(void* base, int B, int k, int V) {
   VerifyWs w;
   char* p = static_cast<char*>(base);
   size_t off = 0;
-  const size_t rt = (size_t)B * (k + 1), rd = (size_t)B * k, bc = (size_t)B * n_chunks(V);
+  const size_t rt = (size_t)B * (k + 1), rd = (size_t)B * k, bg = (size_t)B * n_granules(V);
   auto take = [&](size_t bytes) { char* q = p ? p + off : nullptr; off += ws_round(bytes); return q; };
   w.s_t = reinterpret_cast<double*>(take(rt * kMaxSplit * 8));
   w.s_d = reinterpret_cast<double*>(take(rd * kMaxSplit * 8));
@@ -75,8 +76,7 @@ inline VerifyWs carve_verify_ws(void* base, int B, int k, int V) {
   w.m_d = reinterpret_cast<float*>(take(rd * kMaxSplit * 4));
   w.zx_t = reinterpret_cast<float*>(take(rd * 4));
   w.zx_d = reinterpret_cast<float*>(take(rd * 4));
-  w.mass_r = reinterpret_cast<double*>(take(bc * 8));
-  w.mass_t = reinterpret_cast<double*>(take(bc * 8));
+  w.mass = reinterpret_cast<double*>(take(bg * 8));
   w.plan = reinterpret_cast<Plan*>(take((size_t)B * 32));
   w.chain = reinterpret_cast<ChainHeader*>(take(sizeof(ChainHeader)));
   w.chain_s = reinterpret_cast<double*>(take(rd * 8));

@@ -18,12 +18,14 @@
 //     sequence does this for itself (a few hundred bytes and two fp64
 //     logarithms: less than a kernel boundary costs); the one of chunk 0 writes
 //     the accepted tokens and the plan of the sampling stage.  Then the
-//     workgroup sums its 8192-entry chunk of the sampling row: residual
-//     max(0, P_t - P_d) and P_t.  Touches B rows (pairs).
+//     workgroup sums its 8192-entry chunk of the sampling row in granules of
+//     4096: residual max(0, P_t - P_d) after a rejection, P_t otherwise.
+//     Touches B rows (pairs).
 //
-//  3. verify_pick_kernel   one workgroup per sequence: scans the chunk masses in
-//     order (fp64), locates the chunk holding u' * W, stages that chunk's
-//     weights in LDS and finds the token with a block prefix scan.
+//  3. verify_pick_kernel   one workgroup per sequence: scans the granule masses
+//     in order (fp64), locates the granule holding u' * W, weighs its 4096
+//     entries again, 16 consecutive ones per lane in registers, and finds the
+//     token with a prefix scan.
 //
 // Kernel boundaries carry the cross-workgroup hand-offs (row scalars, plan,
 // chunk masses): device-scope fences inside a kernel were measured to cost far
@@ -44,7 +46,7 @@ namespace sv {
 
 constexpr int kRowsThreads = 256;
 constexpr int kSampleThreads = 256;             // mass kernel: one workgroup per chunk
-constexpr int kPickThreads = 1024;              // pick kernel: one workgroup per sequence
+constexpr int kPickThreads = 256;               // pick kernel: one workgroup per sequence
 constexpr int kMaxChunks = 2048;                // V <= kMaxChunks * kChunk
 static_assert(kMaxSplit == kMaxParts, "fold_row_parts reads up to kMaxParts partials of a row");
 
@@ -232,12 +234,15 @@ struct ProbRow {
     k_lo = (float)(kappa - (double)k_hi);
   }
   __device__ __forceinline__ float p(float z) const {
-    const float head = __builtin_fmaf(z, L, -k_hi);
-    const float tail = __builtin_fmaf(z, l_lo, -k_lo);
+    // (an entry at -inf has no mass whatever finite number far below the row stands for it; the
+    //  differences below stay finite at -1e30 over all temperatures)
+    const float zf = fmaxf(z, -1e30f);
+    const float head = __builtin_fmaf(zf, L, -k_hi);
+    const float tail = __builtin_fmaf(zf, l_lo, -k_lo);
     const float a = head + tail;
     const float r = (head - a) + tail;
     const float e = exp2_fast(a);
-    return e > 0.f ? __builtin_fmaf(e, (float)kLn2 * r, e) : 0.f;   // z = -inf: a is -inf or NaN, mass is 0
+    return __builtin_fmaf(e, (float)kLn2 * r, e);
   }
 };
 
@@ -380,244 +385,266 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   }
 }
 
-// Residual and target mass of chunk c of the sampling row of sequence b, by the whole
-// workgroup (results in every thread).  fp64 sums of the fp32 weights: the pick stage forms
-// the same weights again and adds them in another order, and the two must agree far inside
-// the band of SV_FLAG_NEAR_CDF_EDGE.
+// What the sampling stage weighs: the row (pair) of position n.
 template <int DT, bool CUT>
-__device__ __forceinline__ void chunk_masses(const VerifyArgs& a, int b, const Plan& pl, int c, BlockScratch& red,
-                                             double* mass_r, double* mass_t) {
-  const int n = pl.n;
-  const bool target_ok = pl.target_ok != 0, resid = pl.resid != 0;
-  const void* row_t = target_row<DT>(a, b, n);
-  const void* row_d = resid ? draft_row<DT>(a, b, n) : nullptr;
+struct SampleRow {
+  const void* row_t;
+  const void* row_d;         // used if resid
   ProbRow pt, pd;
-  pt.set(target_ok ? pl.lse_t : 0.0, a.sc_t);
-  pd.set(pl.lse_d, a.sc_d);
-  float cut_t = -INFINITY, cut_d = -INFINITY;
-  if (CUT) { cut_t = target_cut(a, b, n); if (resid) cut_d = draft_cut(a, b, n); }
-  const int v0 = c * kChunk, v1 = min(a.V, v0 + kChunk);
-  double acc_r = 0.0, acc_t = 0.0;
-  if (target_ok) {
-    if (resid) {
-      visit_range<DT, true, 4>(row_t, row_d, v0, v1, [&](int, float zt, float zd) {
-        if (CUT) { zt = cut_below(zt, cut_t); zd = cut_below(zd, cut_d); }
-        const float p = pt.p(zt);
-        acc_t += (double)p;
-        acc_r += (double)fmaxf(0.f, p - pd.p(zd));
-      });
-    } else {
-      visit_range<DT, false, 4>(row_t, nullptr, v0, v1, [&](int, float zt, float) {
-        if (CUT) zt = cut_below(zt, cut_t);
-        acc_t += (double)pt.p(zt);
-      });
-    }
+  float cut_t, cut_d;
+  bool resid;                // weight max(0, P_t - P_d), else P_t
+  __device__ __forceinline__ SampleRow(const VerifyArgs& a, int b, const Plan& pl) {
+    resid = pl.resid != 0;
+    row_t = target_row<DT>(a, b, pl.n);
+    row_d = resid ? draft_row<DT>(a, b, pl.n) : row_t;
+    pt.set(pl.lse_t, a.sc_t);
+    pd.set(pl.lse_d, a.sc_d);
+    cut_t = cut_d = -INFINITY;
+    if (CUT) { cut_t = target_cut(a, b, pl.n); if (resid) cut_d = draft_cut(a, b, pl.n); }
   }
-  *mass_r = block_sum_f64(acc_r, red);
-  *mass_t = block_sum_f64(acc_t, red);
-}
-
-struct MassShared {
-  BlockScratch red;
-  Plan plan;
+  __device__ __forceinline__ float weight_t(float zt) const { return pt.p(CUT ? cut_below(zt, cut_t) : zt); }
+  __device__ __forceinline__ float weight_r(float zt, float zd) const {
+    return fmaxf(0.f, weight_t(zt) - pd.p(CUT ? cut_below(zd, cut_d) : zd));
+  }
 };
 
+// fp64 sum of the fp32 weights of entries [v0, v1) handled by this lane, the lane being number
+// `lane` of `lanes` (v0 a multiple of the vector length).  The pick stage forms the same weights
+// again and adds them in another order; the two agree far inside the band of
+// SV_FLAG_NEAR_CDF_EDGE because the additions are fp64.
+template <int DT, bool RESID, bool CUT>
+__device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0, int v1, int lane, int lanes) {
+  constexpr int EPV = Elem<DT>::per_vec;
+  constexpr int U = 4;                                       // vector (pairs) in flight per lane
+  double acc = 0.0;
+  auto add_vec = [&](const u32x4& qt, const u32x4& qd) {
+    float ft[EPV], fd[EPV];
+    unpack<DT>(qt, ft);
+    if (RESID) unpack<DT>(qd, fd);
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) acc += (double)(RESID ? sr.weight_r(ft[j], fd[j]) : sr.weight_t(ft[j]));
+  };
+  const int i1 = v1 / EPV;
+  for (int i = v0 / EPV + lane; i < i1; i += U * lanes) {
+    u32x4 qt[U], qd[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i + u * lanes < i1) {
+        qt[u] = load_vec(sr.row_t, i + u * lanes);
+        if (RESID) qd[u] = load_vec(sr.row_d, i + u * lanes);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * lanes < i1) add_vec(qt[u], qd[u]);
+  }
+  for (int v = max(v0, i1 * EPV) + lane; v < v1; v += lanes) {
+    const float zt = load_elem<DT>(sr.row_t, v);
+    acc += (double)(RESID ? sr.weight_r(zt, load_elem<DT>(sr.row_d, v)) : sr.weight_t(zt));
+  }
+  return acc;
+}
+
 // grid (chunks, B): the accept decision of the sequence (every workgroup forms it for
-// itself, chunk 0 publishes it), then the residual and target mass of one chunk of the
-// sampling row.
+// itself, chunk 0 publishes it), then the masses of the two granules of one chunk of the
+// sampling row, two wavefronts per granule.  Bound by the latency chain partials ->
+// decision -> row -> sum on small batches and by the weights' arithmetic on large ones
+// (two exponentials and about twenty further operations per entry pair).
 template <int DT, bool CUT, bool CHAIN>
 __global__ __launch_bounds__(kSampleThreads, 8) void verify_mass_kernel(VerifyArgs a) {
-  __shared__ MassShared sh;
-  const int b = blockIdx.y, c = blockIdx.x, C = gridDim.x;
+  __shared__ Plan plan;
+  __shared__ double part[kSampleThreads / kWave];
+  constexpr int kLanes = kSampleThreads * kGranule / kChunk;           // lanes per granule
+  const int b = blockIdx.y, c = blockIdx.x;
   const int tid = threadIdx.x;
   SV_PHASE_MARK(6)
-  if (tid < kWave) accept_plan<DT, CHAIN>(a, b, tid, c == 0, &sh.plan);
+  if (tid < kWave) accept_plan<DT, CHAIN>(a, b, tid, c == 0, &plan);
   __syncthreads();
   SV_PHASE_MARK(7)
-  const Plan pl = sh.plan;
-  double mass_r, mass_t;
-  chunk_masses<DT, CUT>(a, b, pl, c, sh.red, &mass_r, &mass_t);
+  const Plan pl = plan;
+  const int g = tid / kLanes, lane = tid - g * kLanes;
+  const int v0 = c * kChunk + g * kGranule, v1 = min(a.V, v0 + kGranule);
+  double acc = 0.0;
+  if (pl.target_ok && v0 < v1) {
+    const SampleRow<DT, CUT> sr(a, b, pl);
+    acc = sr.resid ? lane_mass<DT, true, CUT>(sr, v0, v1, lane, kLanes) : lane_mass<DT, false, CUT>(sr, v0, v1, lane, kLanes);
+  }
+  acc = wave_sum_f64(acc);
+  if ((tid & (kWave - 1)) == 0) part[tid / kWave] = acc;
+  __syncthreads();
   SV_PHASE_MARK(8)
-  if (tid == 0) {
-    a.ws.mass_r[b * C + c] = mass_r;
-    a.ws.mass_t[b * C + c] = mass_t;
+  constexpr int kWaves = kLanes / kWave;                               // wavefronts per granule
+  if (lane == 0 && v0 < v1) {
+    double m = part[g * kWaves];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) m += part[g * kWaves + w];
+    a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m;
   }
   SV_PHASE_MARK(9)
 }
 
-template <int THREADS>
-struct PickShared {
-  static constexpr int kSegT = kChunk / THREADS;      // contiguous weights per thread in the final scan
-  BlockScratch red;
-  union {
-    float w[kChunk + kChunk / kSegT];  // weights of the located chunk (skewed)
-    double mass[2 * kMaxChunks];     // before that: residual / target mass of every chunk
-  };
-  uint32_t flags;
-  int chunk;
-  int use_resid;
-  int found_thread;
-  double tau_local;
-  double W;
-};
-
-// The token of sequence b from the chunk masses in sh.mass ([0, C) residual, [C, 2C) target;
-// filled and visible to the whole workgroup of THREADS lanes): locate the chunk holding
-// u' * W, stage its weights in LDS and find the token with a block prefix scan.
-template <int DT, bool CUT, int THREADS>
-__device__ __forceinline__ void pick_token(const VerifyArgs& a, const int b, const Plan& pl, PickShared<THREADS>& sh,
-                                           const int C) {
-  constexpr int kSegT = PickShared<THREADS>::kSegT;
-  static_assert(sizeof(double) * 2 * kMaxChunks <= sizeof(float) * (kChunk + kChunk / kSegT), "mass fits under w");
-  auto skew = [](int p) { return p + p / kSegT; };     // one padding word per segment: segment walks hit different banks
-  const int tid = threadIdx.x;
-  const int k = a.k, V = a.V;
-  const int n = pl.n;
-  const bool target_ok = pl.target_ok != 0;
-  const bool resid = pl.resid != 0;
-  const void* row_t = target_row<DT>(a, b, n);
-  const void* row_d = resid ? draft_row<DT>(a, b, n) : nullptr;
-  ProbRow pt, pd;
-  pt.set(target_ok ? pl.lse_t : 0.0, a.sc_t);
-  pd.set(resid ? pl.lse_d : 0.0, a.sc_d);
-  float cut_t = -INFINITY, cut_d = -INFINITY;
-  if (CUT) { cut_t = target_cut(a, b, n); if (resid) cut_d = draft_cut(a, b, n); }
-  if (tid == 0) {
-    uint32_t flags = pl.flags;
-    const double* mr = sh.mass;
-    const double* mt = sh.mass + C;
-    double Wr = 0.0, Wt = 0.0;
-    for (int j = 0; j < C; ++j) { Wr += mr[j]; Wt += mt[j]; }
-    int use_resid = resid;
-    // a residual of any mass is drawn from; only one without mass (or a non-finite one) is not
-    if (target_ok && resid && !(isfinite(Wr) && Wr > 0.0)) { use_resid = 0; flags |= SV_FLAG_RESIDUAL_FALLBACK; }
-    const double W = use_resid ? Wr : Wt;
-    int chunk = -1;
-    double tau_local = 0.0;
-    if (target_ok && isfinite(W) && W > 0.0) {
-      const U4 r = philox4x32_10((uint32_t)n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
-      const double tau = unit_from_word(r.w[1]) * W;
-      const double* ms = use_resid ? mr : mt;
-      double excl = 0.0;
-      int last_pos = -1;
-      double last_excl = 0.0;
-      for (int j = 0; j < C; ++j) {
-        const double mj = ms[j];
-        if (mj > 0.0) { last_pos = j; last_excl = excl; }
-        if (excl + mj > tau) { chunk = j; tau_local = tau - excl; break; }
-        excl += mj;
+// grid (B): the granule of the sampling row that holds u' * W from the granule masses, then
+// the token.  A chain of three trips to memory (plan and masses, the granule's logits, the
+// result) with one barrier; nothing is staged in LDS.  4.2 us for one sequence of 32000 fp32
+// entries, 6.0 us for 64 of 152064 bf16, 6.8 us for 512 of 32000 (8.1, 11.3 and 18.7 us with
+// 1024 lanes that staged 8192 weights in LDS and scanned the masses serially).
+template <int DT, bool CUT>
+__global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a) {
+  constexpr int EPV = Elem<DT>::per_vec;
+  constexpr int kRun = kGranule / kPickThreads;                        // consecutive entries per lane
+  constexpr int kWaves = kPickThreads / kWave;
+  __shared__ double wave_tot[kWaves];
+  __shared__ int last_positive;
+  SV_PHASE_MARK(0)
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int G = n_granules(a.V);
+  const double* mass = a.ws.mass + (size_t)b * G;
+  // every wavefront scans all granule masses: lane l owns the run [l * q, (l + 1) * q)
+  const int q = (G + kWave - 1) / kWave;
+  const int g0 = min(lane * q, G), g1 = min(g0 + q, G);
+  double run = 0.0;
+  for (int j = g0; j < g1; ++j) run += mass[j];
+  const Plan pl = a.ws.plan[b];
+  if (tid == 0) last_positive = -1;
+  SampleRow<DT, CUT> sr(a, b, pl);
+  int32_t* out = a.out_tokens + (size_t)b * (a.k + 1);
+  uint32_t flags = pl.flags;
+  const U4 rnd = philox4x32_10((uint32_t)pl.n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
+  const double u = unit_from_word(rnd.w[1]);
+  double incl = wave_scan_f64(run);
+  double W = lane_f64(incl, kWave - 1);
+  int gran = -1;
+  double tau_local = 0.0;                                              // threshold inside the granule
+  if (pl.target_ok && sr.resid && !(isfinite(W) && W > 0.0)) {
+    // A residual of any mass is drawn from; only one without mass (or a non-finite one) is not: the
+    // target distribution instead, whose masses nobody has formed (rare: equal rows whose
+    // drafted token has no mass in either).
+    sr.resid = false;
+    flags |= SV_FLAG_RESIDUAL_FALLBACK;
+    auto granule_mass = [&](int g) {
+      __syncthreads();
+      const double w = wave_sum_f64(lane_mass<DT, false, CUT>(sr, g * kGranule, min(a.V, (g + 1) * kGranule), tid, kPickThreads));
+      if (lane == 0) wave_tot[wave] = w;
+      __syncthreads();
+      double m = wave_tot[0];
+      for (int i = 1; i < kWaves; ++i) m += wave_tot[i];
+      return m;
+    };
+    W = 0.0;
+    for (int g = 0; g < G; ++g) W += granule_mass(g);
+    if (isfinite(W) && W > 0.0) {
+      double before = 0.0;
+      for (int g = 0; g < G; ++g) {
+        const double m = granule_mass(g);
+        if (m > 0.0) { gran = g; tau_local = u * W - before; }         // (rounding: the last granule with mass)
+        if (before + m > u * W) break;
+        before += m;
       }
-      if (chunk < 0) { chunk = last_pos; tau_local = tau - last_excl; }   // rounding: last chunk with mass
-    } else {
-      flags |= SV_FLAG_BAD_ROW;
     }
-    sh.chunk = chunk;
-    sh.tau_local = tau_local;
-    sh.use_resid = use_resid;
-    sh.W = W;
-    sh.flags = flags;
-    sh.found_thread = THREADS;
+    __syncthreads();
+  } else if (pl.target_ok && isfinite(W) && W > 0.0) {
+    const double tau = u * W;
+    const unsigned long long at = __ballot(incl > tau && run > 0.0), has = __ballot(run > 0.0);
+    const int owner = at ? (int)__builtin_ctzll(at) : 63 - (int)__builtin_clzll(has);
+    double before = lane_f64(incl - run, owner);
+    const int h0 = min(owner * q, G), h1 = min(h0 + q, G);
+    for (int g = h0; g < h1; ++g) {
+      const double m = mass[g];
+      if (m > 0.0) { gran = g; tau_local = tau - before; }             // (rounding: the last granule with mass)
+      if (before + m > tau) break;
+      before += m;
+    }
   }
-  __syncthreads();
-  SV_PHASE_MARK(2)
-  const int chunk = sh.chunk;
-  const int use_resid = sh.use_resid;
-  int32_t* out = a.out_tokens + (size_t)b * (k + 1);
-  if (chunk < 0) {                                     // nothing can be drawn
-    if (tid == 0) a.flags[b] = sh.flags;
+  if (gran < 0) {                                                      // nothing can be drawn
+    if (tid == 0) a.flags[b] = flags | SV_FLAG_BAD_ROW;
     return;
   }
-  __syncthreads();                                     // masses are dead: w may overwrite them
+  SV_PHASE_MARK(2)
 
-  // stage the chunk's weights in LDS in vocabulary order
-  const int w0 = chunk * kChunk, w1 = min(V, w0 + kChunk);
-  for (int j = (w1 - w0) + tid; j < kChunk; j += THREADS) sh.w[skew(j)] = 0.f;
-  if (use_resid) {
-    visit_range<DT, true, 4>(row_t, row_d, w0, w1, [&](int v, float zt, float zd) {
-      if (CUT) { zt = cut_below(zt, cut_t); zd = cut_below(zd, cut_d); }
-      sh.w[skew(v - w0)] = fmaxf(0.f, pt.p(zt) - pd.p(zd));
-    });
-  } else {
-    visit_range<DT, false, 4>(row_t, nullptr, w0, w1, [&](int v, float zt, float) {
-      if (CUT) zt = cut_below(zt, cut_t);
-      sh.w[skew(v - w0)] = pt.p(zt);
-    });
-  }
-  __syncthreads();
-  SV_PHASE_MARK(3)
-
-  // block prefix scan over contiguous per-thread segments (fp64)
-  static_assert(kSegT * THREADS == kChunk && (kSegT & (kSegT - 1)) == 0, "one segment per thread");
-  const float* wseg = sh.w + tid * (kSegT + 1);         // this thread's segment, skewed
-  double seg_sum = 0.0;
-#pragma unroll 8
-  for (int j = 0; j < kSegT; ++j) seg_sum += (double)wseg[j];
-  // inclusive scan inside the wavefront, then across wavefronts through LDS
-  double incl = seg_sum;
-  const int lane = tid & 63, wave = tid >> 6;
+  // the weights of this lane's 16 consecutive entries, and their sum in order
+  const int v0 = gran * kGranule + tid * kRun;
+  float w[kRun];
+  double mine = 0.0;
+  const int nvec = a.V / EPV;
+  if (v0 / EPV + kRun / EPV <= nvec) {
+    u32x4 qt[kRun / EPV], qd[kRun / EPV];
 #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    int lo = __double2loint(incl), hi = __double2hiint(incl);
-    lo = __shfl_up(lo, off, kWave);
-    hi = __shfl_up(hi, off, kWave);
-    const double o = __hiloint2double(hi, lo);
-    if (lane >= off) incl += o;
-  }
-  if (lane == 63) sh.red.d[wave] = incl;
-  __syncthreads();
-  double wave_base = 0.0;
-  for (int w = 0; w < wave; ++w) wave_base += sh.red.d[w];
-  incl += wave_base;
-  const double excl = incl - seg_sum;
-  const double tau_local = sh.tau_local;
-  // first thread whose inclusive sum passes the threshold; none when rounding
-  // between the two passes put the threshold at or beyond the chunk total
-  if (incl > tau_local) atomicMin(&sh.found_thread, tid);
-  __syncthreads();
-  SV_PHASE_MARK(4)
-  int owner = sh.found_thread;
-  const bool beyond = owner >= THREADS;
-  if (beyond) owner = THREADS - 1;
-  if (tid != owner) return;
-
-  const double W = sh.W;
-  double run = excl, prev = excl;
-  int y = -1;
-  if (!beyond) {
-    for (int j = 0; j < kSegT; ++j) {
-      prev = run;
-      run += (double)wseg[j];
-      if (run > tau_local) { y = tid * kSegT + j; break; }
+    for (int i = 0; i < kRun / EPV; ++i) {
+      qt[i] = load_vec(sr.row_t, v0 / EPV + i);
+      qd[i] = sr.resid ? load_vec(sr.row_d, v0 / EPV + i) : qt[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kRun / EPV; ++i) {
+      float ft[EPV], fd[EPV];
+      unpack<DT>(qt[i], ft);
+      unpack<DT>(qd[i], fd);
+#pragma unroll
+      for (int j = 0; j < EPV; ++j) w[i * EPV + j] = sr.resid ? sr.weight_r(ft[j], fd[j]) : sr.weight_t(ft[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+      w[j] = 0.f;
+      if (v0 + j < a.V) {
+        const float zt = load_elem<DT>(sr.row_t, v0 + j);
+        w[j] = sr.resid ? sr.weight_r(zt, load_elem<DT>(sr.row_d, v0 + j)) : sr.weight_t(zt);
+      }
     }
   }
-  uint32_t fl = sh.flags;
-  if (y >= 0) {
-    if (fmin(run - tau_local, tau_local - prev) < kCdfEdgeRel * W + kCdfEdgeAbs) fl |= SV_FLAG_NEAR_CDF_EDGE;
-  } else {
-    // rounding left no entry whose running sum passes the threshold: take the
-    // last positive-weight entry at or before the end of this segment
-    fl |= SV_FLAG_NEAR_CDF_EDGE;
-    for (int p = (tid + 1) * kSegT - 1; p >= 0; --p)
-      if (sh.w[skew(p)] > 0.f) { y = p; break; }
-  }
-  if (y >= 0) out[n] = w0 + y; else fl |= SV_FLAG_BAD_ROW;   // y < 0: the chunk holds no mass at all
-  a.flags[b] = fl;
-}
-
-// grid (B): the chunk masses of the sequence from the workspace, then the token.
-template <int DT, bool CUT>
-__global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a, int C) {
-  __shared__ PickShared<kPickThreads> sh;
-  SV_PHASE_MARK(0)
-  const int b = blockIdx.x;
-  const Plan pl = a.ws.plan[b];
-  for (int j = threadIdx.x; j < C; j += kPickThreads) {          // all chunk masses in one round of loads
-    sh.mass[j] = a.ws.mass_r[(size_t)b * C + j];
-    sh.mass[C + j] = a.ws.mass_t[(size_t)b * C + j];
-  }
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) mine += (double)w[j];
+  SV_PHASE_MARK(3)
+  incl = wave_scan_f64(mine);
+  if (lane == kWave - 1) wave_tot[wave] = incl;
   __syncthreads();
-  SV_PHASE_MARK(1)
-  pick_token<DT, CUT, kPickThreads>(a, b, pl, sh, C);
+  // the first lane whose inclusive sum passes the threshold owns the token
+  double base = 0.0, upto = 0.0;
+  bool earlier = false, any = false;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    if (i == wave) base = upto;
+    upto += wave_tot[i];
+    if (upto > tau_local) { any = true; if (i < wave) earlier = true; }
+  }
+  SV_PHASE_MARK(4)
+  const double excl = base + incl - mine;
+  if (any) {
+    const unsigned long long pass = __ballot(base + incl > tau_local);
+    if (earlier || !pass || lane != (int)__builtin_ctzll(pass)) return;
+    double prev = excl, acc = excl, next = excl;
+    int y = -1;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+      acc += (double)w[j];
+      if (y < 0 && acc > tau_local) { y = v0 + j; next = acc; }
+      if (y < 0) prev = acc;
+    }
+    if (y >= 0) {
+      if (fmin(next - tau_local, tau_local - prev) < kCdfEdgeRel * W + kCdfEdgeAbs) flags |= SV_FLAG_NEAR_CDF_EDGE;
+    } else {
+      // rounding between the lane's own sum and its place in the scan: its last entry with weight
+      flags |= SV_FLAG_NEAR_CDF_EDGE;
+#pragma unroll
+      for (int j = 0; j < kRun; ++j)
+        if (w[j] > 0.f) y = v0 + j;
+    }
+    if (y >= 0) out[pl.n] = y; else flags |= SV_FLAG_BAD_ROW;
+    a.flags[b] = flags;
+    return;
+  }
+  // rounding between the mass pass and this one put the threshold at or beyond the granule's
+  // total: its last entry with weight
+  int y = -1;
+#pragma unroll
+  for (int j = 0; j < kRun; ++j)
+    if (w[j] > 0.f) y = v0 + j;
+  if (y >= 0) atomicMax(&last_positive, y);
+  __syncthreads();
+  if (tid == 0) {
+    flags |= SV_FLAG_NEAR_CDF_EDGE;
+    if (last_positive >= 0) out[pl.n] = last_positive; else flags |= SV_FLAG_BAD_ROW;
+    a.flags[b] = flags;
+  }
   SV_PHASE_MARK(5)
 }
 
@@ -648,7 +675,7 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;
   {
     TapScope tap(SV_KERNEL_VERIFY_PICK, st);
-    hipLaunchKernelGGL((verify_pick_kernel<DT, CUT>), dim3(a.B), dim3(kPickThreads), 0, st, a, C);
+    hipLaunchKernelGGL((verify_pick_kernel<DT, CUT>), dim3(a.B), dim3(kPickThreads), 0, st, a);
   }
   return launch_status();
 }
