@@ -412,14 +412,22 @@ struct SampleRow {
 // `lane` of `lanes` (v0 a multiple of the vector length).  The pick stage forms the same weights
 // again and adds them in another order; the two agree far inside the band of
 // SV_FLAG_NEAR_CDF_EDGE because the additions are fp64.
-template <int DT, bool RESID, bool CUT>
+// U: vector (pairs) in flight per lane.
+template <int DT, bool RESID, bool CUT, int U = 4>
 __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0, int v1, int lane, int lanes) {
   constexpr int EPV = Elem<DT>::per_vec;
-  constexpr int U = 4;                                       // vector (pairs) in flight per lane
   double acc = 0.0;
   auto add_vec = [&](const u32x4& qt, const u32x4& qd) {
     float ft[EPV], fd[EPV];
     unpack<DT>(qt, ft);
+    if (CUT) {
+      // outside the target's support there is no weight of either kind: most vectors of a
+      // warped row have none of it
+      float top = ft[0];
+#pragma unroll
+      for (int j = 1; j < EPV; ++j) top = fmaxf(top, ft[j]);
+      if (top < sr.cut_t) return;
+    }
     if (RESID) unpack<DT>(qd, fd);
 #pragma unroll
     for (int j = 0; j < EPV; ++j) acc += (double)(RESID ? sr.weight_r(ft[j], fd[j]) : sr.weight_t(ft[j]));
@@ -498,12 +506,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   SV_PHASE_MARK(0)
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int G = n_granules(a.V);
-  const double* mass = a.ws.mass + (size_t)b * G;
-  // every wavefront scans all granule masses: lane l owns the run [l * q, (l + 1) * q)
-  const int q = (G + kWave - 1) / kWave;
-  const int g0 = min(lane * q, G), g1 = min(g0 + q, G);
-  double run = 0.0;
-  for (int j = g0; j < g1; ++j) run += mass[j];
+  double* mass = a.ws.mass + (size_t)b * G;
   const Plan pl = a.ws.plan[b];
   if (tid == 0) last_positive = -1;
   SampleRow<DT, CUT> sr(a, b, pl);
@@ -511,38 +514,38 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   uint32_t flags = pl.flags;
   const U4 rnd = philox4x32_10((uint32_t)pl.n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
   const double u = unit_from_word(rnd.w[1]);
-  double incl = wave_scan_f64(run);
-  double W = lane_f64(incl, kWave - 1);
-  int gran = -1;
-  double tau_local = 0.0;                                              // threshold inside the granule
+  // every wavefront scans all granule masses: lane l owns the run [l * q, (l + 1) * q)
+  const int q = (G + kWave - 1) / kWave;
+  const int g0 = min(lane * q, G), g1 = min(g0 + q, G);
+  double run = 0.0, incl = 0.0, W = 0.0;
+  auto scan_masses = [&]() {
+    run = 0.0;
+    for (int j = g0; j < g1; ++j) run += mass[j];
+    incl = wave_scan_f64(run);
+    W = lane_f64(incl, kWave - 1);
+  };
+  scan_masses();
   if (pl.target_ok && sr.resid && !(isfinite(W) && W > 0.0)) {
     // A residual of any mass is drawn from; only one without mass (or a non-finite one) is not: the
-    // target distribution instead, whose masses nobody has formed (rare: equal rows whose
-    // drafted token has no mass in either).
+    // target distribution instead, whose masses nobody has formed yet.  Rows that are equal
+    // and whose drafted token has no mass in either, such as two nuclei of the same single token: a
+    // few percent of warped batches, so the granules are spread over the wavefronts and take the
+    // residual's places in the workspace (V = 128256 bf16, nucleus cutoffs: 17.5 us, 48 us with the
+    // workgroup walking them one after another, twice).
     sr.resid = false;
     flags |= SV_FLAG_RESIDUAL_FALLBACK;
-    auto granule_mass = [&](int g) {
-      __syncthreads();
-      const double w = wave_sum_f64(lane_mass<DT, false, CUT>(sr, g * kGranule, min(a.V, (g + 1) * kGranule), tid, kPickThreads));
-      if (lane == 0) wave_tot[wave] = w;
-      __syncthreads();
-      double m = wave_tot[0];
-      for (int i = 1; i < kWaves; ++i) m += wave_tot[i];
-      return m;
-    };
-    W = 0.0;
-    for (int g = 0; g < G; ++g) W += granule_mass(g);
-    if (isfinite(W) && W > 0.0) {
-      double before = 0.0;
-      for (int g = 0; g < G; ++g) {
-        const double m = granule_mass(g);
-        if (m > 0.0) { gran = g; tau_local = u * W - before; }         // (rounding: the last granule with mass)
-        if (before + m > u * W) break;
-        before += m;
-      }
+    __syncthreads();                                                   // all have read the residual's masses
+    for (int g = wave; g < G; g += kWaves) {
+      const double m = wave_sum_f64(
+          lane_mass<DT, false, CUT, 8>(sr, g * kGranule, min(a.V, (g + 1) * kGranule), lane, kWave));
+      if (lane == 0) mass[g] = m;
     }
     __syncthreads();
-  } else if (pl.target_ok && isfinite(W) && W > 0.0) {
+    scan_masses();
+  }
+  int gran = -1;
+  double tau_local = 0.0;                                              // threshold inside the granule
+  if (pl.target_ok && isfinite(W) && W > 0.0) {
     const double tau = u * W;
     const unsigned long long at = __ballot(incl > tau && run > 0.0), has = __ballot(run > 0.0);
     const int owner = at ? (int)__builtin_ctzll(at) : 63 - (int)__builtin_clzll(has);
