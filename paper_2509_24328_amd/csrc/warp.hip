@@ -15,9 +15,11 @@
 //   settle   sort the list, read off the K-th largest value, walk the groups of equal
 //            value until their mass reaches P
 // The list is exact whenever it holds at least K entries and (top-p alone) at
-// least P of the row's mass; a list that does not settle a top-p row is rebuilt
-// once with a lower tau (the 384-th lane maximum).  Otherwise - flat rows, huge K,
-// more than 2048 candidates - the general path takes over: radix selection on an
+// least P of the row's mass; a list that does not settle a row is rebuilt
+// once with a lower tau (top-p alone: the 384-th lane maximum, if a support is to be
+// written).  A nucleus that is too deep for a list (top-p alone) is cut where a running
+// mass over fine steps of the exponent passes P (list_nucleus_step).  Otherwise - huge K,
+// massive ties - the general path takes over: radix selection on an
 // order-preserving 32-bit key of the logit (11 + 11 + 10 bits; bfloat16 rows are
 // resolved after two levels), one histogram sweep of counts and masses per level.
 // Masses are fp64 sums of exponentials everywhere: on the candidate path in a fixed
@@ -44,6 +46,7 @@ namespace sv {
 constexpr int kWarpThreads = 512;
 constexpr int kBins = 2048;
 constexpr int kCand = 2048;          // capacity of the candidate list
+constexpr int kSteps = 8192;         // counters of list_nucleus_step
 constexpr int kGuessRank = 384;      // top-p alone: tau = this rank among the lane maxima
 constexpr double kNearTie = 3e-6;    // flagged band of a top-p decision
 
@@ -75,6 +78,7 @@ struct alignas(16) WarpShared {
       double mass[kBins];      // fp64: a bin may collect 1e5 nearly equal terms (a flat row at a
                                // high temperature), whose fp32 sum would be off by 1e-4
     };
+    uint32_t steps[kSteps + kSteps / 16];   // top-p alone: entries per step of the exponent
     struct {                   // candidate path
       uint64_t key[kCand];     // (order key of the value, ~token id): sorted descending
       double w[kCand];         // masses exp((z - m) / T) of the sorted candidates
@@ -83,134 +87,70 @@ struct alignas(16) WarpShared {
   };
   uint32_t tau_key;
   float theta;
-  int n_cand, settled, n_keep, out_done, first_reach, near_any;
+  int n_cand, settled, n_keep, out_done, first_reach, last_reach, near_any;
   double z_keep;               // mass of the kept entries
   int sel_digit;
   uint32_t sel_count_above;
   double sel_mass_above;
   double sel_mass_bin;
+  double wave_c[kWarpThreads / kWave], wave_m[kWarpThreads / kWave];
+  double row_s, row_Z;         // the row's normaliser relative to 2^c(m), and sum_v exp((z_v - m) / T)
   int near_tie;
 };
 
-// Scan the histograms from the top digit down.  by_count: find the digit where
-// the cumulative count reaches `k_rem`; else where the cumulative mass reaches
-// `target`.  One lane; results in LDS.
+// Walk the histograms from the top digit down.  by_count: find the digit where the cumulative
+// count reaches `k_rem`; else where the cumulative mass reaches `target`.  Every lane owns a run
+// of consecutive digits, placed by a scan over the workgroup (2048 digits by one lane, with a
+// division each, took 120 us per level).  Results in LDS, valid in every thread on return.
 __device__ __forceinline__ void scan_bins(WarpShared& sh, int nbins, bool by_count, uint32_t k_rem, double target,
                                           double total_for_tie) {
-  uint32_t c_above = 0;
-  double m_above = 0.0;
-  int found = 0;
-  for (int d = nbins - 1; d >= 0; --d) {
-    const uint32_t c = sh.cnt[d];
-    const double mm = sh.mass[d];
-    const bool hit = by_count ? (c_above + c >= k_rem) : (m_above + mm >= target && c > 0);
-    if (!by_count && c > 0 && total_for_tie > 0.0) {
-      // the candidate group boundaries at this level: flag a decision that sits on P
-      const double fr = (m_above + mm) / total_for_tie, want = target / total_for_tie;
-      if (fabs(fr - want) < kNearTie) sh.near_tie = 1;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  constexpr int kWaves = kWarpThreads / kWave;
+  const int run = nbins / kWarpThreads;                   // 4 or 2 digits per lane
+  const int p0 = tid * run;                               // place 0 is the top digit
+  double c_mine = 0.0, m_mine = 0.0;                      // (counts are exact in fp64)
+  for (int j = 0; j < run; ++j) {
+    c_mine += (double)sh.cnt[nbins - 1 - p0 - j];
+    m_mine += sh.mass[nbins - 1 - p0 - j];
+  }
+  const double c_incl = wave_scan_f64(c_mine), m_incl = wave_scan_f64(m_mine);
+  if (lane == kWave - 1) { sh.wave_c[wave] = c_incl; sh.wave_m[wave] = m_incl; }
+  if (tid == 0) sh.first_reach = nbins - 1;               // nothing reaches it: the lowest digit
+  __syncthreads();
+  double c_above = c_incl - c_mine, m_above = m_incl - m_mine;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w)
+    if (w < wave) { c_above += sh.wave_c[w]; m_above += sh.wave_m[w]; }
+  {
+    double c = c_above, m = m_above;
+    for (int j = 0; j < run; ++j) {
+      const int d = nbins - 1 - p0 - j;
+      const uint32_t cd = sh.cnt[d];
+      c += (double)cd;
+      m += sh.mass[d];
+      if (by_count ? c >= (double)k_rem : (m >= target && cd > 0)) { atomicMin(&sh.first_reach, p0 + j); break; }
     }
-    if (hit || d == 0) { found = d; sh.sel_mass_bin = mm; break; }
-    c_above += c;
+  }
+  __syncthreads();
+  const int found = sh.first_reach;
+  for (int j = 0; j < run && p0 + j <= found; ++j) {
+    const int d = nbins - 1 - p0 - j;
+    const uint32_t cd = sh.cnt[d];
+    const double mm = sh.mass[d];
+    // the candidate group boundaries at this level: flag a decision that sits on P
+    if (!by_count && cd > 0 && total_for_tie > 0.0 &&
+        fabs((m_above + mm) / total_for_tie - target / total_for_tie) < kNearTie)
+      sh.near_tie = 1;
+    if (p0 + j == found) {
+      sh.sel_digit = d;
+      sh.sel_count_above = (uint32_t)c_above;
+      sh.sel_mass_above = m_above;
+      sh.sel_mass_bin = mm;
+    }
+    c_above += (double)cd;
     m_above += mm;
   }
-  sh.sel_digit = found;
-  sh.sel_count_above = c_above;
-  sh.sel_mass_above = m_above;
-}
-
-// General path: radix selection over the whole row (m = row maximum, finite).
-// Returns the cutoff in every thread; sets sh.near_tie.
-template <int DT>
-__device__ __noinline__ float general_cutoff(const void* row, int V, float lt, int top_k, float top_p, float m,
-                                             WarpShared& sh) {
-  const int tid = threadIdx.x;
-  constexpr int kLevels = (DT == DT_BF16) ? 2 : 3;
-  const bool use_k = top_k > 0 && top_k < V, use_p = top_p < 1.0f;
-  const float c_ref = m * lt;
-
-  // histogram sweep over the entries under `prefix` at `level`, optionally only z >= floor_v
-  auto histogram = [&](int level, uint32_t prefix, float floor_v) {
-    for (int d = tid; d < kBins; d += blockDim.x) { sh.cnt[d] = 0; sh.mass[d] = 0.0; }
-    __syncthreads();
-    visit_range<DT, false, 1>(row, nullptr, 0, V, [&](int, float v, float) {   // (one vector at a time: few registers)
-      const uint32_t key = okey(v);
-      if (under_prefix(key, prefix, level) && v >= floor_v) {
-        const uint32_t d = digit_of(key, level);
-        atomicAdd(&sh.cnt[d], 1u);
-        atomicAdd(&sh.mass[d], (double)exp2_fast(__builtin_fmaf(v, lt, -c_ref)));
-      }
-    });
-    __syncthreads();
-  };
-
-  // sweep 2: level 0 over everything
-  histogram(0, 0u, -INFINITY);
-  double total0 = 0.0;
-  {
-    double part = 0.0;
-    for (int d = tid; d < kBins; d += blockDim.x) part += sh.mass[d];
-    total0 = block_sum_f64(part, sh.red);
-  }
-
-  // ---- top-k: K-th largest value ------------------------------------------
-  float t_k = -INFINITY;
-  double total_k = total0;
-  int dk0 = -1;                       // level-0 digit of t_k
-  double surv_in_dk0 = 0.0;           // mass of the survivors inside that digit
-  if (use_k) {
-    uint32_t prefix = 0, k_rem = (uint32_t)top_k;
-    double mass_above = 0.0, mass_above_l0 = 0.0;
-    for (int level = 0; level < kLevels; ++level) {
-      if (level > 0) histogram(level, prefix, -INFINITY);
-      if (tid == 0) scan_bins(sh, 1 << level_bits(level), true, k_rem, 0.0, 0.0);
-      __syncthreads();
-      const int d = sh.sel_digit;
-      k_rem -= sh.sel_count_above;
-      mass_above += sh.sel_mass_above;
-      if (level == 0) { dk0 = d; mass_above_l0 = sh.sel_mass_above; }
-      prefix = (prefix << level_bits(level)) | (uint32_t)d;
-      if (level == kLevels - 1) total_k = mass_above + sh.sel_mass_bin;
-      __syncthreads();
-    }
-    // bfloat16: the ten low key bits are all ones for negative values, zero otherwise
-    const uint32_t key = (DT == DT_BF16) ? ((prefix << 10) | ((prefix >> 21) ? 0u : 0x3ffu)) : prefix;
-    t_k = from_okey(key);
-    surv_in_dk0 = total_k - mass_above_l0;
-  }
-
-  // ---- top-p over the survivors -------------------------------------------
-  float theta = t_k;
-  if (use_p) {
-    const double target = (double)top_p * total_k;
-    // level 0 again (the top-k levels have overwritten it; keeping a copy would cost the 16 KB of LDS
-    // that decide whether three or four workgroups fit a compute unit, and this path is the rare one):
-    // digits above dk0 survive whole, dk0 in part, below not at all
-    if (use_k) histogram(0, 0u, -INFINITY);
-    for (int d = tid; d < kBins; d += blockDim.x) {
-      double mm = sh.mass[d];
-      uint32_t c = mm > 0.0 ? 1u : 0u;             // counts only mark non-empty bins here
-      if (use_k) {
-        if (d < dk0) { mm = 0.0; c = 0u; }
-        else if (d == dk0) { mm = surv_in_dk0; c = 1u; }
-      }
-      sh.mass[d] = mm;
-      sh.cnt[d] = c;
-    }
-    __syncthreads();
-    uint32_t prefix = 0;
-    double acc = 0.0;
-    for (int level = 0; level < kLevels; ++level) {
-      if (level > 0) histogram(level, prefix, t_k);
-      if (tid == 0) scan_bins(sh, 1 << level_bits(level), false, 0u, target - acc, level == kLevels - 1 ? total_k : 0.0);
-      __syncthreads();
-      acc += sh.sel_mass_above;
-      prefix = (prefix << level_bits(level)) | (uint32_t)sh.sel_digit;
-      __syncthreads();
-    }
-    const uint32_t key = (DT == DT_BF16) ? ((prefix << 10) | ((prefix >> 21) ? 0u : 0x3ffu)) : prefix;
-    theta = fmaxf(from_okey(key), t_k);
-  }
-  return theta;
+  __syncthreads();
 }
 
 // Bitonic sort of c[0..n2) in descending order by the whole workgroup (n2 a power of two).
@@ -287,7 +227,15 @@ __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online
                 q3 = load_vec_nt(row, i + 3 * nt);
     add_vec(q0, i); add_vec(q1, i + nt); add_vec(q2, i + 2 * nt); add_vec(q3, i + 3 * nt);
   }
-  for (; i < nvec; i += nt) add_vec(load_vec_nt(row, i), i);
+  if (i < nvec) {                                     // the last, partial round: its loads go out together as well
+    u32x4 q[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (i + u * nt < nvec) q[u] = load_vec_nt(row, i + u * nt);
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (i + u * nt < nvec) add_vec(q[u], i + u * nt);
+  }
   for (int v = nvec * EPV + tid; v < V; v += nt) acc.add1(load_elem<DT>(row, v), L);
 }
 
@@ -351,12 +299,355 @@ __device__ __forceinline__ void sort_desc_runs(uint64_t* keys, uint64_t* tmp, in
 }
 
 
+// Top-p alone, a nucleus of any depth: lists the stretch of values that holds the cutoff.
+// The entries under m - T ln(V / (1 - P)) have less than 1 - P of the mass between them, so the
+// cutoff is above that.  A sweep (from cache) counts the entries in 8192 equal steps of z / T over
+// that range.  An entry's mass is known from its step to within the step's width, which bounds
+// the running mass from both sides, and the few steps between the two places where a bound
+// passes P hold the cutoff.  A last sweep lists the entries of those steps in sh.key[0 .. sh.n_cand)
+// and sums the mass above them exactly (sh.sel_mass_above, relative to 2^c(m)); if they are more
+// than the list holds, they are first counted again in steps that are finer by as much.
+// False: no such steps, or ties that no width resolves.
+// Counts in LDS instead of masses: no exponential and no fp64 atomic per entry, and the sums do
+// not depend on an order.  Equal steps spread a row over thousands of counters, so that
+// the lanes of a wavefront rarely add to the same one; the radix digits of the general path are
+// quarters of an octave, and most entries of a row fall into a dozen of them.
+// 200 rows of 32000 bf16 entries, P = 0.9, 3000-9000 tokens kept, the whole cutoff kernel: 47 us,
+// of which a row spends 7 on the count, 5 on the scan, 7 on the list and 6 on settling it (504 us by
+// the general path with one lane walking its digits).
+template <int DT>
+__device__ __forceinline__ bool list_nucleus_step(const void* row, int V, float lt, float top_p, float m,
+                                                  WarpShared& sh) {
+  SV_PHASE_MARK(8)
+  constexpr int kRun = kSteps / kWarpThreads, EPV = Elem<DT>::per_vec, U = 4;
+  static_assert(kRun == 16, "slot_of pads one word per lane's run");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, p0 = tid * kRun;
+  const float c_ref = ref_of(m, lt);
+  const double target = (double)top_p * sh.row_s;
+  float from = __builtin_fmaf(-m, lt, c_ref);              // depth = log2(2^c / mass) of an entry; here of the top one
+  float range = log2f((float)V / (1.0f - top_p)) + 1.0f;
+  float per_step = 0.f;
+  int lo = 0, hi = 0;
+  auto slot_of = [](int d) { return d + (d >> 4); };       // (the lanes' runs start on different banks)
+  auto depth_of = [&](float v) { return __builtin_fmaf(-v, lt, c_ref); };
+  // place of an entry in units of steps, monotone in its value; negative above the range
+  auto place_of = [&](float depth) { return (depth - from) * per_step; };
+  // the row by vectors, U of them in flight per lane, the last round's too; body(entries, first index)
+  auto each_entry = [&](auto&& body) {
+    const int nvec = V / EPV;
+    for (int i = tid; i < nvec; i += U * kWarpThreads) {
+      u32x4 q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i + u * kWarpThreads < nvec) q[u] = load_vec(row, i + u * kWarpThreads);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i + u * kWarpThreads < nvec) {
+          float f[EPV];
+          unpack<DT>(q[u], f);
+#pragma unroll
+          for (int e = 0; e < EPV; ++e) body(f[e], (i + u * kWarpThreads) * EPV + e);
+        }
+    }
+    for (int v = nvec * EPV + tid; v < V; v += kWarpThreads) body(load_elem<DT>(row, v), v);
+  };
+  for (int round = 0;; ++round) {
+    if (round == 3) return false;
+    per_step = (float)kSteps / range;
+    for (int d = tid; d < kSteps + kSteps / kRun; d += kWarpThreads) sh.steps[d] = 0;
+    if (tid == 0) { sh.first_reach = kSteps; sh.last_reach = kSteps - 1; sh.n_cand = 0; }
+    __syncthreads();
+    // (no branches: an entry outside the range adds nothing to a counter of the lane's own)
+    each_entry([&](float v, int) {
+      const float t = place_of(depth_of(v));
+      const bool in = t >= 0.f && t < (float)kSteps;
+      atomicAdd(&sh.steps[in ? slot_of((int)t) : tid], in ? 1u : 0u);
+    });
+    double over = 0.0;                                     // mass above the range (none in the first round)
+    if (round > 0) {
+      each_entry([&](float v, int) {
+        const float depth = depth_of(v);
+        over += place_of(depth) < 0.f ? (double)exp2_fast(-depth) : 0.0;
+      });
+    }
+    over = block_sum_f64(over, sh.red);
+    SV_PHASE_MARK(9)
+    const float h = range * (1.0f / kSteps);
+    // upper bound of the mass of step p0 + j of this lane's run: every entry at its top
+    auto step_mass = [&](int j) {
+      return (double)sh.steps[slot_of(p0 + j)] * (double)exp2_fast(-__builtin_fmaf((float)(p0 + j), h, from));
+    };
+    double m_mine = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < kRun; ++j) m_mine += step_mass(j);
+    const double m_incl = wave_scan_f64(m_mine);
+    if (lane == kWave - 1) sh.wave_m[wave] = m_incl;
+    __syncthreads();
+    double before = m_incl - m_mine;
+#pragma unroll
+    for (int w = 0; w < kWarpThreads / kWave; ++w)
+      if (w < wave) before += sh.wave_m[w];
+    // (1e-5: what rounding can move an entry across a step's edge, and the weights' own)
+    const double lower = (double)exp2_fast(-h) * (1.0 - 1e-5);
+    const double at_lo = target / (1.0 + 1e-5) - over, at_hi = (target - over) / lower;
+    // (a run that ends under a threshold or starts clearly over it does not hold its place)
+    auto find = [&](double at, int& place) {
+      double m = before;
+      if (m + m_mine < at || m > at * (1.0 + 1e-9)) return;
+      for (int j = 0; j < kRun; ++j) {
+        m += step_mass(j);
+        if (m >= at) { atomicMin(&place, p0 + j); return; }
+      }
+    };
+    find(at_lo, sh.first_reach);
+    find(at_hi, sh.last_reach);
+    __syncthreads();
+    lo = sh.first_reach;
+    hi = sh.last_reach;
+    if (lo == kSteps) return false;
+    int in_window = 0;                                     // entries in steps lo..hi
+    for (int d = lo + tid; d <= hi; d += kWarpThreads) in_window += (int)sh.steps[slot_of(d)];
+    if (in_window) atomicAdd(&sh.n_cand, in_window);
+    __syncthreads();
+    const int n = sh.n_cand;
+    __syncthreads();
+    if (n == 0) return false;
+    if (n <= kCand) break;
+    from += (float)max(lo - 1, 0) * h;                     // (a step to either side for rounding)
+    range = (float)(hi - lo + 3) * h;
+  }
+  SV_PHASE_MARK(10)
+  if (tid == 0) sh.n_cand = 0;
+  __syncthreads();
+  double above = 0.0;
+  each_entry([&](float zv, int v) {
+    const float depth = depth_of(zv), t = place_of(depth);
+    above += t < (float)lo ? (double)exp2_fast(-depth) : 0.0;
+    if (t >= (float)lo && t < (float)(hi + 1)) {
+      const int at = atomicAdd(&sh.n_cand, 1);
+      if (at < kCand) sh.key[at] = ((uint64_t)okey(zv) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)v);
+    }
+  });
+  above = block_sum_f64(above, sh.red);
+  SV_PHASE_MARK(11)
+  if (tid == 0) sh.sel_mass_above = above;
+  __syncthreads();
+  return sh.n_cand <= kCand;
+}
+
+// Descending order of keys[0..n), n <= kRankMax distinct non-zero keys: every key's rank by comparing it
+// with all of them (LDS broadcasts, two keys each).  About 32 n cycles, 13000 for sort_desc_runs.
+constexpr int kRankMax = 256;
+__device__ __forceinline__ void sort_desc_ranks(uint64_t* keys, int n) {
+  const int tid = threadIdx.x;
+  if (tid == 0) keys[n] = 0;                               // (an odd count reads one more)
+  __syncthreads();
+  const uint64_t key = tid < n ? keys[tid] : 0;
+  int rank = 0;
+  if ((tid & ~(kWave - 1)) < n)
+    for (int j = 0; j < n; j += 2) {
+      const uint64_t a = keys[j], b = keys[j + 1];
+      rank += (a > key ? 1 : 0) + (b > key ? 1 : 0);
+    }
+  __syncthreads();
+  if (tid < n) keys[rank] = key;
+  __syncthreads();
+}
+
+// The cutoff of a top-p row from the list of list_nucleus_step and the mass above it: the end of
+// the first group of equal values whose running mass reaches P.  False if rounding puts P past
+// the list's end.
+__device__ __forceinline__ bool settle_step(float top_p, double inv_t, float m, WarpShared& sh, float* cutoff) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int n = sh.n_cand;
+  const double Z = sh.row_Z, above = sh.sel_mass_above * (Z / sh.row_s), want = (double)top_p * Z;
+  if (above >= want) return false;                        // (the bounds should not allow it)
+  if (n <= kRankMax) {
+    sort_desc_ranks(sh.key, n);
+  } else if (n <= kWarpThreads) {
+    sort_desc_runs(sh.key, sh.key + kCand / 2, n);
+  } else {
+    int n2 = kWarpThreads;
+    while (n2 < n) n2 <<= 1;
+    for (int i = n + tid; i < n2; i += kWarpThreads) sh.key[i] = 0;        // below every real key
+    __syncthreads();
+    sort_desc(sh.key, n2);
+  }
+  SV_PHASE_MARK(12)
+  constexpr int kRun = kCand / kWarpThreads;
+  const int i0 = tid * kRun;
+  double w[kRun], mine = 0.0;
+  float v[kRun + 1];
+#pragma unroll
+  for (int j = 0; j <= kRun; ++j) v[j] = i0 + j < n ? key_value(sh.key[i0 + j]) : -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) {
+    w[j] = i0 + j < n ? exp(((double)v[j] - (double)m) * inv_t) : 0.0;
+    mine += w[j];
+  }
+  const double incl = wave_scan_f64(mine);
+  if (lane == kWave - 1) sh.wave_m[wave] = incl;
+  if (tid == 0) sh.first_reach = n;
+  __syncthreads();
+  double base = incl - mine;
+#pragma unroll
+  for (int i = 0; i < kWarpThreads / kWave; ++i)
+    if (i < wave) base += sh.wave_m[i];
+  base += above;
+  double run = base;
+  bool done = false;
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) {
+    run += w[j];
+    if (!done && i0 + j < n && v[j + 1] != v[j] && run >= want) { atomicMin(&sh.first_reach, i0 + j); done = true; }
+  }
+  __syncthreads();
+  const int at = sh.first_reach;
+  if (at == n) return false;
+  run = base;
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) {
+    run += w[j];
+    if (i0 + j <= at && v[j + 1] != v[j] && fabs(run / Z - (double)top_p) < kNearTie) sh.near_tie = 1;
+  }
+  // a decision on the edge between the list and what lies above it belongs to both sides
+  if (tid == 0 && fabs(above / Z - (double)top_p) < kNearTie) sh.near_tie = 1;
+  SV_PHASE_MARK(13)
+#ifdef SV_PHASE_N
+  if (tid == 0 && blockIdx.x < 4096) sv_phase_buf[blockIdx.x * 16 + 15] = n;
+#endif
+  *cutoff = key_value(sh.key[at]);
+  return true;
+}
+
+// What the lists do not settle (m = row maximum, finite; sh.near_tie cleared): the steps of a
+// nucleus, else radix selection over the whole row.  Returns the cutoff in every thread; sets
+// sh.near_tie.
+template <int DT>
+__device__ __forceinline__ float general_cutoff(const void* row, int V, float lt, double inv_t, int top_k, float top_p,
+                                             float m, WarpShared& sh) {
+  const int tid = threadIdx.x;
+  constexpr int kLevels = (DT == DT_BF16) ? 2 : 3;
+  const bool use_k = top_k > 0 && top_k < V, use_p = top_p < 1.0f;
+  const float c_ref = m * lt;
+
+  if (!use_k && use_p) {
+    float cutoff;
+    if (list_nucleus_step<DT>(row, V, lt, top_p, m, sh) && settle_step(top_p, inv_t, m, sh, &cutoff)) return cutoff;
+    __syncthreads();
+    if (tid == 0) sh.near_tie = 0;
+  }
+
+  // histogram sweep over the entries under `prefix` at `level`, optionally only z >= floor_v
+  auto histogram = [&](int level, uint32_t prefix, float floor_v) {
+    for (int d = tid; d < kBins; d += blockDim.x) { sh.cnt[d] = 0; sh.mass[d] = 0.0; }
+    __syncthreads();
+    visit_range<DT, false, 1>(row, nullptr, 0, V, [&](int, float v, float) {   // (one vector at a time: few registers)
+      const uint32_t key = okey(v);
+      if (under_prefix(key, prefix, level) && v >= floor_v) {
+        const uint32_t d = digit_of(key, level);
+        atomicAdd(&sh.cnt[d], 1u);
+        atomicAdd(&sh.mass[d], (double)exp2_fast(__builtin_fmaf(v, lt, -c_ref)));
+      }
+    });
+    __syncthreads();
+  };
+
+  // sweep 2: level 0 over everything
+  histogram(0, 0u, -INFINITY);
+  double total0 = 0.0;
+  {
+    double part = 0.0;
+    for (int d = tid; d < kBins; d += blockDim.x) part += sh.mass[d];
+    total0 = block_sum_f64(part, sh.red);
+  }
+
+  // ---- top-k: K-th largest value ------------------------------------------
+  float t_k = -INFINITY;
+  double total_k = total0;
+  int dk0 = -1;                       // level-0 digit of t_k
+  double surv_in_dk0 = 0.0;           // mass of the survivors inside that digit
+  if (use_k) {
+    uint32_t prefix = 0, k_rem = (uint32_t)top_k;
+    double mass_above = 0.0, mass_above_l0 = 0.0;
+    for (int level = 0; level < kLevels; ++level) {
+      if (level > 0) histogram(level, prefix, -INFINITY);
+      scan_bins(sh, 1 << level_bits(level), true, k_rem, 0.0, 0.0);
+      const int d = sh.sel_digit;
+      k_rem -= sh.sel_count_above;
+      mass_above += sh.sel_mass_above;
+      if (level == 0) { dk0 = d; mass_above_l0 = sh.sel_mass_above; }
+      prefix = (prefix << level_bits(level)) | (uint32_t)d;
+      if (level == kLevels - 1) total_k = mass_above + sh.sel_mass_bin;
+      __syncthreads();
+    }
+    // bfloat16: the ten low key bits are all ones for negative values, zero otherwise
+    const uint32_t key = (DT == DT_BF16) ? ((prefix << 10) | ((prefix >> 21) ? 0u : 0x3ffu)) : prefix;
+    t_k = from_okey(key);
+    surv_in_dk0 = total_k - mass_above_l0;
+  }
+
+  // ---- top-p over the survivors -------------------------------------------
+  float theta = t_k;
+  if (use_p) {
+    const double target = (double)top_p * total_k;
+    // level 0 again (the top-k levels have overwritten it; keeping a copy would cost the 16 KB of LDS
+    // that decide whether three or four workgroups fit a compute unit, and this path is the rare one):
+    // digits above dk0 survive whole, dk0 in part, below not at all
+    if (use_k) histogram(0, 0u, -INFINITY);
+    for (int d = tid; d < kBins; d += blockDim.x) {
+      double mm = sh.mass[d];
+      uint32_t c = mm > 0.0 ? 1u : 0u;             // counts only mark non-empty bins here
+      if (use_k) {
+        if (d < dk0) { mm = 0.0; c = 0u; }
+        else if (d == dk0) { mm = surv_in_dk0; c = 1u; }
+      }
+      sh.mass[d] = mm;
+      sh.cnt[d] = c;
+    }
+    __syncthreads();
+    uint32_t prefix = 0;
+    double acc = 0.0;
+    for (int level = 0; level < kLevels; ++level) {
+      if (level > 0) histogram(level, prefix, t_k);
+      scan_bins(sh, 1 << level_bits(level), false, 0u, target - acc, level == kLevels - 1 ? total_k : 0.0);
+      acc += sh.sel_mass_above;
+      prefix = (prefix << level_bits(level)) | (uint32_t)sh.sel_digit;
+      __syncthreads();
+    }
+    const uint32_t key = (DT == DT_BF16) ? ((prefix << 10) | ((prefix >> 21) ? 0u : 0x3ffu)) : prefix;
+    theta = fmaxf(from_okey(key), t_k);
+  }
+  return theta;
+}
+
+// A row that the lists did not settle, to its end: the last thing its workgroup does, so that no
+// register of the caller has to survive the call.
+template <int DT>
+__device__ __noinline__ void cut_general_row(const void* row, int r, int V, float lt, double inv_t, int top_k,
+                                             float top_p, float m, float* cutoff, uint32_t* flags, int32_t* count,
+                                             float* lse, WarpShared& sh) {
+  __syncthreads();
+  if (threadIdx.x == 0) sh.near_tie = 0;
+  __syncthreads();
+  const float theta = general_cutoff<DT>(row, V, lt, inv_t, top_k, top_p, m, sh);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (cutoff) cutoff[r] = theta;
+    if (flags) flags[r] = sh.near_tie ? SV_FLAG_NEAR_TIE : 0u;
+    if (count) { count[r] = -1; lse[r] = __builtin_nanf(""); }
+  }
+}
+
 // top-p alone has no K and guesses the depth of the nucleus from the lane maxima: a
 // list of about rank + rank^2 / 1024 entries, short enough for the one-wavefront
 // settle when the largest 48 lane maxima already carry P of the row's mass, a deeper
 // one otherwise
 constexpr int kNucleusRank = 48;
 constexpr int kNucleusRank2 = 256;
+// the deeper list holds about 320 entries, seven times as many as the first, and each is lighter: where
+// the largest 48 lane maxima have less than this share of P, it hardly ever reaches P
+constexpr double kHopeless = 0.8;
 
 // One row (r of tensor z) by the whole workgroup.
 template <int DT>
@@ -398,6 +689,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   }
   const double m_t = (double)m * sc.inv_t;
   const double Z = exp(lse_row - m_t);                  // sum_v exp((z_v - m) / T)
+  if (tid == 0) { sh.row_s = merged[0].s; sh.row_Z = Z; }
 
   // The rank-th largest of the 512 lane maxima, to the 16 upper bits of its order key
   // (exact for bfloat16, rounded down for fp32): a lower bound of the rank-th largest
@@ -634,7 +926,8 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     float tau = lane_max_of_rank(use_k ? top_k : kNucleusRank);
     if (!use_k) {
       // top-p alone: does the mass of the lane maxima above tau already reach P?  Then the
-      // list above tau certainly does; otherwise ask for a deeper list straight away.
+      // list above tau certainly does; otherwise ask for a deeper list straight away, or, with
+      // no support to write and too little mass for that one as well, for none (kHopeless).
       if (tid < kWave) {
         const uint32_t t16 = sh.tau_key >> 16;
         double above = 0.0;
@@ -648,9 +941,10 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
         if (tid == 0) sh.z_keep = above;
       }
       __syncthreads();
-      const bool deep = sh.z_keep < (double)top_p * Z * (1.0 + 1e-6);
+      const double share = sh.z_keep / ((double)top_p * Z);
       __syncthreads();
-      if (deep) tau = lane_max_of_rank(kNucleusRank2);
+      if (!out.count && share < kHopeless) tau = -INFINITY;
+      else if (share < 1.0 + 1e-6) tau = lane_max_of_rank(kNucleusRank2);
     }
     SV_PHASE_MARK(2)
     const uint32_t tau_key = sh.tau_key;
@@ -685,7 +979,8 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   }
 
   // ---- attempt 2: a second sweep (from cache) lists every entry >= tau -------
-  if (!settled && (V <= kCand || !use_k || top_k <= kWarpThreads)) {
+  // (a cutoff alone is found through the steps of the general path at the same price, whatever the depth)
+  if (!settled && (V <= kCand || (use_k ? top_k <= kWarpThreads : out.count != nullptr))) {
     float tau = -INFINITY;                              // V <= kCand: every entry is a candidate
     if (V > kCand) tau = lane_max_of_rank(use_k ? top_k : kGuessRank);
     __syncthreads();
@@ -700,22 +995,20 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     __syncthreads();
     settled = settle(tau);
   }
-  float theta = sh.theta;
   if (!settled) {
-    __syncthreads();
-    if (tid == 0) { sh.near_tie = 0; sh.n_keep = -1; }
-    theta = general_cutoff<DT>(row, V, lt, top_k, top_p, m, sh);
+    cut_general_row<DT>(row, r, V, lt, sc.inv_t, top_k, top_p, m, cutoff, flags, out.count, out.lse, sh);
+    return;
   }
   if (tid == 0) {
-    if (cutoff) cutoff[r] = theta;
+    if (cutoff) cutoff[r] = sh.theta;
     if (flags) flags[r] = sh.near_tie ? SV_FLAG_NEAR_TIE : 0u;
   }
-  if (!out.count || (settled && sh.out_done)) return;    // (the wavefront path has written the support already)
+  if (!out.count || sh.out_done) return;    // (the wavefront path has written the support already)
 
   // ---- support of the warped row: token ids ascending, fp64 probabilities ----
   __syncthreads();
   const int nk = sh.n_keep;
-  if (nk < 0 || nk > out.cap) {                         // not settled on the list, or too wide
+  if (nk < 0 || nk > out.cap) {                         // too wide
     if (tid == 0) { out.count[r] = -1; out.lse[r] = __builtin_nanf(""); }
     return;
   }
