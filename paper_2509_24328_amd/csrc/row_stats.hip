@@ -14,14 +14,10 @@
 // discussed in Sec. 2 of the paper.)
 // A = min(1, P_c(x) / P_d(x)) is a scalar epilogue in fp64.
 //
-// Two kernels:
-//  * row_stats_stash_kernel (rows on 16-byte boundaries): 512 lanes, two
-//    workgroups per CU, so that one's arithmetic overlaps the other's loads.
-//    Sweep 1 parks what it reads on chip - the first 10 vector pairs of every
-//    lane stay in registers, the next 2432 pairs go to LDS (76 KB) - and only
-//    the rest of the pair (about three fifths at V = 152064, bf16) is read
-//    again, most recent bytes first so that they are still in L2.
-//  * row_stats_kernel: plain two-sweep version for rows of any alignment.
+// One kernel in three shapes (StashWide, StashTwo, StashThree: lanes per workgroup, workgroups per
+// CU).  Sweep 1 parks what it reads on chip - the first vector pairs of every lane stay in
+// registers, the next go to LDS - and only the rest of the pair, if any, is read again, most
+// recent bytes first so that they are still in L2.
 // Algorithmic HBM traffic: 2 * V * elem_size bytes per workgroup.
 #include "sv_device.hpp"
 #include "sv_host.hpp"
@@ -33,8 +29,6 @@
 #endif
 
 namespace sv {
-
-constexpr int kStatsThreads = 1024;
 
 struct StatsArgs {
   const void* z_d;
@@ -60,50 +54,11 @@ struct StatsArgs {
   float* chain_m;
   float* chain_zx;
   int dtype;
+  bool aligned;           // rows start on 16 bytes
 };
 
-// Online sweep of two rows at once (more independent loads in flight).
-// WARP: each row has its own exponent scale and support cutoff.
-template <int DT, bool WARP>
-__device__ __forceinline__ void sweep_online_pair(const void* ra, const void* rb, int V,
-                                                  Online& acc_a, Online& acc_b,
-                                                  const float La, const float Lb, const float cut_a,
-                                                  const float cut_b) {
-  constexpr int EPV = Elem<DT>::per_vec;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  auto add_vec = [&](const u32x4& q, Online& acc, const float L, const float cut) {
-    float f[EPV];
-    unpack<DT>(q, f);
-    if (WARP) {
-#pragma unroll
-      for (int j = 0; j < EPV; ++j) f[j] = cut_below(f[j], cut);
-    }
-    acc.add(f, L);
-  };
-  auto add_one = [&](int v) {
-    const float za = load_elem<DT>(ra, v), zb = load_elem<DT>(rb, v);
-    acc_a.add1(WARP ? cut_below(za, cut_a) : za, La);
-    acc_b.add1(WARP ? cut_below(zb, cut_b) : zb, Lb);
-  };
-  const int nvec = V / EPV;
-  int i = tid;
-  for (; i + nt < nvec; i += 2 * nt) {
-    const u32x4 a0 = load_vec(ra, i), b0 = load_vec(rb, i), a1 = load_vec(ra, i + nt), b1 = load_vec(rb, i + nt);
-    add_vec(a0, acc_a, La, cut_a);
-    add_vec(b0, acc_b, Lb, cut_b);
-    add_vec(a1, acc_a, La, cut_a);
-    add_vec(b1, acc_b, Lb, cut_b);
-  }
-  for (; i < nvec; i += nt) {
-    const u32x4 a0 = load_vec(ra, i), b0 = load_vec(rb, i);
-    add_vec(a0, acc_a, La, cut_a);
-    add_vec(b0, acc_b, Lb, cut_b);
-  }
-  for (int v = nvec * EPV + tid; v < V; v += nt) add_one(v);
-}
-
-// Sweep-2 arithmetic for one vocabulary entry (see row_stats_kernel for the
-// head/tail split of the normalisers).
+// Sweep-2 arithmetic for one vocabulary entry (head/tail split of the
+// normalisers: see sweep 2 of the kernel).
 template <bool WITH_KL>
 struct MinAcc {
   float kd, kc, delta;
@@ -145,7 +100,7 @@ struct MinAcc {
   }
 };
 
-// Scalar epilogue shared by both kernels: A, flags and the stores.
+// Scalar epilogue: A, flags and the stores.
 template <int DT, bool WITH_KL, bool WARP = false>
 __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, const void* rd, const void* rc,
                                                double lse_d, double lse_c, double S, double KL, double H_d,
@@ -196,10 +151,21 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
   if (a.flags) a.flags[pair] = fl;
 }
 
-constexpr int kStashThreads = 512;
-constexpr int kLdsVecs = 2432;       // vector pairs parked in LDS (2 * 2432 * 16 B = 76 KB)
-constexpr int kLdsIters = (kLdsVecs + kStashThreads - 1) / kStashThreads;
-constexpr size_t kStashLdsBytes = 2 * (size_t)kLdsVecs * 16;
+// How a workgroup is laid out: lanes, vector pairs per lane parked in registers (kl: with the sums
+// of KL and entropy, which need registers of their own), vector pairs parked in LDS (a multiple
+// of 64), wavefronts per SIMD that have to fit.  The rule between them stands at launch_stats.
+struct StashTwo {                                                      // two workgroups per CU
+  static constexpr int threads = 512, waves = 4, lds_vecs = 2432;      // 76 KB
+  template <bool KL> static constexpr int regs() { return KL ? 8 : 10; }
+};
+struct StashThree {                                                    // three per CU
+  static constexpr int threads = 512, waves = 6, lds_vecs = 1600;      // 50 KB
+  template <bool KL> static constexpr int regs() { return KL ? 3 : 4; }
+};
+struct StashWide {                                                     // one, twice the lanes for its pair
+  static constexpr int threads = 1024, waves = 8, lds_vecs = 2432;
+  template <bool KL> static constexpr int regs() { return 2; }
+};
 
 // Per-pair constants of sweep 2, formed once (fp64 log2 is ~100 instructions)
 // by lanes 0 and 1 of wavefront 0 after the merge and shared through LDS.
@@ -242,14 +208,10 @@ __device__ __forceinline__ void load_to_lds(const u32x4* src, u32x4* lds_wave_ba
       16, 0, 0);
 }
 
-// vector pairs per lane parked in registers: what fits beside the sweep-2
-// arithmetic within the 128 VGPRs that two 512-lane workgroups per CU leave each lane
-template <bool WITH_KL>
-constexpr int reg_iters() { return WITH_KL ? 8 : 10; }
-
-template <int DT, bool WITH_KL, bool WARP>
-__global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(StatsArgs a) {
-  constexpr int kRegIters = reg_iters<WITH_KL>();
+template <int DT, bool WITH_KL, bool WARP, class Shape>
+__global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_kernel(StatsArgs a) {
+  constexpr int kRegIters = Shape::template regs<WITH_KL>(), kLdsVecs = Shape::lds_vecs, nt = Shape::threads;
+  constexpr int kLdsIters = (kLdsVecs + nt - 1) / nt;
   extern __shared__ u32x4 park[];                      // [kLdsVecs] draft, then [kLdsVecs] companion
   __shared__ BlockScratch sm;
   __shared__ MergeScratch<2> mg;
@@ -257,14 +219,14 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
   constexpr int EPV = Elem<DT>::per_vec;
   constexpr uint32_t kNegInfWord = (DT == DT_BF16) ? 0xFF80FF80u : 0xFF800000u;
   const int tid = threadIdx.x;
-  constexpr int nt = kStashThreads;
   const int pair = blockIdx.x;
   const size_t row_bytes = (size_t)a.V * Elem<DT>::bytes;
-  const u32x4* pd = reinterpret_cast<const u32x4*>(static_cast<const char*>(a.z_d) + pair * row_bytes);
-  const u32x4* pc = reinterpret_cast<const u32x4*>(static_cast<const char*>(a.z_c) + pair * row_bytes);
-  const int nvec = a.V / EPV;                           // rows are whole vectors here
+  const char* pd = static_cast<const char*>(a.z_d) + pair * row_bytes;
+  const char* pc = static_cast<const char*>(a.z_c) + pair * row_bytes;
+  const int nvec = a.V / EPV;
   const int lds_begin = kRegIters * nt;
-  const int lds_end = min(nvec, lds_begin + kLdsVecs);
+  // rows that do not start on 16 bytes go without the LDS share
+  const int lds_end = min(nvec, lds_begin + (a.aligned ? kLdsVecs : 0));
   const u32x4 neg = {kNegInfWord, kNegInfWord, kNegInfWord, kNegInfWord};
   Scale sc_d = unit_scale(), sc_c = unit_scale();
   float cut_d = -INFINITY, cut_c = -INFINITY;
@@ -298,7 +260,7 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
     const int i = tid + j * nt;
     sd[j] = neg;
     sc[j] = neg;
-    if (i < nvec) { sd[j] = __builtin_nontemporal_load(pd + i); sc[j] = __builtin_nontemporal_load(pc + i); }
+    if (i < nvec) { sd[j] = load_vec_nt(pd, i); sc[j] = load_vec_nt(pc, i); }
   }
   // the LDS share goes straight from memory into LDS (no registers in between)
   // and lands while the register share is being accumulated
@@ -309,18 +271,20 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
       const int slot = j * nt + wave_base;              // LDS slot of lane 0; the hardware adds lane * 16 B
       const int i = lds_begin + j * nt + tid;
       if (i < lds_end) {
-        load_to_lds(pd + i, park + slot);
-        load_to_lds(pc + i, park + kLdsVecs + slot);
+        load_to_lds(reinterpret_cast<const u32x4*>(pd) + i, park + slot);
+        load_to_lds(reinterpret_cast<const u32x4*>(pc) + i, park + kLdsVecs + slot);
       }
     }
   }
   SV_PHASE_MARK(1)
 #pragma unroll
   for (int j = 0; j < kRegIters; ++j) {                 // -inf padding adds nothing
-    add1(od, sd[j], Ld, cut_d);
-    __builtin_amdgcn_sched_barrier(0);
-    add1(oc, sc[j], Lc, cut_c);
-    __builtin_amdgcn_sched_barrier(0);                  // one pair at a time: the parked vectors own the registers
+    if (j * nt < nvec) {
+      add1(od, sd[j], Ld, cut_d);
+      __builtin_amdgcn_sched_barrier(0);
+      add1(oc, sc[j], Lc, cut_c);
+      __builtin_amdgcn_sched_barrier(0);                // one pair at a time: the parked vectors own the registers
+    }
   }
   SV_PHASE_MARK(2)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // LDS share has landed (own lanes only: no barrier)
@@ -332,7 +296,7 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
   {
     int i = lds_end + tid;
     for (; i + nt < nvec; i += 2 * nt) {
-      const u32x4 d0 = pd[i], c0 = pc[i], d1 = pd[i + nt], c1 = pc[i + nt];
+      const u32x4 d0 = load_vec(pd, i), c0 = load_vec(pc, i), d1 = load_vec(pd, i + nt), c1 = load_vec(pc, i + nt);
       add1(od, d0, Ld, cut_d);
       __builtin_amdgcn_sched_barrier(0);
       add1(oc, c0, Lc, cut_c);
@@ -343,10 +307,20 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
       __builtin_amdgcn_sched_barrier(0);
     }
     for (; i < nvec; i += nt) {
-      const u32x4 d0 = pd[i], c0 = pc[i];
+      const u32x4 d0 = load_vec(pd, i), c0 = load_vec(pc, i);
       add1(od, d0, Ld, cut_d);
       add1(oc, c0, Lc, cut_c);
     }
+  }
+  // the entries past the last whole vector (rows off 16 bytes only): fewer than a vector's worth
+  const int tail = nvec * EPV + tid;
+  float tail_zd = -INFINITY, tail_zc = -INFINITY;
+  if (tail < a.V) {
+    tail_zd = load_elem<DT>(pd, tail);
+    tail_zc = load_elem<DT>(pc, tail);
+    if (WARP) { tail_zd = cut_below(tail_zd, cut_d); tail_zc = cut_below(tail_zc, cut_c); }
+    od.add1(tail_zd, Ld);
+    oc.add1(tail_zc, Lc);
   }
   SV_PHASE_MARK(4)
   publish_pair_consts(on, mg, consts, a, pair, sc_d, sc_c);
@@ -357,6 +331,11 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
   // ---- sweep 2: rest of the pair from L2/HBM (newest first), then LDS, then registers
   double S = __builtin_nan(""), KL = __builtin_nan(""), H_d = __builtin_nan("");
   if (!bad) {
+    // kappa = log2-domain normaliser consistent with the L32 exponent scale,
+    // split into an fp32 head and a tail.  With a = z*L32 - head:
+    // P_d = f_d 2^(a_d),  P_c = f_d 2^(a_c + delta),
+    // f_d = 2^(-tail_d), delta = tail_d - tail_c, so one scalar factor at the
+    // end removes the rounding of both heads.
     const double kappa_d = consts.kappa[0], kappa_c = consts.kappa[1];
     MinAcc<WITH_KL> acc;
     acc.kd = (float)kappa_d;
@@ -364,14 +343,15 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
     const double tail_d = kappa_d - (double)acc.kd, tail_c = kappa_c - (double)acc.kc;
     acc.delta = (float)(tail_d - tail_c);
     acc.Ld = Ld; acc.Lc = Lc;
+    if (tail < a.V) acc.add(tail_zd, tail_zc);
     {
       // walk the re-read region backwards: its end was read last in sweep 1
       const int n_rest = nvec - lds_end;
       int r = tid;
       for (; r + nt < n_rest; r += 2 * nt) {
         const int i0 = nvec - 1 - r, i1 = nvec - 1 - (r + nt);
-        const u32x4 d0 = __builtin_nontemporal_load(pd + i0), c0 = __builtin_nontemporal_load(pc + i0),
-                    d1 = __builtin_nontemporal_load(pd + i1), c1 = __builtin_nontemporal_load(pc + i1);
+        const u32x4 d0 = load_vec_nt(pd, i0), c0 = load_vec_nt(pc, i0), d1 = load_vec_nt(pd, i1),
+                    c1 = load_vec_nt(pc, i1);
         acc.template add_vec<DT, WARP>(d0, c0, cut_d, cut_c);
         __builtin_amdgcn_sched_barrier(0);
         acc.template add_vec<DT, WARP>(d1, c1, cut_d, cut_c);
@@ -379,7 +359,7 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
       }
       for (; r < n_rest; r += nt) {
         const int i0 = nvec - 1 - r;
-        acc.template add_vec<DT, WARP>(pd[i0], pc[i0], cut_d, cut_c);
+        acc.template add_vec<DT, WARP>(load_vec(pd, i0), load_vec(pc, i0), cut_d, cut_c);
       }
     }
     SV_PHASE_MARK(6)
@@ -392,8 +372,10 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
       // floats of sweep 1 are kept alive for reuse and spill
       asm volatile("" : "+v"(sd[j].x), "+v"(sd[j].y), "+v"(sd[j].z), "+v"(sd[j].w));
       asm volatile("" : "+v"(sc[j].x), "+v"(sc[j].y), "+v"(sc[j].z), "+v"(sc[j].w));
-      acc.template add_vec<DT, WARP>(sd[j], sc[j], cut_d, cut_c);
-      __builtin_amdgcn_sched_barrier(0);
+      if (j * nt < nvec) {
+        acc.template add_vec<DT, WARP>(sd[j], sc[j], cut_d, cut_c);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     SV_PHASE_MARK(8)
     S = block_sum_f64((double)acc.acc_s, sm);
@@ -413,88 +395,42 @@ __global__ __launch_bounds__(kStashThreads, 4) void row_stats_stash_kernel(Stats
   if (tid == 0) stats_epilogue<DT, WITH_KL, WARP>(a, pair, pd, pc, lse_d, lse_c, S, KL, H_d, cut_d, cut_c);
 }
 
-template <int DT, bool WITH_KL, bool WARP>
-__global__ __launch_bounds__(kStatsThreads) void row_stats_kernel(StatsArgs a) {
-  __shared__ BlockScratch sm;
-  __shared__ MergeScratch<2> mg;
-  __shared__ PairConsts consts;
-  const int pair = blockIdx.x;                       // b * k + i
-  const size_t row_bytes = (size_t)a.V * Elem<DT>::bytes;
-  const void* rd = static_cast<const char*>(a.z_d) + pair * row_bytes;
-  const void* rc = static_cast<const char*>(a.z_c) + pair * row_bytes;
-
-  Scale sc_d = unit_scale(), sc_c = unit_scale();
-  float cut_d = -INFINITY, cut_c = -INFINITY;
-  if (WARP) {
-    sc_d = a.sc_d; sc_c = a.sc_c;
-    if (a.cut_d) cut_d = a.cut_d[pair];
-    if (a.cut_c) cut_c = a.cut_c[pair];
+template <int DT, bool WITH_KL, bool WARP, class Shape>
+static int launch_shape(const StatsArgs& a, hipStream_t st) {
+  constexpr size_t lds_bytes = 2 * (size_t)Shape::lds_vecs * 16;
+  // more than 64 KB of dynamic LDS has to be allowed once per kernel and device
+  constexpr int kMaxDevices = 64;
+  static bool allowed[kMaxDevices] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return SV_ERR_LAUNCH;
+  if (dev < 0 || dev >= kMaxDevices || !allowed[dev]) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&row_stats_stash_kernel<DT, WITH_KL, WARP, Shape>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
+      return SV_ERR_LAUNCH;
+    if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
   }
-  Online on[2];
-  on[0].init();
-  on[1].init();
-  sweep_online_pair<DT, WARP>(rd, rc, a.V, on[0], on[1], sc_d.L, sc_c.L, cut_d, cut_c);
-  publish_pair_consts(on, mg, consts, a, pair, sc_d, sc_c);
-  const double lse_d = consts.lse[0], lse_c = consts.lse[1];
-  const bool bad = isnan(lse_d) || isnan(lse_c);
-
-  double S = __builtin_nan(""), KL = __builtin_nan(""), H_d = __builtin_nan("");
-  if (!bad) {
-    // kappa = log2-domain normaliser consistent with the L32 exponent scale,
-    // split into an fp32 head and a tail.  With a = z*L32 - head:
-    // P_d = f_d 2^(a_d),  P_c = f_d 2^(a_c + delta),
-    // f_d = 2^(-tail_d), delta = tail_d - tail_c, so one scalar factor at the
-    // end removes the rounding of both heads.
-    const double kappa_d = consts.kappa[0], kappa_c = consts.kappa[1];
-    MinAcc<WITH_KL> acc;
-    acc.kd = (float)kappa_d;
-    acc.kc = (float)kappa_c;
-    const double tail_d = kappa_d - (double)acc.kd, tail_c = kappa_c - (double)acc.kc;
-    acc.delta = (float)(tail_d - tail_c);
-    acc.Ld = sc_d.L; acc.Lc = sc_c.L;
-    visit_range<DT, true>(rd, rc, 0, a.V, [&](int, float zd, float zc) {
-      if (WARP) { zd = cut_below(zd, cut_d); zc = cut_below(zc, cut_c); }
-      acc.add(zd, zc);
-    });
-    S = block_sum_f64((double)acc.acc_s, sm);
-    if (WITH_KL) {
-      KL = block_sum_f64((double)acc.acc_kl, sm);
-      const double pa = block_sum_f64((double)acc.acc_pa, sm), p1 = block_sum_f64((double)acc.acc_p, sm);
-      H_d = pa - tail_d * p1;
-    }
-    if (threadIdx.x == 0) {
-      const double f_d = exp2(-tail_d);
-      S *= f_d;
-      KL *= f_d * kLn2;
-      H_d *= -f_d * kLn2;
-    }
-  }
-  if (threadIdx.x == 0)
-    stats_epilogue<DT, WITH_KL, WARP>(a, pair, rd, rc, lse_d, lse_c, S, KL, H_d, cut_d, cut_c);
+  TapScope tap(SV_KERNEL_ROW_STATS, st);
+  hipLaunchKernelGGL((row_stats_stash_kernel<DT, WITH_KL, WARP, Shape>), dim3(a.B * a.k), dim3(Shape::threads),
+                     lds_bytes, st, a);
+  return launch_status();
 }
 
+// Which shape (us of the kernel, bf16 unless said otherwise).
+//  * At most one pair per CU: more lanes per pair.  256 x 128256: wide 38.8, two 40.6; 128 x 128256:
+//    32.5 and 36.8, fp32 36.3 and 43.1; 64 x 32000: 14.0 and 15.
+//  * Rows that three workgroups keep (nearly) on chip, or whose arithmetic they overlap better than
+//    the bytes they read twice cost: 8192 x 32000: three 192, two 235; 1024 x 50304: 52.7 and 56.6; 512 x
+//    100352: 54.2 and 55.5.  fp32 has half the arithmetic per byte: 512 x 20000: 22.9 and 24.5; 800 x 32000:
+//    55 and 51.
+//  * Longer rows are bound by what is read twice (the lines lie between): 512 x 128256: two 67.6, three 72;
+//    512 x 152064: 80 and 87; fp32 512 x 65536: 63 and 73.
 template <int DT, bool WITH_KL, bool WARP>
-static int launch_stats(const StatsArgs& a, bool rows_aligned, hipStream_t st) {
-  const dim3 grid(a.B * a.k);
-  if (rows_aligned) {
-    // more than 64 KB of dynamic LDS has to be allowed once per kernel and device
-    constexpr int kMaxDevices = 64;
-    static bool allowed[kMaxDevices] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return SV_ERR_LAUNCH;
-    if (dev < 0 || dev >= kMaxDevices || !allowed[dev]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&row_stats_stash_kernel<DT, WITH_KL, WARP>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStashLdsBytes) != hipSuccess)
-        return SV_ERR_LAUNCH;
-      if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
-    }
-    TapScope tap(SV_KERNEL_ROW_STATS, st);
-    hipLaunchKernelGGL((row_stats_stash_kernel<DT, WITH_KL, WARP>), grid, dim3(kStashThreads), kStashLdsBytes, st, a);
-  } else {
-    TapScope tap(SV_KERNEL_ROW_STATS, st);
-    hipLaunchKernelGGL((row_stats_kernel<DT, WITH_KL, WARP>), grid, dim3(kStatsThreads), 0, st, a);
-  }
-  return launch_status();
+static int launch_stats(const StatsArgs& a, hipStream_t st) {
+  constexpr int kCUs = 256, kThreeMax = DT == DT_BF16 ? 13000 : 6500;      // vectors of a row
+  const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
+  if (pairs <= kCUs && nvec > StashWide::threads) return launch_shape<DT, WITH_KL, WARP, StashWide>(a, st);
+  if (nvec <= kThreeMax) return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
+  return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
 }
 
 // Argument checks and launch shared by sv_row_stats and sv_row_stats_warped.
@@ -518,22 +454,22 @@ static int row_stats_checked(const void* z_d, const void* z_c, const int32_t* x,
              SV_ERR_WORKSPACE);
   const VerifyWs w = carve_verify_ws(ws, B, k, V);
   StatsArgs a{z_d, z_c, x, B, k, V, lse_d, lse_c, S, A, kl, entropy_d, pd_x, flags, sc_d, sc_c, cut_d, cut_c,
-              w.chain, w.chain_s, w.chain_m, w.chain_zx, dtype};
+              w.chain, w.chain_s, w.chain_m, w.chain_zx, dtype,
+              is_aligned(z_d, 16) && is_aligned(z_c, 16) && ((size_t)V * eb) % 16 == 0};
   const bool extended = kl || entropy_d;   // sums that need P_d of every entry
-  const bool rows_aligned = is_aligned(z_d, 16) && is_aligned(z_c, 16) && ((size_t)V * eb) % 16 == 0;
   hipStream_t st = as_stream(stream);
   if (warped) {
     if (dtype == SV_F32)
-      return extended ? launch_stats<DT_F32, true, true>(a, rows_aligned, st)
-                      : launch_stats<DT_F32, false, true>(a, rows_aligned, st);
-    return extended ? launch_stats<DT_BF16, true, true>(a, rows_aligned, st)
-                    : launch_stats<DT_BF16, false, true>(a, rows_aligned, st);
+      return extended ? launch_stats<DT_F32, true, true>(a, st)
+                      : launch_stats<DT_F32, false, true>(a, st);
+    return extended ? launch_stats<DT_BF16, true, true>(a, st)
+                    : launch_stats<DT_BF16, false, true>(a, st);
   }
   if (dtype == SV_F32)
-    return extended ? launch_stats<DT_F32, true, false>(a, rows_aligned, st)
-                    : launch_stats<DT_F32, false, false>(a, rows_aligned, st);
-  return extended ? launch_stats<DT_BF16, true, false>(a, rows_aligned, st)
-                  : launch_stats<DT_BF16, false, false>(a, rows_aligned, st);
+    return extended ? launch_stats<DT_F32, true, false>(a, st)
+                    : launch_stats<DT_F32, false, false>(a, st);
+  return extended ? launch_stats<DT_BF16, true, false>(a, st)
+                  : launch_stats<DT_BF16, false, false>(a, st);
 }
 
 }  // namespace sv

@@ -1,0 +1,34 @@
+"""sv_row_stats at the edges of its workgroup shapes: as many pairs as compute units and one more,
+rows that end inside, at and past the register share, the LDS share and the limits of the rule,
+on and off 16 bytes, with and without the sums of KL and entropy."""
+import numpy as np
+import pytest
+import torch
+
+import svgen
+from oracle import sv_oracle as O
+
+import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("pairs,V,dtype", [
+    (257, 1, "f32"), (257, 4096, "bf16"),                       # less than a vector; one vector per lane
+    (256, 8192, "bf16"), (256, 8200, "bf16"), (256, 8193, "bf16"),   # 1024 vectors and one more: wide from there on
+    (257, 16384, "bf16"), (257, 29184, "bf16"), (257, 29192, "bf16"),   # three: registers full, LDS full, one over
+    (3, 35840, "bf16"), (3, 35848, "bf16"), (2, 36001, "f32"),  # wide: LDS full, one over; off 16 bytes
+    (257, 26000, "f32"), (257, 26004, "f32"),                   # three / two in float32
+    (257, 104000, "bf16"), (257, 104008, "bf16"), (257, 104001, "bf16")])
+@pytest.mark.parametrize("with_kl", [True, False])
+def test_row_stats_at_the_edges_of_the_shapes(pairs, V, dtype, with_kl):
+    # a few sequences' rows, repeated over the pairs: every workgroup of a launch has its turn
+    n = min(pairs, 5)
+    cfg = svgen.make_config(1, seed=V + pairs, B=n, k=1, V=V, dtype=dtype)
+    inp = H.oracle_inputs(cfg)
+    ref = O.row_stats(inp["z_d"], inp["z_c"], inp["x"])
+    at = np.arange(pairs) % n
+    ref = {name: np.asarray(v)[at] for name, v in ref.items()}
+    t = torch.from_numpy(at)
+    got = H.gpu_row_stats(cfg["z_d"][t].cuda(), cfg["z_c"][t].cuda(), cfg["x"][t].cuda(), with_kl)
+    H.assert_row_stats(got, ref, with_kl)
