@@ -8,14 +8,17 @@
 // the batch-level greedy rule, Sec. 5, batch scheduling) is always the
 // largest not-yet-taken c.  Because c is non-increasing along a sequence,
 // sorting all (b,j) by (c descending, b, j ascending) reproduces the greedy
-// order.  One workgroup: products (one lane per sequence); pairwise merging of
-// the per-sequence lists in LDS (they are sorted already); the running sum E_M
+// order.  One workgroup: products (one lane per sequence); the values alone are sorted in LDS
+// (ties are the same value, whichever key it came from); the running sum E_M
 // is defined in exactly that order (fp64, one addition after another, so that
 // the integer outputs do not depend on a reduction tree) - a parallel scan with
 // an error bound decides every comparison that is not a near tie, one lane
-// re-sums in order otherwise; goodput and first-peak search in parallel; counts
-// and offsets.  Launch-latency bound at the paper's batch sizes (12 us at 512
-// keys; 55 us at 4096, 120 us at 8192).
+// re-sums in order otherwise; goodput and first-peak search in parallel; then a
+// sequence takes the products above the M-th largest value, and those equal to it
+// in the order of the keys.  Latency bound at the paper's batch sizes (8 us at 512
+// keys, 12 us at 1024, 51 us at 8192; 11.5, 17 and 130 us with merges of (value, key) pairs).
+#include <type_traits>
+
 #include "sv_bins.hpp"
 #include "sv_device.hpp"
 #include "sv_host.hpp"
@@ -30,7 +33,13 @@ namespace sv {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelMax = SV_SELECT_MAX_KEYS;   // power of two
-constexpr int kMergeMax = kSelMax / 2;         // up to here the upper half of the key arrays is a second buffer
+constexpr int kKeysPerLane = kSelMax / kSelThreads;
+
+// Place of key i in an LDS buffer: a gap after every eight, so that lanes that own runs of
+// eight, or sequences of eight or sixteen, start on different banks.
+__host__ __device__ __forceinline__ constexpr int slot(int i) { return i + (i >> 3); }
+// Bytes of the two buffers for a power of two of keys.
+constexpr size_t select_lds_bytes(int npad) { return 2 * sizeof(double) * (size_t)slot(npad); }
 
 __device__ __forceinline__ double clean_p(float p) {
   if (isnan(p)) return 0.0;
@@ -94,124 +103,207 @@ __device__ __forceinline__ float estimate_of(const EstimateArgs& e, const float*
   return p;
 }
 
-template <bool FUSED>
+// The estimates of keys tid, tid + nt, ... (Q of them): a round of loads for all, one walk
+// over the edges, one round of table lookups.  (Results and side outputs as estimate_of.)
+template <int Q, class Put>
+__device__ __forceinline__ void estimate_keys(const EstimateArgs& e, const float* es, const float* ea, int n, Put&& put) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  float s[Q], a[Q];
+  int bs[Q], ba[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int j = tid + q * nt;
+    s[q] = a[q] = 0.f;
+    if (j < n) { s[q] = e.S[j]; a[q] = e.A[j]; }
+    bs[q] = ba[q] = 0;
+  }
+  for (int j = 1; j <= e.n_s; ++j) {
+    const float edge = es[j];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (edge <= s[q]) bs[q] = j;                     // (never for NaN: cell 0)
+  }
+  for (int j = 1; j <= e.n_a; ++j) {
+    const float edge = ea[j];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (edge <= a[q]) ba[q] = j;
+  }
+  float p[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (tid + q * nt < n) p[q] = e.table[min(bs[q], e.n_s - 1) * e.n_a + min(ba[q], e.n_a - 1)];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int j = tid + q * nt;
+    if (j < n) {
+      put(j, p[q]);
+      if (e.p_hat) e.p_hat[j] = p[q];
+      if (e.edge_flag) e.edge_flag[j] = (near_edge(s[q], es, e.n_s) || near_edge(a[q], ea, e.n_a)) ? 1 : 0;
+    }
+  }
+}
+
+// Value of the lane whose number differs in the bits of MASK.
+template <int MASK>
+__device__ __forceinline__ double lane_xor_f64(double v) {
+  int lo = __double2loint(v), hi = __double2hiint(v);
+  auto dpp = [](int x, auto ctrl) { return __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, 0xf, 0xf, false); };
+  if constexpr (MASK == 1) {                           // quad_perm 1 0 3 2
+    lo = dpp(lo, std::integral_constant<int, 0xB1>()); hi = dpp(hi, std::integral_constant<int, 0xB1>());
+  } else if constexpr (MASK == 2) {                    // quad_perm 2 3 0 1
+    lo = dpp(lo, std::integral_constant<int, 0x4E>()); hi = dpp(hi, std::integral_constant<int, 0x4E>());
+  } else if constexpr (MASK == 4) {                    // half row mirrored (^7), quads mirrored (^3)
+    lo = dpp(dpp(lo, std::integral_constant<int, 0x141>()), std::integral_constant<int, 0x1B>());
+    hi = dpp(dpp(hi, std::integral_constant<int, 0x141>()), std::integral_constant<int, 0x1B>());
+  } else if constexpr (MASK == 8) {                    // row rotated by 8
+    lo = dpp(lo, std::integral_constant<int, 0x128>()); hi = dpp(hi, std::integral_constant<int, 0x128>());
+  } else {
+    lo = __shfl_xor(lo, MASK, kWave); hi = __shfl_xor(hi, MASK, kWave);
+  }
+  return __hiloint2double(hi, lo);
+}
+
+// Descending bitonic sort of npad <= 1024 values, one per lane of the workgroup (no NaNs).  Partners
+// inside a wavefront are reached in registers, those in another one through LDS, place by place
+// and so without bank conflicts.  Returns the buffer that holds the result.
+// Phase of 512 keys: 6300 cycles; 16000 with pairwise merges by binary search (a gather of 64 doubles
+// takes about 26 cycles of LDS time), 14000 with one round of searches in all eight sorted runs.
+__device__ __forceinline__ double* sort_small(double* src, double* dst, int npad) {
+  const int tid = threadIdx.x;
+  double v = src[slot(tid)];
+  auto exchange = [&](double other, int k2, int j) {
+    const bool desc = (tid & k2) == 0, lower = (tid & j) == 0;
+    v = lower == desc ? fmax(v, other) : fmin(v, other);
+  };
+  auto steps = [&](int k2, auto top) {                   // partners at top, top / 2, ..., 1
+    constexpr int J = decltype(top)::value;
+    if constexpr (J >= 32) exchange(lane_xor_f64<32>(v), k2, 32);
+    if constexpr (J >= 16) exchange(lane_xor_f64<16>(v), k2, 16);
+    if constexpr (J >= 8) exchange(lane_xor_f64<8>(v), k2, 8);
+    if constexpr (J >= 4) exchange(lane_xor_f64<4>(v), k2, 4);
+    if constexpr (J >= 2) exchange(lane_xor_f64<2>(v), k2, 2);
+    exchange(lane_xor_f64<1>(v), k2, 1);
+  };
+  steps(2, std::integral_constant<int, 1>());
+  steps(4, std::integral_constant<int, 2>());
+  steps(8, std::integral_constant<int, 4>());
+  steps(16, std::integral_constant<int, 8>());
+  steps(32, std::integral_constant<int, 16>());
+#pragma unroll 1
+  for (int k2 = kWave; k2 <= npad; k2 <<= 1) {
+#pragma unroll 1
+    for (int j = k2 >> 1; j >= kWave; j >>= 1) {
+      double* t = src; src = dst; dst = t;               // (the other buffer: the last one may still be read)
+      src[slot(tid)] = v;
+      __syncthreads();
+      exchange(src[slot(tid ^ j)], k2, j);
+    }
+    steps(k2, std::integral_constant<int, 32>());
+  }
+  dst[slot(tid)] = v;
+  __syncthreads();
+  return dst;
+}
+
+// Descending sort of n > 1024 values that come in sorted runs of `len`: rounds of pairwise merges between
+// two buffers, every lane writing a run of R consecutive values.  It finds by binary search how many
+// of the values before its first come from either list and then takes the larger head, one LDS
+// read a value: 8 + log2 reads against 8 log2 with a search per value.
+// Phase of 8192 keys (512 sequences of 16): 65000 cycles, 231000 with a search per value.
+__device__ __forceinline__ double* sort_large(double* src, double* dst, int n, int len, int R) {
+  const int p0 = threadIdx.x * R, p1 = min(n, p0 + R);
+  for (; len < n; len <<= 1) {
+    int mid = 0, end = 0, i = 0, j = 0;                // heads of the two lists, their ends
+    double vi = 0.0, vj = 0.0;
+    for (int p = p0; p < p1; ++p) {
+      if (p == p0 || p == end) {
+        const int base = (p / (2 * len)) * (2 * len), d = p - base;
+        mid = min(n, base + len);
+        end = min(n, base + 2 * len);
+        int lo = max(0, d - (end - mid)), hi = min(d, mid - base);
+        while (lo < hi) {
+          const int m = (lo + hi) >> 1;
+          if (src[slot(base + m)] >= src[slot(mid + d - 1 - m)]) lo = m + 1; else hi = m;
+        }
+        i = base + lo;
+        j = mid + d - lo;
+        vi = src[slot(min(i, n - 1))];
+        vj = src[slot(min(j, n - 1))];
+      }
+      const bool take_i = j >= end || (i < mid && vi >= vj);
+      dst[slot(p)] = take_i ? vi : vj;
+      if (take_i) vi = src[slot(min(++i, n - 1))]; else vj = src[slot(min(++j, n - 1))];
+    }
+    __syncthreads();
+    double* t = src; src = dst; dst = t;
+  }
+  return src;
+}
+
+// KEYS: keys per lane that the code has registers for, 1 (n <= 1024) or kKeysPerLane.  One workgroup
+// runs through this code once, so its instructions arrive from L2 as it goes and every line
+// that is not there is time saved: the few-key code is compiled without the other's unrolled runs
+// (512 keys: 28000 cycles in all, 31000 with one code for both), and loops stay rolled.
+template <bool FUSED, int KEYS>
 __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     const float* p_hat, int B, int k, const float* latency, int32_t* gamma, int32_t* t_offsets,
-    int32_t* total_M, EstimateArgs est) {
-  __shared__ double key_c[kSelMax];     // sort keys, later the running sums E_M
-  __shared__ int key_i[kSelMax];        // first the raw estimates (as float bits), then key indices
-  __shared__ int part[kSelThreads];
-  __shared__ int m_star;
+    int32_t* total_M, int npad, EstimateArgs est) {
+  extern __shared__ double buffers[];   // two of slot(npad) places; the values, later the running sums E_M
+  __shared__ int part[kSelThreads / kWave];
+  __shared__ int m_star, over;           // M*, products above the M*-th largest value
   const int tid = threadIdx.x, nt = blockDim.x;
-  const int n = B * k;
-  int npad = kWave;                    // a power of two >= max(n, 64)
-  while (npad < n) npad <<= 1;
+  const int lane = tid & (kWave - 1), wave = tid >> 6;
+  const int n = B * k;                 // npad: a power of two >= max(n, 64)
+  double* src = buffers;
+  double* dst = buffers + slot(npad);
 
   SV_PHASE_MARK(0)
   // the latencies this lane divides by after the sort: asked for now, so that the
   // memory latency passes behind the sort
-  constexpr int kRunMax = kSelMax / kSelThreads;
-  const int R = (npad + nt - 1) / nt;                  // keys per lane in the goodput scan
-  float lat_run[kRunMax];
+  const int R = KEYS == 1 ? 1 : npad / nt;             // keys per lane in the goodput scan
+  float lat_run[KEYS];
 #pragma unroll
-  for (int j = 0; j < kRunMax; ++j) {
+  for (int j = 0; j < KEYS; ++j) {
     const int idx = tid * R + j;
     lat_run[j] = (j < R && idx < n) ? latency[idx + 1] : 1.f;
   }
   // estimates into LDS with one round of coalesced loads
-  float* p_lds = reinterpret_cast<float*>(key_i);
+  float* p_lds = reinterpret_cast<float*>(dst);
   if (FUSED) {
     __shared__ float e_lds[kEdgeLds];
     const bool in_lds = stage_edges(e_lds, est.edges_s, est.n_s, est.edges_a, est.n_a);
     const float* es = in_lds ? e_lds : est.edges_s;
     const float* ea = in_lds ? e_lds + est.n_s + 1 : est.edges_a;
-    for (int j = tid; j < n; j += nt) p_lds[j] = estimate_of(est, es, ea, j);
+    auto put = [&](int j, float p) { p_lds[slot(j)] = p; };
+    estimate_keys<KEYS>(est, es, ea, n, put);
   } else {
-    for (int j = tid; j < n; j += nt) p_lds[j] = p_hat[j];
+    for (int j = tid; j < n; j += nt) p_lds[slot(j)] = p_hat[j];
   }
+  if (tid == 0) m_star = n;
   __syncthreads();
   for (int b = tid; b < B; b += nt) {
     double acc = 1.0;
     for (int j = 0; j < k; ++j) {
-      acc = acc * clean_p(p_lds[b * k + j]);
-      key_c[b * k + j] = acc;
+      acc = acc * clean_p(p_lds[slot(b * k + j)]);
+      src[slot(b * k + j)] = acc;
     }
   }
-  __syncthreads();
-  for (int j = tid; j < npad; j += nt) {
-    if (j < n) { key_i[j] = j; } else { key_c[j] = -1.0; key_i[j] = 0x7fffffff; }
-  }
-  if (tid == 0) m_star = n;
+  for (int j = n + tid; j < npad; j += nt) src[slot(j)] = -1.0;
   __syncthreads();
 
   SV_PHASE_MARK(1)
-  // Sort into selection order.  Every sequence's keys are already in order
-  // (c is non-increasing along a sequence), so up to kMergeMax keys are merged
-  // pairwise, list lengths k, 2k, 4k, ...: a key's new position is its position
-  // in its own list plus the number of keys of the partner list that come
-  // before it, found by binary search.  Ties between the two lists go to the
-  // left one (lower sequence indices), which is the tie order of the keys.
-  if (n <= kMergeMax) {
-    // ping-pong between the lower and the upper half of the key arrays
-    int src = 0, dst = kMergeMax;
-    for (int len = k; len < n; len <<= 1) {
-      for (int p = tid; p < n; p += nt) {
-        const int base = (p / (2 * len)) * (2 * len);
-        const int mid = min(n, base + len), end = min(n, base + 2 * len);
-        const bool left = p < mid;
-        const double c = key_c[src + p];
-        int lo = left ? mid : base, hi = left ? end : mid;
-        const int first = lo;
-        while (lo < hi) {
-          const int probe = (lo + hi) >> 1;
-          const double v = key_c[src + probe];
-          if (left ? (v > c) : (v >= c)) lo = probe + 1; else hi = probe;
-        }
-        const int q = base + (left ? p - base : p - mid) + (lo - first);
-        key_c[dst + q] = c;
-        key_i[dst + q] = key_i[src + p];
-      }
-      __syncthreads();
-      const int t = src; src = dst; dst = t;
-    }
-    if (src != 0) {                              // odd number of rounds: bring the result down
-      for (int p = tid; p < n; p += nt) { key_c[p] = key_c[src + p]; key_i[p] = key_i[src + p]; }
-      __syncthreads();
-    }
-  } else {
-    // More keys than the second buffer holds: the same merge rounds in place.  Every
-    // lane first takes its keys of the round into registers and finds their new
-    // positions (reading the old order), then, after a barrier, scatters them.
-    for (int len = k; len < n; len <<= 1) {
-      double c_reg[kRunMax];
-      int i_reg[kRunMax], q_reg[kRunMax];
+  // the products of keys tid, tid + nt, ... for the end (the sort takes their places)
+  double own[KEYS];
 #pragma unroll
-      for (int j = 0; j < kRunMax; ++j) {
-        const int p = tid + j * nt;
-        q_reg[j] = -1;
-        if (p < n) {
-          const int base = (p / (2 * len)) * (2 * len);
-          const int mid = min(n, base + len), end = min(n, base + 2 * len);
-          const bool left = p < mid;
-          const double c = key_c[p];
-          int lo = left ? mid : base, hi = left ? end : mid;
-          const int first = lo;
-          while (lo < hi) {
-            const int probe = (lo + hi) >> 1;
-            const double v = key_c[probe];
-            if (left ? (v > c) : (v >= c)) lo = probe + 1; else hi = probe;
-          }
-          c_reg[j] = c;
-          i_reg[j] = key_i[p];
-          q_reg[j] = base + (left ? p - base : p - mid) + (lo - first);
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kRunMax; ++j)
-        if (q_reg[j] >= 0) { key_c[q_reg[j]] = c_reg[j]; key_i[q_reg[j]] = i_reg[j]; }
-      __syncthreads();
-    }
+  for (int q = 0; q < KEYS; ++q) {
+    own[q] = -1.0;
+    if (tid + q * nt < n) own[q] = src[slot(tid + q * nt)];
+  }
+  {
+    double* sorted;
+    if constexpr (KEYS == 1) sorted = sort_small(src, dst, npad); else sorted = sort_large(src, dst, n, k, R);
+    if (sorted != src) { dst = src; src = sorted; }
   }
 
   SV_PHASE_MARK(2)
@@ -230,37 +322,30 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     __shared__ double wave_last_g[kSelThreads / kWave];
     __shared__ int first_stop, first_open;
     if (tid == 0) { first_stop = n; first_open = n; }
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
     // every lane owns a run of R consecutive keys (R = 1 up to 1024 keys)
-    double e_run[kRunMax];
+    double e_run[KEYS];
     double run = 0.0;
 #pragma unroll
-    for (int j = 0; j < kRunMax; ++j) {
+    for (int j = 0; j < KEYS; ++j) {
       const int idx = tid * R + j;
-      if (j < R) run += (idx < n) ? key_c[idx] : 0.0;
+      if (j < R) run += (idx < n) ? src[slot(idx)] : 0.0;
       e_run[j] = run;                              // inclusive inside the run
     }
-    double e = run;                                // inclusive scan of the run totals
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      int lo = __double2loint(e), hi = __double2hiint(e);
-      lo = __shfl_up(lo, off, kWave);
-      hi = __shfl_up(hi, off, kWave);
-      if (lane >= off) e += __hiloint2double(hi, lo);
-    }
+    double e = wave_scan_f64(run);                 // inclusive scan of the run totals
     if (lane == kWave - 1) wave_tot[wave] = e;
     __syncthreads();
     for (int w = 0; w < wave; ++w) e += wave_tot[w];
     const double base = e - run;                   // E' of everything before this lane's run
-    double g_run[kRunMax];                         // G'_{idx+1} of the run's keys
+    double g_run[KEYS];                    // G'_{idx+1} of the run's keys
 #pragma unroll
-    for (int j = 0; j < kRunMax; ++j) {
+    for (int j = 0; j < KEYS; ++j) {
       const int idx = tid * R + j;
-      g_run[j] = (j < R && idx < n) ? (base + e_run[j]) / (double)lat_run[j] : 0.0;
+      g_run[j] = 0.0;
+      if (j < R && idx < n) g_run[j] = (base + e_run[j]) / (double)lat_run[j];
     }
     double g_last = 0.0;                           // G' of the last key of the run
 #pragma unroll
-    for (int j = 0; j < kRunMax; ++j) if (j == R - 1) g_last = g_run[j];
+    for (int j = 0; j < KEYS; ++j) if (j == R - 1) g_last = g_run[j];
     if (lane == kWave - 1) wave_last_g[wave] = g_last;
     __syncthreads();
     int lo = __double2loint(g_last), hi = __double2hiint(g_last);
@@ -268,57 +353,95 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     hi = __shfl_up(hi, 1, kWave);
     double g_cur = __hiloint2double(hi, lo);                                 // G' of the key before the run
     if (lane == 0) g_cur = (wave == 0) ? 0.0 : wave_last_g[wave - 1];
+    int stop = n, open = n;                        // the lane's first decided stop, first undecided comparison
 #pragma unroll
-    for (int j = 0; j < kRunMax; ++j) {
+    for (int j = 0; j < KEYS; ++j) {
       const int idx = tid * R + j;
       if (j < R && idx < n) {
         const double g_nxt = g_run[j];
         const double bound = 8.0 * (double)(n + 2) * 1.1102230246251565e-16 * fmax(g_nxt, g_cur);
         const double d = g_nxt - g_cur;
-        if (d < -bound) atomicMin(&first_stop, idx);
-        else if (!(d > bound)) atomicMin(&first_open, idx);                  // undecided (or NaN)
+        if (d < -bound) stop = min(stop, idx);
+        else if (!(d > bound)) open = min(open, idx);                        // undecided (or NaN)
         g_cur = g_nxt;
       }
     }
+    // (runs rise with the lanes: the first lane that has one holds the wavefront's first)
+    const unsigned long long stops = __ballot(stop < n), opens = __ballot(open < n);
+    if (stops && lane == (int)__builtin_ctzll(stops)) atomicMin(&first_stop, stop);
+    if (opens && lane == (int)__builtin_ctzll(opens)) atomicMin(&first_open, open);
     __syncthreads();
     if (first_open < first_stop) need_exact = true;  // block-uniform
     else if (tid == 0) m_star = first_stop;
   }
   SV_PHASE_MARK(3)
   if (need_exact) {
-    // ordered sum by one lane: key_c[M-1] becomes E_M.  The padding keys sort
-    // last, so running over whole batches of 16 never touches E_1..E_n.
+    // ordered sum by one lane: place M-1 of the other buffer becomes E_M.  The padding values
+    // sort last, so running over whole batches of 16 never touches E_1..E_n.
     __syncthreads();
     if (tid == 0) {
       double E = 0.0;
       for (int j0 = 0; j0 < npad; j0 += 16) {   // batches of loads keep LDS latency off the add chain
         double v[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = key_c[j0 + q];
+        for (int q = 0; q < 16; ++q) v[q] = src[slot(j0 + q)];
 #pragma unroll
         for (int q = 0; q < 16; ++q) { E += v[q]; v[q] = E; }
 #pragma unroll
-        for (int q = 0; q < 16; ++q) key_c[j0 + q] = v[q];
+        for (int q = 0; q < 16; ++q) dst[slot(j0 + q)] = v[q];
       }
     }
     __syncthreads();
     for (int M = tid; M < n; M += nt) {
-      const double g_cur = (M == 0) ? 0.0 : key_c[M - 1] / (double)latency[M];
-      const double g_nxt = key_c[M] / (double)latency[M + 1];
+      const double g_cur = (M == 0) ? 0.0 : dst[slot(M - 1)] / (double)latency[M];
+      const double g_nxt = dst[slot(M)] / (double)latency[M + 1];
       if (!(g_nxt > g_cur)) atomicMin(&m_star, M);
     }
   }
   __syncthreads();
   SV_PHASE_MARK(4)
+  // The M largest products: all above the M-th value, and of those equal to it as many as are
+  // missing, in the order of the keys (sequence, then position; a sequence's products never rise,
+  // so what it takes is a prefix).
   const int M = m_star;
-  int* cnt = reinterpret_cast<int*>(key_c);      // the keys are dead: selected tokens per sequence
-  for (int b = tid; b < B; b += nt) cnt[b] = 0;
-  __syncthreads();
-  for (int r = tid; r < M; r += nt) atomicAdd(&cnt[key_i[r] / k], 1);
   if (tid == 0) *total_M = M;
+  const double last = M > 0 ? src[slot(M - 1)] : 2.0;    // (no product is above 1)
+  int* above = reinterpret_cast<int*>(dst);              // per sequence, B <= n of each
+  int* equal = above + B;
+  for (int b = tid; b < 2 * B; b += nt) above[b] = 0;
+  if (tid == 0) over = 0;
   __syncthreads();
+  int mine_over = 0;
+#pragma unroll
+  for (int q = 0; q < KEYS; ++q) {
+    mine_over += __popcll(__ballot(own[q] > last));
+    if (own[q] > last) atomicAdd(&above[(tid + q * nt) / k], 1);
+    else if (own[q] == last) atomicAdd(&equal[(tid + q * nt) / k], 1);
+  }
+  if (lane == 0) atomicAdd(&over, mine_over);
+  __syncthreads();
+  {
+    const int q = (B + nt - 1) / nt, b0 = min(tid * q, B), b1 = min(b0 + q, B);
+    int mine = 0;
+    for (int b = b0; b < b1; ++b) mine += equal[b];
+    int incl = mine;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int up = __shfl_up(incl, off, kWave);
+      if (lane >= off) incl += up;
+    }
+    if (lane == kWave - 1) part[wave] = incl;
+    __syncthreads();
+    int left = M - over - (incl - mine);                 // ties still to give out at sequence b0
+    for (int w = 0; w < wave; ++w) left -= part[w];
+    for (int b = b0; b < b1; ++b) {
+      above[b] += min(max(left, 0), equal[b]);
+      left -= equal[b];
+    }
+    __syncthreads();
+  }
   SV_PHASE_MARK(5)
-  offsets_scan(cnt, B, gamma, t_offsets, part);
+  offsets_scan(above, B, gamma, t_offsets, part);
   SV_PHASE_MARK(6)
 }
 
@@ -363,6 +486,24 @@ __global__ __launch_bounds__(kSelThreads) void select_per_sequence_kernel(
 }  // namespace sv
 
 namespace sv {
+// The buffers of more than 2048 keys exceed 64 KB of LDS, which has to be allowed once per device.
+constexpr size_t kLdsDefault = 48 * 1024;
+static bool allow_select_lds() {
+  constexpr int kMaxDevices = 64;
+  static bool allowed[kMaxDevices] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (dev >= 0 && dev < kMaxDevices && allowed[dev]) return true;
+  const int bytes = (int)select_lds_bytes(kSelMax);
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<true, kKeysPerLane>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess ||
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<false, kKeysPerLane>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
+    return false;
+  if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
+  return true;
+}
+
 // Argument checks and launch shared by sv_select_length and sv_estimate_select.
 static int select_checked(const float* p_hat, int B, int k, const float* latency, int n_latency, int mode,
                           int32_t* gamma, int32_t* t_offsets, int32_t* total_M, const EstimateArgs* est,
@@ -384,19 +525,23 @@ static int select_checked(const float* p_hat, int B, int k, const float* latency
                SV_ERR_ALIGN);
   }
   hipStream_t st = as_stream(stream);
-  TapScope tap(SV_KERNEL_SELECT_LENGTH, st);
   // one lane per (padded) key up to the workgroup limit
   int threads = 64;
   while (threads < kSelThreads && threads < B * k) threads <<= 1;
   const EstimateArgs none = {};
   if (mode == SV_BATCH_GREEDY) {
-    if (est)
-      hipLaunchKernelGGL(select_batch_kernel<true>, dim3(1), dim3(threads), 0, st, p_hat, B, k, latency, gamma,
-                         t_offsets, total_M, *est);
-    else
-      hipLaunchKernelGGL(select_batch_kernel<false>, dim3(1), dim3(threads), 0, st, p_hat, B, k, latency, gamma,
-                         t_offsets, total_M, none);
+    int npad = kWave;                    // a power of two >= max(n, 64)
+    while (npad < B * k) npad <<= 1;
+    const size_t lds = select_lds_bytes(npad);
+    if (lds > kLdsDefault && !allow_select_lds()) return SV_ERR_LAUNCH;
+    TapScope tap(SV_KERNEL_SELECT_LENGTH, st);
+    const bool few = npad <= kSelThreads;
+    auto kernel = est ? (few ? select_batch_kernel<true, 1> : select_batch_kernel<true, kKeysPerLane>)
+                      : (few ? select_batch_kernel<false, 1> : select_batch_kernel<false, kKeysPerLane>);
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, st, p_hat, B, k, latency, gamma, t_offsets, total_M, npad,
+                       est ? *est : none);
   } else {
+    TapScope tap(SV_KERNEL_SELECT_LENGTH, st);
     if (est)
       hipLaunchKernelGGL(select_per_sequence_kernel<true>, dim3(1), dim3(kSelThreads), 0, st, p_hat, B, k, latency,
                          gamma, t_offsets, total_M, *est);
