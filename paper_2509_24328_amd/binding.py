@@ -137,8 +137,14 @@ def _ptr(t):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """Address of a stream (None -> the current stream of the current device).  Asked of
+    torch's C layer where that is up: torch.cuda.current_stream() builds a Stream object, 2.8 us a
+    call, a third of what a small batch's step spends on the host."""
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    if torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _dtype_tag(t):
