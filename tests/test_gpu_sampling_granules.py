@@ -55,3 +55,14 @@ def test_residual_without_mass(V, dtype):
     z_d = z_t[:, :1].clone()
     seen = _check(z_t, z_d, x, 1, range(6), fallback=True)
     assert V < 9000 or len(seen) > 1
+
+
+@pytest.mark.parametrize("offset", [0.0, 600.0, -700.0, 708.0, 712.0, -712.0, 5000.0, 1e6])
+def test_probabilities_on_either_side_of_the_short_form(offset):
+    """The short form of the probabilities holds while |log2 of the normaliser| < 1024 (logits near 710);
+    residuals of nearly equal rows, whose mass is what both forms have to leave unbiased."""
+    V = 9001
+    cfg = svgen.make_config(1, seed=int(abs(offset)) + 5, B=6, k=2, V=V, dtype="f32")
+    z_t = cfg["z_t"] + offset
+    z_d = z_t[:, :2] + 0.05 * torch.randn(z_t[:, :2].shape, generator=torch.Generator().manual_seed(3))
+    _check(z_t, z_d.contiguous(), cfg["x"], 2, range(8))
