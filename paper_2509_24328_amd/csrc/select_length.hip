@@ -17,8 +17,6 @@
 // sequence takes the products above the M-th largest value, and those equal to it
 // in the order of the keys.  Latency bound at the paper's batch sizes (8 us at 512
 // keys, 12 us at 1024, 51 us at 8192; 11.5, 17 and 130 us with merges of (value, key) pairs).
-#include <type_traits>
-
 #include "sv_bins.hpp"
 #include "sv_device.hpp"
 #include "sv_host.hpp"
@@ -144,66 +142,15 @@ __device__ __forceinline__ void estimate_keys(const EstimateArgs& e, const float
   }
 }
 
-// Value of the lane whose number differs in the bits of MASK.
-template <int MASK>
-__device__ __forceinline__ double lane_xor_f64(double v) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  auto dpp = [](int x, auto ctrl) { return __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, 0xf, 0xf, false); };
-  if constexpr (MASK == 1) {                           // quad_perm 1 0 3 2
-    lo = dpp(lo, std::integral_constant<int, 0xB1>()); hi = dpp(hi, std::integral_constant<int, 0xB1>());
-  } else if constexpr (MASK == 2) {                    // quad_perm 2 3 0 1
-    lo = dpp(lo, std::integral_constant<int, 0x4E>()); hi = dpp(hi, std::integral_constant<int, 0x4E>());
-  } else if constexpr (MASK == 4) {                    // half row mirrored (^7), quads mirrored (^3)
-    lo = dpp(dpp(lo, std::integral_constant<int, 0x141>()), std::integral_constant<int, 0x1B>());
-    hi = dpp(dpp(hi, std::integral_constant<int, 0x141>()), std::integral_constant<int, 0x1B>());
-  } else if constexpr (MASK == 8) {                    // row rotated by 8
-    lo = dpp(lo, std::integral_constant<int, 0x128>()); hi = dpp(hi, std::integral_constant<int, 0x128>());
-  } else {
-    lo = __shfl_xor(lo, MASK, kWave); hi = __shfl_xor(hi, MASK, kWave);
-  }
-  return __hiloint2double(hi, lo);
-}
-
-// Descending bitonic sort of npad <= 1024 values, one per lane of the workgroup (no NaNs).  Partners
-// inside a wavefront are reached in registers, those in another one through LDS, place by place
-// and so without bank conflicts.  Returns the buffer that holds the result.
-// Phase of 512 keys: 6300 cycles; 16000 with pairwise merges by binary search (a gather of 64 doubles
+// Descending sort of npad <= 1024 values in place, one per lane (the other buffer is used up).
+// Phase of 512 keys: 6500 cycles; 16000 with pairwise merges by binary search (a gather of 64 doubles
 // takes about 26 cycles of LDS time), 14000 with one round of searches in all eight sorted runs.
-__device__ __forceinline__ double* sort_small(double* src, double* dst, int npad) {
+__device__ __forceinline__ void sort_small(double* src, double* dst, int npad) {
   const int tid = threadIdx.x;
-  double v = src[slot(tid)];
-  auto exchange = [&](double other, int k2, int j) {
-    const bool desc = (tid & k2) == 0, lower = (tid & j) == 0;
-    v = lower == desc ? fmax(v, other) : fmin(v, other);
-  };
-  auto steps = [&](int k2, auto top) {                   // partners at top, top / 2, ..., 1
-    constexpr int J = decltype(top)::value;
-    if constexpr (J >= 32) exchange(lane_xor_f64<32>(v), k2, 32);
-    if constexpr (J >= 16) exchange(lane_xor_f64<16>(v), k2, 16);
-    if constexpr (J >= 8) exchange(lane_xor_f64<8>(v), k2, 8);
-    if constexpr (J >= 4) exchange(lane_xor_f64<4>(v), k2, 4);
-    if constexpr (J >= 2) exchange(lane_xor_f64<2>(v), k2, 2);
-    exchange(lane_xor_f64<1>(v), k2, 1);
-  };
-  steps(2, std::integral_constant<int, 1>());
-  steps(4, std::integral_constant<int, 2>());
-  steps(8, std::integral_constant<int, 4>());
-  steps(16, std::integral_constant<int, 8>());
-  steps(32, std::integral_constant<int, 16>());
-#pragma unroll 1
-  for (int k2 = kWave; k2 <= npad; k2 <<= 1) {
-#pragma unroll 1
-    for (int j = k2 >> 1; j >= kWave; j >>= 1) {
-      double* t = src; src = dst; dst = t;               // (the other buffer: the last one may still be read)
-      src[slot(tid)] = v;
-      __syncthreads();
-      exchange(src[slot(tid ^ j)], k2, j);
-    }
-    steps(k2, std::integral_constant<int, 32>());
-  }
-  dst[slot(tid)] = v;
+  const double v = block_sort<true>(src[slot(tid)], dst, src, npad, [](int i) { return slot(i); });
+  __syncthreads();                                       // (both buffers may still be read)
+  src[slot(tid)] = v;
   __syncthreads();
-  return dst;
 }
 
 // Descending sort of n > 1024 values that come in sorted runs of `len`: rounds of pairwise merges between
@@ -301,8 +248,8 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     if (tid + q * nt < n) own[q] = src[slot(tid + q * nt)];
   }
   {
-    double* sorted;
-    if constexpr (KEYS == 1) sorted = sort_small(src, dst, npad); else sorted = sort_large(src, dst, n, k, R);
+    double* sorted = src;
+    if constexpr (KEYS == 1) sort_small(src, dst, npad); else sorted = sort_large(src, dst, n, k, R);
     if (sorted != src) { dst = src; src = sorted; }
   }
 

@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sv {
 
 constexpr int kWave = 64;
@@ -205,6 +207,75 @@ __device__ __forceinline__ double lane_f64(double v, int lane) {
 }
 __device__ __forceinline__ float lane_f32(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Value of the lane whose number differs in the bits of MASK (a power of two): register moves up to 8,
+// the LDS crossbar above.
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+template <int MASK>
+__device__ __forceinline__ int lane_xor(int v) {
+  if constexpr (MASK == 1) return dpp_move<0xB1>(v);                   // quad_perm 1 0 3 2
+  else if constexpr (MASK == 2) return dpp_move<0x4E>(v);              // quad_perm 2 3 0 1
+  else if constexpr (MASK == 4) return dpp_move<0x1B>(dpp_move<0x141>(v));   // half row mirrored (^7), quads mirrored (^3)
+  else if constexpr (MASK == 8) return dpp_move<0x128>(v);             // row rotated by 8
+  else return __shfl_xor(v, MASK, kWave);
+}
+template <int MASK>
+__device__ __forceinline__ double lane_xor(double v) {
+  return __hiloint2double(lane_xor<MASK>(__double2hiint(v)), lane_xor<MASK>(__double2loint(v)));
+}
+template <int MASK>
+__device__ __forceinline__ float lane_xor(float v) {
+  return __int_as_float(lane_xor<MASK>(__float_as_int(v)));
+}
+
+__device__ __forceinline__ double max_of(double a, double b) { return fmax(a, b); }
+__device__ __forceinline__ double min_of(double a, double b) { return fmin(a, b); }
+__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ float min_of(float a, float b) { return fminf(a, b); }
+
+// Bitonic sort of n (a power of two, 64 to 1024) values without NaNs, one per lane of the workgroup,
+// in descending or ascending order.  Partners inside a wavefront are reached in registers,
+// those in another one through two LDS buffers, place by place (no bank conflicts).  The sizes from 64 up
+// share one copy of the steps inside a wavefront: a workgroup that sorts once fetches its
+// instructions as it goes.  (One copy for the smaller sizes too, most of whose steps it branches
+// around: 11800 cycles for 512 doubles, 6500 this way.)
+template <bool DESCENDING, class T, class Slot>
+__device__ __forceinline__ T block_sort(T v, T* a, T* b, int n, Slot&& slot) {
+  const int tid = threadIdx.x;
+  auto exchange = [&](T other, int k2, int j) {
+    const bool down = ((tid & k2) == 0) == DESCENDING, lower = (tid & j) == 0;
+    v = lower == down ? max_of(v, other) : min_of(v, other);
+  };
+  auto steps = [&](int k2, auto top) {                   // partners at top, top / 2, ..., 1
+    constexpr int J = decltype(top)::value;
+    if constexpr (J >= 32) exchange(lane_xor<32>(v), k2, 32);
+    if constexpr (J >= 16) exchange(lane_xor<16>(v), k2, 16);
+    if constexpr (J >= 8) exchange(lane_xor<8>(v), k2, 8);
+    if constexpr (J >= 4) exchange(lane_xor<4>(v), k2, 4);
+    if constexpr (J >= 2) exchange(lane_xor<2>(v), k2, 2);
+    exchange(lane_xor<1>(v), k2, 1);
+  };
+  steps(2, std::integral_constant<int, 1>());
+  steps(4, std::integral_constant<int, 2>());
+  steps(8, std::integral_constant<int, 4>());
+  steps(16, std::integral_constant<int, 8>());
+  steps(32, std::integral_constant<int, 16>());
+#pragma unroll 1
+  for (int k2 = kWave; k2 <= n; k2 <<= 1) {
+#pragma unroll 1
+    for (int j = k2 >> 1; j >= kWave; j >>= 1) {
+      a[slot(tid)] = v;
+      __syncthreads();
+      exchange(a[slot(tid ^ j)], k2, j);
+      T* t = a; a = b; b = t;                           // (the other buffer next: this one may still be read)
+    }
+    steps(k2, std::integral_constant<int, 32>());
+  }
+  return v;
 }
 
 __device__ __forceinline__ float wave_max_f32(float v) {
