@@ -562,8 +562,9 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
     flags |= SV_FLAG_RESIDUAL_FALLBACK;
     __syncthreads();                                                   // all have read the residual's masses
     for (int g = wave; g < G; g += kWaves) {
-      const double m = wave_sum_f64(
-          lane_mass<DT, false, CUT, false, 8>(sr, g * kGranule, min(a.V, (g + 1) * kGranule), lane, kWave));
+      const int v0 = g * kGranule, v1 = min(a.V, v0 + kGranule);
+      const double m = wave_sum_f64(sr.small ? lane_mass<DT, false, CUT, true, 8>(sr, v0, v1, lane, kWave)
+                                             : lane_mass<DT, false, CUT, false, 8>(sr, v0, v1, lane, kWave));
       if (lane == 0) mass[g] = m;
     }
     __syncthreads();
@@ -595,33 +596,37 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   float w[kRun];
   double mine = 0.0;
   const int nvec = a.V / EPV;
-  if (v0 / EPV + kRun / EPV <= nvec) {
-    u32x4 qt[kRun / EPV], qd[kRun / EPV];
+  auto weigh = [&](auto small) {                          // the form the mass pass used: the same weights, bit for bit
+    constexpr bool kSmall = decltype(small)::value;
+    if (v0 / EPV + kRun / EPV <= nvec) {
+      u32x4 qt[kRun / EPV], qd[kRun / EPV];
 #pragma unroll
-    for (int i = 0; i < kRun / EPV; ++i) {
-      qt[i] = load_vec(sr.row_t, v0 / EPV + i);
-      qd[i] = sr.resid ? load_vec(sr.row_d, v0 / EPV + i) : qt[i];
-    }
+      for (int i = 0; i < kRun / EPV; ++i) {
+        qt[i] = load_vec(sr.row_t, v0 / EPV + i);
+        qd[i] = sr.resid ? load_vec(sr.row_d, v0 / EPV + i) : qt[i];
+      }
 #pragma unroll
-    for (int i = 0; i < kRun / EPV; ++i) {
-      float ft[EPV], fd[EPV];
-      unpack<DT>(qt[i], ft);
-      unpack<DT>(qd[i], fd);
+      for (int i = 0; i < kRun / EPV; ++i) {
+        float ft[EPV], fd[EPV];
+        unpack<DT>(qt[i], ft);
+        unpack<DT>(qd[i], fd);
 #pragma unroll
-      for (int j = 0; j < EPV; ++j)
-        w[i * EPV + j] = sr.resid ? sr.template weight_r<false>(ft[j], fd[j]) : sr.template weight_t<false>(ft[j]);
-    }
-  } else {
+        for (int j = 0; j < EPV; ++j)
+          w[i * EPV + j] = sr.resid ? sr.template weight_r<kSmall>(ft[j], fd[j]) : sr.template weight_t<kSmall>(ft[j]);
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < kRun; ++j) {
-      w[j] = 0.f;
-      if (v0 + j < a.V) {
-        const float zt = load_elem<DT>(sr.row_t, v0 + j);
-        w[j] = sr.resid ? sr.template weight_r<false>(zt, load_elem<DT>(sr.row_d, v0 + j))
-                        : sr.template weight_t<false>(zt);
+      for (int j = 0; j < kRun; ++j) {
+        w[j] = 0.f;
+        if (v0 + j < a.V) {
+          const float zt = load_elem<DT>(sr.row_t, v0 + j);
+          w[j] = sr.resid ? sr.template weight_r<kSmall>(zt, load_elem<DT>(sr.row_d, v0 + j))
+                          : sr.template weight_t<kSmall>(zt);
+        }
       }
     }
-  }
+  };
+  if (sr.small) weigh(std::true_type()); else weigh(std::false_type());
 #pragma unroll
   for (int j = 0; j < kRun; ++j) mine += (double)w[j];
   SV_PHASE_MARK(3)
