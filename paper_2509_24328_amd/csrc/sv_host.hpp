@@ -52,7 +52,8 @@ struct VerifyWs {
   float* m_d;         // [B*k*kMaxSplit]
   float* zx_t;        // [B*k] target logit of the drafted token
   float* zx_d;        // [B*k] draft logit of the drafted token
-  double* mass;       // [B*n_granules] mass of each granule of the sampling row (residual or target)
+  double* mass;       // [B*n_granules] mass of each granule of the sampling row: the residual's or the target's;
+                      // a granule without residual: the target's, negative
   Plan* plan;          // [B] per-sequence sampling plan (verify_sample.hip)
   // written by sv_row_stats, read by sv_verify_sample_chained
   ChainHeader* chain;  // [1]

@@ -19,7 +19,8 @@
 //     logarithms: less than a kernel boundary costs); the one of chunk 0 writes
 //     the accepted tokens and the plan of the sampling stage.  Then the
 //     workgroup sums its 8192-entry chunk of the sampling row in granules of
-//     4096: residual max(0, P_t - P_d) after a rejection, P_t otherwise.
+//     4096: residual max(0, P_t - P_d) after a rejection, P_t otherwise and
+//     where a granule has no residual (the residual may turn out to be empty).
 //     Touches B rows (pairs).
 //
 //  3. verify_pick_kernel   one workgroup per sequence: scans the granule masses
@@ -411,6 +412,7 @@ struct SampleRow {
   float cut_t, cut_d;
   bool resid;                // weight max(0, P_t - P_d), else P_t
   bool small;                // both normalisers allow the short form of the probabilities
+  SampleRow() = default;
   __device__ __forceinline__ SampleRow(const VerifyArgs& a, int b, const Plan& pl) {
     resid = pl.resid != 0;
     row_t = target_row<DT>(a, b, pl.n);
@@ -424,8 +426,8 @@ struct SampleRow {
   template <bool SMALL>
   __device__ __forceinline__ float weight_t(float zt) const { return pt.p<SMALL>(CUT ? cut_below(zt, cut_t) : zt); }
   template <bool SMALL>
-  __device__ __forceinline__ float weight_r(float zt, float zd) const {
-    return fmaxf(0.f, weight_t<SMALL>(zt) - pd.p<SMALL>(CUT ? cut_below(zd, cut_d) : zd));
+  __device__ __forceinline__ float weight_r(float wt, float zd) const {          // wt: weight_t of the entry
+    return fmaxf(0.f, wt - pd.p<SMALL>(CUT ? cut_below(zd, cut_d) : zd));
   }
 };
 
@@ -433,11 +435,18 @@ struct SampleRow {
 // `lane` of `lanes` (v0 a multiple of the vector length).  The pick stage forms the same weights
 // again and adds them in another order; the two agree far inside the band of
 // SV_FLAG_NEAR_CDF_EDGE because the additions are fp64.
-// U: vector (pairs) in flight per lane.
-template <int DT, bool RESID, bool CUT, bool SMALL, int U = 4>
-__device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0, int v1, int lane, int lanes) {
-  constexpr int EPV = Elem<DT>::per_vec;
+// RESID && CUT: mass_t receives the sum of the target's weights as well (few vectors of a warped row
+// come that far).
+template <int DT, bool RESID, bool CUT, bool SMALL>
+__device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0, int v1, int lane, int lanes,
+                                            double& mass_t) {
+  constexpr int EPV = Elem<DT>::per_vec, U = 4;              // U: vector (pairs) in flight per lane
   double acc = 0.0;
+  auto add = [&](float zt, float zd) {
+    const float wt = sr.template weight_t<SMALL>(zt);
+    acc += (double)(RESID ? sr.template weight_r<SMALL>(wt, zd) : wt);
+    if (RESID && CUT) mass_t += (double)wt;
+  };
   auto add_vec = [&](const u32x4& qt, const u32x4& qd) {
     float ft[EPV], fd[EPV];
     unpack<DT>(qt, ft);
@@ -451,7 +460,7 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
     }
     if (RESID) unpack<DT>(qd, fd);
 #pragma unroll
-    for (int j = 0; j < EPV; ++j) acc += (double)(RESID ? sr.template weight_r<SMALL>(ft[j], fd[j]) : sr.template weight_t<SMALL>(ft[j]));
+    for (int j = 0; j < EPV; ++j) add(ft[j], RESID ? fd[j] : 0.f);
   };
   const int i1 = v1 / EPV;
   for (int i = v0 / EPV + lane; i < i1; i += U * lanes) {
@@ -467,11 +476,22 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
     for (int u = 0; u < U; ++u)
       if (i + u * lanes < i1) add_vec(qt[u], qd[u]);
   }
-  for (int v = max(v0, i1 * EPV) + lane; v < v1; v += lanes) {
-    const float zt = load_elem<DT>(sr.row_t, v);
-    acc += (double)(RESID ? sr.template weight_r<SMALL>(zt, load_elem<DT>(sr.row_d, v)) : sr.template weight_t<SMALL>(zt));
-  }
+  for (int v = max(v0, i1 * EPV) + lane; v < v1; v += lanes)
+    add(load_elem<DT>(sr.row_t, v), RESID ? load_elem<DT>(sr.row_d, v) : 0.f);
   return acc;
+}
+
+// The target's masses of an unwarped row, out of line: inlined, it costs the mass kernel 17 to 29 registers
+// more than it has.
+template <int DT>
+__device__ __noinline__ double lane_mass_of_target(const void* row_t, ProbRow pt, int v0, int v1, int lane, int lanes) {
+  SampleRow<DT, false> sr;
+  sr.row_t = sr.row_d = row_t;
+  sr.pt = pt;
+  sr.resid = false;
+  double none = 0.0;
+  return pt.small ? lane_mass<DT, false, false, true>(sr, v0, v1, lane, lanes, none)
+                  : lane_mass<DT, false, false, false>(sr, v0, v1, lane, lanes, none);
 }
 
 // grid (chunks, B): the accept decision of the sequence (every workgroup forms it for
@@ -482,8 +502,9 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
 template <int DT, bool CUT, bool CHAIN>
 __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyArgs a) {
   __shared__ Plan plan;
-  __shared__ double part[kSampleThreads / kWave];
   constexpr int kLanes = kSampleThreads * kGranule / kChunk;           // lanes per granule
+  constexpr int kGran = kChunk / kGranule, kWaves = kLanes / kWave;    // granules, wavefronts per granule
+  __shared__ double part[2][kGran * kWaves];                           // mass, target's mass where there is none
   const int b = blockIdx.y, c = blockIdx.x;
   const int tid = threadIdx.x;
   SV_PHASE_MARK(6)
@@ -493,27 +514,54 @@ __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyAr
   const Plan pl = plan;
   const int g = tid / kLanes, lane = tid - g * kLanes;
   const int v0 = c * kChunk + g * kGranule, v1 = min(a.V, v0 + kGranule);
-  double acc = 0.0;
-  if (pl.target_ok && v0 < v1) {
+  const bool live = pl.target_ok && v0 < v1, resid = pl.resid != 0;
+  double acc = 0.0, acc_t = 0.0;
+  if (live) {
     const SampleRow<DT, CUT> sr(a, b, pl);
     if (sr.small)
-      acc = sr.resid ? lane_mass<DT, true, CUT, true>(sr, v0, v1, lane, kLanes)
-                     : lane_mass<DT, false, CUT, true>(sr, v0, v1, lane, kLanes);
+      acc = resid ? lane_mass<DT, true, CUT, true>(sr, v0, v1, lane, kLanes, acc_t)
+                  : lane_mass<DT, false, CUT, true>(sr, v0, v1, lane, kLanes, acc_t);
     else
-      acc = sr.resid ? lane_mass<DT, true, CUT, false>(sr, v0, v1, lane, kLanes)
-                     : lane_mass<DT, false, CUT, false>(sr, v0, v1, lane, kLanes);
+      acc = resid ? lane_mass<DT, true, CUT, false>(sr, v0, v1, lane, kLanes, acc_t)
+                  : lane_mass<DT, false, CUT, false>(sr, v0, v1, lane, kLanes, acc_t);
   }
+  const bool first = (tid & (kWave - 1)) == 0;
   acc = wave_sum_f64(acc);
-  if ((tid & (kWave - 1)) == 0) part[tid / kWave] = acc;
+  if (CUT && acc == 0.0 && __any(acc_t != 0.0)) acc_t = wave_sum_f64(acc_t);     // (read only where acc = 0)
+  if (first) { part[0][tid / kWave] = acc; part[1][tid / kWave] = acc_t; }
   __syncthreads();
-  SV_PHASE_MARK(8)
-  constexpr int kWaves = kLanes / kWave;                               // wavefronts per granule
-  if (lane == 0 && v0 < v1) {
-    double m = part[g * kWaves];
+  auto granule = [&](const double* p, int q) {
+    double sum = p[q * kWaves];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m += part[g * kWaves + w];
-    a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m;
+    for (int w = 1; w < kWaves; ++w) sum += p[q * kWaves + w];
+    return sum;
+  };
+  double m = granule(part[0], g);
+  // Without any residual the target distribution is drawn from (a few percent of warped batches
+  // hold such a sequence: two nuclei of the same single token).  A granule that has none therefore leaves the
+  // target's mass, with a minus sign, and the pick reads either kind from the same place: 5.9 us whatever
+  // the batch holds, where its one workgroup needed 17.8 us to sum the target's row of V = 128256 bf16 itself (80 us
+  // at 2^20).  Price under cutoffs: 0.4 us of this kernel at 32 x 128256, 0.9 us at 256 x 32000 with thousands
+  // of tokens per nucleus.
+  if (resid) {
+    bool some_empty = false;                                           // (the same in every lane)
+#pragma unroll
+    for (int q = 0; q < kGran; ++q) some_empty |= granule(part[0], q) == 0.0;
+    if (!CUT && some_empty) {
+      // (a rare thing without cutoffs: the target's row is read once more, from cache)
+      if (live && m == 0.0) {
+        ProbRow pt;
+        pt.set(plan.lse_t, a.sc_t);
+        acc_t = lane_mass_of_target<DT>(target_row<DT>(a, b, plan.n), pt, v0, v1, lane, kLanes);
+      }
+      acc_t = wave_sum_f64(acc_t);
+      if (first) part[1][tid / kWave] = acc_t;
+      __syncthreads();
+    }
+    if (m == 0.0) m = -granule(part[1], g);
   }
+  SV_PHASE_MARK(8)
+  if (lane == 0 && v0 < v1) a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m;
   SV_PHASE_MARK(9)
 }
 
@@ -532,7 +580,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   SV_PHASE_MARK(0)
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int G = n_granules(a.V);
-  double* mass = a.ws.mass + (size_t)b * G;
+  const double* mass = a.ws.mass + (size_t)b * G;
   const Plan pl = a.ws.plan[b];
   if (tid == 0) last_positive = -1;
   SampleRow<DT, CUT> sr(a, b, pl);
@@ -543,32 +591,21 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   // every wavefront scans all granule masses: lane l owns the run [l * q, (l + 1) * q)
   const int q = (G + kWave - 1) / kWave;
   const int g0 = min(lane * q, G), g1 = min(g0 + q, G);
-  double run = 0.0, incl = 0.0, W = 0.0;
-  auto scan_masses = [&]() {
-    run = 0.0;
-    for (int j = g0; j < g1; ++j) run += mass[j];
-    incl = wave_scan_f64(run);
-    W = lane_f64(incl, kWave - 1);
-  };
-  scan_masses();
-  if (pl.target_ok && sr.resid && !(isfinite(W) && W > 0.0)) {
-    // A residual of any mass is drawn from; only one without mass (or a non-finite one) is not: the
-    // target distribution instead, whose masses nobody has formed yet.  Rows that are equal
-    // and whose drafted token has no mass in either, such as two nuclei of the same single token: a
-    // few percent of warped batches, so the granules are spread over the wavefronts and take the
-    // residual's places in the workspace (V = 128256 bf16, nucleus cutoffs: 17.5 us, 48 us with the
-    // workgroup walking them one after another, twice).
+  double run = 0.0, run_t = 0.0;                                       // (negative: see the mass pass)
+  for (int j = g0; j < g1; ++j) {
+    const double m = mass[j];
+    run += fmax(m, 0.0);
+    run_t += fmax(-m, 0.0);
+  }
+  double incl = wave_scan_f64(run), W = lane_f64(incl, kWave - 1);
+  const bool empty = sr.resid && !(W > 0.0);
+  if (pl.target_ok && empty) {
+    // a residual of any mass is drawn from; only one without mass is not: the target distribution instead
     sr.resid = false;
     flags |= SV_FLAG_RESIDUAL_FALLBACK;
-    __syncthreads();                                                   // all have read the residual's masses
-    for (int g = wave; g < G; g += kWaves) {
-      const int v0 = g * kGranule, v1 = min(a.V, v0 + kGranule);
-      const double m = wave_sum_f64(sr.small ? lane_mass<DT, false, CUT, true, 8>(sr, v0, v1, lane, kWave)
-                                             : lane_mass<DT, false, CUT, false, 8>(sr, v0, v1, lane, kWave));
-      if (lane == 0) mass[g] = m;
-    }
-    __syncthreads();
-    scan_masses();
+    run = run_t;
+    incl = wave_scan_f64(run);
+    W = lane_f64(incl, kWave - 1);
   }
   int gran = -1;
   double tau_local = 0.0;                                              // threshold inside the granule
@@ -579,7 +616,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
     double before = lane_f64(incl - run, owner);
     const int h0 = min(owner * q, G), h1 = min(h0 + q, G);
     for (int g = h0; g < h1; ++g) {
-      const double m = mass[g];
+      const double m = fmax(empty ? -mass[g] : mass[g], 0.0);
       if (m > 0.0) { gran = g; tau_local = tau - before; }             // (rounding: the last granule with mass)
       if (before + m > tau) break;
       before += m;
@@ -596,8 +633,12 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   float w[kRun];
   double mine = 0.0;
   const int nvec = a.V / EPV;
-  auto weigh = [&](auto small) {                          // the form the mass pass used: the same weights, bit for bit
+  auto weight = [&](auto small, float zt, float zd) {     // the form the mass pass used: the same weights, bit for bit
     constexpr bool kSmall = decltype(small)::value;
+    const float wt = sr.template weight_t<kSmall>(zt);
+    return sr.resid ? sr.template weight_r<kSmall>(wt, zd) : wt;
+  };
+  auto weigh = [&](auto small) {
     if (v0 / EPV + kRun / EPV <= nvec) {
       u32x4 qt[kRun / EPV], qd[kRun / EPV];
 #pragma unroll
@@ -612,7 +653,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
         unpack<DT>(qd[i], fd);
 #pragma unroll
         for (int j = 0; j < EPV; ++j)
-          w[i * EPV + j] = sr.resid ? sr.template weight_r<kSmall>(ft[j], fd[j]) : sr.template weight_t<kSmall>(ft[j]);
+          w[i * EPV + j] = weight(small, ft[j], fd[j]);
       }
     } else {
 #pragma unroll
@@ -620,8 +661,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
         w[j] = 0.f;
         if (v0 + j < a.V) {
           const float zt = load_elem<DT>(sr.row_t, v0 + j);
-          w[j] = sr.resid ? sr.template weight_r<kSmall>(zt, load_elem<DT>(sr.row_d, v0 + j))
-                          : sr.template weight_t<kSmall>(zt);
+          w[j] = weight(small, zt, sr.resid ? load_elem<DT>(sr.row_d, v0 + j) : 0.f);
         }
       }
     }

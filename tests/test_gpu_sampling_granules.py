@@ -1,13 +1,16 @@
 """The sampling stage at the edges of its 4096-entry granules: vocabularies around one lane's run,
 a granule and a chunk, more granules than a wavefront has lanes, all mass in one granule, and a
-residual without mass, for which the granules of the target row are summed on the spot."""
+residual without mass, with and without support cutoffs, where the target's masses are drawn from."""
 import numpy as np
 import pytest
 import torch
 
 import svgen
+from oracle import sv_oracle as O
+from oracle import warp_oracle as W
 
 import harness as H
+from test_gpu_warped import _cut32, _gpu_verify_warped
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +69,92 @@ def test_probabilities_on_either_side_of_the_short_form(offset):
     z_t = cfg["z_t"] + offset
     z_d = z_t[:, :2] + 0.05 * torch.randn(z_t[:, :2].shape, generator=torch.Generator().manual_seed(3))
     _check(z_t, z_d.contiguous(), cfg["x"], 2, range(8))
+
+
+def _nuclei(V, dtype, B, peaks_t, peaks_d, seed):
+    """Flat rows under a few peaks of mass: z_t [B, 2, V], z_d [B, 1, V], a drafted token under all peaks, and
+    the cutoffs and warped rows at P = 0.9, where the peaks are the nucleus."""
+    g = torch.Generator().manual_seed(seed)
+    z_t = torch.randn((B, 2, V), generator=g)
+    z_d = z_t[:, :1].clone()
+    for j, v in enumerate(peaks_t):
+        z_t[:, :, v] = 24.0 + 0.25 * j
+    for j, v in enumerate(peaks_d):
+        z_d[:, :, v] = 24.0 + 0.25 * j
+    z_t, z_d = z_t.to(dtype), z_d.to(dtype)
+    y_t, cut_t, _ = W.warp_rows(svgen.to_numpy_bits(z_t), 1.0, 0, 0.9)
+    y_d, cut_d, _ = W.warp_rows(svgen.to_numpy_bits(z_d), 1.0, 0, 0.9)
+    assert np.isfinite(y_t[:, 0]).sum() == B * len(peaks_t) and np.isfinite(y_d).sum() == B * len(peaks_d)
+    x = torch.full((B, 1), (set(range(len(peaks_t) + len(peaks_d) + 1)) - set(peaks_t) - set(peaks_d)).pop(),
+                   dtype=torch.int32)
+    return z_t, z_d, x, y_t, y_d, _cut32(cut_t), _cut32(cut_d)
+
+
+@pytest.mark.parametrize("chained", [False, True])
+@pytest.mark.parametrize("V,dtype", [(300, torch.float32), (9001, torch.float32), (12290, torch.bfloat16),
+                                     (40000, torch.bfloat16), (270001, torch.bfloat16), (280003, torch.float32)])
+def test_residual_without_mass_under_cutoffs(V, dtype, chained):
+    """Equal nuclei of one token and of several, in one granule and in different ones, the drafted token outside
+    both: no residual, the target distribution instead.  Then a draft nucleus that lacks one of the target's
+    tokens, or has another one's place: a residual in one granule, none in the others."""
+    P = H.sv()
+    B = 6
+    far = [V - 1, 2, V // 2, V // 3]
+    for peaks_t, peaks_d, empty in (([V // 2], [V // 2], True), ([7, 9, 30], [7, 9, 30], True), (far, far, True),
+                                    (far, far[:3], False), ([V - 1], [2], False)):
+        z_t, z_d, x, y_t, y_d, cut_t, cut_d = _nuclei(V, dtype, B, peaks_t, peaks_d, V)
+        z_t, z_d = z_t.cuda(), z_d.cuda()
+        for seed in range(3):
+            ref = H.oracle_verify(y_t, y_d, x.numpy(), seed=seed, step=4)
+            if chained:
+                f32 = lambda: torch.empty((B, 1), dtype=torch.float32, device="cuda")
+                i32 = lambda *s: torch.full(s, -5, dtype=torch.int32, device="cuda")
+                ws = P.alloc_workspace(B, 1, V, P.binding._dtype_tag(z_d))
+                xd, tokens, n_acc, flags, ratio = x.cuda(), i32(B, 2), i32(B), i32(B), f32()
+                P.sv_row_stats_warped(z_d, z_d, xd, 1.0, cut_d, 1.0, cut_d, f32(), f32(), f32(), f32(), None, None, ws)
+                P.sv_verify_sample_warped_chained(z_t, None, z_d, xd, None, 1.0, cut_t, 1.0, cut_d, seed, 4, tokens,
+                                                  n_acc, flags, ratio, ws)
+                torch.cuda.synchronize()
+                got = dict(tokens=tokens.cpu().numpy(), n_accept=n_acc.cpu().numpy(),
+                           flags=flags.cpu().numpy().astype(np.uint32), ratio=ratio.cpu().numpy())
+            else:
+                got = _gpu_verify_warped(z_t, z_d, x.cuda(), 1.0, cut_t, 1.0, cut_d, seed=seed, step=4)
+            assert (got["n_accept"] == 0).all() and (ref["n_accept"] == 0).all()
+            assert (((got["flags"] & O.FLAG_RESIDUAL_FALLBACK) != 0) == empty).all()
+            assert np.isin(got["tokens"][:, 0], peaks_t).all()
+            clear = ((got["flags"] | ref["flags"]) & O.FLAG_NEAR_CDF_EDGE) == 0
+            assert clear.sum() >= B - 1 and np.array_equal(got["tokens"][clear], ref["tokens"][clear])
+
+
+@pytest.mark.parametrize("warped", [False, True])
+def test_an_empty_residual_costs_the_token_pick_no_walk(warped):
+    """The pick reads one granule of the row whether the residual has mass or not.  At 2^20 entries a walk over
+    the row by its one workgroup takes more than ten times as long as that."""
+    P = H.sv()
+    V = 1 << 20
+    mid = V // 2 + 5
+    times = []
+    for peaks_d in ([mid], [3]):
+        z_t, z_d, x, _, _, cut_t, cut_d = _nuclei(V, torch.bfloat16, 1, [mid], peaks_d, 1)
+        if not warped:
+            z_t[:, :, int(x[0, 0])] = z_d[:, :, int(x[0, 0])] = -np.inf
+        z_t, z_d, x = z_t.cuda(), z_d.cuda(), x.cuda()
+        i32 = lambda *s: torch.empty(s, dtype=torch.int32, device="cuda")
+        tokens, n_acc, flags = i32(1, 2), i32(1), i32(1)
+        ws = P.alloc_workspace(1, 1, V, P.SV_BF16)
+        best = np.inf
+        for _ in range(20):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record(), e1.record()                       # (the handles exist from here on)
+            P.sv_set_timing_events(P.binding.SV_KERNEL_VERIFY_PICK, e0.cuda_event, e1.cuda_event)
+            if warped:
+                P.sv_verify_sample_warped(z_t, None, z_d, x, None, 1.0, cut_t, 1.0, cut_d, 0, 0, tokens, n_acc, flags,
+                                          None, ws)
+            else:
+                P.sv_verify_sample(z_t, None, z_d, x, None, 0, 0, tokens, n_acc, flags, None, ws)
+            P.sv_set_timing_events(P.binding.SV_KERNEL_VERIFY_PICK, None, None)
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 1e3)
+        assert bool(int(flags[0]) & O.FLAG_RESIDUAL_FALLBACK) == (peaks_d == [mid]) and int(tokens[0, 0]) == mid
+        times.append(best)
+    assert times[0] < 3.0 * times[1], times
