@@ -19,8 +19,8 @@
 //     logarithms: less than a kernel boundary costs); the one of chunk 0 writes
 //     the accepted tokens and the plan of the sampling stage.  Then the
 //     workgroup sums its 8192-entry chunk of the sampling row in granules of
-//     4096: residual max(0, P_t - P_d) after a rejection, P_t otherwise and
-//     where a granule has no residual (the residual may turn out to be empty).
+//     4096: residual max(0, P_t - P_d) after a rejection, P_t otherwise and,
+//     if the residual may turn out to be empty, where a granule has none.
 //     Touches B rows (pairs).
 //
 //  3. verify_pick_kernel   one workgroup per sequence: scans the granule masses
@@ -178,7 +178,7 @@ __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScra
   // round trips to memory (6 + the rest, whose loads also go out together) instead of three or four
   if (row) sweep_online<DT, CUT, true, 6>(row, a.V, r.part, a.split, acc[0], L, cut);
   MS merged[1];
-  block_merge<1>(acc, sm, merged, L);
+  block_merge(acc, sm, merged, L);
   r.ms = merged[0];                                      // s = 0 for a missing row => bad row
   if (threadIdx.x == 0 && r.part == 0 && r.i < a.k && row) {
     const int tok = a.x[r.b * a.k + r.i];
@@ -294,7 +294,7 @@ struct alignas(16) Plan {
   double lse_t, lse_d;
   int n;               // accepted count = position that is sampled
   uint32_t flags;
-  int resid;           // 1: residual max(0, P_t - P_d), 0: target distribution
+  int resid;           // 0: target distribution; 1: residual max(0, P_t - P_d); 2: residual that may be empty
   int target_ok;
 };
 
@@ -314,6 +314,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   bool accept = true;
   uint32_t fl = 0;
   double rho = __builtin_nan("");
+  float gap = 0.f;                                // about P_d(x) - P_t(x); NaN where neither holds x
   double lse_t = __builtin_nan(""), lse_d = __builtin_nan("");
   bool have_target = false;
   // chained: everything the statistics pass left goes into flight at once, before any branch
@@ -353,6 +354,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
       const double lt = (double)zx_t * a.sc_t.inv_t - lse_t;
       const double ld = (double)zx_d * a.sc_d.inv_t - lse_d;
       rho = exp(lt - ld);                         // -inf - -inf = NaN: rejected
+      gap = exp2_fast((float)(ld * kLog2e)) * (1.f - (float)rho);
     }
     const U4 r = philox4x32_10((uint32_t)i, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
     const double u = unit_from_word(r.w[0]);
@@ -371,12 +373,18 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   }
   // the plan of position n, from the values of lane n (position n = 64, the bonus
   // row of a fully accepted k = 64, has no lane: lane 0 forms them itself)
+  // The residual's mass is at least the gap at the rejected token, so that it can only be found empty where
+  // the gap is within what the computed probabilities of two rows may be off in sum: 6e-6 for the entries,
+  // and for the normalisers the roundings of fp32 lane sums of at most V / 1024 terms each, all to one side.
+  const float may_be_off = 1e-5f + (float)V * (1.f / 1024.f) * 1.2e-7f;
   double lse_t_n, lse_d_n;
-  int have_target_n;
+  int have_target_n, maybe_empty = 0;
   if (n < kWave) {
     lse_t_n = __shfl(lse_t, n, kWave);
     lse_d_n = __shfl(lse_d, n, kWave);
-    have_target_n = __shfl((int)have_target, n, kWave);
+    const int both = __shfl((int)have_target | (gap > may_be_off ? 0 : 2), n, kWave);
+    have_target_n = both & 1;
+    maybe_empty = both >> 1;
   } else {
     lse_t_n = lse_from_ms(target_ms(a, b, n), a.sc_t);
     lse_d_n = __builtin_nan("");
@@ -394,7 +402,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     if (CHAIN && !chain_ok) flags |= SV_FLAG_NO_CHAIN;
     Plan pl;
     pl.lse_t = lse_t_n; pl.lse_d = resid ? lse_d_n : 0.0; pl.n = n; pl.flags = flags;
-    pl.resid = resid ? 1 : 0; pl.target_ok = target_ok ? 1 : 0;
+    pl.resid = resid ? 1 + maybe_empty : 0; pl.target_ok = target_ok ? 1 : 0;
     *plan_out = pl;
     if (publish) {
       a.ws.plan[b] = pl;
@@ -411,10 +419,11 @@ struct SampleRow {
   ProbRow pt, pd;
   float cut_t, cut_d;
   bool resid;                // weight max(0, P_t - P_d), else P_t
+  bool maybe_empty;          // (wavefront-uniform to the compiler as well)
   bool small;                // both normalisers allow the short form of the probabilities
-  SampleRow() = default;
   __device__ __forceinline__ SampleRow(const VerifyArgs& a, int b, const Plan& pl) {
     resid = pl.resid != 0;
+    maybe_empty = __builtin_amdgcn_readfirstlane(pl.resid) == 2;
     row_t = target_row<DT>(a, b, pl.n);
     row_d = resid ? draft_row<DT>(a, b, pl.n) : row_t;
     pt.set(pl.lse_t, a.sc_t);
@@ -435,18 +444,12 @@ struct SampleRow {
 // `lane` of `lanes` (v0 a multiple of the vector length).  The pick stage forms the same weights
 // again and adds them in another order; the two agree far inside the band of
 // SV_FLAG_NEAR_CDF_EDGE because the additions are fp64.
-// RESID && CUT: mass_t receives the sum of the target's weights as well (few vectors of a warped row
-// come that far).
-template <int DT, bool RESID, bool CUT, bool SMALL>
+// BOTH: mass_t receives the target's mass beside the residual's.
+template <int DT, bool RESID, bool BOTH, bool CUT, bool SMALL>
 __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0, int v1, int lane, int lanes,
                                             double& mass_t) {
   constexpr int EPV = Elem<DT>::per_vec, U = 4;              // U: vector (pairs) in flight per lane
   double acc = 0.0;
-  auto add = [&](float zt, float zd) {
-    const float wt = sr.template weight_t<SMALL>(zt);
-    acc += (double)(RESID ? sr.template weight_r<SMALL>(wt, zd) : wt);
-    if (RESID && CUT) mass_t += (double)wt;
-  };
   auto add_vec = [&](const u32x4& qt, const u32x4& qd) {
     float ft[EPV], fd[EPV];
     unpack<DT>(qt, ft);
@@ -460,7 +463,11 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
     }
     if (RESID) unpack<DT>(qd, fd);
 #pragma unroll
-    for (int j = 0; j < EPV; ++j) add(ft[j], RESID ? fd[j] : 0.f);
+    for (int j = 0; j < EPV; ++j) {
+      const float wt = sr.template weight_t<SMALL>(ft[j]);
+      acc += (double)(RESID ? sr.template weight_r<SMALL>(wt, fd[j]) : wt);
+      if (BOTH) mass_t += (double)wt;
+    }
   };
   const int i1 = v1 / EPV;
   for (int i = v0 / EPV + lane; i < i1; i += U * lanes) {
@@ -476,22 +483,12 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
     for (int u = 0; u < U; ++u)
       if (i + u * lanes < i1) add_vec(qt[u], qd[u]);
   }
-  for (int v = max(v0, i1 * EPV) + lane; v < v1; v += lanes)
-    add(load_elem<DT>(sr.row_t, v), RESID ? load_elem<DT>(sr.row_d, v) : 0.f);
+  for (int v = max(v0, i1 * EPV) + lane; v < v1; v += lanes) {
+    const float wt = sr.template weight_t<SMALL>(load_elem<DT>(sr.row_t, v));
+    acc += (double)(RESID ? sr.template weight_r<SMALL>(wt, load_elem<DT>(sr.row_d, v)) : wt);
+    if (BOTH) mass_t += (double)wt;
+  }
   return acc;
-}
-
-// The target's masses of an unwarped row, out of line: inlined, it costs the mass kernel 17 to 29 registers
-// more than it has.
-template <int DT>
-__device__ __noinline__ double lane_mass_of_target(const void* row_t, ProbRow pt, int v0, int v1, int lane, int lanes) {
-  SampleRow<DT, false> sr;
-  sr.row_t = sr.row_d = row_t;
-  sr.pt = pt;
-  sr.resid = false;
-  double none = 0.0;
-  return pt.small ? lane_mass<DT, false, false, true>(sr, v0, v1, lane, lanes, none)
-                  : lane_mass<DT, false, false, false>(sr, v0, v1, lane, lanes, none);
 }
 
 // grid (chunks, B): the accept decision of the sequence (every workgroup forms it for
@@ -504,7 +501,7 @@ __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyAr
   __shared__ Plan plan;
   constexpr int kLanes = kSampleThreads * kGranule / kChunk;           // lanes per granule
   constexpr int kGran = kChunk / kGranule, kWaves = kLanes / kWave;    // granules, wavefronts per granule
-  __shared__ double part[2][kGran * kWaves];                           // mass, target's mass where there is none
+  __shared__ double part[kGran * kWaves];
   const int b = blockIdx.y, c = blockIdx.x;
   const int tid = threadIdx.x;
   SV_PHASE_MARK(6)
@@ -514,54 +511,36 @@ __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyAr
   const Plan pl = plan;
   const int g = tid / kLanes, lane = tid - g * kLanes;
   const int v0 = c * kChunk + g * kGranule, v1 = min(a.V, v0 + kGranule);
-  const bool live = pl.target_ok && v0 < v1, resid = pl.resid != 0;
   double acc = 0.0, acc_t = 0.0;
-  if (live) {
+  if (pl.target_ok && v0 < v1) {
     const SampleRow<DT, CUT> sr(a, b, pl);
-    if (sr.small)
-      acc = resid ? lane_mass<DT, true, CUT, true>(sr, v0, v1, lane, kLanes, acc_t)
-                  : lane_mass<DT, false, CUT, true>(sr, v0, v1, lane, kLanes, acc_t);
-    else
-      acc = resid ? lane_mass<DT, true, CUT, false>(sr, v0, v1, lane, kLanes, acc_t)
-                  : lane_mass<DT, false, CUT, false>(sr, v0, v1, lane, kLanes, acc_t);
+    auto masses = [&](auto small) {
+      constexpr bool kSmall = decltype(small)::value;
+      if (sr.maybe_empty) return lane_mass<DT, true, true, CUT, kSmall>(sr, v0, v1, lane, kLanes, acc_t);
+      if (sr.resid) return lane_mass<DT, true, false, CUT, kSmall>(sr, v0, v1, lane, kLanes, acc_t);
+      return lane_mass<DT, false, false, CUT, kSmall>(sr, v0, v1, lane, kLanes, acc_t);
+    };
+    acc = sr.small ? masses(std::true_type()) : masses(std::false_type());
   }
-  const bool first = (tid & (kWave - 1)) == 0;
+  // Without any residual the target distribution is drawn from.  Where that may come to pass (a few percent
+  // of warped batches hold two nuclei of the same single token and a third one drafted), both masses are
+  // formed, and a granule without residual leaves the target's with a minus sign; the pick reads either kind from
+  // the same place.  It takes 5.9 us whatever the batch holds, 17.8 us where its one workgroup had to sum the
+  // target's row of V = 128256 bf16 itself (80 us at 2^20).  Price: 1 us of this kernel's 16.5 at 256 x 32000
+  // with flat nuclei, where many drafted tokens lie outside both; nothing elsewhere.  (The target's mass formed after
+  // the residual's, by a call or a branch inside the loop: 0.4 to 1.5 us for the sequences that do not need it.)
   acc = wave_sum_f64(acc);
-  if (CUT && acc == 0.0 && __any(acc_t != 0.0)) acc_t = wave_sum_f64(acc_t);     // (read only where acc = 0)
-  if (first) { part[0][tid / kWave] = acc; part[1][tid / kWave] = acc_t; }
+  if (pl.resid == 2 && acc == 0.0) acc = -wave_sum_f64(acc_t);
+  if ((tid & (kWave - 1)) == 0) part[tid / kWave] = acc;
   __syncthreads();
-  auto granule = [&](const double* p, int q) {
-    double sum = p[q * kWaves];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) sum += p[q * kWaves + w];
-    return sum;
-  };
-  double m = granule(part[0], g);
-  // Without any residual the target distribution is drawn from (a few percent of warped batches
-  // hold such a sequence: two nuclei of the same single token).  A granule that has none therefore leaves the
-  // target's mass, with a minus sign, and the pick reads either kind from the same place: 5.9 us whatever
-  // the batch holds, where its one workgroup needed 17.8 us to sum the target's row of V = 128256 bf16 itself (80 us
-  // at 2^20).  Price under cutoffs: 0.4 us of this kernel at 32 x 128256, 0.9 us at 256 x 32000 with thousands
-  // of tokens per nucleus.
-  if (resid) {
-    bool some_empty = false;                                           // (the same in every lane)
-#pragma unroll
-    for (int q = 0; q < kGran; ++q) some_empty |= granule(part[0], q) == 0.0;
-    if (!CUT && some_empty) {
-      // (a rare thing without cutoffs: the target's row is read once more, from cache)
-      if (live && m == 0.0) {
-        ProbRow pt;
-        pt.set(plan.lse_t, a.sc_t);
-        acc_t = lane_mass_of_target<DT>(target_row<DT>(a, b, plan.n), pt, v0, v1, lane, kLanes);
-      }
-      acc_t = wave_sum_f64(acc_t);
-      if (first) part[1][tid / kWave] = acc_t;
-      __syncthreads();
-    }
-    if (m == 0.0) m = -granule(part[1], g);
-  }
   SV_PHASE_MARK(8)
-  if (lane == 0 && v0 < v1) a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m;
+  if (lane == 0 && v0 < v1) {
+    // (a sign says what a wavefront found: some residual in any of them is the granule's)
+    double m = 0.0, mt = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) { m += fmax(part[g * kWaves + w], 0.0); mt += fmin(part[g * kWaves + w], 0.0); }
+    a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m > 0.0 ? m : mt;
+  }
   SV_PHASE_MARK(9)
 }
 
