@@ -120,13 +120,28 @@ __device__ __forceinline__ void unpack(const u32x4& q, float (&f)[Elem<DT>::per_
 
 // ---------------------------------------------------------------------------
 // online (max, sum 2^(z L - c)) accumulator, one per lane
+//   Online      fp32 sum
+//   OnlineWide  fp64 sum over a reference that is a whole number, so that raising it scales the sum exactly: nothing in it grows with the
+//               number of entries.  Millions of equal terms, which round the same way in every lane, leave an
+//               fp32 sum 1.4e-6 off at 2^18 entries and 2e-5 at 2^22.
 // ---------------------------------------------------------------------------
-struct Online {
+template <class Sum>
+struct OnlineOf {
+  static constexpr bool kWide = sizeof(Sum) == 8;
   float m;   // running maximum (raw units); -inf before the first element
-  float c;   // max(fl32(m * L), kRefFloor)
-  float s;   // sum of 2^(z*L - c) so far
+  float c;   // max(fl32(m * L), kRefFloor), for the wide sum rounded up to a whole number
+  Sum s;     // sum of 2^(z*L - c) so far
 
-  __device__ __forceinline__ void init() { m = -INFINITY; c = kRefFloor; s = 0.f; }
+  __device__ __forceinline__ void init() { m = -INFINITY; c = kRefFloor; s = 0; }
+
+  static __device__ __forceinline__ float ref(float mx, const float L) {
+    const float r = fmaxf(mx * L, kRefFloor);
+    return kWide ? __builtin_ceilf(r) : r;
+  }
+  static __device__ __forceinline__ float scaled(float s, float scale, float t) { return __builtin_fmaf(s, scale, t); }
+  static __device__ __forceinline__ double scaled(double s, float scale, float t) {
+    return __builtin_fma(s, (double)scale, (double)t);
+  }
 
   template <int N>
   __device__ __forceinline__ void add(const float (&z)[N], const float L = kL32) {
@@ -134,7 +149,7 @@ struct Online {
 #pragma unroll
     for (int j = 0; j + 1 < N; j += 2) mx = fmaxf(fmaxf(mx, z[j]), z[j + 1]);   // v_max3_f32
     if (N & 1) mx = fmaxf(mx, z[N - 1]);
-    const float cn = fmaxf(mx * L, kRefFloor);
+    const float cn = ref(mx, L);
     const float scale = exp2_fast(c - cn);
     float e[N];
 #pragma unroll
@@ -149,19 +164,21 @@ struct Online {
 #pragma unroll
       for (int j = 0; j < N; ++j) t += e[j];
     }
-    s = __builtin_fmaf(s, scale, t);
+    s = scaled(s, scale, t);
     m = mx;
     c = cn;
   }
 
   __device__ __forceinline__ void add1(float z, const float L = kL32) {
     const float mx = fmaxf(m, z);
-    const float cn = fmaxf(mx * L, kRefFloor);
-    s = __builtin_fmaf(s, exp2_fast(c - cn), exp2_fast(__builtin_fmaf(z, L, -cn)));
+    const float cn = ref(mx, L);
+    s = scaled(s, exp2_fast(c - cn), exp2_fast(__builtin_fmaf(z, L, -cn)));
     m = mx;
     c = cn;
   }
 };
+using Online = OnlineOf<float>;
+using OnlineWide = OnlineOf<double>;
 
 // A row's normaliser: exact maximum m and fp64 sum s relative to c(m).
 struct MS {
@@ -330,8 +347,8 @@ struct MergeScratch {
   double s[NR][16];
 };
 
-template <int NR>
-__device__ __forceinline__ void block_merge(const Online (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
+template <int NR, class Sum>
+__device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
                                             const float L = kL32) {
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
@@ -413,8 +430,8 @@ __device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, in
 // also takes the scalar tail).
 // ---------------------------------------------------------------------------
 // NT: the row is not read again soon (non-temporal loads).  U: vectors in flight per lane.
-template <int DT, bool CUT = false, bool NT = true, int U = 4>
-__device__ __forceinline__ void sweep_online(const void* row, int V, int part, int split, Online& acc,
+template <int DT, bool CUT = false, bool NT = true, int U = 4, class Acc = Online>
+__device__ __forceinline__ void sweep_online(const void* row, int V, int part, int split, Acc& acc,
                                              const float L = kL32, const float cut = -INFINITY) {
   constexpr int EPV = Elem<DT>::per_vec;
   const int tid = threadIdx.x, nt = blockDim.x;

@@ -53,3 +53,45 @@ def test_cutoffs_and_supports_do_not_depend_on_the_route():
     torch.cuda.synchronize()
     same = (c1 == c2) | ((fl1 | fl2) != 0)
     assert same.all() and (fl1 != 0).sum() <= 4
+
+
+def _check_cutoffs(z, groups, offset):
+    """Cutoffs of one row of tied values at P = the end of a group of ties (counted from the top) + offset."""
+    P = H.sv()
+    vals, counts = np.unique(z, return_counts=True)
+    vals, counts = vals[::-1].astype(np.float64), counts[::-1]
+    share = np.cumsum(counts * np.exp(vals))
+    share /= share[-1]
+    row = torch.from_numpy(z)[None].cuda()
+    cut, flags = torch.empty(1, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    for g in groups:
+        top_p = float(np.float32(share[g] + offset))
+        want = vals[np.searchsorted(share, top_p)]                           # the first group whose end reaches P
+        assert np.abs(share - top_p).min() > 7e-6                            # (the flagged band: 3e-6)
+        P.sv_warp_cutoffs(row, 1.0, 0, top_p, cut, flags)
+        torch.cuda.synchronize()
+        assert int(flags[0]) == 0 and float(cut[0]) == want, (g, float(cut[0]), want)
+
+
+@pytest.mark.parametrize("offset", [-1e-5, 1e-5])
+def test_the_row_total_of_a_deep_nucleus_of_ties(offset):
+    """Millions of equal terms round the same way in every lane: float32 lane sums of the first sweep are
+    2e-5 too large on this row, and a P that lies 1e-5 from the end of a group of ties has to be
+    decided by better than that.  A large entry for every lane, a tied value with most of the mass, and
+    below it groups of ties down to half its weight."""
+    V, per = 1 << 22, 500
+    n_low = 1200 * per
+    z = np.full(V, -3.7)                                                     # (exponents of two)
+    z[:2048:4] = 0.0                                                         # (512 lanes, vectors of four)
+    z[V - n_low:] = np.repeat(np.linspace(-4.3, -5.0, 1200), per)
+    _check_cutoffs((z * np.log(2.0)).astype(np.float32), (50, 300, 700, 1000), offset)
+
+
+@pytest.mark.parametrize("offset", [-9e-6, 9e-6])
+def test_the_row_total_of_a_short_nucleus_over_ties(offset):
+    """The same where a few entries are the nucleus and the ties are the rest: float32 lane sums are 2.9e-5
+    too small."""
+    z = np.full(1 << 24, -20.0)
+    z[:2048:4] = -18.6
+    z[:160:4] = np.linspace(0.0, -0.6, 40)
+    _check_cutoffs((z * np.log(2.0)).astype(np.float32), (20, 30, 35), offset)
