@@ -59,26 +59,35 @@ struct StatsArgs {
 
 // Sweep-2 arithmetic for one vocabulary entry (head/tail split of the
 // normalisers: see sweep 2 of the kernel).
-template <bool WITH_KL>
+// PER_VECTOR: the terms of a vector are added to each other before they go into the lane's sums, which
+// then carry one rounding per vector.  The workgroups of 512 lanes, whose sums are twice as long as those of 1024 (S of
+// a flat row of 151869 bf16 entries with itself: off by 4.4e-6 without it, 1e-7 with it; times equal).
+template <bool WITH_KL, bool PER_VECTOR>
 struct MinAcc {
   float kd, kc, delta;
   float Ld = kL32, Lc = kL32;          // exponent scales of the two rows
   float acc_s = 0.f, acc_kl = 0.f;
   float acc_pa = 0.f, acc_p = 0.f;     // sum P_d * log2-arg and sum P_d (draft entropy)
-  __device__ __forceinline__ void add(float zd, float zc) {
+  // terms of one entry
+  __device__ __forceinline__ void terms(float zd, float zc, float& s, float& kl, float& pa, float& p) const {
     const float ad = __builtin_fmaf(zd, Ld, -kd);
     const float ac = __builtin_fmaf(zc, Lc, -kc) + delta;
     if (WITH_KL) {
-      const float pd = exp2_fast(ad);
-      acc_s += fminf(pd, exp2_fast(ac));
-      const float t = pd * (ad - ac);          // 0 * inf when P_d underflows: dropped below
-      acc_kl += (pd > 0.f) ? t : 0.f;
-      const float u = pd * ad;
-      acc_pa += (pd > 0.f) ? u : 0.f;
-      acc_p += pd;
+      p = exp2_fast(ad);
+      s = fminf(p, exp2_fast(ac));
+      const float t = p * (ad - ac);           // 0 * inf when P_d underflows: dropped below
+      kl = (p > 0.f) ? t : 0.f;
+      const float u = p * ad;
+      pa = (p > 0.f) ? u : 0.f;
     } else {
-      acc_s += exp2_fast(fminf(ad, ac));
+      s = exp2_fast(fminf(ad, ac));
     }
+  }
+  __device__ __forceinline__ void add(float zd, float zc) {
+    float s, kl, pa, p;
+    terms(zd, zc, s, kl, pa, p);
+    acc_s += s;
+    if (WITH_KL) { acc_kl += kl; acc_pa += pa; acc_p += p; }
   }
   template <int DT, bool WARP = false>
   __device__ __forceinline__ void add_vec(const u32x4& qd, const u32x4& qc, const float cut_d = -INFINITY,
@@ -90,12 +99,24 @@ struct MinAcc {
 #pragma unroll
       for (int j = 0; j < Elem<DT>::per_vec; ++j) { fd[j] = cut_below(fd[j], cut_d); fc[j] = cut_below(fc[j], cut_c); }
     }
+    float s, kl, pa, p;
+    if (!PER_VECTOR) { s = acc_s; kl = acc_kl; pa = acc_pa; p = acc_p; }
 #pragma unroll
     for (int j = 0; j < Elem<DT>::per_vec; ++j) {
-      add(fd[j], fc[j]);
+      float s1, kl1, pa1, p1;
+      terms(fd[j], fc[j], s1, kl1, pa1, p1);
+      const bool first = PER_VECTOR && j == 0;
+      s = first ? s1 : s + s1;
+      if (WITH_KL) { kl = first ? kl1 : kl + kl1; pa = first ? pa1 : pa + pa1; p = first ? p1 : p + p1; }
       // both sums advance together: otherwise all S terms are formed first and
       // the exponents wait in scratch for the KL terms
-      if (WITH_KL && (j & 1)) asm volatile("" : "+v"(acc_s), "+v"(acc_kl), "+v"(acc_pa), "+v"(acc_p));
+      if (WITH_KL && (j & 1)) asm volatile("" : "+v"(s), "+v"(kl), "+v"(pa), "+v"(p));
+    }
+    acc_s = PER_VECTOR ? acc_s + s : s;
+    if (WITH_KL) {
+      acc_kl = PER_VECTOR ? acc_kl + kl : kl;
+      acc_pa = PER_VECTOR ? acc_pa + pa : pa;
+      acc_p = PER_VECTOR ? acc_p + p : p;
     }
   }
 };
@@ -337,7 +358,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
     // f_d = 2^(-tail_d), delta = tail_d - tail_c, so one scalar factor at the
     // end removes the rounding of both heads.
     const double kappa_d = consts.kappa[0], kappa_c = consts.kappa[1];
-    MinAcc<WITH_KL> acc;
+    MinAcc<WITH_KL, (nt < 1024)> acc;
     acc.kd = (float)kappa_d;
     acc.kc = (float)kappa_c;
     const double tail_d = kappa_d - (double)acc.kd, tail_c = kappa_c - (double)acc.kc;
