@@ -138,12 +138,16 @@ def _ptr(t):
 
 def _stream(stream):
     """Address of a stream (None -> the current stream of the current device).  Asked of
-    torch's C layer where that is up: torch.cuda.current_stream() builds a Stream object, 2.8 us a
-    call, a third of what a small batch's step spends on the host."""
+    torch's C layer where that is up and has the two (private) functions for it:
+    torch.cuda.current_stream() builds a Stream object, 2.8 us a call, a third of what a small
+    batch's step spends on the host."""
     if stream is not None:
         return ctypes.c_void_p(stream.cuda_stream)
     if torch.cuda.is_initialized():
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        try:
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        except AttributeError:
+            pass
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 

@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 import paper_2509_24328_amd as P
 from paper_2509_24328_amd import binding as Bd
 
@@ -216,3 +219,18 @@ def test_accept_ratio_sparse_argument_errors():
     assert call(x=None) == Bd.SV_ERR_NULL
     assert call(ratio=ctypes.c_void_p(256 * 1024 + 2)) == Bd.SV_ERR_ALIGN
     assert call(B=0) == Bd.SV_OK
+
+
+@pytest.mark.parametrize("name", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_private_functions_of_torch(monkeypatch, name):
+    class Stream:
+        cuda_stream = 4096
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 8192, raising=False)
+    assert Bd._stream(None).value == 8192
+    assert Bd._stream(Stream).value == 4096
+    monkeypatch.delattr(torch._C, name)
+    assert Bd._stream(None).value == 4096
