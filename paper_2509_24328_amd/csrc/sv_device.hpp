@@ -309,7 +309,6 @@ __device__ __forceinline__ double wave_sum_f64(double v) { return lane_f64(wave_
 
 // Scratch for the workgroup reductions below (up to 16 waves).
 struct BlockScratch {
-  float f[16];
   double d[16];
 };
 
@@ -321,17 +320,6 @@ __device__ __forceinline__ double block_sum_f64(double v, BlockScratch& sm) {
   __syncthreads();
   double r = 0.0;
   for (int w = 0; w < nw; ++w) r += sm.d[w];
-  __syncthreads();
-  return r;
-}
-
-__device__ __forceinline__ float block_max_f32(float v, BlockScratch& sm) {
-  v = wave_max_f32(v);
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) sm.f[wave] = v;
-  __syncthreads();
-  float r = sm.f[0];
-  for (int w = 1; w < nw; ++w) r = fmaxf(r, sm.f[w]);
   __syncthreads();
   return r;
 }
@@ -474,44 +462,30 @@ __device__ __forceinline__ void sweep_online(const void* row, int V, int part, i
 }
 
 // ---------------------------------------------------------------------------
-// Visit elements [v0, v1) of one row (PAIR = false) or of two rows at the same
-// vocabulary index (PAIR = true) with the whole workgroup: f(v, za, zb).
+// Visit elements [v0, v1) of one row with the whole workgroup: f(v, z).
 // v0 is a multiple of the vector length.
 // ---------------------------------------------------------------------------
-template <int DT, bool PAIR, int UNROLL = 2, class F>
-__device__ __forceinline__ void visit_range(const void* a, const void* b, int v0, int v1, F&& f) {
+template <int DT, int UNROLL = 2, class F>
+__device__ __forceinline__ void visit_range(const void* row, int v0, int v1, F&& f) {
   constexpr int EPV = Elem<DT>::per_vec;
   const int tid = threadIdx.x, nt = blockDim.x;
   const int i1 = v1 / EPV;
+  auto visit_vec = [&](const u32x4& q, int i) {
+    float z[EPV];
+    unpack<DT>(q, z);
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) f(i * EPV + j, z[j]);
+  };
   int i = v0 / EPV + tid;
-  for (; i + (UNROLL - 1) * nt < i1; i += UNROLL * nt) {      // UNROLL vector (pairs) in flight per lane
-    u32x4 qa[UNROLL], qb[UNROLL];
+  for (; i + (UNROLL - 1) * nt < i1; i += UNROLL * nt) {      // UNROLL vectors in flight per lane
+    u32x4 q[UNROLL];
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      qa[u] = load_vec(a, i + u * nt);
-      qb[u] = PAIR ? load_vec(b, i + u * nt) : qa[u];
-    }
+    for (int u = 0; u < UNROLL; ++u) q[u] = load_vec(row, i + u * nt);
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      float fa[EPV], fb[EPV];
-      unpack<DT>(qa[u], fa); unpack<DT>(qb[u], fb);
-#pragma unroll
-      for (int j = 0; j < EPV; ++j) f((i + u * nt) * EPV + j, fa[j], fb[j]);
-    }
+    for (int u = 0; u < UNROLL; ++u) visit_vec(q[u], i + u * nt);
   }
-  for (; i < i1; i += nt) {
-    const u32x4 qa = load_vec(a, i);
-    u32x4 qb = qa;
-    if (PAIR) qb = load_vec(b, i);
-    float fa[EPV], fb[EPV];
-    unpack<DT>(qa, fa); unpack<DT>(qb, fb);
-#pragma unroll
-    for (int j = 0; j < EPV; ++j) f(i * EPV + j, fa[j], fb[j]);
-  }
-  for (int v = i1 * EPV + tid; v < v1; v += nt) {
-    const float za = load_elem<DT>(a, v);
-    f(v, za, PAIR ? load_elem<DT>(b, v) : za);
-  }
+  for (; i < i1; i += nt) visit_vec(load_vec(row, i), i);
+  for (int v = i1 * EPV + tid; v < v1; v += nt) f(v, load_elem<DT>(row, v));
 }
 
 // ---------------------------------------------------------------------------

@@ -535,9 +535,6 @@ __device__ __forceinline__ bool settle_step(float top_p, double inv_t, float m, 
   // a decision on the edge between the list and what lies above it belongs to both sides
   if (tid == 0 && fabs(above / Z - (double)top_p) < kNearTie) sh.near_tie = 1;
   SV_PHASE_MARK(13)
-#ifdef SV_PHASE_N
-  if (tid == 0 && blockIdx.x < 4096) sv_phase_buf[blockIdx.x * 16 + 15] = n;
-#endif
   *cutoff = key_value(sh.key[at]);
   return true;
 }
@@ -564,7 +561,7 @@ __device__ __forceinline__ float general_cutoff(const void* row, int V, float lt
   auto histogram = [&](int level, uint32_t prefix, float floor_v) {
     for (int d = tid; d < kBins; d += blockDim.x) { sh.cnt[d] = 0; sh.mass[d] = 0.0; }
     __syncthreads();
-    visit_range<DT, false, 1>(row, nullptr, 0, V, [&](int, float v, float) {   // (one vector at a time: few registers)
+    visit_range<DT, 1>(row, 0, V, [&](int, float v) {   // (one vector at a time: few registers)
       const uint32_t key = okey(v);
       if (under_prefix(key, prefix, level) && v >= floor_v) {
         const uint32_t d = digit_of(key, level);
@@ -1008,7 +1005,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     __syncthreads();
     if (tid == 0) sh.n_cand = 0;
     __syncthreads();
-    visit_range<DT, false, 4>(row, nullptr, 0, V, [&](int v, float zv, float) {
+    visit_range<DT, 4>(row, 0, V, [&](int v, float zv) {
       if (zv >= tau && zv > -INFINITY) {                // entries at -inf carry no mass and are never listed
         const int at = atomicAdd(&sh.n_cand, 1);        // a few per row: the shared counter is not a bottleneck
         if (at < kCand) sh.key[at] = ((uint64_t)okey(zv) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)v);
