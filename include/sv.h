@@ -23,9 +23,10 @@
  *     and returns.  Results are valid once the stream has reached that point.
  *   - Tensors are dense row-major with the vocabulary innermost.  Logits are
  *     SV_F32 (IEEE binary32) or SV_BF16 (bfloat16, the upper 16 bits of a
- *     binary32).  Base pointers need only element alignment; rows that start
- *     on a 16-byte boundary (always the case when V*elem_size is a multiple of
- *     16 and the base is 16-byte aligned) take the vector-load path.
+ *     binary32).  Base pointers need only element alignment, and rows are read
+ *     in 16-byte vectors wherever they start; sv_row_stats keeps more of a pair
+ *     on chip, and is faster, when all rows start on a 16-byte boundary (V*elem_size
+ *     a multiple of 16 and 16-byte aligned bases).
  *   - Return value: SV_OK or a negative SV_ERR_* for argument errors detected
  *     on the host (nothing is enqueued then).  Data-dependent conditions (NaN
  *     rows, token ids out of range, near-ties) are never errors: they set
@@ -106,8 +107,8 @@ enum {
   SV_KERNEL_ACCEPT_ESTIMATE = 1,
   SV_KERNEL_SELECT_LENGTH = 2,
   SV_KERNEL_VERIFY_ROWS = 3,    /* first kernel of sv_verify_sample: row normalisers          */
-  SV_KERNEL_VERIFY_MASS = 4,    /* second: accept decision, chunk masses of the sampled row    */
-  SV_KERNEL_VERIFY_PICK = 5,    /* third: chunk scan, LDS prefix scan, token                   */
+  SV_KERNEL_VERIFY_MASS = 4,    /* second: accept decision, granule masses of the sampled row  */
+  SV_KERNEL_VERIFY_PICK = 5,    /* third: scan of the granule masses, prefix scan, token       */
   SV_KERNEL_COUNT = 6
 };
 

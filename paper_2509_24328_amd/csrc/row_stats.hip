@@ -183,7 +183,7 @@ struct StashThree {                                                    // three 
   static constexpr int threads = 512, waves = 6, lds_vecs = 1600;      // 50 KB
   template <bool KL> static constexpr int regs() { return KL ? 3 : 4; }
 };
-struct StashWide {                                                     // one, twice the lanes for its pair
+struct StashWide {                                                     // one pair per CU, twice the lanes for it (two fit)
   static constexpr int threads = 1024, waves = 8, lds_vecs = 2432;
   template <bool KL> static constexpr int regs() { return 2; }
 };
@@ -436,15 +436,20 @@ static int launch_shape(const StatsArgs& a, hipStream_t st) {
   return launch_status();
 }
 
-// Which shape (us of the kernel, bf16 unless said otherwise).
-//  * At most one pair per CU: more lanes per pair.  256 x 128256: wide 38.8, two 40.6; 128 x 128256:
-//    32.5 and 36.8, fp32 36.3 and 43.1; 64 x 32000: 14.0 and 15.
+// Which shape (us between events around the call, two or three sets of rows in turn; pairs x entries, bf16 unless
+// said otherwise; wide / two / three).
+//  * At most one pair per CU: more lanes per pair.  256 x 128256: 39.3 / 41.3 / 41.1; 128 x 128256: 32.6 / 37.0 / 35.3,
+//    fp32 44.1 / 54.0 / 54.4; 64 x 32000: 14.0 / 15.2 / 14.2.  Below a vector per lane half of the lanes have nothing to do:
+//    256 x 8192: 10.3 / 10.2 / 9.8.  (Just above that line it is still 1 us behind: 256 x 12288: 12.1 / 11.6 / 11.1.)
 //  * Rows that three workgroups keep (nearly) on chip, or whose arithmetic they overlap better than
-//    the bytes they read twice cost: 8192 x 32000: three 192, two 235; 1024 x 50304: 52.7 and 56.6; 512 x
-//    100352: 54.2 and 55.5.  fp32 has half the arithmetic per byte: 512 x 20000: 22.9 and 24.5; 800 x 32000:
-//    55 and 51.
-//  * Longer rows are bound by what is read twice (the lines lie between): 512 x 128256: two 67.6, three 72;
-//    512 x 152064: 80 and 87; fp32 512 x 65536: 63 and 73.
+//    the bytes they read twice cost: 8192 x 32000: two 248, three 210; 1024 x 50304: 55.6 and 53.1; 512 x
+//    100352: 54.2 and 54.0, 512 x 112000: 60.7 and 61.5.  fp32 has half the arithmetic per byte: 512 x 26000: 28.9 and
+//    26.7, 512 x 32000: 32.4 and 31.7, but 800 x 32000: 51.4 and 56.0.  (The lines are a compromise: 512 pairs, resident
+//    at once either way, gain up to them and a little beyond; several rounds of pairs cross earlier, 1024 x 88000: 89.0
+//    and 90.4, with KL 112.5 and 109.5; fp32 2100 x 24000: 79.8 and 83.5.)
+//  * Longer rows are bound by what is read twice: 512 x 128256: 67.5 and 72.2; 512 x 152064: 80.1 and 87.4; fp32 512 x
+//    65536: 62.8 and 73.2.
+// Rows off 16 bytes follow the same lines; without the LDS share they read more of a pair twice (512 x 128257: 85.5).
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr int kCUs = 256, kThreeMax = DT == DT_BF16 ? 13000 : 6500;      // vectors of a row

@@ -76,9 +76,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // one 128-bit loa
 
 // Sixteen bytes of a row at element alignment only.  gfx950 serves a 128-bit load from any
 // address (global_load_dwordx4; a wavefront touches one cache line more than an aligned one),
-// so rows of an odd vocabulary, which start on any element, are read as fast as any other:
-// 24 x 5 positions of 32001 bfloat16 entries, the whole three-call step: 50.1 us, 74.6 us with
-// scalar loads.
+// so rows of an odd vocabulary, which start on any element, are swept with the loads of any other:
+// 24 x 5 positions of 32001 bfloat16 entries, the whole three-call step: 39.9 us, 75.8 us with
+// scalar loads.  (Loads straight into LDS do need 16-byte addresses: the row statistics of such rows
+// park less of a pair on chip, 512 x 128257: 85.5 us, 512 x 128256: 67.7.)
 typedef u32x4 u32x4_row __attribute__((aligned(2)));
 
 __device__ __forceinline__ u32x4 load_vec(const void* row, int i) {

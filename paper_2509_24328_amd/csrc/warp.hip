@@ -665,7 +665,10 @@ __device__ __noinline__ void cut_general_row(const void* row, int r, int V, floa
 constexpr int kNucleusRank = 48;
 constexpr int kNucleusRank2 = 256;
 // the deeper list holds about 320 entries, seven times as many as the first, and each is lighter: where
-// the largest 48 lane maxima have less than this share of P, it hardly ever reaches P
+// the largest 48 lane maxima have less than this share of P, it hardly ever reaches P.  Cutoffs of 200 rows of
+// 32000 at P = 0.9, us with 0.6 / 0.8 / 1.0 (always a list first: 59): 3600 tokens kept 57 / 42 / 43, 310 kept
+// 54 / 38 / 39, 39 kept 29 / 30 / 35, 12 kept 26 / 26 / 30; 800 of 128256: 1140 kept 187 / 187 / 172, 98 kept 108 / 100 / 158, 41
+// kept 86 / 88 / 127.
 constexpr double kHopeless = 0.8;
 
 // One row (r of tensor z) by the whole workgroup.

@@ -72,7 +72,7 @@ def _same_as_unchained(got, plain):
 
 
 # (config index, B, k, V, dtype): aligned bf16, the headline vocabulary, fp32, rows that are not
-# whole 16-byte vectors (the plain two-sweep statistics kernel), a vocabulary below one chunk
+# whole 16-byte vectors (statistics without the LDS share), a vocabulary below one chunk
 CASES = [(1, 6, 5, 32000, "bf16"), (3, 3, 4, 152064, "bf16"), (0, 3, 3, 40000, "f32"), (2, 4, 3, 20011, "bf16"),
          (0, 2, 2, 4099, "f32"), (1, 2, 1, 777, "bf16")]
 

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 SMALL = [
     (0, 1, 4, 32000, "f32"),      # config 1 at full size
     (1, 8, 8, 32000, "bf16"),     # config 2 at full size
-    (0, 2, 3, 4099, "f32"),       # odd V: rows not 16-byte aligned -> scalar path
+    (0, 2, 3, 4099, "f32"),       # odd V: rows not 16-byte aligned, entries past the last vector
     (1, 3, 2, 8200 + 3, "bf16"),  # odd V bf16
     (3, 4, 3, 8192 * 2 + 8, "bf16"),   # just over two sampling chunks
     (2, 3, 2, 20000, "bf16"),     # heavy-tailed rows

@@ -135,8 +135,8 @@ def test_verify_sample_warped_packed_and_ragged():
 
 def test_unit_warp_equals_plain_entry_points():
     """T = 1 without cutoffs: sv_verify_sample_warped runs the same kernels as
-    sv_verify_sample and must give identical bits; sv_row_stats_warped runs the
-    plain two-sweep kernel and must agree to rounding."""
+    sv_verify_sample and must give identical bits; sv_row_stats_warped runs another
+    instantiation of the same kernel and must agree to rounding."""
     cfg = svgen.make_config(1, seed=12, B=4, k=4, V=32000, dtype="bf16", device="cuda")
     plain = H.gpu_verify(cfg["z_t"], cfg["z_d"], cfg["x"], seed=3, step=1)
     warped = _gpu_verify_warped(cfg["z_t"], cfg["z_d"], cfg["x"], 1.0, None, 1.0, None, seed=3, step=1)
