@@ -550,8 +550,8 @@ __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyAr
 
 // grid (B): the granule of the sampling row that holds u' * W from the granule masses, then
 // the token.  A chain of three trips to memory (plan and masses, the granule's logits, the
-// result) with one barrier; nothing is staged in LDS.  4.2 us for one sequence of 32000 fp32
-// entries, 6.0 us for 64 of 152064 bf16, 6.8 us for 512 of 32000 (8.1, 11.3 and 18.7 us with
+// result) with one barrier; nothing is staged in LDS.  4.3 us for one sequence of 32000 fp32
+// entries, 5.8 us for 64 of 152064 bf16, 7.4 us for 512 of 32000 (8.1, 11.3 and 18.7 us with
 // 1024 lanes that staged 8192 weights in LDS and scanned the masses serially).
 template <int DT, bool CUT>
 __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a) {
