@@ -189,7 +189,7 @@ struct StashWide {                                                     // one pa
 };
 
 // Per-pair constants of sweep 2, formed once (fp64 log2 is ~100 instructions)
-// by lanes 0 and 1 of wavefront 0 after the merge and shared through LDS.
+// by two lanes of wavefront 0 after the merge and shared through LDS.
 struct PairConsts {
   double lse[2];      // natural-log normalisers (NaN: bad row)
   double kappa[2];    // L32-consistent log2 normalisers
@@ -209,13 +209,17 @@ __device__ __forceinline__ void publish_pair_consts(const Online (&on)[2], Merge
     if ((threadIdx.x & 63) == 0) { mg.m[r][wave] = mw; mg.s[r][wave] = sw; }
   }
   __syncthreads();
-  if (threadIdx.x < 2) {
-    const int r = threadIdx.x;
+  if (wave == 0) {
+    // lanes 0-15 fold the draft row's partials, lanes 16-31 the companion's (the others repeat them); lanes 15 and 31
+    // hold the sums
+    const int r = (threadIdx.x >> 4) & 1;
     const Scale sc = r == 0 ? sc_d : sc_c;
-    const MS ms = fold_parts(mg.m[r], mg.s[r], nw, sc.L);
-    pc.lse[r] = lse_from_ms(ms, sc);
-    pc.kappa[r] = kappa_l32(ms, sc.L);
-    if (r == 0) { a.chain_m[pair] = ms.m; a.chain_s[pair] = ms.s; }
+    const MS ms = fold_waves_row16(mg.m[r], mg.s[r], nw, sc.L);
+    if (threadIdx.x == 15 || threadIdx.x == 31) {
+      pc.lse[r] = lse_from_ms(ms, sc);
+      pc.kappa[r] = kappa_l32(ms, sc.L);
+      if (r == 0) { a.chain_m[pair] = ms.m; a.chain_s[pair] = ms.s; }
+    }
   }
   __syncthreads();
 }

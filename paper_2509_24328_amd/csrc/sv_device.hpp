@@ -206,6 +206,7 @@ __device__ __forceinline__ float dpp_max_f32(float v) {
   return fmaxf(v, __int_as_float(o));
 }
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppRor1 = 0x121, kDppRor2 = 0x122, kDppRor4 = 0x124, kDppRor8 = 0x128;    // rows rotated
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
 
 // Inclusive prefix sum over the lanes.
@@ -216,6 +217,20 @@ __device__ __forceinline__ double wave_scan_f64(double v) {
   v = dpp_add_f64<kDppShr8, 0xf>(v);
   v = dpp_add_f64<kDppBcast15, 0xa>(v);
   return dpp_add_f64<kDppBcast31, 0xc>(v);
+}
+
+// Rows of 16 lanes: the row's sum in its lane 15, its maximum in all of its lanes.
+__device__ __forceinline__ double row16_sum_f64(double v) {
+  v = dpp_add_f64<kDppShr1, 0xf>(v);
+  v = dpp_add_f64<kDppShr2, 0xf>(v);
+  v = dpp_add_f64<kDppShr4, 0xf>(v);
+  return dpp_add_f64<kDppShr8, 0xf>(v);
+}
+__device__ __forceinline__ float row16_max_all_f32(float v) {
+  v = dpp_max_f32<kDppRor1, 0xf>(v);
+  v = dpp_max_f32<kDppRor2, 0xf>(v);
+  v = dpp_max_f32<kDppRor4, 0xf>(v);
+  return dpp_max_f32<kDppRor8, 0xf>(v);
 }
 
 // Value of one lane (a constant or wavefront-uniform index) in every lane.
@@ -313,14 +328,20 @@ struct BlockScratch {
   double d[16];
 };
 
+// The partials that the (up to 16) wavefronts of a workgroup left in LDS are folded by a row of 16
+// lanes, one partial each, in a fixed order: one LDS read and four register steps, where a lane that
+// walks them pays an LDS latency for each (sixteen of them: 0.9 us at the end of a kernel of 10).
+__device__ __forceinline__ double fold_sums(const double* part, int nw) {
+  const int w = threadIdx.x & 15;
+  return lane_f64(row16_sum_f64(w < nw ? part[w] : 0.0), 15);
+}
+
 // Workgroup sum of fp64 partials in a fixed order; result in every thread.
 __device__ __forceinline__ double block_sum_f64(double v, BlockScratch& sm) {
   v = wave_sum_f64(v);
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) sm.d[wave] = v;
+  if ((threadIdx.x & 63) == 0) sm.d[threadIdx.x >> 6] = v;
   __syncthreads();
-  double r = 0.0;
-  for (int w = 0; w < nw; ++w) r += sm.d[w];
+  const double r = fold_sums(sm.d, blockDim.x >> 6);
   __syncthreads();
   return r;
 }
@@ -329,12 +350,23 @@ __device__ __forceinline__ double block_sum_f64(double v, BlockScratch& sm) {
 // valid in every thread after a single barrier.  Inside a wavefront every lane
 // rescales its sum to the wavefront's reference (a factor 2^(c_lane - c_wave)
 // <= 1 from v_exp_f32) and the sums are added in fp64; the per-wavefront
-// pairs go through LDS and every thread folds them in the same fixed order.
+// pairs go through LDS and every wavefront folds them in the same fixed order.
 template <int NR>
 struct MergeScratch {
   float m[NR][16];
   double s[NR][16];
 };
+
+// (valid in lane 15 of every row of 16 lanes, each of which may be given another logit row)
+__device__ __forceinline__ MS fold_waves_row16(const float* m, const double* s, int nw, const float L = kL32) {
+  const int w = threadIdx.x & 15;
+  const float mw = w < nw ? m[w] : -INFINITY;
+  const double sw = w < nw ? s[w] : 0.0;
+  MS r;
+  r.m = row16_max_all_f32(mw);
+  r.s = row16_sum_f64(sw * (double)exp2_fast(ref_of(mw, L) - ref_of(r.m, L)));
+  return r;
+}
 
 template <int NR, class Sum>
 __device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
@@ -349,13 +381,9 @@ __device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeS
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    float m = sm.m[r][0];
-    for (int w = 1; w < nw; ++w) m = fmaxf(m, sm.m[r][w]);
-    const float cr = ref_of(m, L);
-    double acc = 0.0;
-    for (int w = 0; w < nw; ++w) acc += sm.s[r][w] * (double)exp2_fast(ref_of(sm.m[r][w], L) - cr);
-    out[r].m = m;
-    out[r].s = acc;
+    const MS f = fold_waves_row16(sm.m[r], sm.s[r], nw, L);
+    out[r].m = lane_f32(f.m, 15);
+    out[r].s = lane_f64(f.s, 15);
   }
 }
 
@@ -377,20 +405,8 @@ __device__ __forceinline__ double kappa_l32(const MS& r, const float L = kL32) {
   return (double)ref_of(r.m, L) + log2(r.s);
 }
 
-// Fold `n` partial normalisers (consecutive entries).
-__device__ __forceinline__ MS fold_parts(const float* m, const double* s, int n, const float L = kL32) {
-  MS r;
-  r.m = m[0];
-  for (int p = 1; p < n; ++p) r.m = fmaxf(r.m, m[p]);
-  const float cr = ref_of(r.m, L);
-  r.s = 0.0;
-  for (int p = 0; p < n; ++p) r.s += s[p] * (double)exp2_fast(ref_of(m[p], L) - cr);
-  return r;
-}
-
-// The same for the `split` <= kMaxParts parts of a row held in global memory:
-// all loads are issued before the first use (the loop above would pay one
-// memory latency per part).
+// Normaliser of a row from the `split` <= kMaxParts partials held in global memory: all loads
+// are issued before the first use (a loop would pay one memory latency per part).
 constexpr int kMaxParts = 8;
 
 __device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L = kL32) {
