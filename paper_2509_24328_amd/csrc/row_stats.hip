@@ -121,22 +121,24 @@ struct MinAcc {
   }
 };
 
-// Scalar epilogue: A, flags and the stores.
-template <int DT, bool WITH_KL, bool WARP = false>
-__device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, const void* rd, const void* rc,
-                                               double lse_d, double lse_c, double S, double KL, double H_d,
-                                               const float cut_d = -INFINITY, const float cut_c = -INFINITY) {
+// What a pair's second sweep and its epilogue need, formed once by two lanes of wavefront 0 after the
+// merge and shared through LDS: the natural-log normalisers (NaN: bad row), the L32-consistent log2
+// normalisers, the logits of the drafted token (NaN: no such token).
+struct PairConsts {
+  double lse[2];
+  double kappa[2];
+  float zx[2];
+};
+
+// Scalar epilogue of one pair: A, flags and the stores.
+template <bool WITH_KL, bool WARP>
+__device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, const PairConsts& pc, int tok, double S,
+                                               double KL, double pa, double p1) {
+  const double lse_d = pc.lse[0], lse_c = pc.lse[1];
   const bool bad = isnan(lse_d) || isnan(lse_c);
   uint32_t fl = bad ? SV_FLAG_BAD_ROW : 0u;
   double A = __builtin_nan(""), pdx = __builtin_nan("");
-  const int tok = a.x[pair];
-  const bool tok_ok = tok >= 0 && tok < a.V;
-  float zxd = __builtin_nanf("");
-  if (tok_ok) {
-    zxd = load_elem<DT>(rd, tok);
-    if (WARP) zxd = cut_below(zxd, cut_d);
-  }
-  a.chain_zx[pair] = zxd;                  // whatever the companion row is like
+  a.chain_zx[pair] = pc.zx[0];             // whatever the companion row is like
   if (pair == 0) {
     ChainHeader h;
     h.z_d = reinterpret_cast<uint64_t>(a.z_d); h.x = reinterpret_cast<uint64_t>(a.x);
@@ -146,18 +148,24 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
     h.magic = kChainMagic;
     *a.chain = h;
   }
-  if (!bad) {
-    if (!tok_ok) {
+  double H_d = __builtin_nan("");
+  if (bad) {
+    S = KL = __builtin_nan("");
+  } else {
+    // the sums of sweep 2 are relative to the head of kappa_d (MinAcc)
+    const double tail_d = pc.kappa[0] - (double)(float)pc.kappa[0], f_d = exp2(-tail_d);
+    S *= f_d;
+    if (WITH_KL) {
+      KL *= f_d * kLn2;
+      H_d = (pa - tail_d * p1) * (-f_d * kLn2);
+    }
+    if (tok < 0 || tok >= a.V) {
       fl |= SV_FLAG_BAD_TOKEN;
     } else {
-      float zxc = load_elem<DT>(rc, tok);
       double inv_td = 1.0, inv_tc = 1.0;
-      if (WARP) {
-        zxc = cut_below(zxc, cut_c);
-        inv_td = a.sc_d.inv_t; inv_tc = a.sc_c.inv_t;
-      }
-      const double ld = (double)zxd * inv_td - lse_d;
-      const double lc = (double)zxc * inv_tc - lse_c;
+      if (WARP) { inv_td = a.sc_d.inv_t; inv_tc = a.sc_c.inv_t; }
+      const double ld = (double)pc.zx[0] * inv_td - lse_d;
+      const double lc = (double)pc.zx[1] * inv_tc - lse_c;
       A = (ld == -INFINITY) ? 1.0 : fmin(1.0, exp(lc - ld));
       pdx = exp(ld);
     }
@@ -188,40 +196,31 @@ struct StashWide {                                                     // one pa
   template <bool KL> static constexpr int regs() { return 2; }
 };
 
-// Per-pair constants of sweep 2, formed once (fp64 log2 is ~100 instructions)
-// by two lanes of wavefront 0 after the merge and shared through LDS.
-struct PairConsts {
-  double lse[2];      // natural-log normalisers (NaN: bad row)
-  double kappa[2];    // L32-consistent log2 normalisers
-};
-
-// Folds the per-wavefront partials left by the first half of block_merge and
-// publishes the constants.  Must be called by all threads; ends with a barrier.
-__device__ __forceinline__ void publish_pair_consts(const Online (&on)[2], MergeScratch<2>& mg, PairConsts& pc,
-                                                    const StatsArgs& a, const int pair,
-                                                    const Scale sc_d = unit_scale(), const Scale sc_c = unit_scale()) {
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+// A wavefront's partial normalisers of the pair go to LDS.
+__device__ __forceinline__ void store_partials(const Online (&on)[2], MergeScratch<2>& mg, const float Ld, const float Lc) {
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     const float mw = wave_max_f32(on[r].m);
-    const float L = r == 0 ? sc_d.L : sc_c.L;
-    const double sw = wave_sum_f64((double)on[r].s * (double)exp2_fast(on[r].c - ref_of(mw, L)));
-    if ((threadIdx.x & 63) == 0) { mg.m[r][wave] = mw; mg.s[r][wave] = sw; }
+    const double sw = wave_sum_f64((double)on[r].s * (double)exp2_fast(on[r].c - ref_of(mw, r == 0 ? Ld : Lc)));
+    if ((threadIdx.x & (kWave - 1)) == 0) { mg.m[r][threadIdx.x / kWave] = mw; mg.s[r][threadIdx.x / kWave] = sw; }
   }
-  __syncthreads();
-  if (wave == 0) {
-    // lanes 0-15 fold the draft row's partials, lanes 16-31 the companion's (the others repeat them); lanes 15 and 31
-    // hold the sums
-    const int r = (threadIdx.x >> 4) & 1;
-    const Scale sc = r == 0 ? sc_d : sc_c;
-    const MS ms = fold_waves_row16(mg.m[r], mg.s[r], nw, sc.L);
-    if (threadIdx.x == 15 || threadIdx.x == 31) {
-      pc.lse[r] = lse_from_ms(ms, sc);
-      pc.kappa[r] = kappa_l32(ms, sc.L);
-      if (r == 0) { a.chain_m[pair] = ms.m; a.chain_s[pair] = ms.s; }
-    }
+}
+
+// Wavefront 0 folds the wavefronts' partials and forms the pair's constants: lanes 0-15 the draft row's, lanes 16-31
+// the companion's (the others repeat them); lanes 15 and 31 hold the sums and, in zx, the rows' logits of the
+// drafted token.
+constexpr int kLaneDraft = 15, kLaneCompanion = 31;
+__device__ __forceinline__ void publish_consts(const MergeScratch<2>& mg, int waves, PairConsts& pc, const StatsArgs& a,
+                                               const int pair, const float zx, const Scale& sc_d, const Scale& sc_c) {
+  const int r = (threadIdx.x >> 4) & 1;
+  const Scale sc = r == 0 ? sc_d : sc_c;
+  const MS ms = fold_waves_row16(mg.m[r], mg.s[r], waves, sc.L);
+  if (threadIdx.x == kLaneDraft || threadIdx.x == kLaneCompanion) {
+    pc.lse[r] = lse_from_ms(ms, sc);
+    pc.kappa[r] = kappa_l32(ms, sc.L);
+    pc.zx[r] = zx;
+    if (r == 0) { a.chain_m[pair] = ms.m; a.chain_s[pair] = ms.s; }
   }
-  __syncthreads();
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l of the
@@ -233,13 +232,35 @@ __device__ __forceinline__ void load_to_lds(const u32x4* src, u32x4* lds_wave_ba
       16, 0, 0);
 }
 
+// A wavefront's sums of sweep 2 go to LDS.
+template <bool WITH_KL, bool PER_VECTOR, int N, int W>
+__device__ __forceinline__ void store_sums(const MinAcc<WITH_KL, PER_VECTOR>& acc, double (&sums)[N][W]) {
+  const float v[4] = {acc.acc_s, acc.acc_kl, acc.acc_pa, acc.acc_p};
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const double t = wave_sum_f64((double)v[q]);
+    if ((threadIdx.x & (kWave - 1)) == 0) sums[q][threadIdx.x / kWave] = t;
+  }
+}
+
+// One wavefront folds them and writes the pair's results.
+template <bool WITH_KL, bool WARP, int N, int W>
+__device__ __forceinline__ void end_pair(const StatsArgs& a, int pair, const PairConsts& pc, int tok,
+                                         const double (&sums)[N][W]) {
+  double total[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < N; ++q) total[q] = fold_sums(sums[q], W);
+  if ((threadIdx.x & (kWave - 1)) == 0) stats_epilogue<WITH_KL, WARP>(a, pair, pc, tok, total[0], total[1], total[2], total[3]);
+}
+
 template <int DT, bool WITH_KL, bool WARP, class Shape>
 __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_kernel(StatsArgs a) {
   constexpr int kRegIters = Shape::template regs<WITH_KL>(), kLdsVecs = Shape::lds_vecs, nt = Shape::threads;
   constexpr int kLdsIters = (kLdsVecs + nt - 1) / nt;
   extern __shared__ u32x4 park[];                      // [kLdsVecs] draft, then [kLdsVecs] companion
-  __shared__ BlockScratch sm;
+  constexpr int kWaves = nt / kWave, kSums = WITH_KL ? 4 : 1;
   __shared__ MergeScratch<2> mg;
+  __shared__ double sums[kSums][kWaves];               // a wavefront's share of S, KL, sum P log P, sum P
   __shared__ PairConsts consts;
   constexpr int EPV = Elem<DT>::per_vec;
   constexpr uint32_t kNegInfWord = (DT == DT_BF16) ? 0xFF80FF80u : 0xFF800000u;
@@ -337,6 +358,12 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
       add1(oc, c0, Lc, cut_c);
     }
   }
+  // the logits of the drafted token, by the two lanes that publish them: their way from memory passes under the
+  // merge, where the epilogue would wait for the token and then for the logits
+  const int tok = a.x[pair];
+  float zx = __builtin_nanf("");
+  if (tok >= 0 && tok < a.V && (tid == kLaneDraft || tid == kLaneCompanion))
+    zx = load_elem<DT>(tid == kLaneDraft ? pd : pc, tok);
   // the entries past the last whole vector (rows off 16 bytes only): fewer than a vector's worth
   const int tail = nvec * EPV + tid;
   float tail_zd = -INFINITY, tail_zc = -INFINITY;
@@ -348,21 +375,21 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
     oc.add1(tail_zc, Lc);
   }
   SV_PHASE_MARK(4)
-  publish_pair_consts(on, mg, consts, a, pair, sc_d, sc_c);
-  const double lse_d = consts.lse[0], lse_c = consts.lse[1];
-  const bool bad = isnan(lse_d) || isnan(lse_c);
+  store_partials(on, mg, Ld, Lc);
+  __syncthreads();
+  if (tid < kWave) publish_consts(mg, kWaves, consts, a, pair, WARP ? cut_below(zx, tid == kLaneDraft ? cut_d : cut_c) : zx, sc_d, sc_c);
+  __syncthreads();
 
   SV_PHASE_MARK(5)
   // ---- sweep 2: rest of the pair from L2/HBM (newest first), then LDS, then registers
-  double S = __builtin_nan(""), KL = __builtin_nan(""), H_d = __builtin_nan("");
-  if (!bad) {
+  MinAcc<WITH_KL, (nt < 1024)> acc;
+  {
     // kappa = log2-domain normaliser consistent with the L32 exponent scale,
     // split into an fp32 head and a tail.  With a = z*L32 - head:
     // P_d = f_d 2^(a_d),  P_c = f_d 2^(a_c + delta),
     // f_d = 2^(-tail_d), delta = tail_d - tail_c, so one scalar factor at the
-    // end removes the rounding of both heads.
+    // end removes the rounding of both heads.  (A bad row's sums are dropped by the epilogue.)
     const double kappa_d = consts.kappa[0], kappa_c = consts.kappa[1];
-    MinAcc<WITH_KL, (nt < 1024)> acc;
     acc.kd = (float)kappa_d;
     acc.kc = (float)kappa_c;
     const double tail_d = kappa_d - (double)acc.kd, tail_c = kappa_c - (double)acc.kc;
@@ -403,21 +430,11 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
       }
     }
     SV_PHASE_MARK(8)
-    S = block_sum_f64((double)acc.acc_s, sm);
-    if (WITH_KL) {
-      KL = block_sum_f64((double)acc.acc_kl, sm);
-      const double pa = block_sum_f64((double)acc.acc_pa, sm), p1 = block_sum_f64((double)acc.acc_p, sm);
-      H_d = pa - tail_d * p1;                  // sum 2^(a_d) * log2 P_d, still without f_d
-    }
-    if (tid == 0) {
-      const double f_d = exp2(-tail_d);
-      S *= f_d;
-      KL *= f_d * kLn2;
-      H_d *= -f_d * kLn2;
-    }
+    store_sums(acc, sums);
   }
+  __syncthreads();
   SV_PHASE_MARK(9)
-  if (tid == 0) stats_epilogue<DT, WITH_KL, WARP>(a, pair, pd, pc, lse_d, lse_c, S, KL, H_d, cut_d, cut_c);
+  if (tid < kWave) end_pair<WITH_KL, WARP>(a, pair, consts, tok, sums);
 }
 
 template <int DT, bool WITH_KL, bool WARP, class Shape>

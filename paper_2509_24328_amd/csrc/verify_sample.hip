@@ -172,6 +172,11 @@ __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScra
   const float L = r.is_target ? a.sc_t.L : a.sc_d.L;
   float cut = -INFINITY;
   if (CUT) cut = r.is_target ? target_cut(a, r.b, r.i) : draft_cut(a, r.b, r.i);
+  // the logit of the drafted token travels with the first loads (two dependent trips to memory at the end otherwise)
+  if (threadIdx.x == 0 && r.part == 0 && r.i < a.k && row) {
+    const int tok = a.x[r.b * a.k + r.i];
+    if (tok >= 0 && tok < a.V) r.zx = load_elem<DT>(row, tok);
+  }
   Online acc[1];
   acc[0].init();
   // six vectors in flight per lane: a part is 8-10 vectors per lane at the benchmark shapes, i.e. two
@@ -180,11 +185,7 @@ __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScra
   MS merged[1];
   block_merge(acc, sm, merged, L);
   r.ms = merged[0];                                      // s = 0 for a missing row => bad row
-  if (threadIdx.x == 0 && r.part == 0 && r.i < a.k && row) {
-    const int tok = a.x[r.b * a.k + r.i];
-    if (tok >= 0 && tok < a.V) r.zx = load_elem<DT>(row, tok);
-    if (CUT) r.zx = cut_below(r.zx, cut);
-  }
+  if (CUT) r.zx = cut_below(r.zx, cut);
   return r;
 }
 
