@@ -14,6 +14,9 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
          # accumulator relies on c(m) being the same rounded fp32 number
          # everywhere it is used
          "-ffp-contract=off",
+         # the constants of an fp64 logarithm or exponential stay where they are used: hoisted out of the
+         # loop over pairs of row_stats.hip they take dozens of the registers that hold the rows
+         "-mllvm", "-disable-machine-licm",
          # packed-fp32 code generation is switched off on this target
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -14,11 +14,16 @@
 // discussed in Sec. 2 of the paper.)
 // A = min(1, P_c(x) / P_d(x)) is a scalar epilogue in fp64.
 //
-// One kernel in three shapes (StashWide, StashTwo, StashThree: lanes per workgroup, workgroups per
-// CU).  Sweep 1 parks what it reads on chip - the first vector pairs of every lane stay in
-// registers, the next go to LDS - and only the rest of the pair, if any, is read again, most
-// recent bytes first so that they are still in L2.
-// Algorithmic HBM traffic: 2 * V * elem_size bytes per workgroup.
+// Two kernels (the rule between them stands at launch_stats).  In both, sweep 1 parks what it reads on
+// chip, in registers and in LDS, and only the rest of a pair, if any, is read again, most recent
+// bytes first so that they are still in L2.
+//   row_stats_loop_kernel    workgroups that fill the chip once and walk through the pairs: the places that
+//                            sweep 2 of a pair leaves take the next pair's loads
+//   row_stats_stash_kernel   a workgroup per pair: very short rows, and very many pairs of short ones
+// Algorithmic HBM traffic: 2 * V * elem_size bytes per pair.
+#include <algorithm>
+#include <type_traits>
+
 #include "sv_device.hpp"
 #include "sv_host.hpp"
 
@@ -57,12 +62,15 @@ struct StatsArgs {
   bool aligned;           // rows start on 16 bytes
 };
 
+// v_mul_legacy_f32: a product that is 0 where either factor is, whatever the other.
+extern "C" __device__ float mul_zero_wins(float, float) __asm("llvm.amdgcn.fmul.legacy");
+
 // Sweep-2 arithmetic for one vocabulary entry (head/tail split of the
 // normalisers: see sweep 2 of the kernel).
-// PER_VECTOR: the terms of a vector are added to each other before they go into the lane's sums, which
-// then carry one rounding per vector.  The workgroups of 512 lanes, whose sums are twice as long as those of 1024 (S of
-// a flat row of 151869 bf16 entries with itself: off by 4.4e-6 without it, 1e-7 with it; times equal).
-template <bool WITH_KL, bool PER_VECTOR>
+// The terms of a vector are added to each other before they go into the lane's sums, which then carry one
+// rounding per vector (S of a flat row of 151869 bf16 entries with itself: off by 4.4e-6 entry by entry, by 1e-7 this
+// way; times equal).
+template <bool WITH_KL>
 struct MinAcc {
   float kd, kc, delta;
   float Ld = kL32, Lc = kL32;          // exponent scales of the two rows
@@ -75,10 +83,9 @@ struct MinAcc {
     if (WITH_KL) {
       p = exp2_fast(ad);
       s = fminf(p, exp2_fast(ac));
-      const float t = p * (ad - ac);           // 0 * inf when P_d underflows: dropped below
-      kl = (p > 0.f) ? t : 0.f;
-      const float u = p * ad;
-      pa = (p > 0.f) ? u : 0.f;
+      // (0 whatever the other factor where P_d underflows: 0 * inf adds nothing)
+      kl = mul_zero_wins(p, ad - ac);
+      pa = mul_zero_wins(p, ad);
     } else {
       s = exp2_fast(fminf(ad, ac));
     }
@@ -99,25 +106,19 @@ struct MinAcc {
 #pragma unroll
       for (int j = 0; j < Elem<DT>::per_vec; ++j) { fd[j] = cut_below(fd[j], cut_d); fc[j] = cut_below(fc[j], cut_c); }
     }
-    float s, kl, pa, p;
-    if (!PER_VECTOR) { s = acc_s; kl = acc_kl; pa = acc_pa; p = acc_p; }
+    float s = 0.f, kl = 0.f, pa = 0.f, p = 0.f;
 #pragma unroll
     for (int j = 0; j < Elem<DT>::per_vec; ++j) {
       float s1, kl1, pa1, p1;
       terms(fd[j], fc[j], s1, kl1, pa1, p1);
-      const bool first = PER_VECTOR && j == 0;
-      s = first ? s1 : s + s1;
-      if (WITH_KL) { kl = first ? kl1 : kl + kl1; pa = first ? pa1 : pa + pa1; p = first ? p1 : p + p1; }
+      s = j == 0 ? s1 : s + s1;
+      if (WITH_KL) { kl = j == 0 ? kl1 : kl + kl1; pa = j == 0 ? pa1 : pa + pa1; p = j == 0 ? p1 : p + p1; }
       // both sums advance together: otherwise all S terms are formed first and
       // the exponents wait in scratch for the KL terms
       if (WITH_KL && (j & 1)) asm volatile("" : "+v"(s), "+v"(kl), "+v"(pa), "+v"(p));
     }
-    acc_s = PER_VECTOR ? acc_s + s : s;
-    if (WITH_KL) {
-      acc_kl = PER_VECTOR ? acc_kl + kl : kl;
-      acc_pa = PER_VECTOR ? acc_pa + pa : pa;
-      acc_p = PER_VECTOR ? acc_p + p : p;
-    }
+    acc_s += s;
+    if (WITH_KL) { acc_kl += kl; acc_pa += pa; acc_p += p; }
   }
 };
 
@@ -180,9 +181,9 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
   if (a.flags) a.flags[pair] = fl;
 }
 
-// How a workgroup is laid out: lanes, vector pairs per lane parked in registers (kl: with the sums
-// of KL and entropy, which need registers of their own), vector pairs parked in LDS (a multiple
-// of 64), wavefronts per SIMD that have to fit.  The rule between them stands at launch_stats.
+// How a workgroup of the kernel with one pair each is laid out: lanes, vector pairs per lane parked in registers (kl: with
+// the sums of KL and entropy, which need registers of their own), vector pairs parked in LDS (a multiple
+// of 64), wavefronts per SIMD that have to fit.
 struct StashTwo {                                                      // two workgroups per CU
   static constexpr int threads = 512, waves = 4, lds_vecs = 2432;      // 76 KB
   template <bool KL> static constexpr int regs() { return KL ? 8 : 10; }
@@ -190,10 +191,6 @@ struct StashTwo {                                                      // two wo
 struct StashThree {                                                    // three per CU
   static constexpr int threads = 512, waves = 6, lds_vecs = 1600;      // 50 KB
   template <bool KL> static constexpr int regs() { return KL ? 3 : 4; }
-};
-struct StashWide {                                                     // one pair per CU, twice the lanes for it (two fit)
-  static constexpr int threads = 1024, waves = 8, lds_vecs = 2432;
-  template <bool KL> static constexpr int regs() { return 2; }
 };
 
 // A wavefront's partial normalisers of the pair go to LDS.
@@ -233,8 +230,8 @@ __device__ __forceinline__ void load_to_lds(const u32x4* src, u32x4* lds_wave_ba
 }
 
 // A wavefront's sums of sweep 2 go to LDS.
-template <bool WITH_KL, bool PER_VECTOR, int N, int W>
-__device__ __forceinline__ void store_sums(const MinAcc<WITH_KL, PER_VECTOR>& acc, double (&sums)[N][W]) {
+template <bool WITH_KL, int N, int W>
+__device__ __forceinline__ void store_sums(const MinAcc<WITH_KL>& acc, double (&sums)[N][W]) {
   const float v[4] = {acc.acc_s, acc.acc_kl, acc.acc_pa, acc.acc_p};
 #pragma unroll
   for (int q = 0; q < N; ++q) {
@@ -382,7 +379,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
 
   SV_PHASE_MARK(5)
   // ---- sweep 2: rest of the pair from L2/HBM (newest first), then LDS, then registers
-  MinAcc<WITH_KL, (nt < 1024)> acc;
+  MinAcc<WITH_KL> acc;
   {
     // kappa = log2-domain normaliser consistent with the L32 exponent scale,
     // split into an fp32 head and a tail.  With a = z*L32 - head:
@@ -437,47 +434,284 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
   if (tid < kWave) end_pair<WITH_KL, WARP>(a, pair, consts, tok, sums);
 }
 
+// Workgroups that walk through several pairs: REGS places of the register share, PER_CU workgroups on a CU.
+template <int REGS, int PER_CU>
+struct Loop {
+  static constexpr int threads = 512, groups = 256 * PER_CU, waves = 2 * PER_CU, regs = REGS;
+  static constexpr int lds_vecs = (PER_CU == 1 ? 9 : 4) * threads;      // 144 KB, 64 KB
+  static constexpr int ahead = PER_CU == 1 ? 4 : 2;                     // vector pairs per lane in flight
+};
+
+// A workgroup walks the pairs blockIdx.x, + gridDim.x, ...  A pass is sweep 2 of one pair and, as that
+// leaves them, the loading of the next pair into the same places on chip, with sweep 1 following
+// `ahead` places behind: loads, sweep 1 and sweep 2 share the compute unit instead of taking turns.  (The first
+// pass has no pair to sweep a second time, the last one none to load.)
+// Bound, on long rows, by one read of the pair (51 thousand cycles at the share of a compute unit of 6.4 TB/s, 608 KB
+// of 152064 bf16 entries) and by the arithmetic (48 thousand), which overlap but for the first pair's loads and the last
+// pair's sweep 2: 71 us for 512 such pairs, 30 us for every 256 more.  89 % of a pair stays on chip: two wavefronts
+// per SIMD have 512 registers between them for the rows (four have 320: 76 us).  On short rows: launch, the
+// first loads' latency, a merge (two fp64 logarithms) and the arithmetic of a pair on one compute unit.
+// What it rests on: a wavefront issues in order, and with all loads of a share ahead of all arithmetic it stands in
+// the memory queue (30 thousand cycles for 480 KB) with data to sum at hand.  The waits must tell the loads
+// apart: rows end inside the last place of the register share or after it, so that every load of it is unconditional,
+// and nothing is loaded straight into LDS - with either, the compiler's wait for one load becomes a wait for all that are
+// in flight.
 template <int DT, bool WITH_KL, bool WARP, class Shape>
-static int launch_shape(const StatsArgs& a, hipStream_t st) {
-  constexpr size_t lds_bytes = 2 * (size_t)Shape::lds_vecs * 16;
-  // more than 64 KB of dynamic LDS has to be allowed once per kernel and device
-  constexpr int kMaxDevices = 64;
-  static bool allowed[kMaxDevices] = {};
+__global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_kernel(StatsArgs a) {
+  constexpr int kRegIters = Shape::regs, kLdsVecs = Shape::lds_vecs, nt = Shape::threads;
+  constexpr int kAhead = Shape::ahead, kWaves = nt / kWave;
+  constexpr int kSums = WITH_KL ? 4 : 1;
+  extern __shared__ u32x4 park[];                      // [kLdsVecs] draft, then [kLdsVecs] companion
+  __shared__ MergeScratch<2> mg;
+  __shared__ double sums[kSums][kWaves];
+  __shared__ PairConsts consts[2];
+  constexpr int EPV = Elem<DT>::per_vec;
+  constexpr uint32_t kNegInfWord = (DT == DT_BF16) ? 0xFF80FF80u : 0xFF800000u;
+  const u32x4 neg = {kNegInfWord, kNegInfWord, kNegInfWord, kNegInfWord};
+  int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int pairs = a.B * a.k;
+  const size_t row_bytes = (size_t)a.V * Elem<DT>::bytes;
+  int nvec = a.V / EPV;
+  constexpr int lds_begin = kRegIters * nt;
+  static_assert(kLdsVecs % nt == 0, "a place for every lane");
+  static_assert(kRegIters % 2 == 0, "the register share is summed by twos");
+  const Scale sc_d = WARP ? a.sc_d : unit_scale(), sc_c = WARP ? a.sc_c : unit_scale();
+  const float Ld = sc_d.L, Lc = sc_c.L;
+
+  u32x4 sd[kRegIters], sc[kRegIters];                  // the register share: place j of this lane
+  // the pair of sweep 2
+  const char *cd = nullptr, *cc = nullptr;
+  float cut_cd = -INFINITY, cut_cc = -INFINITY;
+  int cur = 0, tok_cur = 0, at = 0;
+  // the pair that is loaded
+  const char *nd = nullptr, *nc = nullptr;
+  float cut_nd = -INFINITY, cut_nc = -INFINITY;
+  int next = blockIdx.x;
+
+  auto pass = [&](auto has_cur, auto has_next) {
+    constexpr bool CUR = decltype(has_cur)::value, NEXT = decltype(has_next)::value;
+    // (nothing derived from these is kept over the passes: dozens of addresses, one per place)
+    asm volatile("" : "+s"(nvec), "+v"(tid));
+    const int lds_end = max(lds_begin, min(nvec, lds_begin + kLdsVecs));
+    const int lds_steps = (lds_end - lds_begin + nt - 1) / nt, rest_steps = (nvec - lds_end + nt - 1) / nt;   // (or less than 1)
+    const int tail = nvec * EPV + tid;                 // entries past the last whole vector (rows off 16 bytes only)
+    int tok_next = 0;
+    if (NEXT) {
+      nd = static_cast<const char*>(a.z_d) + next * row_bytes;
+      nc = static_cast<const char*>(a.z_c) + next * row_bytes;
+      if (WARP && a.cut_d) cut_nd = a.cut_d[next];
+      if (WARP && a.cut_c) cut_nc = a.cut_c[next];
+    }
+    Online on[2];
+    on[0].init();
+    on[1].init();
+    MinAcc<WITH_KL> acc;
+    if (CUR) {
+      // (head and tail of the normalisers: see row_stats_stash_kernel)
+      const PairConsts& pc = consts[at];
+      acc.kd = (float)pc.kappa[0];
+      acc.kc = (float)pc.kappa[1];
+      acc.delta = (float)((pc.kappa[0] - (double)acc.kd) - (pc.kappa[1] - (double)acc.kc));
+      acc.Ld = Ld; acc.Lc = Lc;
+    }
+    // places of sweep 1 (two vectors of a row share one rescaling of its sum), a place of sweep 2
+    auto add_row = [&](Online& o, const auto&... q) {
+      float f[sizeof...(q) * EPV];
+      int at = 0;
+      ((unpack<DT>(q, *reinterpret_cast<float(*)[EPV]>(f + at)), at += EPV), ...);
+      if (WARP) {
+        const float cut = &o == on ? cut_nd : cut_nc;
+#pragma unroll
+        for (int j = 0; j < (int)sizeof...(q) * EPV; ++j) f[j] = cut_below(f[j], cut);
+      }
+      o.add(f, &o == on ? Ld : Lc);
+      __builtin_amdgcn_sched_barrier(0);               // one at a time: the parked vectors own the registers
+    };
+    auto add = [&](const u32x4& qd, const u32x4& qc) {
+      add_row(on[0], qd);
+      add_row(on[1], qc);
+    };
+    auto add2 = [&](const u32x4& qd0, const u32x4& qd1, const u32x4& qc0, const u32x4& qc1) {
+      add_row(on[0], qd0, qd1);
+      add_row(on[1], qc0, qc1);
+    };
+    auto add_min = [&](const u32x4& qd, const u32x4& qc) {
+      acc.template add_vec<DT, WARP>(qd, qc, cut_cd, cut_cc);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // `steps` vector pairs per lane of the run [lo, hi) of two rows, two of them in flight: place(s) is the lane's
+    // vector (past either end: one that exists, replaced by -inf, which adds nothing)
+    auto stream = [&](const char* rd, const char* rc, int steps, int lo, int hi, auto&& place, auto&& load, auto&& use) {
+      u32x4 d0, c0, d1, c1;
+      auto get = [&](int s, u32x4& qd, u32x4& qc) {
+        const int i = min(max(place(s), lo), hi - 1);
+        qd = load(rd, i);
+        qc = load(rc, i);
+      };
+      auto put = [&](int s, const u32x4& qd, const u32x4& qc) {
+        const int i = place(s);
+        const bool in = i >= lo && i < hi;
+        use(s, in ? qd : neg, in ? qc : neg);
+      };
+      if (steps <= 0) return;
+      get(0, d0, c0);
+      get(1, d1, c1);
+#pragma unroll 1
+      for (int s = 0; s < steps; s += 2) {
+        put(s, d0, c0);
+        get(s + 2, d0, c0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 < steps) put(s + 1, d1, c1);
+        get(s + 3, d1, c1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto temporal = [](const char* r, int i) { return load_vec(r, i); };
+    auto last_use = [](const char* r, int i) { return load_vec_nt(r, i); };
+
+    // ---- sweep 2 of what was not parked, from L2 or memory: the most recently read first
+    if (CUR) {
+      if (tail < a.V) {
+        float zd = load_elem<DT>(cd, tail), zc = load_elem<DT>(cc, tail);
+        if (WARP) { zd = cut_below(zd, cut_cd); zc = cut_below(zc, cut_cc); }
+        acc.add(zd, zc);
+      }
+      stream(cd, cc, rest_steps, lds_end, nvec, [&](int s) { return nvec - 1 - (s * nt + tid); }, last_use,
+             [&](int, const u32x4& qd, const u32x4& qc) { add_min(qd, qc); });
+    }
+    // ---- the LDS share: a lane reads only places that it fills itself, so there is no barrier
+    auto parked = [&](int s) { add_min(park[s * nt + tid], park[kLdsVecs + s * nt + tid]); };
+    if constexpr (NEXT) {
+      stream(nd, nc, lds_steps, lds_begin, lds_end, [&](int s) { return lds_begin + s * nt + tid; }, last_use,
+             [&](int s, const u32x4& qd, const u32x4& qc) {
+               if (CUR) parked(s);
+               add(qd, qc);
+               park[s * nt + tid] = qd;
+               park[kLdsVecs + s * nt + tid] = qc;
+             });
+    } else {
+#pragma unroll 1
+      for (int s = 0; s < lds_steps; ++s) parked(s);
+    }
+    // ---- the register share
+#pragma unroll
+    for (int j = 0; j < kRegIters + (NEXT ? kAhead : 0); ++j) {
+      if (j < kRegIters) {
+        if (CUR) add_min(sd[j], sc[j]);
+        if (NEXT) {
+          const int i = j + 1 < kRegIters ? tid + j * nt : min(tid + j * nt, nvec - 1);
+          sd[j] = load_vec_nt(nd, i);
+          sc[j] = load_vec_nt(nc, i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (NEXT && j == kRegIters - 1 + kAhead) {       // (rows may end inside the last place)
+        const bool in = tid + (kRegIters - 1) * nt < nvec;
+        sd[kRegIters - 1] = in ? sd[kRegIters - 1] : neg;
+        sc[kRegIters - 1] = in ? sc[kRegIters - 1] : neg;
+      }
+      if (NEXT && j >= kAhead && ((j - kAhead) & 1))
+        add2(sd[j - kAhead - 1], sd[j - kAhead], sc[j - kAhead - 1], sc[j - kAhead]);
+    }
+    if (CUR) store_sums(acc, sums);
+    // ---- the rest of sweep 1
+    float zx = __builtin_nanf("");
+    if (NEXT) {
+      stream(nd, nc, rest_steps, lds_end, nvec, [&](int s) { return lds_end + s * nt + tid; }, temporal,
+             [&](int, const u32x4& qd, const u32x4& qc) { add(qd, qc); });
+      tok_next = a.x[next];
+      if (tok_next >= 0 && tok_next < a.V && (tid == kLaneDraft || tid == kLaneCompanion))
+        zx = load_elem<DT>(tid == kLaneDraft ? nd : nc, tok_next);
+      if (tail < a.V) {
+        float zd = load_elem<DT>(nd, tail), zc = load_elem<DT>(nc, tail);
+        if (WARP) { zd = cut_below(zd, cut_nd); zc = cut_below(zc, cut_nc); }
+        on[0].add1(zd, Ld);
+        on[1].add1(zc, Lc);
+      }
+      store_partials(on, mg, Ld, Lc);
+    }
+    __syncthreads();
+    // ---- wavefront 1 ends the pair of sweep 2 while wavefront 0 prepares the next one's
+    if (CUR && wave == 1) end_pair<WITH_KL, WARP>(a, cur, consts[at], tok_cur, sums);
+    if (NEXT) {
+      if (wave == 0)
+        publish_consts(mg, kWaves, consts[at ^ 1], a, next,
+                       WARP ? cut_below(zx, tid == kLaneDraft ? cut_nd : cut_nc) : zx, sc_d, sc_c);
+      __syncthreads();
+      cur = next; tok_cur = tok_next; at ^= 1;
+      cd = nd; cc = nc;
+      cut_cd = cut_nd; cut_cc = cut_nc;
+      next += gridDim.x;
+    }
+  };
+  pass(std::false_type(), std::true_type());
+#pragma unroll 1
+  while (next < pairs) pass(std::true_type(), std::true_type());
+  pass(std::true_type(), std::false_type());
+}
+
+// More than 64 KB of dynamic LDS has to be allowed once per kernel and device.
+template <class Kernel>
+static int launch_kernel(Kernel* kernel, bool (&allowed)[64], int groups, int threads, size_t lds_bytes, const StatsArgs& a,
+                         hipStream_t st) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return SV_ERR_LAUNCH;
-  if (dev < 0 || dev >= kMaxDevices || !allowed[dev]) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&row_stats_stash_kernel<DT, WITH_KL, WARP, Shape>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
+  if (dev < 0 || dev >= 64 || !allowed[dev]) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes) != hipSuccess)
       return SV_ERR_LAUNCH;
-    if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
+    if (dev >= 0 && dev < 64) allowed[dev] = true;
   }
   TapScope tap(SV_KERNEL_ROW_STATS, st);
-  hipLaunchKernelGGL((row_stats_stash_kernel<DT, WITH_KL, WARP, Shape>), dim3(a.B * a.k), dim3(Shape::threads),
-                     lds_bytes, st, a);
+  hipLaunchKernelGGL(kernel, dim3(groups), dim3(threads), lds_bytes, st, a);
   return launch_status();
 }
 
-// Which shape (us between events around the call, two or three sets of rows in turn; pairs x entries, bf16 unless
-// said otherwise; wide / two / three).
-//  * At most one pair per CU: more lanes per pair.  256 x 128256: 39.3 / 41.3 / 41.1; 128 x 128256: 32.6 / 37.0 / 35.3,
-//    fp32 44.1 / 54.0 / 54.4; 64 x 32000: 14.0 / 15.2 / 14.2.  Below a vector per lane half of the lanes have nothing to do:
-//    256 x 8192: 10.3 / 10.2 / 9.8.  (Just above that line it is still 1 us behind: 256 x 12288: 12.1 / 11.6 / 11.1.)
-//  * Rows that three workgroups keep (nearly) on chip, or whose arithmetic they overlap better than
-//    the bytes they read twice cost: 8192 x 32000: two 248, three 210; 1024 x 50304: 55.6 and 53.1; 512 x
-//    100352: 54.2 and 54.0, 512 x 112000: 60.7 and 61.5.  fp32 has half the arithmetic per byte: 512 x 26000: 28.9 and
-//    26.7, 512 x 32000: 32.4 and 31.7, but 800 x 32000: 51.4 and 56.0.  (The lines are a compromise: 512 pairs, resident
-//    at once either way, gain up to them and a little beyond; several rounds of pairs cross earlier, 1024 x 88000: 89.0
-//    and 90.4, with KL 112.5 and 109.5; fp32 2100 x 24000: 79.8 and 83.5.)
-//  * Longer rows are bound by what is read twice: 512 x 128256: 67.5 and 72.2; 512 x 152064: 80.1 and 87.4; fp32 512 x
-//    65536: 62.8 and 73.2.
-// Rows off 16 bytes follow the same lines; without the LDS share they read more of a pair twice (512 x 128257: 85.5).
+template <int DT, bool WITH_KL, bool WARP, class Shape>
+static int launch_shape(const StatsArgs& a, hipStream_t st) {
+  static bool allowed[64] = {};
+  return launch_kernel(&row_stats_stash_kernel<DT, WITH_KL, WARP, Shape>, allowed, a.B * a.k, Shape::threads,
+                       2 * (size_t)Shape::lds_vecs * 16, a, st);
+}
+
+template <int DT, bool WITH_KL, bool WARP, class Shape>
+static int launch_loop(const StatsArgs& a, hipStream_t st) {
+  static bool allowed[64] = {};
+  return launch_kernel(&row_stats_loop_kernel<DT, WITH_KL, WARP, Shape>, allowed, std::min(Shape::groups, a.B * a.k),
+                       Shape::threads, 2 * (size_t)Shape::lds_vecs * 16, a, st);
+}
+
+// Which kernel and shape (pairs x entries, bf16 unless said otherwise; us between events around the call, two sets of
+// rows in turn; the former kernel, one pair per workgroup with all loads ahead of all arithmetic / as it is now).
+//  * The loop kernel nearly everywhere, with a register share about as long as the row.  64 x 8192: 9.0 / 8.1; 64 x 32000:
+//    13.8 / 11.7; 256 x 32000: 16.6 / 13.7; 1024 x 32000: 38.0 / 33.4; 4096 x 32000: 108 / 104; 256 x 128256: 38.8 / 34.0; 512 x
+//    152064: 79.2 / 71.5; 1024 x 152064: 151 / 127; rows off 16 bytes, 512 x 128257: 86.3 / 72.3; fp32, 256 x 128256: 74.5 / 61.4;
+//    with KL, 512 x 152064: 101 / 88, 256 x 32000: 20.8 / 16.7.
+//  * One workgroup per CU from 5632 vectors on if there are no more pairs than CUs, else from 7168 on; below, two, which
+//    cover each other's merges.  256 x 50304: one 18.3, two 19.0; 1024 x 50304: 51.6 and 49.4.
+//  * Many pairs of short rows have enough to overlap as they are, three to a CU, and the hardware to balance them: 4096 x
+//    25000: loop 98.8, three 85.7; 2048 x 17000: 42.7 and 39.4; fp32 4096 x 6000: 50.5 and 49.2.  (1024 x 25000: 30.5 and 32.0.)
+//  * A few pairs more than CUs, of rows that do not stay on chip: a CU that has two takes longer one after the other than
+//    side by side.  300 x 262144: loop 115, two 110; fp32 300 x 65536: 45.4 and 41.8; 341 x 65536: 47.4 and 45.4.
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
-  constexpr int kCUs = 256, kThreeMax = DT == DT_BF16 ? 13000 : 6500;      // vectors of a row
+  constexpr bool kBf16 = DT == DT_BF16;
+  constexpr int kCUs = 256, nt = 512;
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
-  if (pairs <= kCUs && nvec > StashWide::threads) return launch_shape<DT, WITH_KL, WARP, StashWide>(a, st);
-  if (nvec <= kThreeMax) return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
-  return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
+  const bool one = nvec > (pairs <= kCUs ? 11 * nt : 14 * nt);
+  const bool many = (kBf16 && nvec <= 7 * nt && pairs > 6 * kCUs) || (nvec <= 3 * nt && pairs > 12 * kCUs);
+  const bool few_more = pairs > kCUs && (kBf16 ? nvec > 20000 && pairs <= 400
+                                               : nvec > 12800 && pairs <= (nvec > 24000 ? 340 : 390));
+  if (nvec <= nt || many) return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
+  if (few_more) return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
+  if (nvec > 23 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 18 : WARP ? 22 : 24, 1>>(a, st);
+  if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 12 : 16, 1>>(a, st);
+  if (one) return launch_loop<DT, WITH_KL, WARP, Loop<12, 1>>(a, st);
+  if (nvec > 7 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL || WARP ? 6 : 8, 2>>(a, st);
+  if (nvec > 5 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<6, 2>>(a, st);
+  if (nvec > 3 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<4, 2>>(a, st);
+  return launch_loop<DT, WITH_KL, WARP, Loop<2, 2>>(a, st);
 }
 
 // Argument checks and launch shared by sv_row_stats and sv_row_stats_warped.

@@ -78,8 +78,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // one 128-bit loa
 // address (global_load_dwordx4; a wavefront touches one cache line more than an aligned one),
 // so rows of an odd vocabulary, which start on any element, are swept with the loads of any other:
 // 24 x 5 positions of 32001 bfloat16 entries, the whole three-call step: 39.9 us, 75.8 us with
-// scalar loads.  (Loads straight into LDS do need 16-byte addresses: the row statistics of such rows
-// park less of a pair on chip, 512 x 128257: 85.5 us, 512 x 128256: 67.7.)
+// scalar loads.  (Row statistics, 512 x 128257: 72.3 us, 512 x 128256: 58.6.)
 typedef u32x4 u32x4_row __attribute__((aligned(2)));
 
 __device__ __forceinline__ u32x4 load_vec(const void* row, int i) {
@@ -157,10 +156,13 @@ struct OnlineOf {
     for (int j = 0; j < N; ++j) e[j] = exp2_fast(__builtin_fmaf(z[j], L, -cn));
     // pairwise tree so that no single chain carries all roundings
     float t = 0.f;
-    if constexpr (N == 8) {
-      t = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-    } else if constexpr (N == 4) {
-      t = (e[0] + e[1]) + (e[2] + e[3]);
+    if constexpr (N == 4 || N == 8 || N == 16) {
+#pragma unroll
+      for (int h = 1; h < N; h <<= 1) {
+#pragma unroll
+        for (int j = 0; j < N; j += 2 * h) e[j] += e[j + h];
+      }
+      t = e[0];
     } else {
 #pragma unroll
       for (int j = 0; j < N; ++j) t += e[j];
