@@ -393,8 +393,11 @@ __device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeS
 // log2 of sum_v 2^(z_v L); the natural-log LSE of the row z / T follows after
 // removing the temperature offset around the maximum.  Bad rows (NaN, +inf, no
 // finite entry) give NaN.
+__device__ __forceinline__ bool bad_row(const MS& r, const float L) {
+  return !(r.s > 0.0) || !isfinite(r.s) || !isfinite(r.m) || ref_of(r.m, L) > kRefCeil;
+}
 __device__ __forceinline__ double lse_from_ms(const MS& r, const Scale sc = unit_scale()) {
-  if (!(r.s > 0.0) || !isfinite(r.s) || !isfinite(r.m) || ref_of(r.m, sc.L) > kRefCeil) return __builtin_nan("");
+  if (bad_row(r, sc.L)) return __builtin_nan("");
   const double kappa = (double)ref_of(r.m, sc.L) + log2(r.s);
   return kappa * kLn2 - sc.tau1 * ((double)r.m * sc.inv_t);
 }

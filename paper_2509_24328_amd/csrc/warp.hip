@@ -261,10 +261,6 @@ __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online
   for (int v = nvec * EPV + tid; v < V; v += nt) acc.add1(load_elem<DT>(row, v), L);
 }
 
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
-  const uint32_t lo = __shfl((uint32_t)v, src, kWave), hi = __shfl((uint32_t)(v >> 32), src, kWave);
-  return ((uint64_t)hi << 32) | lo;
-}
 __device__ __forceinline__ double shfl_f64(double v, int src) {
   int lo = __double2loint(v), hi = __double2hiint(v);
   lo = __shfl(lo, src, kWave);
@@ -274,17 +270,33 @@ __device__ __forceinline__ double shfl_f64(double v, int src) {
 
 // Descending bitonic sort of one 64-bit key per lane inside a wavefront: the first n2
 // lanes (a power of two) are sorted among themselves, which is all that is needed
-// when the other lanes hold zeros.
+// when the other lanes hold zeros.  Partners up to 8 lanes away are register moves (64 keys: 1300 cycles, 3000 with
+// shuffles throughout).
+template <int MASK>
+__device__ __forceinline__ uint64_t lane_xor_u64(uint64_t v) {
+  return ((uint64_t)(uint32_t)lane_xor<MASK>((int)(v >> 32)) << 32) | (uint32_t)lane_xor<MASK>((int)(uint32_t)v);
+}
 __device__ __forceinline__ uint64_t wave_sort_desc(uint64_t key, int n2 = kWave) {
   const int lane = threadIdx.x & 63;
-  for (int k2 = 2; k2 <= n2; k2 <<= 1) {
-    for (int j = k2 >> 1; j > 0; j >>= 1) {
-      const uint64_t other = shfl_u64(key, lane ^ j);
-      const bool desc = (lane & k2) == 0, lower = (lane & j) == 0;
-      const uint64_t hi = key > other ? key : other, lo = key > other ? other : key;
-      key = (lower == desc) ? hi : lo;
-    }
-  }
+  auto exchange = [&](uint64_t other, int k2, int j) {
+    const bool desc = (lane & k2) == 0, lower = (lane & j) == 0;
+    key = (lower == desc) == (key > other) ? key : other;   // (equal keys, zeros, may change places)
+  };
+  auto steps = [&](int k2, auto top) {                   // partners at top, top / 2, ..., 1
+    constexpr int J = decltype(top)::value;
+    if constexpr (J >= 32) exchange(lane_xor_u64<32>(key), k2, 32);
+    if constexpr (J >= 16) exchange(lane_xor_u64<16>(key), k2, 16);
+    if constexpr (J >= 8) exchange(lane_xor_u64<8>(key), k2, 8);
+    if constexpr (J >= 4) exchange(lane_xor_u64<4>(key), k2, 4);
+    if constexpr (J >= 2) exchange(lane_xor_u64<2>(key), k2, 2);
+    exchange(lane_xor_u64<1>(key), k2, 1);
+  };
+  steps(2, std::integral_constant<int, 1>());
+  if (n2 > 2) steps(4, std::integral_constant<int, 2>());
+  if (n2 > 4) steps(8, std::integral_constant<int, 4>());
+  if (n2 > 8) steps(16, std::integral_constant<int, 8>());
+  if (n2 > 16) steps(32, std::integral_constant<int, 16>());
+  if (n2 > 32) steps(64, std::integral_constant<int, 32>());
   return key;
 }
 
@@ -691,8 +703,8 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   block_merge(acc, sh.mg, merged, lt);
   const float m = merged[0].m;
   SV_PHASE_MARK(1)
-  const double lse_row = lse_from_ms(merged[0], sc);   // of z / T over the whole row; NaN: bad row
-  if (isnan(lse_row)) {
+  const double row_s = merged[0].s;
+  if (bad_row(merged[0], lt)) {
     if (tid == 0) {
       if (cutoff) cutoff[r] = __builtin_nanf("");
       if (flags) flags[r] = SV_FLAG_BAD_ROW;
@@ -705,33 +717,44 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     if (tid == 0) {
       if (cutoff) cutoff[r] = -INFINITY;
       if (flags) flags[r] = 0;
-      if (out.count) { out.count[r] = -1; out.lse[r] = (float)lse_row; }
+      if (out.count) { out.count[r] = -1; out.lse[r] = (float)lse_from_ms(merged[0], sc); }   // of z / T over the whole row
     }
     return;
   }
   const double m_t = (double)m * sc.inv_t;
-  const double Z = exp(lse_row - m_t);                  // sum_v exp((z_v - m) / T)
-  if (tid == 0) { sh.row_s = merged[0].s; sh.row_Z = Z; }
 
   // The rank-th largest of the 512 lane maxima, to the 16 upper bits of its order key
   // (exact for bfloat16, rounded down for fp32): a lower bound of the rank-th largest
   // entry of the row.  Wavefront 0 holds eight maxima per lane and bisects the 16 bits
   // with ballots.
   sh.lane_key[tid] = okey(acc[0].m) >> 16;
+  if (tid == 0) { sh.n_cand = 0; sh.near_tie = 0; sh.settled = 0; sh.n_keep = -1; sh.out_done = 0; }
   __syncthreads();
+  if (tid == kWave) {
+    // sum_v exp((z_v - m) / T), by one lane while wavefront 0 looks for tau (by every lane, the rows of a compute unit
+    // keep it busy for 6 thousand cycles); a barrier comes before its first use
+    sh.row_s = row_s;
+    sh.row_Z = row_s * exp((double)ref_of(m, lt) * kLn2 - sc.tau1 * m_t - m_t);
+  }
   auto lane_max_of_rank = [&](int rank) {
     if (tid < kWave) {
       uint32_t kk[kWarpThreads / kWave];
 #pragma unroll
       for (int j = 0; j < kWarpThreads / kWave; ++j) kk[j] = sh.lane_key[tid + kWave * j];
-      uint32_t t = 0;
-      for (int bit = 15; bit >= 0; --bit) {
-        const uint32_t cand = t | (1u << bit);
+      auto reached = [&](uint32_t cand) {                  // at least `rank` keys from there up
         int c = 0;
 #pragma unroll
         for (int j = 0; j < kWarpThreads / kWave; ++j) c += __popcll(__ballot(kk[j] >= cand));
-        if (c >= rank) t = cand;
-      }
+        return c >= rank;
+      };
+      // the lane maxima lie close under the row's: a window under it first, widened until it holds them
+      const uint32_t top16 = okey(m) >> 16;
+      uint32_t width = 64, t = 0;
+      while (width <= top16 && !reached(top16 - width + 1)) width <<= 2;
+      if (width <= top16) t = top16 - width + 1; else width = 1u << 16;
+      // (t is reached; what lies `width` above it is not, unless fewer keys than the rank are above anything)
+      for (uint32_t half = width >> 1; half > 0; half >>= 1)
+        if (reached(t + half)) t += half;
       if (tid == 0) sh.tau_key = t << 16;
     }
     __syncthreads();
@@ -744,6 +767,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   // with shuffles (no barriers, no serial walk); it also writes the row's support.
   auto settle_wave = [&](int n) {
     const int lane = tid;                                // wavefront 0: tid = lane
+    const double Z = sh.row_Z;
     uint64_t key = lane < n ? sh.key[lane] : 0;
     int n2 = 2;
     while (n2 < n) n2 <<= 1;
@@ -756,7 +780,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     double total = Z;
     if (use_k) {
       if (n >= top_k) {
-        t_k = __shfl(v, top_k - 1, kWave);
+        t_k = lane_f32(v, top_k - 1);
         ns = __popcll(__ballot(valid && v >= t_k));      // a prefix: the list is sorted
       }
       total = wave_sum_f64(lane < ns ? w : 0.0);
@@ -767,12 +791,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     bool ok = true;
     int near = 0;
     if (use_p) {
-      double incl = lane < ns ? w : 0.0;                 // inclusive prefix masses
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const double o = shfl_f64(incl, max(lane - off, 0));
-        if (lane >= off) incl += o;
-      }
+      const double incl = wave_scan_f64(lane < ns ? w : 0.0);   // prefix masses
       const float v_next = __shfl(v, min(lane + 1, kWave - 1), kWave);
       const bool group_end = lane < ns && (lane == ns - 1 || v_next != v);
       const double frac = incl / total;
@@ -782,9 +801,9 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
       ok = d >= 0;
       if (ok) {
         near = __ballot(group_end && lane <= d && fabs(frac - (double)top_p) < kNearTie) != 0;
-        th = __shfl(v, d, kWave);
+        th = lane_f32(v, d);
         nk = d + 1;
-        kept = shfl_f64(incl, d);
+        kept = lane_f64(incl, d);
       }
     } else if (!use_k) {
       kept = wave_sum_f64(w);                            // no warp at all (short rows)
@@ -824,6 +843,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   // sh.n_keep, sh.z_keep are set and the kept entries are sh.key[0 .. n_keep)).
   auto settle = [&](float tau) {
     const int n = sh.n_cand;
+    const double Z = sh.row_Z;
     if (n <= kWave && (!use_k || n >= top_k || tau == -INFINITY)) {
       if (tid < kWave) settle_wave(n);
       __syncthreads();
@@ -832,7 +852,9 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
     // fewer than K candidates happens only when tau = -inf lists every finite entry
     // of the row (masked vocabularies): top-k then keeps them all
     if (!(n <= kCand && (!use_k || n >= top_k || tau == -INFINITY))) return false;
-    if (n <= kWarpThreads) {
+    if (n <= kRankMax) {
+      sort_desc_ranks(sh.key, n);
+    } else if (n <= kWarpThreads) {
       sort_desc_runs(sh.key, reinterpret_cast<uint64_t*>(sh.w), n);    // (the masses are not there yet)
     } else {
       int n2 = kWarpThreads;
@@ -873,13 +895,8 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
       mine += wv[j];
     }
     vv[kRun] = i0 + kRun < n ? key_value(sh.key[i0 + kRun]) : -INFINITY;
-    double incl = mine;                               // inclusive scan of the lanes' sums
     const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const double o = shfl_f64(incl, max(lane - off, 0));
-      if (lane >= off) incl += o;
-    }
+    const double incl = wave_scan_f64(mine);          // of the lanes' sums
     if (lane == kWave - 1) sh.red.d[wave] = incl;
     if (tid == 0) { sh.first_reach = 0x7fffffff; sh.near_any = 0; }
     __syncthreads();
@@ -938,8 +955,6 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   };
 
   bool settled = false;
-  if (tid == 0) { sh.n_cand = 0; sh.near_tie = 0; sh.settled = 0; sh.n_keep = -1; sh.out_done = 0; }
-  __syncthreads();
 
   // ---- attempt 1: only the lanes' largest vectors are read again.
   // A lane whose fourth-largest vector may reach tau may hide a fifth one that
@@ -952,18 +967,20 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
       // no support to write and too little mass for that one as well, for none (kHopeless).
       if (tid < kWave) {
         const uint32_t t16 = sh.tau_key >> 16;
-        double above = 0.0;
+        // (an estimate, relative to 2^c(m): it chooses between ways to the same cutoff)
+        const float c_ref = ref_of(m, lt);
+        float above = 0.f;
 #pragma unroll
         for (int j = 0; j < kWarpThreads / kWave; ++j) {
           const uint32_t k16 = sh.lane_key[tid + kWave * j];
           // (the 16-bit key rounds an fp32 maximum down: the sum is a lower bound)
-          if (k16 >= t16 && k16 > (okey(-INFINITY) >> 16)) above += exp((double)from_okey(k16 << 16) * sc.inv_t - m_t);
+          if (k16 >= t16 && k16 > (okey(-INFINITY) >> 16)) above += exp2_fast(__builtin_fmaf(from_okey(k16 << 16), lt, -c_ref));
         }
-        above = wave_sum_f64(above);
-        if (tid == 0) sh.z_keep = above;
+        const double sum = wave_sum_f64((double)above);
+        if (tid == 0) sh.z_keep = sum;
       }
       __syncthreads();
-      const double share = sh.z_keep / ((double)top_p * Z);
+      const double share = sh.z_keep / ((double)top_p * row_s);
       __syncthreads();
       if (!out.count && share < kHopeless) tau = -INFINITY;
       else if (share < 1.0 + 1e-6) tau = lane_max_of_rank(kNucleusRank2);
@@ -978,20 +995,26 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
           if (at < kCand) sh.key[at] = ((uint64_t)okey(f) << 32) | (uint64_t)(0xFFFFFFFFu - v);
         }
       };
-      auto list_vector = [&](uint32_t vec) {
+      auto list_vector = [&](const u32x4& q, uint32_t vec) {
         float f[EPV];
-        unpack<DT>(load_vec(row, (int)vec), f);
+        unpack<DT>(q, f);
 #pragma unroll
         for (int e = 0; e < EPV; ++e) list_entry(f[e], vec * EPV + (uint32_t)e);
       };
       for (int v = V / EPV * EPV + tid; v < V; v += kWarpThreads) list_entry(load_elem<DT>(row, v), (uint32_t)v);
       if (top.k4 >= tau_key) {
-        for (uint32_t vec = (uint32_t)tid; vec < (uint32_t)(V / EPV); vec += kWarpThreads) list_vector(vec);
+        for (uint32_t vec = (uint32_t)tid; vec < (uint32_t)(V / EPV); vec += kWarpThreads)
+          list_vector(load_vec(row, (int)vec), vec);
       } else {
+        // (the loads of the up to three vectors go out together)
         const uint32_t keys[3] = {top.k1, top.k2, top.k3};
+        u32x4 q[3];
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
-          if (keys[q] >= tau_key) list_vector((keys[q] & 0xFFFFu) * kWarpThreads + (uint32_t)tid);
+        for (int k = 0; k < 3; ++k)
+          if (keys[k] >= tau_key) q[k] = load_vec(row, (int)((keys[k] & 0xFFFFu) * kWarpThreads + (uint32_t)tid));
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          if (keys[k] >= tau_key) list_vector(q[k], (keys[k] & 0xFFFFu) * kWarpThreads + (uint32_t)tid);
       }
       __syncthreads();
       SV_PHASE_MARK(3)
