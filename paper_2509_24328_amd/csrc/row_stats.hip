@@ -706,11 +706,12 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
   if (nvec <= nt || many) return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
   if (few_more) return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
   if (nvec > 23 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 18 : WARP ? 22 : 24, 1>>(a, st);
-  if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 12 : 16, 1>>(a, st);
+  constexpr bool kPlain = !WITH_KL && !WARP;              // (a kernel less for every form where the neighbour will do)
+  if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 16 : 12, 1>>(a, st);
   if (one) return launch_loop<DT, WITH_KL, WARP, Loop<12, 1>>(a, st);
-  if (nvec > 7 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL || WARP ? 6 : 8, 2>>(a, st);
+  if (nvec > 7 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 8 : 6, 2>>(a, st);
   if (nvec > 5 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<6, 2>>(a, st);
-  if (nvec > 3 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<4, 2>>(a, st);
+  if (nvec > 3 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 4 : 2, 2>>(a, st);
   return launch_loop<DT, WITH_KL, WARP, Loop<2, 2>>(a, st);
 }
 
