@@ -130,10 +130,10 @@ def _ptr(t):
     read as if it were."""
     if t is None:
         return None
-    if not t.is_cuda or not t.is_contiguous():
-        raise ValueError("sv: tensors must be contiguous device tensors "
-                         f"(got device={t.device}, contiguous={t.is_contiguous()})")
-    return ctypes.c_void_p(t.data_ptr())
+    if t.is_cuda and t.is_contiguous():
+        return t.data_ptr()                 # (an int: fifty c_void_p objects are 4 us of a step's host time)
+    raise ValueError("sv: tensors must be contiguous device tensors "
+                     f"(got device={t.device}, contiguous={t.is_contiguous()})")
 
 
 def _stream(stream):
@@ -145,7 +145,7 @@ def _stream(stream):
         return ctypes.c_void_p(stream.cuda_stream)
     if torch.cuda.is_initialized():
         try:
-            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         except AttributeError:
             pass
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
@@ -277,7 +277,7 @@ def sv_warp_cutoffs(z, temperature, top_k, top_p, cutoff, flags=None, stream=Non
 
 def _host_ptrs(tensors):
     """Host array of the device addresses of `tensors` (None entries -> NULL)."""
-    return (ctypes.c_void_p * len(tensors))(*[None if t is None else _ptr(t).value for t in tensors])
+    return (ctypes.c_void_p * len(tensors))(*[None if t is None else _ptr(t) for t in tensors])
 
 
 def _warp_lists(zs, temperature, top_k, top_p):
