@@ -47,6 +47,7 @@ namespace sv {
 
 constexpr int kRowsThreads = 256;
 constexpr int kSampleThreads = 256;             // mass kernel: one workgroup per chunk
+constexpr int kWideThreads = 512;               // mass kernel of a small batch: one workgroup per granule
 constexpr int kPickThreads = 256;               // pick kernel: one workgroup per sequence
 constexpr int kMaxChunks = 2048;                // V <= kMaxChunks * kChunk
 static_assert(kMaxSplit == kMaxParts, "fold_row_parts reads up to kMaxParts partials of a row");
@@ -227,7 +228,7 @@ __global__ __launch_bounds__(kRowsThreads) void verify_rows_kernel(VerifyArgs a)
 // 2^10 + 150, l_lo / L and k_lo / kappa at most 2^-24), and 2^head (1 + ln2 tail) is right to
 // 5e-9 (`small`).  The tail is formed from the head there, tail = head l_lo / L + (k_hi l_lo / L -
 // k_lo), and the head is kept above -256, which stands for any entry without mass: five
-// operations against eleven (the mass pass of 64 x 152064 bf16: 15.1 us, 17.5 us with the general form).
+// operations against eleven (the mass pass of 64 x 152064 bf16: 15.1 us, 17.5 us with the general form when this was chosen).
 // Against 64 bits the two are equally exact: 1-norm of a row's errors, mean over 324 rows of each of five kinds
 // (general / short, normalisers from fp32 sums as here): 1.43 / 1.41, 1.30 / 1.31, 0.19 / 0.18, 0.65 / 0.63, 0.65 / 0.65 e-7.
 struct ProbRow {
@@ -297,8 +298,9 @@ struct alignas(16) Plan {
   double lse_t, lse_d;
   int n;               // accepted count = position that is sampled
   uint32_t flags;
-  int resid;           // 0: target distribution; 1: residual max(0, P_t - P_d); 2: residual that may be empty
-  int target_ok;
+  int16_t resid;       // 0: target distribution; 1: residual max(0, P_t - P_d); 2: residual that may be empty
+  int16_t target_ok;
+  uint32_t random;     // Philox word of the sampling uniform
 };
 
 static_assert(sizeof(Plan) == 32, "workspace carve-up reserves 32 bytes per sequence");
@@ -347,6 +349,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     have_target = target_there;
     lse_t = lse_from_ms(ms_t, a.sc_t);
   }
+  const U4 random = philox4x32_10((uint32_t)i, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
   if (evaluated) {
     lse_d = lse_from_ms(ms_d, a.sc_d);
     if (tok < 0 || tok >= V) {
@@ -359,8 +362,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
       rho = exp(lt - ld);                         // -inf - -inf = NaN: rejected
       gap = exp2_fast((float)(ld * kLog2e)) * (1.f - (float)rho);
     }
-    const U4 r = philox4x32_10((uint32_t)i, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
-    const double u = unit_from_word(r.w[0]);
+    const double u = unit_from_word(random.w[0]);
     accept = u < rho;                             // false for NaN
     if (!isnan(rho) && fabs(u - fmin(1.0, rho)) < 1e-6) fl |= SV_FLAG_NEAR_TIE;
   }
@@ -368,7 +370,8 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   const int n = rej ? (int)__builtin_ctzll(rej) : g;          // leading accepts
   // flags of the positions that were actually evaluated: 0..min(n, g-1)
   if (!(evaluated && i <= n)) fl = 0;
-  for (int off = 32; off >= 1; off >>= 1) fl |= __shfl_xor(fl, off, kWave);
+  fl = (__ballot(fl & SV_FLAG_BAD_TOKEN) ? SV_FLAG_BAD_TOKEN : 0u) | (__ballot(fl & SV_FLAG_BAD_ROW) ? SV_FLAG_BAD_ROW : 0u) |
+       (__ballot(fl & SV_FLAG_NEAR_TIE) ? SV_FLAG_NEAR_TIE : 0u);
   if (publish) {
     if (a.ratio && i < k) a.ratio[b * k + i] = (evaluated && i <= n) ? (float)rho : __builtin_nanf("");
     int32_t* out = a.out_tokens + (size_t)b * (k + 1);
@@ -382,16 +385,19 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   const float may_be_off = 1e-5f + (float)V * (1.f / 1024.f) * 1.2e-7f;
   double lse_t_n, lse_d_n;
   int have_target_n, maybe_empty = 0;
+  uint32_t random_n;
   if (n < kWave) {
-    lse_t_n = __shfl(lse_t, n, kWave);
-    lse_d_n = __shfl(lse_d, n, kWave);
-    const int both = __shfl((int)have_target | (gap > may_be_off ? 0 : 2), n, kWave);
+    lse_t_n = lane_f64(lse_t, n);
+    lse_d_n = lane_f64(lse_d, n);
+    const int both = __builtin_amdgcn_readlane((int)have_target | (gap > may_be_off ? 0 : 2), n);
     have_target_n = both & 1;
     maybe_empty = both >> 1;
+    random_n = (uint32_t)__builtin_amdgcn_readlane((int)random.w[1], n);
   } else {
     lse_t_n = lse_from_ms(target_ms(a, b, n), a.sc_t);
     lse_d_n = __builtin_nan("");
     have_target_n = target_row<DT>(a, b, n) != nullptr;
+    random_n = philox4x32_10((uint32_t)n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi).w[1];
   }
   if (i == 0) {
     uint32_t flags = fl;
@@ -405,7 +411,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     if (CHAIN && !chain_ok) flags |= SV_FLAG_NO_CHAIN;
     Plan pl;
     pl.lse_t = lse_t_n; pl.lse_d = resid ? lse_d_n : 0.0; pl.n = n; pl.flags = flags;
-    pl.resid = resid ? 1 + maybe_empty : 0; pl.target_ok = target_ok ? 1 : 0;
+    pl.resid = (int16_t)(resid ? 1 + maybe_empty : 0); pl.target_ok = target_ok ? 1 : 0; pl.random = random_n;
     *plan_out = pl;
     if (publish) {
       a.ws.plan[b] = pl;
@@ -426,7 +432,7 @@ struct SampleRow {
   bool small;                // both normalisers allow the short form of the probabilities
   __device__ __forceinline__ SampleRow(const VerifyArgs& a, int b, const Plan& pl) {
     resid = pl.resid != 0;
-    maybe_empty = __builtin_amdgcn_readfirstlane(pl.resid) == 2;
+    maybe_empty = __builtin_amdgcn_readfirstlane((int)pl.resid) == 2;
     row_t = target_row<DT>(a, b, pl.n);
     row_d = resid ? draft_row<DT>(a, b, pl.n) : row_t;
     pt.set(pl.lse_t, a.sc_t);
@@ -496,16 +502,16 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
 
 // grid (chunks, B): the accept decision of the sequence (every workgroup forms it for
 // itself, chunk 0 publishes it), then the masses of the two granules of one chunk of the
-// sampling row, two wavefronts per granule.  Bound by the latency chain partials ->
+// sampling row, two wavefronts per granule (WIDE: the mass of one, eight wavefronts).  Bound by the latency chain partials ->
 // decision -> row -> sum on small batches; on large ones, once the decision (3.4 us) has named them, the
-// row pairs go through at 3.4 TB/s (64 x 152064 bf16: 15.0 us; 512 x 32000: 23.6), bound by two exponentials and
+// row pairs go through at 3 TB/s (64 x 152064 bf16: 16.6 us; 512 x 32000: 23.7), bound by two exponentials and
 // some twenty further operations per entry pair.  Seven wavefronts per SIMD: eight leave 64 registers, of which bf16
 // spills 8 and, under cutoffs, 20.
-template <int DT, bool CUT, bool CHAIN>
-__global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyArgs a) {
+template <int DT, bool CUT, bool CHAIN, bool WIDE>
+__global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7) void verify_mass_kernel(VerifyArgs a) {
   __shared__ Plan plan;
-  constexpr int kLanes = kSampleThreads * kGranule / kChunk;           // lanes per granule
-  constexpr int kGran = kChunk / kGranule, kWaves = kLanes / kWave;    // granules, wavefronts per granule
+  constexpr int kGran = WIDE ? 1 : kChunk / kGranule;                  // granules of a workgroup
+  constexpr int kLanes = (WIDE ? kWideThreads : kSampleThreads) / kGran, kWaves = kLanes / kWave;    // of a granule
   __shared__ double part[kGran * kWaves];
   const int b = blockIdx.y, c = blockIdx.x;
   const int tid = threadIdx.x;
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(kSampleThreads, 7) void verify_mass_kernel(VerifyAr
   SV_PHASE_MARK(7)
   const Plan pl = plan;
   const int g = tid / kLanes, lane = tid - g * kLanes;
-  const int v0 = c * kChunk + g * kGranule, v1 = min(a.V, v0 + kGranule);
+  const int v0 = (c * kGran + g) * kGranule, v1 = min(a.V, v0 + kGranule);
   double acc = 0.0, acc_t = 0.0;
   if (pl.target_ok && v0 < v1) {
     const SampleRow<DT, CUT> sr(a, b, pl);
@@ -570,8 +576,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   SampleRow<DT, CUT> sr(a, b, pl);
   int32_t* out = a.out_tokens + (size_t)b * (a.k + 1);
   uint32_t flags = pl.flags;
-  const U4 rnd = philox4x32_10((uint32_t)pl.n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
-  const double u = unit_from_word(rnd.w[1]);
+  const double u = unit_from_word(pl.random);
   // every wavefront scans all granule masses: lane l owns the run [l * q, (l + 1) * q)
   const int q = (G + kWave - 1) / kWave;
   const int g0 = min(lane * q, G), g1 = min(g0 + q, G);
@@ -598,12 +603,17 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
     const unsigned long long at = __ballot(incl > tau && run > 0.0), has = __ballot(run > 0.0);
     const int owner = at ? (int)__builtin_ctzll(at) : 63 - (int)__builtin_clzll(has);
     double before = lane_f64(incl - run, owner);
-    const int h0 = min(owner * q, G), h1 = min(h0 + q, G);
-    for (int g = h0; g < h1; ++g) {
-      const double m = fmax(empty ? -mass[g] : mass[g], 0.0);
-      if (m > 0.0) { gran = g; tau_local = tau - before; }             // (rounding: the last granule with mass)
-      if (before + m > tau) break;
-      before += m;
+    if (q == 1) {                                                      // up to 64 granules: the lane's own
+      gran = owner;
+      tau_local = tau - before;
+    } else {
+      const int h0 = min(owner * q, G), h1 = min(h0 + q, G);
+      for (int g = h0; g < h1; ++g) {
+        const double m = fmax(empty ? -mass[g] : mass[g], 0.0);
+        if (m > 0.0) { gran = g; tau_local = tau - before; }           // (rounding: the last granule with mass)
+        if (before + m > tau) break;
+        before += m;
+      }
     }
   }
   if (gran < 0) {                                                      // nothing can be drawn
@@ -718,6 +728,12 @@ static int rows_split(int rows, int V) {
   return std::max(1, std::min(s, kMaxSplit));
 }
 
+// Up to this many (sequence, granule) pairs the mass pass takes a workgroup of 512 lanes for each: a granule is then one vector
+// per lane.  Above, where the chip is full anyway, a workgroup of 256 lanes takes two granules and decides once for both.
+// us, two granules / one: 8 x 32000 bf16 7.2 / 5.7, 24 x 32001 8.0 / 6.2, 1 x 32000 fp32 6.4 / 5.9, under cutoffs 8 x 32000 8.8 / 7.2;
+// 32 x 128256 (1024 granules) 8.3 / 10.5, 64 x 152064 (2432) 16.6 / 25.6.
+constexpr int kWideGroups = 512;
+
 template <int DT, bool CUT>
 static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   const int rows = a.B * (a.chained ? a.k + 1 : 2 * a.k + 1);
@@ -729,8 +745,17 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   const int C = n_chunks(a.V);
   {
     TapScope tap(SV_KERNEL_VERIFY_MASS, st);
-    if (a.chained) hipLaunchKernelGGL((verify_mass_kernel<DT, CUT, true>), dim3(C, a.B), dim3(kSampleThreads), 0, st, a);
-    else hipLaunchKernelGGL((verify_mass_kernel<DT, CUT, false>), dim3(C, a.B), dim3(kSampleThreads), 0, st, a);
+    auto launch = [&](auto* kernel, int groups, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(groups, a.B), dim3(threads), 0, st, a);
+    };
+    const int G = n_granules(a.V);
+    if ((long)G * a.B <= kWideGroups) {
+      if (a.chained) launch(&verify_mass_kernel<DT, CUT, true, true>, G, kWideThreads);
+      else launch(&verify_mass_kernel<DT, CUT, false, true>, G, kWideThreads);
+    } else {
+      if (a.chained) launch(&verify_mass_kernel<DT, CUT, true, false>, C, kSampleThreads);
+      else launch(&verify_mass_kernel<DT, CUT, false, false>, C, kSampleThreads);
+    }
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;
   {
