@@ -16,7 +16,7 @@
 // re-sums in order otherwise; goodput and first-peak search in parallel; then a
 // sequence takes the products above the M-th largest value, and those equal to it
 // in the order of the keys.  Latency bound at the paper's batch sizes (8 us at 512
-// keys, 12 us at 1024, 51 us at 8192; 11.5, 17 and 130 us with merges of (value, key) pairs).
+// keys, 12 us at 1024; of 8192 keys the 1024 largest are sorted, 27 us, all of them 51 us).
 #include "sv_bins.hpp"
 #include "sv_device.hpp"
 #include "sv_host.hpp"
@@ -32,6 +32,8 @@ namespace sv {
 constexpr int kSelThreads = 1024;
 constexpr int kSelMax = SV_SELECT_MAX_KEYS;   // power of two
 constexpr int kKeysPerLane = kSelMax / kSelThreads;
+constexpr int kSelSteps = 2048;       // histogram of more than 1024 keys ...
+constexpr double kSelFloor = 1.0 / 64;   // ... from here up: most products of long drafts are all but zero and would queue at one counter
 
 // Place of key i in an LDS buffer: a gap after every eight, so that lanes that own runs of
 // eight, or sequences of eight or sixteen, start on different banks.
@@ -206,15 +208,9 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
   double* dst = buffers + slot(npad);
 
   SV_PHASE_MARK(0)
-  // the latencies this lane divides by after the sort: asked for now, so that the
+  // the latency this lane divides by after the sort: asked for now, so that the
   // memory latency passes behind the sort
-  const int R = KEYS == 1 ? 1 : npad / nt;             // keys per lane in the goodput scan
-  float lat_run[KEYS];
-#pragma unroll
-  for (int j = 0; j < KEYS; ++j) {
-    const int idx = tid * R + j;
-    lat_run[j] = (j < R && idx < n) ? latency[idx + 1] : 1.f;
-  }
+  const float lat_own[1] = {tid < n ? latency[tid + 1] : 1.f};
   // estimates into LDS with one round of coalesced loads
   float* p_lds = reinterpret_cast<float*>(dst);
   if (FUSED) {
@@ -247,13 +243,9 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     own[q] = -1.0;
     if (tid + q * nt < n) own[q] = src[slot(tid + q * nt)];
   }
-  {
-    double* sorted = src;
-    if constexpr (KEYS == 1) sort_small(src, dst, npad); else sorted = sort_large(src, dst, n, k, R);
-    if (sorted != src) { dst = src; src = sorted; }
-  }
-
-  SV_PHASE_MARK(2)
+  __shared__ double wave_tot[kSelThreads / kWave];
+  __shared__ double wave_last_g[kSelThreads / kWave];
+  __shared__ int first_stop, first_open;
   // First peak of the estimated goodput G_M = E_M / latency[M], G_0 = 0:
   // M* = first M >= 0 with not (G_{M+1} > G_M).  E_M is DEFINED as the running
   // sum in selection order (fp64, one addition after another), so that the
@@ -263,19 +255,18 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
   // bound the comparison is already decided.  Only if an undecided comparison
   // comes before the first decided stop does one lane run the ordered sum.
   // (The bound holds for any summation tree, so lanes may own runs of keys.)
-  bool need_exact = false;
-  {
-    __shared__ double wave_tot[kSelThreads / kWave];
-    __shared__ double wave_last_g[kSelThreads / kWave];
-    __shared__ int first_stop, first_open;
+  // On the first `count` values in selection order, R <= Q of them per lane (lat: their latencies), with room for
+  // as many sums.  False: no stop among them.  Called by all threads.
+  auto find_peak = [&](auto per_lane, const double* sorted, double* sums, const int count, const int R, const auto& lat) {
+    constexpr int Q = decltype(per_lane)::value;
     if (tid == 0) { first_stop = n; first_open = n; }
     // every lane owns a run of R consecutive keys (R = 1 up to 1024 keys)
-    double e_run[KEYS];
+    double e_run[Q];
     double run = 0.0;
 #pragma unroll
-    for (int j = 0; j < KEYS; ++j) {
+    for (int j = 0; j < Q; ++j) {
       const int idx = tid * R + j;
-      if (j < R) run += (idx < n) ? src[slot(idx)] : 0.0;
+      if (j < R) run += (idx < count) ? sorted[slot(idx)] : 0.0;
       e_run[j] = run;                              // inclusive inside the run
     }
     double e = wave_scan_f64(run);                 // inclusive scan of the run totals
@@ -283,16 +274,16 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     __syncthreads();
     for (int w = 0; w < wave; ++w) e += wave_tot[w];
     const double base = e - run;                   // E' of everything before this lane's run
-    double g_run[KEYS];                    // G'_{idx+1} of the run's keys
+    double g_run[Q];                               // G'_{idx+1} of the run's keys
 #pragma unroll
-    for (int j = 0; j < KEYS; ++j) {
+    for (int j = 0; j < Q; ++j) {
       const int idx = tid * R + j;
       g_run[j] = 0.0;
-      if (j < R && idx < n) g_run[j] = (base + e_run[j]) / (double)lat_run[j];
+      if (j < R && idx < count) g_run[j] = (base + e_run[j]) / (double)lat[j];
     }
     double g_last = 0.0;                           // G' of the last key of the run
 #pragma unroll
-    for (int j = 0; j < KEYS; ++j) if (j == R - 1) g_last = g_run[j];
+    for (int j = 0; j < Q; ++j) if (j == R - 1) g_last = g_run[j];
     if (lane == kWave - 1) wave_last_g[wave] = g_last;
     __syncthreads();
     int lo = __double2loint(g_last), hi = __double2hiint(g_last);
@@ -302,9 +293,9 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     if (lane == 0) g_cur = (wave == 0) ? 0.0 : wave_last_g[wave - 1];
     int stop = n, open = n;                        // the lane's first decided stop, first undecided comparison
 #pragma unroll
-    for (int j = 0; j < KEYS; ++j) {
+    for (int j = 0; j < Q; ++j) {
       const int idx = tid * R + j;
-      if (j < R && idx < n) {
+      if (j < R && idx < count) {
         const double g_nxt = g_run[j];
         const double bound = 8.0 * (double)(n + 2) * 1.1102230246251565e-16 * fmax(g_nxt, g_cur);
         const double d = g_nxt - g_cur;
@@ -318,42 +309,117 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     if (stops && lane == (int)__builtin_ctzll(stops)) atomicMin(&first_stop, stop);
     if (opens && lane == (int)__builtin_ctzll(opens)) atomicMin(&first_open, open);
     __syncthreads();
-    if (first_open < first_stop) need_exact = true;  // block-uniform
-    else if (tid == 0) m_star = first_stop;
-  }
-  SV_PHASE_MARK(3)
-  if (need_exact) {
-    // ordered sum by one lane: place M-1 of the other buffer becomes E_M.  The padding values
-    // sort last, so running over whole batches of 16 never touches E_1..E_n.
-    __syncthreads();
-    if (tid == 0) {
-      double E = 0.0;
-      for (int j0 = 0; j0 < npad; j0 += 16) {   // batches of loads keep LDS latency off the add chain
-        double v[16];
+    if (first_open < first_stop) {                 // (block-uniform)
+      // ordered sum by one lane: place M-1 of `sums` becomes E_M.  Runs over whole batches of 16: what
+      // follows the values, if anything, is not looked at.
+      if (tid == 0) {
+        double E = 0.0;
+        for (int j0 = 0; j0 < count; j0 += 16) {   // batches of loads keep LDS latency off the add chain
+          double v[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = src[slot(j0 + q)];
+          for (int q = 0; q < 16; ++q) v[q] = sorted[slot(j0 + q)];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) { E += v[q]; v[q] = E; }
+          for (int q = 0; q < 16; ++q) { E += v[q]; v[q] = E; }
 #pragma unroll
-        for (int q = 0; q < 16; ++q) dst[slot(j0 + q)] = v[q];
+          for (int q = 0; q < 16; ++q) sums[slot(j0 + q)] = v[q];
+        }
       }
+      __syncthreads();
+      for (int M = tid; M < count; M += nt) {
+        const double g_cur_x = (M == 0) ? 0.0 : sums[slot(M - 1)] / (double)latency[M];
+        const double g_nxt_x = sums[slot(M)] / (double)latency[M + 1];
+        if (!(g_nxt_x > g_cur_x)) atomicMin(&m_star, M);
+      }
+    } else if (tid == 0) {
+      m_star = first_stop;
     }
     __syncthreads();
-    for (int M = tid; M < n; M += nt) {
-      const double g_cur = (M == 0) ? 0.0 : dst[slot(M - 1)] / (double)latency[M];
-      const double g_nxt = dst[slot(M)] / (double)latency[M + 1];
-      if (!(g_nxt > g_cur)) atomicMin(&m_star, M);
+    return m_star < n;
+  };
+
+  const double* sorted = src;
+  double* spare = dst;
+  if constexpr (KEYS == 1) {
+    sort_small(src, dst, npad);
+    SV_PHASE_MARK(2)
+    find_peak(std::integral_constant<int, 1>(), src, dst, n, 1, lat_own);
+  } else {
+    // The largest values first, as many as one lane each can take: the greedy rule hardly ever reaches past them (a
+    // thousand tokens of one batch).  A histogram over 2048 steps of the value says from which step on there are at most 1024.
+    // (Cycles for 8192 keys: 35000 with the sort of the 1024 largest; all of them by merges: 64800.)
+    bool found = false;
+    double* top = dst;
+    double* tmp = dst + slot(kSelThreads);
+    static_assert(2 * slot(kSelThreads) <= slot(2 * kSelThreads), "both fit the second buffer of 2048 keys or more");
+    static_assert(kSelThreads * sizeof(double) >= kSelSteps * sizeof(int), "the histogram fits the second half");
+    int* hist = reinterpret_cast<int*>(tmp);
+    auto step_of = [](double v) { return min((int)(v * (double)kSelSteps), kSelSteps - 1); };
+    __shared__ int n_top, from_step;
+    for (int j = tid; j < kSelSteps; j += nt) hist[j] = 0;
+    if (tid == 0) { n_top = 0; from_step = kSelSteps; }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KEYS; ++q)
+      if (own[q] >= kSelFloor) atomicAdd(&hist[step_of(own[q])], 1);
+    __syncthreads();
+    {
+      // lane t owns the steps 2047 - 2t and 2046 - 2t
+      const int h0 = hist[kSelSteps - 1 - 2 * tid], h1 = hist[kSelSteps - 2 - 2 * tid];
+      const int incl = wave_scan_i32(h0 + h1);
+      if (lane == kWave - 1) part[wave] = incl;
+      __syncthreads();
+      int before = incl - h0 - h1;
+      for (int w = 0; w < wave; ++w) before += part[w];
+      if (before + h0 <= kSelThreads) atomicMin(&from_step, kSelSteps - 1 - 2 * tid);
+      if (before + h0 + h1 <= kSelThreads) atomicMin(&from_step, kSelSteps - 2 - 2 * tid);
+    }
+    __syncthreads();
+    const int from = from_step;
+    top[slot(tid)] = -1.0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KEYS; ++q) {
+      const bool take = own[q] >= kSelFloor && step_of(own[q]) >= from;
+      const unsigned long long who = __ballot(take);
+      int at = 0;
+      if (lane == 0 && who) at = atomicAdd(&n_top, __popcll(who));
+      at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1ull));
+      if (take) top[slot(at)] = own[q];
+    }
+    __syncthreads();
+    const int count = n_top;
+    if (count > 0) {
+      sort_small(top, tmp, kSelThreads);
+      SV_PHASE_MARK(2)
+      found = find_peak(std::integral_constant<int, 1>(), top, tmp, count, 1, lat_own);
+      sorted = top;
+      spare = src;
+    }
+    if (!found && count < n) {
+      // all of them
+      const int R = npad / nt;                     // keys per lane in the goodput scan
+      float lat_run[KEYS];
+#pragma unroll
+      for (int j = 0; j < KEYS; ++j) {
+        const int idx = tid * R + j;
+        lat_run[j] = (j < R && idx < n) ? latency[idx + 1] : 1.f;
+      }
+      __syncthreads();
+      if (tid == 0) m_star = n;
+      double* all = sort_large(src, dst, n, k, R);
+      spare = all == src ? dst : src;
+      sorted = all;
+      find_peak(std::integral_constant<int, KEYS>(), all, spare, n, R, lat_run);
     }
   }
-  __syncthreads();
   SV_PHASE_MARK(4)
   // The M largest products: all above the M-th value, and of those equal to it as many as are
   // missing, in the order of the keys (sequence, then position; a sequence's products never rise,
   // so what it takes is a prefix).
   const int M = m_star;
   if (tid == 0) *total_M = M;
-  const double last = M > 0 ? src[slot(M - 1)] : 2.0;    // (no product is above 1)
-  int* above = reinterpret_cast<int*>(dst);              // per sequence, B <= n of each
+  const double last = M > 0 ? sorted[slot(M - 1)] : 2.0;    // (no product is above 1)
+  int* above = reinterpret_cast<int*>(spare);              // per sequence, B <= n of each
   int* equal = above + B;
   for (int b = tid; b < 2 * B; b += nt) above[b] = 0;
   if (tid == 0) over = 0;
@@ -442,9 +508,7 @@ static bool allow_select_lds() {
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (dev >= 0 && dev < kMaxDevices && allowed[dev]) return true;
   const int bytes = (int)select_lds_bytes(kSelMax);
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<true, kKeysPerLane>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess ||
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<false, kKeysPerLane>),
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<false, kKeysPerLane>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
     return false;
   if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
@@ -472,6 +536,13 @@ static int select_checked(const float* p_hat, int B, int k, const float* latency
                SV_ERR_ALIGN);
   }
   hipStream_t st = as_stream(stream);
+  if (est && mode == SV_BATCH_GREEDY && B * k > kSelThreads) {
+    // thousands of look-ups take the selection's one workgroup 13 us, a launch of their own 5
+    const int rc = sv_accept_estimate(est->S, est->A, B * k, est->edges_s, est->n_s, est->edges_a, est->n_a, est->table,
+                                      est->p_hat, est->edge_flag, stream);
+    if (rc != SV_OK) return rc;
+    est = nullptr;
+  }
   // one lane per (padded) key up to the workgroup limit
   int threads = 64;
   while (threads < kSelThreads && threads < B * k) threads <<= 1;
@@ -483,8 +554,8 @@ static int select_checked(const float* p_hat, int B, int k, const float* latency
     if (lds > kLdsDefault && !allow_select_lds()) return SV_ERR_LAUNCH;
     TapScope tap(SV_KERNEL_SELECT_LENGTH, st);
     const bool few = npad <= kSelThreads;
-    auto kernel = est ? (few ? select_batch_kernel<true, 1> : select_batch_kernel<true, kKeysPerLane>)
-                      : (few ? select_batch_kernel<false, 1> : select_batch_kernel<false, kKeysPerLane>);
+    auto kernel = est ? select_batch_kernel<true, 1>
+                      : few ? select_batch_kernel<false, 1> : select_batch_kernel<false, kKeysPerLane>;
     hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, st, p_hat, B, k, latency, gamma, t_offsets, total_M, npad,
                        est ? *est : none);
   } else {

@@ -211,6 +211,11 @@ constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0
 constexpr int kDppRor1 = 0x121, kDppRor2 = 0x122, kDppRor4 = 0x124, kDppRor8 = 0x128;    // rows rotated
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_move0(int v) {              // v of the lane that CTRL names, else 0
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+
 // Inclusive prefix sum over the lanes.
 __device__ __forceinline__ double wave_scan_f64(double v) {
   v = dpp_add_f64<kDppShr1, 0xf>(v);
@@ -219,6 +224,15 @@ __device__ __forceinline__ double wave_scan_f64(double v) {
   v = dpp_add_f64<kDppShr8, 0xf>(v);
   v = dpp_add_f64<kDppBcast15, 0xa>(v);
   return dpp_add_f64<kDppBcast31, 0xc>(v);
+}
+
+__device__ __forceinline__ int wave_scan_i32(int v) {
+  v += dpp_move0<kDppShr1, 0xf>(v);
+  v += dpp_move0<kDppShr2, 0xf>(v);
+  v += dpp_move0<kDppShr4, 0xf>(v);
+  v += dpp_move0<kDppShr8, 0xf>(v);
+  v += dpp_move0<kDppBcast15, 0xa>(v);
+  return v + dpp_move0<kDppBcast31, 0xc>(v);
 }
 
 // Rows of 16 lanes: the row's sum in its lane 15, its maximum in all of its lanes.
