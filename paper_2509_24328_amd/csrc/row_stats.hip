@@ -1,7 +1,7 @@
 // sv_row_stats: draft/companion indicators of Speculative Verification
 // (Sec. 4.2 of the SV paper and the appendix definitions of S and A).
 //
-// One workgroup per (sequence, position).  Sweep 1 streams the draft row and
+// A pair is a (sequence, position).  Sweep 1 streams the draft row and
 // the companion row together with 128-bit loads and keeps one online
 // (max, sum-exp) accumulator per row and lane.  S = sum_v min(P_d, P_c) needs
 // both normalisers before the element-wise comparison, so a second sweep over
