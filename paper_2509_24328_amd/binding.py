@@ -145,7 +145,7 @@ def _stream(stream):
         return ctypes.c_void_p(stream.cuda_stream)
     if torch.cuda.is_initialized():
         try:
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
         except AttributeError:
             pass
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
