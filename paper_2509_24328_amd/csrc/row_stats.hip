@@ -120,7 +120,38 @@ struct MinAcc {
     acc_s += s;
     if (WITH_KL) { acc_kl += kl; acc_pa += pa; acc_p += p; }
   }
+
+  // The sums so far are put aside (see OnlineOf::hand_over); ended by one more.
+  float far_s = 0.f, far_kl = 0.f, far_pa = 0.f, far_p = 0.f;
+  __device__ __forceinline__ void hand_over() {
+    far_s += acc_s;
+    acc_s = 0.f;
+    if (WITH_KL) {
+      far_kl += acc_kl; far_pa += acc_pa; far_p += acc_p;
+      acc_kl = acc_pa = acc_p = 0.f;
+    }
+  }
 };
+
+// The online sums of a lane's two rows, put aside from time to time.
+struct FarSums {
+  float s[2] = {0.f, 0.f}, c[2] = {kRefFloor, kRefFloor};
+  __device__ __forceinline__ void take(Online (&on)[2]) {
+    on[0].hand_over(s[0], c[0]);
+    on[1].hand_over(s[1], c[1]);
+  }
+  __device__ __forceinline__ void give_back(Online (&on)[2]) {
+    take(on);
+    on[0].s = s[0];
+    on[1].s = s[1];
+  }
+};
+// A lane's sums of the LDS share, of the register share and of every kRunSteps further vectors of a row are formed apart and
+// then added: a single float32 sum of a long row has hundreds of additions, which on flat rows round the same way.
+// Normaliser of flat rows against 64 bits, largest of 200, so / one sum over 512 lanes / one over 1024: 152064 fp32 3.2e-7,
+// 1.1e-6, 6.0e-7; 262144 bf16 3.0e-7, 9.5e-7, 4.8e-7; 2^20 fp32 4.8e-7, 5.2e-6, 3.6e-6.  (Runs of 8: 3.6e-6 at 2^22 fp32, runs of
+// 16: 1.6e-6.)  Rows of which two pairs fit a compute unit have at most 14 vectors per lane: 2 % of the time there, for nothing.
+constexpr int kRunSteps = 16;
 
 // What a pair's second sweep and its epilogue need, formed once by two lanes of wavefront 0 after the
 // merge and shared through LDS: the natural-log normalisers (NaN: bad row), the L32-consistent log2
@@ -186,10 +217,12 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
 // of 64), wavefronts per SIMD that have to fit.
 struct StashTwo {                                                      // two workgroups per CU
   static constexpr int threads = 512, waves = 4, lds_vecs = 2432;      // 76 KB
+  static constexpr bool long_rows = true;                              // whose sums are put aside from time to time
   template <bool KL> static constexpr int regs() { return KL ? 8 : 10; }
 };
 struct StashThree {                                                    // three per CU
   static constexpr int threads = 512, waves = 6, lds_vecs = 1600;      // 50 KB
+  static constexpr bool long_rows = false;
   template <bool KL> static constexpr int regs() { return KL ? 3 : 4; }
 };
 
@@ -232,7 +265,7 @@ __device__ __forceinline__ void load_to_lds(const u32x4* src, u32x4* lds_wave_ba
 // A wavefront's sums of sweep 2 go to LDS.
 template <bool WITH_KL, int N, int W>
 __device__ __forceinline__ void store_sums(const MinAcc<WITH_KL>& acc, double (&sums)[N][W]) {
-  const float v[4] = {acc.acc_s, acc.acc_kl, acc.acc_pa, acc.acc_p};
+  const float v[4] = {acc.far_s + acc.acc_s, acc.far_kl + acc.acc_kl, acc.far_pa + acc.acc_pa, acc.far_p + acc.acc_p};
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     const double t = wave_sum_f64((double)v[q]);
@@ -297,6 +330,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
   Online& oc = on[1];
   od.init();
   oc.init();
+  FarSums far;
   u32x4 sd[kRegIters], sc[kRegIters];
 #pragma unroll
   for (int j = 0; j < kRegIters; ++j) {                 // all loads in flight before any use
@@ -338,7 +372,8 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
   SV_PHASE_MARK(3)
   {
     int i = lds_end + tid;
-    for (; i + nt < nvec; i += 2 * nt) {
+    for (int s = 0; i + nt < nvec; i += 2 * nt, s += 2) {
+      if (Shape::long_rows && s % kRunSteps == 0) far.take(on);
       const u32x4 d0 = load_vec(pd, i), c0 = load_vec(pc, i), d1 = load_vec(pd, i + nt), c1 = load_vec(pc, i + nt);
       add1(od, d0, Ld, cut_d);
       __builtin_amdgcn_sched_barrier(0);
@@ -354,6 +389,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
       add1(od, d0, Ld, cut_d);
       add1(oc, c0, Lc, cut_c);
     }
+    if (Shape::long_rows) far.give_back(on);
   }
   // the logits of the drafted token, by the two lanes that publish them: their way from memory passes under the
   // merge, where the epilogue would wait for the token and then for the logits
@@ -397,7 +433,8 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
       // walk the re-read region backwards: its end was read last in sweep 1
       const int n_rest = nvec - lds_end;
       int r = tid;
-      for (; r + nt < n_rest; r += 2 * nt) {
+      for (int s = 0; r + nt < n_rest; r += 2 * nt, s += 2) {
+        if (Shape::long_rows && s % kRunSteps == 0) acc.hand_over();
         const int i0 = nvec - 1 - r, i1 = nvec - 1 - (r + nt);
         const u32x4 d0 = load_vec_nt(pd, i0), c0 = load_vec_nt(pc, i0), d1 = load_vec_nt(pd, i1),
                     c1 = load_vec_nt(pc, i1);
@@ -410,6 +447,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_stash_
         const int i0 = nvec - 1 - r;
         acc.template add_vec<DT, WARP>(load_vec(pd, i0), load_vec(pc, i0), cut_d, cut_c);
       }
+      if (Shape::long_rows) acc.hand_over();
     }
     SV_PHASE_MARK(6)
     for (int i = lds_begin + tid; i < lds_end; i += nt)
@@ -440,6 +478,7 @@ struct Loop {
   static constexpr int threads = 512, groups = 256 * PER_CU, waves = 2 * PER_CU, regs = REGS;
   static constexpr int lds_vecs = (PER_CU == 1 ? 9 : 4) * threads;      // 144 KB, 64 KB
   static constexpr int ahead = PER_CU == 1 ? 4 : 2;                     // vector pairs per lane in flight
+  static constexpr bool long_rows = PER_CU == 1;
 };
 
 // A workgroup walks the pairs blockIdx.x, + gridDim.x, ...  A pass is sweep 2 of one pair and, as that
@@ -506,6 +545,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
     Online on[2];
     on[0].init();
     on[1].init();
+    FarSums far;
     MinAcc<WITH_KL> acc;
     if (CUR) {
       // (head and tail of the normalisers: see row_stats_stash_kernel)
@@ -578,7 +618,11 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
         acc.add(zd, zc);
       }
       stream(cd, cc, rest_steps, lds_end, nvec, [&](int s) { return nvec - 1 - (s * nt + tid); }, last_use,
-             [&](int, const u32x4& qd, const u32x4& qc) { add_min(qd, qc); });
+             [&](int s, const u32x4& qd, const u32x4& qc) {
+               add_min(qd, qc);
+               if (Shape::long_rows && s % kRunSteps == kRunSteps - 1) acc.hand_over();
+             });
+      if (Shape::long_rows) acc.hand_over();
     }
     // ---- the LDS share: a lane reads only places that it fills itself, so there is no barrier
     auto parked = [&](int s) { add_min(park[s * nt + tid], park[kLdsVecs + s * nt + tid]); };
@@ -590,10 +634,12 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
                park[s * nt + tid] = qd;
                park[kLdsVecs + s * nt + tid] = qc;
              });
+      if (Shape::long_rows) far.take(on);
     } else {
 #pragma unroll 1
       for (int s = 0; s < lds_steps; ++s) parked(s);
     }
+    if (CUR && Shape::long_rows) acc.hand_over();
     // ---- the register share
 #pragma unroll
     for (int j = 0; j < kRegIters + (NEXT ? kAhead : 0); ++j) {
@@ -619,7 +665,11 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
     float zx = __builtin_nanf("");
     if (NEXT) {
       stream(nd, nc, rest_steps, lds_end, nvec, [&](int s) { return lds_end + s * nt + tid; }, temporal,
-             [&](int, const u32x4& qd, const u32x4& qc) { add(qd, qc); });
+             [&](int s, const u32x4& qd, const u32x4& qc) {
+               if (Shape::long_rows && s % kRunSteps == 0) far.take(on);
+               add(qd, qc);
+             });
+      if (Shape::long_rows) far.give_back(on);
       tok_next = a.x[next];
       if (tok_next >= 0 && tok_next < a.V && (tid == kLaneDraft || tid == kLaneCompanion))
         zx = load_elem<DT>(tid == kLaneDraft ? nd : nc, tok_next);

@@ -179,6 +179,14 @@ struct OnlineOf {
     m = mx;
     c = cn;
   }
+
+  // Hands the sum so far over to `far`, relative to far_c, and starts again: a sum of many terms is then one
+  // of a few sums of some terms each, and its rounding error grows with their numbers, not with the product.
+  __device__ __forceinline__ void hand_over(Sum& far, float& far_c) {
+    far = scaled(far, exp2_fast(far_c - c), s);
+    far_c = c;
+    s = 0;
+  }
 };
 using Online = OnlineOf<float>;
 using OnlineWide = OnlineOf<double>;

@@ -46,3 +46,17 @@ def test_the_sums_of_rows_off_16_bytes_do_not_drift(with_kl):
     # the drift, one rounding of the exponential (1.2e-7) and one of the result
     worst = float(np.abs(got["S"] - 1.0).max())
     assert worst < 4e-7
+
+
+@pytest.mark.parametrize("pairs,V,dtype,bound", [(200, 152064, "f32", 2.8e-7), (300, 152064, "f32", 2.8e-7), (200, 262144, "bf16", 2.4e-7),
+                                                 (24, 1 << 20, "f32", 4.8e-7)])
+def test_the_normalisers_of_flat_rows_do_not_drift(pairs, V, dtype, bound):
+    """A flat row's terms are equal, and their float32 sums drift with the number of additions (one sum per lane and
+    row over 512 lanes: 1.1e-6, 9.5e-7 and 5.2e-6 off here).  `bound` is the largest drift of sums that are put
+    aside every 16 vectors, replayed in float32 for every value the terms can have."""
+    z = torch.linspace(-300, 300, pairs).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    z = z.cuda().view(pairs, 1, 1).expand(pairs, 1, V).contiguous()
+    got = H.gpu_row_stats(z, z, torch.zeros((pairs, 1), dtype=torch.int32, device="cuda"), False)
+    # P_d(x) = 1 / V; beside the drift one rounding of the exponential (1.2e-7) and one of the result (6e-8)
+    worst = float(np.abs(got["pd_x"].astype(np.float64) * V - 1.0).max())
+    assert worst < bound + 1.8e-7, worst
