@@ -349,7 +349,6 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     have_target = target_there;
     lse_t = lse_from_ms(ms_t, a.sc_t);
   }
-  const U4 random = philox4x32_10((uint32_t)i, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
   if (evaluated) {
     lse_d = lse_from_ms(ms_d, a.sc_d);
     if (tok < 0 || tok >= V) {
@@ -362,7 +361,8 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
       rho = exp(lt - ld);                         // -inf - -inf = NaN: rejected
       gap = exp2_fast((float)(ld * kLog2e)) * (1.f - (float)rho);
     }
-    const double u = unit_from_word(random.w[0]);
+    const U4 r = philox4x32_10((uint32_t)i, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi);
+    const double u = unit_from_word(r.w[0]);
     accept = u < rho;                             // false for NaN
     if (!isnan(rho) && fabs(u - fmin(1.0, rho)) < 1e-6) fl |= SV_FLAG_NEAR_TIE;
   }
@@ -385,19 +385,16 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   const float may_be_off = 1e-5f + (float)V * (1.f / 1024.f) * 1.2e-7f;
   double lse_t_n, lse_d_n;
   int have_target_n, maybe_empty = 0;
-  uint32_t random_n;
   if (n < kWave) {
     lse_t_n = lane_f64(lse_t, n);
     lse_d_n = lane_f64(lse_d, n);
     const int both = __builtin_amdgcn_readlane((int)have_target | (gap > may_be_off ? 0 : 2), n);
     have_target_n = both & 1;
     maybe_empty = both >> 1;
-    random_n = (uint32_t)__builtin_amdgcn_readlane((int)random.w[1], n);
   } else {
     lse_t_n = lse_from_ms(target_ms(a, b, n), a.sc_t);
     lse_d_n = __builtin_nan("");
     have_target_n = target_row<DT>(a, b, n) != nullptr;
-    random_n = philox4x32_10((uint32_t)n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi).w[1];
   }
   if (i == 0) {
     uint32_t flags = fl;
@@ -411,7 +408,10 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     if (CHAIN && !chain_ok) flags |= SV_FLAG_NO_CHAIN;
     Plan pl;
     pl.lse_t = lse_t_n; pl.lse_d = resid ? lse_d_n : 0.0; pl.n = n; pl.flags = flags;
-    pl.resid = (int16_t)(resid ? 1 + maybe_empty : 0); pl.target_ok = target_ok ? 1 : 0; pl.random = random_n;
+    pl.resid = (int16_t)(resid ? 1 + maybe_empty : 0); pl.target_ok = target_ok ? 1 : 0; pl.random = 0;
+    // (The pick's word, formed by the workgroup that publishes alone.  Kept from the accept test on for every lane it cost
+    //  the mass pass of large batches 30 spilled scalar registers: 64 x 152064 bf16 17.2 us, 16.35 without.)
+    if (publish) pl.random = philox4x32_10((uint32_t)n, (uint32_t)b, 0u, a.step, a.seed_lo, a.seed_hi).w[1];
     *plan_out = pl;
     if (publish) {
       a.ws.plan[b] = pl;
@@ -504,8 +504,8 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
 // itself, chunk 0 publishes it), then the masses of the two granules of one chunk of the
 // sampling row, two wavefronts per granule (WIDE: the mass of one, eight wavefronts).  Bound by the latency chain partials ->
 // decision -> row -> sum on small batches; on large ones, once the decision (3.4 us) has named them, the
-// row pairs go through at 3 TB/s (64 x 152064 bf16: 16.6 us; 512 x 32000: 23.7), bound by two exponentials and
-// some twenty further operations per entry pair.  Seven wavefronts per SIMD: eight leave 64 registers, of which bf16
+// row pairs go through at 3 TB/s (64 x 152064 bf16: 14.5 to 16.4 us, by what the kernels before it left in the caches; 512 x
+// 32000: 23.8), bound by two exponentials and some twenty further operations per entry pair.  Seven wavefronts per SIMD: eight leave 64 registers, of which bf16
 // spills 8 and, under cutoffs, 20.
 template <int DT, bool CUT, bool CHAIN, bool WIDE>
 __global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7) void verify_mass_kernel(VerifyArgs a) {
