@@ -188,8 +188,7 @@ int sv_select_length(const float* p_hat, int B, int k,
                      sv_stream_t stream);
 
 /*
- * sv_accept_estimate and sv_select_length in one launch (same sources; two
- * launches for more than 1024 positions in batch mode): the
+ * sv_accept_estimate and sv_select_length in one launch (same sources): the
  * estimates of the B*k positions are looked up from (S, A) by the rule of
  * sv_accept_estimate, written to p_hat, and the lengths are selected from them
  * by the rule of sv_select_length.  Results are those of the two calls; the

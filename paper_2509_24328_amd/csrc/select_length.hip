@@ -15,8 +15,8 @@
 // an error bound decides every comparison that is not a near tie, one lane
 // re-sums in order otherwise; goodput and first-peak search in parallel; then a
 // sequence takes the products above the M-th largest value, and those equal to it
-// in the order of the keys.  Latency bound at the paper's batch sizes (8 us at 512
-// keys, 12 us at 1024; of 8192 keys the 1024 largest are sorted, 27 us, all of them 51 us).
+// in the order of the keys.  Latency bound at the paper's batch sizes (7 us at 512
+// keys, 11 us at 1024; of 8192 keys the 1024 largest are sorted, 21 us, or all of them, 43 us).
 #include "sv_bins.hpp"
 #include "sv_device.hpp"
 #include "sv_host.hpp"
@@ -32,14 +32,32 @@ namespace sv {
 constexpr int kSelThreads = 1024;
 constexpr int kSelMax = SV_SELECT_MAX_KEYS;   // power of two
 constexpr int kKeysPerLane = kSelMax / kSelThreads;
-constexpr int kSelSteps = 2048;       // histogram of more than 1024 keys ...
-constexpr double kSelFloor = 1.0 / 64;   // ... from here up: most products of long drafts are all but zero and would queue at one counter
+// Above that many keys the largest are looked at first.  us, peak among the 1024 largest / behind them, and the sort of all
+// values alone: 3072 keys 17.0 / 24.9 and 24.0; 4096 17.7 / 28.2 and 27.6; 8192 in sequences of 8 or 16 21.5 / 43 and 42.5, of 1
+// behind them 64.1 and 62.6.  At 2048 keys the sort of all takes 20, and these would take 17 / 21 to 23.  (Looking without asking
+// first whether the goodput still rises behind them cost 12 us more where it does, and at ties up to 7 in the histogram's counters.)
+constexpr int kSelTopMin = 2048;
+constexpr int kSelSteps = 2048;       // histogram of those ...
+constexpr int kSelFloorStep = kSelSteps / 64;   // ... from here up: most products of long drafts are all but zero and would queue at one counter
+// (Rounding to fp32 keeps the order of values, and equal ones together.)
+__device__ __forceinline__ int value_step(double v) { return min((int)((float)v * (float)kSelSteps), kSelSteps - 1); }
 
 // Place of key i in an LDS buffer: a gap after every eight, so that lanes that own runs of
 // eight, or sequences of eight or sixteen, start on different banks.
 __host__ __device__ __forceinline__ constexpr int slot(int i) { return i + (i >> 3); }
 // Bytes of the two buffers for a power of two of keys.
 constexpr size_t select_lds_bytes(int npad) { return 2 * sizeof(double) * (size_t)slot(npad); }
+
+// Sum of the counts of nw <= 16 wavefronts.
+__device__ __forceinline__ int fold_counts(const int* part, int nw) {
+  const int w = threadIdx.x & 15;
+  int v = w < nw ? part[w] : 0;
+  v += dpp_move0<kDppShr1, 0xf>(v);
+  v += dpp_move0<kDppShr2, 0xf>(v);
+  v += dpp_move0<kDppShr4, 0xf>(v);
+  v += dpp_move0<kDppShr8, 0xf>(v);
+  return __builtin_amdgcn_readlane(v, 15);
+}
 
 __device__ __forceinline__ double clean_p(float p) {
   if (isnan(p)) return 0.0;
@@ -194,7 +212,7 @@ __device__ __forceinline__ double* sort_large(double* src, double* dst, int n, i
 // runs through this code once, so its instructions arrive from L2 as it goes and every line
 // that is not there is time saved: the few-key code is compiled without the other's unrolled runs
 // (512 keys: 28000 cycles in all, 31000 with one code for both), and loops stay rolled.
-template <bool FUSED, int KEYS>
+template <bool FUSED, int KEYS, bool TOP = false>
 __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     const float* p_hat, int B, int k, const float* latency, int32_t* gamma, int32_t* t_offsets,
     int32_t* total_M, int npad, EstimateArgs est) {
@@ -208,9 +226,28 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
   double* dst = buffers + slot(npad);
 
   SV_PHASE_MARK(0)
-  // the latency this lane divides by after the sort: asked for now, so that the
+  // the latencies this lane divides by after the sort: asked for now, so that the
   // memory latency passes behind the sort
-  const float lat_own[1] = {tid < n ? latency[tid + 1] : 1.f};
+  const int R = KEYS == 1 ? 1 : npad / nt;             // keys per lane in the goodput scan
+  float lat_run[KEYS];
+#pragma unroll
+  for (int j = 0; j < KEYS; ++j) {
+    const int idx = tid * R + j;
+    lat_run[j] = (j < R && idx < n) ? latency[idx + 1] : 1.f;
+  }
+  const float lat_top[1] = {TOP ? latency[tid + 1] : 1.f}, lat_behind = TOP && tid == 0 ? latency[kSelThreads + 1] : 1.f;
+  // TOP: where the peak lies among the largest values, as many as one lane each can take, no others are sorted
+  // (the greedy rule reaches past a thousand tokens of one batch only where the estimates are high or the latency is
+  // flat).  In the second half of the second buffer a histogram over 2048 steps of the value, cleared here, and the
+  // latencies behind it.
+  int* hist = reinterpret_cast<int*>(dst + slot(npad) / 2) + 1;       // hist[-1]: more than can be taken
+  float* lat_lds = reinterpret_cast<float*>(hist + kSelSteps);         // of 1, 2, ... tokens
+  static_assert(sizeof(double) * slot(2 * kSelTopMin) / 2 >= 4 * (1 + kSelSteps + kSelThreads + 1) &&
+                slot(2 * kSelTopMin) / 2 >= 2 * slot(kSelThreads), "the halves hold what is put there");
+  if constexpr (TOP) {
+    for (int j = tid; j < kSelSteps; j += nt) hist[j] = 0;
+    if (tid == 0) hist[-1] = n;
+  }
   // estimates into LDS with one round of coalesced loads
   float* p_lds = reinterpret_cast<float*>(dst);
   if (FUSED) {
@@ -221,15 +258,36 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
     auto put = [&](int j, float p) { p_lds[slot(j)] = p; };
     estimate_keys<KEYS>(est, es, ea, n, put);
   } else {
-    for (int j = tid; j < n; j += nt) p_lds[slot(j)] = p_hat[j];
+    constexpr int kLoads = TOP ? KEYS : 1;             // in flight
+    for (int j0 = tid; j0 < n; j0 += kLoads * nt) {
+      float p[kLoads];
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) p[q] = j0 + q * nt < n ? p_hat[j0 + q * nt] : 0.f;
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q)
+        if (j0 + q * nt < n) p_lds[slot(j0 + q * nt)] = p[q];
+    }
+  }
+  if (TOP) {
+    lat_lds[tid] = lat_top[0];
+    if (tid == 0) lat_lds[kSelThreads] = lat_behind;
   }
   if (tid == 0) m_star = n;
   __syncthreads();
   for (int b = tid; b < B; b += nt) {
     double acc = 1.0;
-    for (int j = 0; j < k; ++j) {
-      acc = acc * clean_p(p_lds[slot(b * k + j)]);
-      src[slot(b * k + j)] = acc;
+    constexpr int kAhead = TOP ? 4 : 1;              // reads ahead of the chain of products
+    for (int j0 = 0; j0 < k; j0 += kAhead) {
+      float p[kAhead];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) p[j] = p_lds[slot(b * k + min(j0 + j, k - 1))];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        if (j0 + j < k) {
+          acc = acc * clean_p(p[j]);
+          src[slot(b * k + j0 + j)] = acc;
+        }
+      }
     }
   }
   for (int j = n + tid; j < npad; j += nt) src[slot(j)] = -1.0;
@@ -342,73 +400,81 @@ __global__ __launch_bounds__(kSelThreads) void select_batch_kernel(
   if constexpr (KEYS == 1) {
     sort_small(src, dst, npad);
     SV_PHASE_MARK(2)
-    find_peak(std::integral_constant<int, 1>(), src, dst, n, 1, lat_own);
+    find_peak(std::integral_constant<int, 1>(), src, dst, n, 1, lat_run);
   } else {
-    // The largest values first, as many as one lane each can take: the greedy rule hardly ever reaches past them (a
-    // thousand tokens of one batch).  A histogram over 2048 steps of the value says from which step on there are at most 1024.
-    // (Cycles for 8192 keys: 35000 with the sort of the 1024 largest; all of them by merges: 64800.)
-    bool found = false;
-    double* top = dst;
-    double* tmp = dst + slot(kSelThreads);
-    static_assert(2 * slot(kSelThreads) <= slot(2 * kSelThreads), "both fit the second buffer of 2048 keys or more");
-    static_assert(kSelThreads * sizeof(double) >= kSelSteps * sizeof(int), "the histogram fits the second half");
-    int* hist = reinterpret_cast<int*>(tmp);
-    auto step_of = [](double v) { return min((int)(v * (double)kSelSteps), kSelSteps - 1); };
-    __shared__ int n_top, from_step;
-    for (int j = tid; j < kSelSteps; j += nt) hist[j] = 0;
-    if (tid == 0) { n_top = 0; from_step = kSelSteps; }
-    __syncthreads();
+    bool top_only = false, rises = true;
+    int count = 0;
+    if constexpr (TOP) {
+      // With 1025 values above this the goodput still rises behind the 1024 largest, whatever these sum to: all of them then.
+      const float enough = (float)kSelThreads * 1.001f * (lat_lds[kSelThreads] / lat_lds[kSelThreads - 1] - 1.f);
+      int mine = 0;
 #pragma unroll
-    for (int q = 0; q < KEYS; ++q)
-      if (own[q] >= kSelFloor) atomicAdd(&hist[step_of(own[q])], 1);
-    __syncthreads();
-    {
-      // lane t owns the steps 2047 - 2t and 2046 - 2t
-      const int h0 = hist[kSelSteps - 1 - 2 * tid], h1 = hist[kSelSteps - 2 - 2 * tid];
-      const int incl = wave_scan_i32(h0 + h1);
-      if (lane == kWave - 1) part[wave] = incl;
+      for (int q = 0; q < KEYS; ++q) mine += __popcll(__ballot((float)own[q] > enough));
+      if (lane == 0) part[wave] = mine;
       __syncthreads();
-      int before = incl - h0 - h1;
-      for (int w = 0; w < wave; ++w) before += part[w];
-      if (before + h0 <= kSelThreads) atomicMin(&from_step, kSelSteps - 1 - 2 * tid);
-      if (before + h0 + h1 <= kSelThreads) atomicMin(&from_step, kSelSteps - 2 - 2 * tid);
+      rises = fold_counts(part, kSelThreads / kWave) > kSelThreads;
     }
-    __syncthreads();
-    const int from = from_step;
-    top[slot(tid)] = -1.0;
-    __syncthreads();
+    if (TOP && !rises) {
+      // From which step on there are at most 1024 values, and whether the goodput is certain to fall behind them:
+      // none of the others reaches that step, and the values above it sum to no less than their steps do.
 #pragma unroll
-    for (int q = 0; q < KEYS; ++q) {
-      const bool take = own[q] >= kSelFloor && step_of(own[q]) >= from;
-      const unsigned long long who = __ballot(take);
-      int at = 0;
-      if (lane == 0 && who) at = atomicAdd(&n_top, __popcll(who));
-      at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1ull));
-      if (take) top[slot(at)] = own[q];
-    }
-    __syncthreads();
-    const int count = n_top;
-    if (count > 0) {
-      sort_small(top, tmp, kSelThreads);
-      SV_PHASE_MARK(2)
-      found = find_peak(std::integral_constant<int, 1>(), top, tmp, count, 1, lat_own);
-      sorted = top;
-      spare = src;
-    }
-    if (!found && count < n) {
-      // all of them
-      const int R = npad / nt;                     // keys per lane in the goodput scan
-      float lat_run[KEYS];
-#pragma unroll
-      for (int j = 0; j < KEYS; ++j) {
-        const int idx = tid * R + j;
-        lat_run[j] = (j < R && idx < n) ? latency[idx + 1] : 1.f;
+      for (int q = 0; q < KEYS; ++q) {
+        const int step = value_step(own[q]);
+        if (step >= kSelFloorStep) atomicAdd(&hist[step], 1);
       }
       __syncthreads();
-      if (tid == 0) m_star = n;
+      // lane t owns the steps 2047 - 2t and 2046 - 2t
+      __shared__ int weights[kSelThreads / kWave], first_step, n_first, falls;
+      const int s0 = kSelSteps - 1 - 2 * tid, h0 = hist[s0], h1 = hist[s0 - 1], h2 = hist[s0 - 2];
+      int upto = wave_scan_i32(h0 + h1), weight = wave_scan_i32(h0 * s0 + h1 * (s0 - 1));
+      if (lane == kWave - 1) { part[wave] = upto; weights[wave] = weight; }
+      if (tid == 0) falls = 0;
+      __syncthreads();
+      for (int w = 0; w < wave; ++w) { upto += part[w]; weight += weights[w]; }
+      auto end_at = [&](int step, int taken, int sum) {
+        first_step = step;
+        n_first = taken;
+        if (taken > 0) {
+          const float l0 = lat_lds[taken - 1], l1 = lat_lds[taken], next = (float)max(step, kSelFloorStep);
+          falls = l0 > 0.f && next * l0 * 1.001f < (float)sum * (l1 - l0);
+        }
+      };
+      if (upto <= kSelThreads && upto + h2 > kSelThreads) end_at(s0 - 1, upto, weight);
+      else if (upto > kSelThreads && upto - h1 <= kSelThreads) end_at(s0, upto - h1, weight - h1 * (s0 - 1));
+      __syncthreads();
+      top_only = falls;
+      if (top_only) {
+        count = n_first;
+        double* top = dst;
+        double* tmp = dst + slot(kSelThreads);
+        __shared__ int n_top;
+        top[slot(tid)] = -1.0;
+        if (tid == 0) n_top = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < KEYS; ++q) {
+          const bool take = value_step(own[q]) >= max(first_step, kSelFloorStep);
+          const unsigned long long who = __ballot(take);
+          int at = 0;
+          if (lane == 0 && who) at = atomicAdd(&n_top, __popcll(who));
+          at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1ull));
+          if (take) top[slot(at)] = own[q];
+        }
+        __syncthreads();
+        sort_small(top, tmp, kSelThreads);
+        SV_PHASE_MARK(2)
+        const bool stops = find_peak(std::integral_constant<int, 1>(), top, tmp, count, 1, lat_top);
+        if (tid == 0 && !stops) m_star = count;
+        __syncthreads();
+        sorted = top;
+        spare = src;
+      }
+    }
+    if (!top_only) {
       double* all = sort_large(src, dst, n, k, R);
       spare = all == src ? dst : src;
       sorted = all;
+      SV_PHASE_MARK(2)
       find_peak(std::integral_constant<int, KEYS>(), all, spare, n, R, lat_run);
     }
   }
@@ -508,8 +574,12 @@ static bool allow_select_lds() {
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (dev >= 0 && dev < kMaxDevices && allowed[dev]) return true;
   const int bytes = (int)select_lds_bytes(kSelMax);
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_batch_kernel<false, kKeysPerLane>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
+  auto allow = [&](auto* kernel) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) ==
+           hipSuccess;
+  };
+  if (!allow(&select_batch_kernel<true, kKeysPerLane>) || !allow(&select_batch_kernel<false, kKeysPerLane>) ||
+      !allow(&select_batch_kernel<true, kKeysPerLane, true>) || !allow(&select_batch_kernel<false, kKeysPerLane, true>))
     return false;
   if (dev >= 0 && dev < kMaxDevices) allowed[dev] = true;
   return true;
@@ -536,13 +606,6 @@ static int select_checked(const float* p_hat, int B, int k, const float* latency
                SV_ERR_ALIGN);
   }
   hipStream_t st = as_stream(stream);
-  if (est && mode == SV_BATCH_GREEDY && B * k > kSelThreads) {
-    // thousands of look-ups take the selection's one workgroup 13 us, a launch of their own 5
-    const int rc = sv_accept_estimate(est->S, est->A, B * k, est->edges_s, est->n_s, est->edges_a, est->n_a, est->table,
-                                      est->p_hat, est->edge_flag, stream);
-    if (rc != SV_OK) return rc;
-    est = nullptr;
-  }
   // one lane per (padded) key up to the workgroup limit
   int threads = 64;
   while (threads < kSelThreads && threads < B * k) threads <<= 1;
@@ -554,8 +617,11 @@ static int select_checked(const float* p_hat, int B, int k, const float* latency
     if (lds > kLdsDefault && !allow_select_lds()) return SV_ERR_LAUNCH;
     TapScope tap(SV_KERNEL_SELECT_LENGTH, st);
     const bool few = npad <= kSelThreads;
-    auto kernel = est ? select_batch_kernel<true, 1>
-                      : few ? select_batch_kernel<false, 1> : select_batch_kernel<false, kKeysPerLane>;
+    const bool top = B * k > kSelTopMin;                // (npad is at least 4096 then)
+    auto kernel = est ? (few ? select_batch_kernel<true, 1>
+                             : top ? select_batch_kernel<true, kKeysPerLane, true> : select_batch_kernel<true, kKeysPerLane>)
+                      : (few ? select_batch_kernel<false, 1>
+                             : top ? select_batch_kernel<false, kKeysPerLane, true> : select_batch_kernel<false, kKeysPerLane>);
     hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, st, p_hat, B, k, latency, gamma, t_offsets, total_M, npad,
                        est ? *est : none);
   } else {
