@@ -729,10 +729,12 @@ static int rows_split(int rows, int V) {
 }
 
 // Up to this many (sequence, granule) pairs the mass pass takes a workgroup of 512 lanes for each: a granule is then one vector
-// per lane.  Above, where the chip is full anyway, a workgroup of 256 lanes takes two granules and decides once for both.
-// us, two granules / one: 8 x 32000 bf16 7.2 / 5.7, 24 x 32001 8.0 / 6.2, 1 x 32000 fp32 6.4 / 5.9, under cutoffs 8 x 32000 8.8 / 7.2;
-// 32 x 128256 (1024 granules) 8.3 / 10.5, 64 x 152064 (2432) 16.6 / 25.6.
-constexpr int kWideGroups = 512;
+// (bf16) or two (fp32) per lane.  Above, where the chip is full anyway, a workgroup of 256 lanes takes two granules and decides
+// once for both.  us of the chained call, two granules / one, at V = 4096 to 524288: bf16 up to 256 pairs 0.8 in the
+// mean for one granule and never more than 0.1 for two; 320 to 512 pairs from 0.45 for two (256 x 8192: 18.1 / 18.5) to 0.4 for
+// one, but rows of a single granule, which leave half of the 256 lanes without work, 0.4 to 1.9 for one; fp32 1.5 for
+// one up to 256 pairs, 0.9 in the mean (from 0.25 for two) up to 512.
+static int wide_groups(int dtype, int granules) { return dtype == DT_F32 || granules == 1 ? 512 : 256; }
 
 template <int DT, bool CUT>
 static int launch_verify(const VerifyArgs& a, hipStream_t st) {
@@ -749,7 +751,7 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
       hipLaunchKernelGGL(kernel, dim3(groups, a.B), dim3(threads), 0, st, a);
     };
     const int G = n_granules(a.V);
-    if ((long)G * a.B <= kWideGroups) {
+    if ((long)G * a.B <= wide_groups(DT, G)) {
       if (a.chained) launch(&verify_mass_kernel<DT, CUT, true, true>, G, kWideThreads);
       else launch(&verify_mass_kernel<DT, CUT, false, true>, G, kWideThreads);
     } else {
