@@ -60,6 +60,34 @@ def test_residual_without_mass(V, dtype):
     assert V < 9000 or len(seen) > 1
 
 
+@pytest.mark.parametrize("chained", [False, True])
+@pytest.mark.parametrize("V,dtype,B", [(4097, "f32", 260), (8193, "bf16", 130), (12305, "bf16", 90), (9001, "f32", 180)])
+def test_residual_without_mass_in_large_batches(V, dtype, B, chained):
+    """More than 512 (bfloat16: 256) pairs of a sequence and a granule: a workgroup of the mass pass takes two granules.
+    Every third sequence has a residual, in one granule only."""
+    n = 6                                                # a few different sequences, in turn
+    cfg = svgen.make_config(1, seed=V + 3, B=n, k=1, V=V, dtype=dtype)
+    z_t, x = cfg["z_t"], cfg["x"]
+    for b in range(n):
+        z_t[b, 0, int(x[b, 0])] = -np.inf
+    z_d = z_t[:, :1].clone()
+    for b in range(0, n, 3):
+        v = (V - 1, V // 2)[b // 3]
+        z_t[b, 0, v] = z_t[b, 0].max()                   # the target's mass there is the residual
+        z_d[b, 0, v] = -np.inf
+    at = torch.arange(B) % n
+    z_t, z_d, x = z_t[at], z_d[at], x[at]
+    ref = H.oracle_verify(svgen.to_numpy_bits(z_t), svgen.to_numpy_bits(z_d), x.numpy(), seed=1, step=3)
+    args = [t.contiguous().cuda() for t in ((z_t, z_d, z_d, x) if chained else (z_t, z_d, x))]
+    got = (H.gpu_verify_chained if chained else H.gpu_verify)(*args, seed=1, step=3)
+    H.assert_verify(got, ref, 1)
+    empty, fell_back = (np.arange(B) % 3) != 0, (got["flags"] & O.FLAG_RESIDUAL_FALLBACK) != 0
+    # (chained, the two normalisers are sums in different orders: a residual of rounding noise may be found)
+    assert fell_back[empty].any() if chained else fell_back[empty].all()
+    assert not fell_back[~empty].any()
+    assert len({int(t) // 4096 for t in got["tokens"][fell_back, 0]}) > 1
+
+
 @pytest.mark.parametrize("offset", [0.0, 600.0, -700.0, 708.0, 712.0, -712.0, 5000.0, 1e6])
 def test_probabilities_on_either_side_of_the_short_form(offset):
     """The short form of the probabilities holds while |log2 of the normaliser| < 1024 (logits near 710);
@@ -97,14 +125,25 @@ def test_residual_without_mass_under_cutoffs(V, dtype, chained):
     """Equal nuclei of one token and of several, in one granule and in different ones, the drafted token outside
     both: no residual, the target distribution instead.  Then a draft nucleus that lacks one of the target's
     tokens, or has another one's place: a residual in one granule, none in the others."""
+    _check_nuclei(V, dtype, 6, chained, range(3))
+
+
+@pytest.mark.parametrize("chained", [False, True])
+@pytest.mark.parametrize("V,dtype,B", [(4097, torch.float32, 260), (8193, torch.bfloat16, 130), (12290, torch.bfloat16, 90),
+                                       (9001, torch.float32, 180)])
+def test_residual_without_mass_under_cutoffs_in_large_batches(V, dtype, B, chained):
+    """The same where a workgroup takes two granules, the last of them alone in its chunk or with a partner."""
+    _check_nuclei(V, dtype, B, chained, range(1))
+
+
+def _check_nuclei(V, dtype, B, chained, seeds):
     P = H.sv()
-    B = 6
     far = [V - 1, 2, V // 2, V // 3]
     for peaks_t, peaks_d, empty in (([V // 2], [V // 2], True), ([7, 9, 30], [7, 9, 30], True), (far, far, True),
                                     (far, far[:3], False), ([V - 1], [2], False)):
         z_t, z_d, x, y_t, y_d, cut_t, cut_d = _nuclei(V, dtype, B, peaks_t, peaks_d, V)
         z_t, z_d = z_t.cuda(), z_d.cuda()
-        for seed in range(3):
+        for seed in seeds:
             ref = H.oracle_verify(y_t, y_d, x.numpy(), seed=seed, step=4)
             if chained:
                 f32 = lambda: torch.empty((B, 1), dtype=torch.float32, device="cuda")
@@ -123,7 +162,7 @@ def test_residual_without_mass_under_cutoffs(V, dtype, chained):
             assert (((got["flags"] & O.FLAG_RESIDUAL_FALLBACK) != 0) == empty).all()
             assert np.isin(got["tokens"][:, 0], peaks_t).all()
             clear = ((got["flags"] | ref["flags"]) & O.FLAG_NEAR_CDF_EDGE) == 0
-            assert clear.sum() >= B - 1 and np.array_equal(got["tokens"][clear], ref["tokens"][clear])
+            assert clear.sum() >= B - max(1, B // 50) and np.array_equal(got["tokens"][clear], ref["tokens"][clear])
 
 
 @pytest.mark.parametrize("warped", [False, True])
