@@ -220,6 +220,11 @@ struct StashTwo {                                                      // two wo
   static constexpr bool long_rows = true;                              // whose sums are put aside from time to time
   template <bool KL> static constexpr int regs() { return KL ? 8 : 10; }
 };
+struct StashWide {                                                     // a pair per CU, twice the lanes for it
+  static constexpr int threads = 1024, waves = 4, lds_vecs = 2432;
+  static constexpr bool long_rows = true;
+  template <bool KL> static constexpr int regs() { return 2; }
+};
 struct StashThree {                                                    // three per CU
   static constexpr int threads = 512, waves = 6, lds_vecs = 1600;      // 50 KB
   static constexpr bool long_rows = false;
@@ -732,29 +737,40 @@ static int launch_loop(const StatsArgs& a, hipStream_t st) {
                        Shape::threads, 2 * (size_t)Shape::lds_vecs * 16, a, st);
 }
 
-// Which kernel and shape (pairs x entries, bf16 unless said otherwise; us between events around the call, two sets of
-// rows in turn; the former kernel, one pair per workgroup with all loads ahead of all arithmetic / as it is now).
-//  * The loop kernel nearly everywhere, with a register share about as long as the row.  64 x 8192: 9.0 / 8.1; 64 x 32000:
-//    13.8 / 11.7; 256 x 32000: 16.6 / 13.7; 1024 x 32000: 38.0 / 33.4; 4096 x 32000: 108 / 104; 256 x 128256: 38.8 / 34.0; 512 x
-//    152064: 79.2 / 71.5; 1024 x 152064: 151 / 127; rows off 16 bytes, 512 x 128257: 86.3 / 72.3; fp32, 256 x 128256: 74.5 / 61.4;
-//    with KL, 512 x 152064: 101 / 88, 256 x 32000: 20.8 / 16.7.
+// Which kernel and shape (pairs x entries, bf16 unless said otherwise; us per call in a graph of calls, up to three sets of rows
+// in turn).
+//  * The loop kernel nearly everywhere, with a register share about as long as the row (a workgroup per pair, the better one of
+//    two and three to a CU / loop): 64 x 32000: 11.6 / 9.4; 256 x 32000: 14.2 / 11.1; 1024 x 32000: 34.7 / 30.6; 256 x 152064: 43.7 /
+//    39; 512 x 152064: 77.3 / 68.6; 1024 x 152064: 149 / 127; fp32, 256 x 128256: 74.2 / 59.3; with KL, 512 x 152064: 98 / 85.
 //  * One workgroup per CU from 5632 vectors on if there are no more pairs than CUs, else from 7168 on; below, two, which
 //    cover each other's merges.  256 x 50304: one 18.3, two 19.0; 1024 x 50304: 51.6 and 49.4.
-//  * Many pairs of short rows have enough to overlap as they are, three to a CU, and the hardware to balance them: 4096 x
-//    25000: loop 98.8, three 85.7; 2048 x 17000: 42.7 and 39.4; fp32 4096 x 6000: 50.5 and 49.2.  (1024 x 25000: 30.5 and 32.0.)
-//  * A few pairs more than CUs, of rows that do not stay on chip: a CU that has two takes longer one after the other than
-//    side by side.  300 x 262144: loop 115, two 110; fp32 300 x 65536: 45.4 and 41.8; 341 x 65536: 47.4 and 45.4.
+//  * few: at most half as many pairs as CUs, of rows that do not stay on chip, wait for memory with 512 lanes to a pair; 1024 ask
+//    for twice as much at a time.  Loop / 1024 lanes: 64 x 524288 105 / 94; fp32, 16 x 128256 31.8 / 27.4, 64 x 152064 42.9 / 37.4, 64 x
+//    262144 77 / 67; under cutoffs fp32 128 x 152064 52.7 / 48.2.  (Plain fp32 rows are level at 128 pairs, from 3 % slower to 2 %
+//    faster, and lose 2 to 5 % at 160; the other forms still gain up to 6 % there.)
+//  * many: pairs of short rows have enough to overlap as they are, three to a CU, and the hardware to balance them; the more so
+//    the more arithmetic there is to a byte.  Loop / three: 4096 x 23200 80.7 / 77.1; 8192 x 32800 218 / 197, but 1537 x 32000, which
+//    ends in a nearly empty round, 44.6 / 47.7; under cutoffs 4096 x 48000 187 / 178; fp32, 4096 x 9200 61.0 / 56.0, under cutoffs
+//    69.7 / 58.2, 8192 x 14000 154 / 145, 4096 x 20000 102 / 112.
+//  * few_more: a few pairs more than CUs, of rows that do not stay on chip: a CU that has two takes longer one after the other than
+//    side by side.  Loop / three / two: 300 x 256512 111 / 105 / 104; under cutoffs 257 x 140000 69.2 / 66.3 / 69.5; fp32, 300 x 30000
+//    22.3 / 19.8 / 22.9, 300 x 50400 32.5 / 32.9 / 29.7, 341 x 58000 38.1 / 41.5 / 36.7.
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr bool kBf16 = DT == DT_BF16;
   constexpr int kCUs = 256, nt = 512;
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
   const bool one = nvec > (pairs <= kCUs ? 11 * nt : 14 * nt);
-  const bool many = (kBf16 && nvec <= 7 * nt && pairs > 6 * kCUs) || (nvec <= 3 * nt && pairs > 12 * kCUs);
-  const bool few_more = pairs > kCUs && (kBf16 ? nvec > 20000 && pairs <= 400
-                                               : nvec > 12800 && pairs <= (nvec > 24000 ? 340 : 390));
-  if (nvec <= nt || many) return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
+  const auto from = [&](int per_cu, int steps) { return pairs >= per_cu * kCUs && nvec <= steps * nt; };
+  const bool few = pairs <= kCUs / 2 && nvec > 33 * nt;
+  const bool many = kBf16 ? from(6, 7) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
+                          : from(6, WITH_KL || WARP ? 5 : 3) || (WARP ? from(8, 7) || from(12, 9) : !WITH_KL && from(16, 9));
+  const int off_chip = kBf16 ? (WARP ? 16000 : 20000) : (WITH_KL || WARP ? 11 * nt : 14 * nt);
+  const bool few_more = pairs > kCUs && pairs <= (kBf16 ? 400 : nvec > 24000 ? 340 : 390) && nvec > off_chip;
+  if (nvec <= nt || many || (few_more && (nvec <= 20 * nt || (kBf16 && WARP))))
+    return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);
   if (few_more) return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
+  if (few) return launch_shape<DT, WITH_KL, WARP, StashWide>(a, st);
   if (nvec > 23 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 18 : WARP ? 22 : 24, 1>>(a, st);
   constexpr bool kPlain = !WITH_KL && !WARP;              // (a kernel less for every form where the neighbour will do)
   if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 16 : 12, 1>>(a, st);
