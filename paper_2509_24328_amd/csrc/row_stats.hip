@@ -746,8 +746,8 @@ static int launch_loop(const StatsArgs& a, hipStream_t st) {
 //    cover each other's merges.  256 x 50304: one 18.3, two 19.0; 1024 x 50304: 51.6 and 49.4.
 //  * few: at most half as many pairs as CUs, of rows that do not stay on chip, wait for memory with 512 lanes to a pair; 1024 ask
 //    for twice as much at a time.  Loop / 1024 lanes: 64 x 524288 105 / 94; fp32, 16 x 128256 31.8 / 27.4, 64 x 152064 42.9 / 37.4, 64 x
-//    262144 77 / 67; under cutoffs fp32 128 x 152064 52.7 / 48.2.  (Plain fp32 rows are level at 128 pairs, from 3 % slower to 2 %
-//    faster, and lose 2 to 5 % at 160; the other forms still gain up to 6 % there.)
+//    262144 77 / 67; under cutoffs fp32 128 x 152064 52.7 / 48.2.  (Plain fp32 rows gain 5 to 12 % at 96 pairs; at 128 they are
+//    level in turn with themselves and 1.6 us slower in a step, 75.9 / 77.5 with 128 x 128256.)
 //  * many: pairs of short rows have enough to overlap as they are, three to a CU, and the hardware to balance them; the more so
 //    the more arithmetic there is to a byte.  Loop / three: 4096 x 23200 80.7 / 77.1; 8192 x 32800 218 / 197, but 1537 x 32000, which
 //    ends in a nearly empty round, 44.6 / 47.7; under cutoffs 4096 x 48000 187 / 178; fp32, 4096 x 9200 61.0 / 56.0, under cutoffs
@@ -762,7 +762,7 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
   const bool one = nvec > (pairs <= kCUs ? 11 * nt : 14 * nt);
   const auto from = [&](int per_cu, int steps) { return pairs >= per_cu * kCUs && nvec <= steps * nt; };
-  const bool few = pairs <= kCUs / 2 && nvec > 33 * nt;
+  const bool few = pairs <= (kBf16 || WITH_KL || WARP ? kCUs / 2 : kCUs * 3 / 8) && nvec > 33 * nt;
   const bool many = kBf16 ? from(6, 7) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
                           : from(6, WITH_KL || WARP ? 5 : 3) || (WARP ? from(8, 7) || from(12, 9) : !WITH_KL && from(16, 9));
   const int off_chip = kBf16 ? (WARP ? 16000 : 20000) : (WITH_KL || WARP ? 11 * nt : 14 * nt);

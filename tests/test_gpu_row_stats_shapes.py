@@ -33,8 +33,8 @@ pytestmark = pytest.mark.gpu
     (300, 10241 * 4, "f32"), (390, 10241 * 4 + 3, "f32"), (391, 10241 * 4, "f32"), (300, 24001 * 4, "f32"), (341, 24001 * 4, "f32"),
     (257, 20000 * 8, "bf16"), (257, 20001 * 8, "bf16"), (400, 20001 * 8 + 5, "bf16"), (401, 20001 * 8, "bf16"),
     # a pair per compute unit with 1024 lanes: its shortest rows, off 16 bytes, one pair more than it takes
-    (128, 16896 * 8, "bf16"), (128, 16897 * 8, "bf16"), (3, 16897 * 8 + 1, "bf16"), (129, 16897 * 8, "bf16"), (128, 16896 * 4, "f32"),
-    (128, 16897 * 4 + 1, "f32"), (2, 70001 * 4, "f32")])
+    (128, 16896 * 8, "bf16"), (128, 16897 * 8, "bf16"), (3, 16897 * 8 + 1, "bf16"), (129, 16897 * 8, "bf16"), (96, 16896 * 4, "f32"),
+    (96, 16897 * 4 + 1, "f32"), (97, 16897 * 4 + 1, "f32"), (128, 16897 * 4 + 1, "f32"), (2, 70001 * 4, "f32")])
 @pytest.mark.parametrize("with_kl", [True, False])
 def test_row_stats_at_the_edges_of_the_shapes(pairs, V, dtype, with_kl):
     # a few sequences' rows, repeated over the pairs: every workgroup of a launch has its turn
