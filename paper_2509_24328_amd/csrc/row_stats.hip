@@ -19,7 +19,8 @@
 // bytes first so that they are still in L2.
 //   row_stats_loop_kernel    workgroups that fill the chip once and walk through the pairs: the places that
 //                            sweep 2 of a pair leaves take the next pair's loads
-//   row_stats_stash_kernel   a workgroup per pair: very short rows, and very many pairs of short ones
+//   row_stats_stash_kernel   a workgroup per pair: very short rows, very many pairs of short ones, and few pairs, or a few
+//                            more than compute units, of rows that do not stay on chip
 // Algorithmic HBM traffic: 2 * V * elem_size bytes per pair.
 #include <algorithm>
 #include <type_traits>
@@ -62,7 +63,8 @@ struct StatsArgs {
   bool aligned;           // rows start on 16 bytes
 };
 
-// v_mul_legacy_f32: a product that is 0 where either factor is, whatever the other.
+// v_mul_legacy_f32: a product that is 0 where either factor is, whatever the other.  (By the intrinsic's name, which
+// has no builtin; an asm statement would hide from the compiler that v_exp_f32 has just written a factor.)
 extern "C" __device__ float mul_zero_wins(float, float) __asm("llvm.amdgcn.fmul.legacy");
 
 // Sweep-2 arithmetic for one vocabulary entry (head/tail split of the
@@ -493,7 +495,7 @@ struct Loop {
 // Bound, on long rows, by one read of the pair (51 thousand cycles at the share of a compute unit of 6.4 TB/s, 608 KB
 // of 152064 bf16 entries) and by the arithmetic (48 thousand), which overlap but for the first pair's loads and the last
 // pair's sweep 2: 71 us for 512 such pairs, 30 us for every 256 more.  89 % of a pair stays on chip: two wavefronts
-// per SIMD have 512 registers between them for the rows (four have 320: 76 us).  On short rows: launch, the
+// per SIMD hold the rows in 384 of their 512 registers (four in 320 of theirs: 76 us).  On short rows: launch, the
 // first loads' latency, a merge (two fp64 logarithms) and the arithmetic of a pair on one compute unit.
 // What it rests on: a wavefront issues in order, and with all loads of a share ahead of all arithmetic it stands in
 // the memory queue (30 thousand cycles for 480 KB) with data to sum at hand.  The waits must tell the loads

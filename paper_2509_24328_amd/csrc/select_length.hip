@@ -34,8 +34,8 @@ constexpr int kSelMax = SV_SELECT_MAX_KEYS;   // power of two
 constexpr int kKeysPerLane = kSelMax / kSelThreads;
 // Above that many keys the largest are looked at first.  us, peak among the 1024 largest / behind them, and the sort of all
 // values alone: 3072 keys 17.0 / 24.9 and 24.0; 4096 17.7 / 28.2 and 27.6; 8192 in sequences of 8 or 16 21.5 / 43 and 42.5, of 1
-// behind them 64.1 and 62.6.  At 2048 keys the sort of all takes 20, and these would take 17 / 21 to 23.  (Looking without asking
-// first whether the goodput still rises behind them cost 12 us more where it does, and at ties up to 7 in the histogram's counters.)
+// behind them 64.1 and 62.6; up to 2048 keys the sort of all takes 20 or less.  (Without asking first whether the goodput still
+// rises behind them, that case took 3 us longer, and up to 7 where ties queue at the histogram's counters.)
 constexpr int kSelTopMin = 2048;
 constexpr int kSelSteps = 2048;       // histogram of those ...
 constexpr int kSelFloorStep = kSelSteps / 64;   // ... from here up: most products of long drafts are all but zero and would queue at one counter
