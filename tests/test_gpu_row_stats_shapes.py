@@ -65,10 +65,11 @@ def test_the_sums_of_rows_off_16_bytes_do_not_drift(with_kl):
 
 @pytest.mark.parametrize("V,dtype", [(1500 * 8, "bf16"), (3000 * 8, "bf16"), (3000 * 4 + 1, "f32"), (6001 * 4, "f32"), (9216 * 8, "bf16"), (16001 * 8, "bf16"),
                                      (9000 * 4, "f32"), (16897 * 8, "bf16"), (16897 * 4 + 1, "f32")])
-@pytest.mark.parametrize("pairs", [100, 300, 3072])
+@pytest.mark.parametrize("pairs", [100, 300, 770, 3072])
 @pytest.mark.parametrize("with_kl", [True, False])
 def test_warped_rows_in_every_shape(pairs, V, dtype, with_kl):
-    """Neighbouring pairs have different cutoffs, the two rows different temperatures."""
+    """Neighbouring pairs have different cutoffs, the two rows different temperatures; 300 and 770 pairs are more than
+    one for every workgroup that walks, one and two to a compute unit."""
     if pairs * V > 200_000_000:
         pairs = 512
     n = 5
