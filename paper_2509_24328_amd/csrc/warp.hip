@@ -17,8 +17,9 @@
 // The list is exact whenever it holds at least K entries and (top-p alone) at
 // least P of the row's mass; a list that does not settle a row is rebuilt
 // once with a lower tau (top-p alone: the 384-th lane maximum, if a support is to be
-// written).  A nucleus that is too deep for a list (top-p alone) is cut where a running
-// mass over fine steps of the exponent passes P (list_nucleus_step).  Otherwise - huge K,
+// written).  Otherwise the entries of a bfloat16 row are counted value by value (ValueBins); a
+// nucleus of an fp32 row (top-p alone) is cut where a running mass over fine steps of the
+// exponent passes P (list_nucleus_step).  Where neither tells - huge K of fp32 rows,
 // massive ties - the general path takes over: radix selection on an
 // order-preserving 32-bit key of the logit (11 + 11 + 10 bits; bfloat16 rows are
 // resolved after two levels), one histogram sweep of counts and masses per level.
@@ -27,6 +28,9 @@
 // general path accumulated per bin with LDS fp64 atomics, i.e. in an order that can change from
 // run to run in the last bits; a top-p decision within 3e-6 of P is flagged SV_FLAG_NEAR_TIE, which
 // covers that, and the 1e-7 or so of the exponentials themselves.
+//
+// Few bfloat16 rows whose cutoffs alone are wanted are held in registers and counted at once
+// (warp_cutoffs_resident_kernel).
 //
 // sv_warp_compact is the same kernel with one more step: the kept entries of a
 // settled list are the whole support of the warped distribution, so their token
@@ -48,6 +52,7 @@ constexpr int kBins = 2048;
 constexpr int kCand = 2048;          // capacity of the candidate list
 constexpr int kSteps = 8192;         // counters of list_nucleus_step
 constexpr int kGuessRank = 384;      // top-p alone: tau = this rank among the lane maxima
+constexpr int kResidentMax = 16 * kWarpThreads * Elem<DT_BF16>::per_vec;   // entries of a row that a workgroup holds
 constexpr double kNearTie = 3e-6;    // flagged band of a top-p decision
 
 __device__ __forceinline__ uint32_t okey(float f) {            // ascending order-preserving key
@@ -87,6 +92,7 @@ struct alignas(16) WarpShared {
   };
   uint32_t tau_key;
   float theta;
+  int counted;                 // the counts of a row's values have not told its cutoff
   int n_cand, settled, n_keep, out_done, first_reach, last_reach, near_any;
   double z_keep;               // mass of the kept entries
   int sel_digit;
@@ -469,6 +475,156 @@ __device__ __forceinline__ bool list_nucleus_step(const void* row, int V, float 
   return sh.n_cand <= kCand;
 }
 
+// bfloat16 rows: the entries counted by value.  A row's values from m down to the lowest that can matter (under
+// m - T ln(V / (1 - P)) for top-p, or 2^-32 of the top entry's mass where a K has to be found) lie within 32 octaves of
+// either sign, 128 values each, so 8192 counters hold one value each - but for those under 2^-31 of the largest magnitude,
+// which share a counter with zero; a cutoff there, or below the lowest counter, is left to the other ways.  The counts in
+// descending order of the value, times one exponential per counter, are all that top-k and top-p ask about: no further
+// sweep, list or sort, and no order that sums depend on.
+// Cutoffs of 200 rows at P = 0.9, us, lists and steps of the exponent / counts from cache / counts of rows in registers:
+// 32000 entries, 2500 tokens kept 48.9 / 23.0 / 13.9, 40 kept 21.4 / 15.6 / 13.3; 128256, 8000 kept 79.8 / 40.5; K = 2000 and P =
+// 0.95 at 32000 (radix levels before) 59.5 / 22.6 / 14.9, at 128256 166 / 38.
+struct ValueBins {
+  uint32_t base, top;                                      // magnitudes (15 bits) of the lowest and highest counter of a sign
+  float from;                                              // the lowest value that is counted
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  // The entries under m - T ln(V / (1 - P)) have less than 1 - P of the mass between them: top-p alone needs none of them.
+  __device__ __forceinline__ void set(float m, int V, float lt, bool use_k, float top_p) {
+    const float deep = top_p < 1.0f ? log2f((float)V / (1.0f - top_p)) + 1.0f : 0.f;
+    const float lowest = m - (use_k ? fmaxf(deep, 32.f) : deep) / lt;
+    from = use_k ? -INFINITY : lowest;
+    const uint32_t e = __float_as_uint(fmaxf(fabsf(m), fabsf(lowest))) >> 23;      // (255: not finite)
+    base = (uint32_t)max((int)(e + 1) * 128 - kSteps / 2, 0);
+    top = base + kSteps / 2 - 1;
+  }
+  // Counter of a value: 0 for the most negative (and whatever lies below it), 8191 for the largest.  Two values a word.
+  __device__ __forceinline__ u16x2 places(uint32_t word) const {
+    const u16x2 w = __builtin_bit_cast(u16x2, word);
+    const u16x2 lo = {(uint16_t)base, (uint16_t)base}, hi = {(uint16_t)top, (uint16_t)top};
+    u16x2 mag = w & (uint16_t)0x7fff;
+    mag = __builtin_elementwise_min(__builtin_elementwise_max(mag, lo), hi);
+    typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 sign = __builtin_bit_cast(u16x2, __builtin_bit_cast(i16x2, w) >> (int16_t)15);
+    return (mag - lo + (uint16_t)(kSteps / 2)) ^ (sign & (uint16_t)(kSteps - 1));
+  }
+  static __device__ __forceinline__ int slot_of(int place) { return place + (place >> 4); }    // (a lane reads runs of 16)
+  // Counts the entries of a vector (f: its values) that may matter.  An LDS counter takes a few entries a cycle and no
+  // more, so the others, most of a peaked row, are left out.
+  template <int N>
+  __device__ __forceinline__ void count(uint32_t* bins, const u32x4& q, const float (&f)[N]) const {
+    char* b = reinterpret_cast<char*>(bins);
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      u16x2 at = places(q[i]);
+      at = (at + (at >> (uint16_t)4)) << (uint16_t)2;      // the byte offset of slot_of
+      const uint32_t both = __builtin_bit_cast(uint32_t, at);
+      if (f[2 * i] >= from) atomicAdd(reinterpret_cast<uint32_t*>(b + (both & 0xffffu)), 1u);
+      if (f[2 * i + 1] >= from) atomicAdd(reinterpret_cast<uint32_t*>(b + (both >> 16)), 1u);
+    }
+  }
+  __device__ __forceinline__ void count_one(uint32_t* bins, float v) const {
+    if (v >= from) atomicAdd(&bins[slot_of(places(__float_as_uint(v)).y)], 1u);        // (a bfloat16 value is the upper half)
+  }
+  // The value of a counter (of those that share one: the largest magnitude).
+  __device__ __forceinline__ bool shared(int place) const { return place == kSteps / 2 || place == kSteps / 2 - 1; }
+  __device__ __forceinline__ float value(int place) const {
+    const uint32_t sign = place < kSteps / 2 ? 1u : 0u, r = (uint32_t)(sign ? kSteps / 2 - 1 - place : place - kSteps / 2);
+    return __uint_as_float((sign << 31) | ((base + r) << 16));
+  }
+};
+
+__device__ __forceinline__ void clear_bins(WarpShared& sh) {
+  static_assert(sizeof(sh.steps) % sizeof(u32x4) == 0, "cleared by vectors");
+  u32x4* v = reinterpret_cast<u32x4*>(sh.steps);
+  for (int d = threadIdx.x; d < (int)(sizeof(sh.steps) / sizeof(u32x4)); d += kWarpThreads) v[d] = u32x4{0, 0, 0, 0};
+  if (threadIdx.x == 0) sh.near_any = 0;
+}
+
+// The cutoff from the counts of a row's values in sh.steps (complete: a barrier lies between).  Called by all threads.
+// False: the counters do not tell.
+__device__ __forceinline__ bool cutoff_of_bins(const ValueBins& vb, float lt, int top_k, bool use_k, float top_p, float m,
+                                               double row_s, WarpShared& sh, float* cutoff) {
+  constexpr int kRun = kSteps / kWarpThreads, kWaves = kWarpThreads / kWave;
+  static_assert(kRun == 16, "slot_of pads one word per lane's run");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const bool use_p = top_p < 1.0f;
+  const float c_ref = ref_of(m, lt);
+  const int last = kSteps - 1 - tid * kRun;                // this lane's counters: last, last - 1, ..., in descending order
+  // (read again where they are needed again: sixteen registers fewer, and four workgroups fit a compute unit)
+  const uint32_t* run_end = sh.steps + ValueBins::slot_of(last - (kRun - 1));
+  auto count_of = [&](int j) { return run_end[kRun - 1 - j]; };
+  // (a run's values are all of one sign)
+  const uint32_t first_bits = __float_as_uint(vb.value(last)), next_bits = last < kSteps / 2 ? 1u << 16 : ~0u << 16;
+  float e[kRun];                                           // the mass of one entry
+  auto mass_of = [&](uint32_t c, int j) { return (double)c * (double)e[j]; };
+  int n_mine = 0;
+  double m_mine = 0.0;
+#pragma unroll
+  for (int j0 = 0; j0 < kRun; j0 += 4) {
+    uint32_t c[4], any = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { c[j] = count_of(j0 + j); any |= c[j]; n_mine += (int)c[j]; e[j0 + j] = 0.f; }
+    if (__ballot(any != 0)) {                              // (a nucleus lies in the counters of one or two wavefronts)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float w = exp2_fast(__builtin_fmaf(__uint_as_float(first_bits + (uint32_t)(j0 + j) * next_bits), lt, -c_ref));
+        e[j0 + j] = c[j] ? w : 0.f;                        // (infinite for counters far above the row)
+        m_mine += mass_of(c[j], j0 + j);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const double m_incl = wave_scan_f64(m_mine);
+  const int n_incl = wave_scan_i32(n_mine);
+  if (lane == kWave - 1) { sh.wave_m[wave] = m_incl; sh.wave_c[wave] = (double)n_incl; }
+  if (tid == 0) { sh.first_reach = kSteps; sh.last_reach = kSteps; }
+  __syncthreads();
+  double before = m_incl - m_mine, n_before = (double)(n_incl - n_mine);
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w)
+    if (w < wave) { before += sh.wave_m[w]; n_before += sh.wave_c[w]; }
+  double total = row_s;
+  int at_k = 0;                                            // counter of the K-th largest value
+  if (use_k) {
+    if (n_before < (double)top_k && n_before + (double)n_mine >= (double)top_k) {
+      double n = n_before, run = before;
+#pragma unroll
+      for (int j = 0; j < kRun; ++j) {
+        if (n < (double)top_k) {
+          const uint32_t c = count_of(j);
+          n += (double)c;
+          run += mass_of(c, j);
+          if (n >= (double)top_k) { sh.last_reach = last - j; sh.sel_mass_above = run; }
+        }
+      }
+    }
+    __syncthreads();
+    at_k = sh.last_reach;
+    if (at_k == kSteps || at_k == 0 || vb.shared(at_k)) return false;    // (the lowest counter holds all that is below it)
+    total = sh.sel_mass_above;
+    if (!use_p) { *cutoff = vb.value(at_k); return true; }
+  }
+  // The end of the first group of equal values whose running mass reaches P; ends up to it that lie close to P.
+  const double want = (double)top_p * total, tie = kNearTie * total;
+  if (n_mine && before < want && before + m_mine >= want - tie) {
+    double run = before;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) {
+      const uint32_t c = count_of(j);
+      if (c && run < want) {
+        run += mass_of(c, j);
+        if (fabs(run - want) < tie) sh.near_any = 1;
+        if (run >= want) sh.first_reach = last - j;
+      }
+    }
+  }
+  __syncthreads();
+  const int at = sh.first_reach;
+  if (at == kSteps || at == 0 || vb.shared(at)) return false;
+  *cutoff = vb.value(at);
+  return true;
+}
+
 // Descending order of keys[0..n), n <= kRankMax distinct non-zero keys: every key's rank by comparing it
 // with all of them (LDS broadcasts, two keys each).  About 32 n cycles, 13000 for sort_desc_runs.
 constexpr int kRankMax = 256;
@@ -551,8 +707,8 @@ __device__ __forceinline__ bool settle_step(float top_p, double inv_t, float m, 
   return true;
 }
 
-// What the lists do not settle (m = row maximum, finite; sh.near_tie cleared): the steps of a
-// nucleus, else radix selection over the whole row.  Returns the cutoff in every thread; sets
+// What the lists do not settle (m = row maximum, finite; sh.near_tie cleared): the counts of a bfloat16
+// row's values, the steps of a nucleus, else radix selection over the whole row.  Returns the cutoff in every thread; sets
 // sh.near_tie.
 template <int DT>
 __device__ __forceinline__ float general_cutoff(const void* row, int V, float lt, double inv_t, int top_k, float top_p,
@@ -562,6 +718,38 @@ __device__ __forceinline__ float general_cutoff(const void* row, int V, float lt
   const bool use_k = top_k > 0 && top_k < V, use_p = top_p < 1.0f;
   const float c_ref = m * lt;
 
+  if constexpr (DT == DT_BF16) {
+    if (!sh.counted) {                                    // (from cache)
+      ValueBins vb;
+      vb.set(m, V, lt, use_k, top_p);
+      clear_bins(sh);
+      __syncthreads();
+      constexpr int EPV = Elem<DT>::per_vec, U = 4;
+      const int nvec = V / EPV;
+      for (int i = tid; i < nvec; i += U * kWarpThreads) {
+        u32x4 q[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i + u * kWarpThreads < nvec) q[u] = load_vec(row, i + u * kWarpThreads);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i + u * kWarpThreads < nvec) {
+            float f[EPV];
+            unpack<DT>(q[u], f);
+            vb.count(sh.steps, q[u], f);
+          }
+      }
+      if (nvec * EPV + tid < V) vb.count_one(sh.steps, load_elem<DT>(row, nvec * EPV + tid));
+      __syncthreads();
+      float cutoff;
+      const bool told = cutoff_of_bins(vb, lt, top_k, use_k, top_p, m, sh.row_s, sh, &cutoff);
+      if (told) {
+        if (tid == 0) sh.near_tie = sh.near_any;
+        return cutoff;
+      }
+      __syncthreads();
+    }
+  }
   if (!use_k && use_p) {
     float cutoff;
     if (list_nucleus_step<DT>(row, V, lt, top_p, m, sh) && settle_step(top_p, inv_t, m, sh, &cutoff)) return cutoff;
@@ -678,15 +866,21 @@ constexpr int kNucleusRank = 48;
 constexpr int kNucleusRank2 = 256;
 // the deeper list holds about 320 entries, seven times as many as the first, and each is lighter: where
 // the largest 48 lane maxima have less than this share of P, it hardly ever reaches P.  Cutoffs of 200 rows of
-// 32000 at P = 0.9, us with 0.6 / 0.8 / 1.0 (always a list first: 59): 3600 tokens kept 57 / 42 / 43, 310 kept
+// 32000 fp32 entries at P = 0.9, us with 0.6 / 0.8 / 1.0 (always a list first: 59): 3600 tokens kept 57 / 42 / 43, 310 kept
 // 54 / 38 / 39, 39 kept 29 / 30 / 35, 12 kept 26 / 26 / 30; 800 of 128256: 1140 kept 187 / 187 / 172, 98 kept 108 / 100 / 158, 41
 // kept 86 / 88 / 127.
+// The counts of a bfloat16 row's values cost less than that list, where the row comes from cache: with 0.8 / 1.0, 200 x
+// 128256 66.8 / 38.4 (600 kept) and 34.9 / 29.1 (30 kept), 800 x 32000 56.4 / 50.5 and 24.7 / 21.2; but 1600 x 128256, where
+// it comes from memory, 115 / 144 (120 kept), 800 x 152064 91 / 98.
 constexpr double kHopeless = 0.8;
+// (bfloat16 rows beside one another, and their entries, up to which a list has to promise all of P)
+constexpr long long kHopelessRows = 1024, kHopelessEntries = 105000000;
 
 // One row (r of tensor z) by the whole workgroup.
 template <int DT>
 __device__ __forceinline__ void warp_row(const void* z, const int r, int V, const Scale sc, int top_k, float top_p,
-                                         float* cutoff, uint32_t* flags, const CompactOut out, WarpShared& sh) {
+                                         float* cutoff, uint32_t* flags, const CompactOut out, const double& hopeless,
+                                         WarpShared& sh) {
   const int tid = threadIdx.x;
   const void* row = static_cast<const char*>(z) + (size_t)r * V * Elem<DT>::bytes;
   const float lt = sc.L;
@@ -728,7 +922,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   // entry of the row.  Wavefront 0 holds eight maxima per lane and bisects the 16 bits
   // with ballots.
   sh.lane_key[tid] = okey(acc[0].m) >> 16;
-  if (tid == 0) { sh.n_cand = 0; sh.near_tie = 0; sh.settled = 0; sh.n_keep = -1; sh.out_done = 0; }
+  if (tid == 0) { sh.n_cand = 0; sh.near_tie = 0; sh.settled = 0; sh.n_keep = -1; sh.out_done = 0; sh.counted = 0; }
   __syncthreads();
   if (tid == kWave) {
     // sum_v exp((z_v - m) / T), by one lane while wavefront 0 looks for tau (by every lane, the rows of a compute unit
@@ -982,7 +1176,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
       __syncthreads();
       const double share = sh.z_keep / ((double)top_p * row_s);
       __syncthreads();
-      if (!out.count && share < kHopeless) tau = -INFINITY;
+      if (!out.count && share < hopeless) tau = -INFINITY;
       else if (share < 1.0 + 1e-6) tau = lane_max_of_rank(kNucleusRank2);
     }
     SV_PHASE_MARK(2)
@@ -1099,6 +1293,7 @@ struct WarpBatch {
   float* cutoff[kWarpMaxTensors];
   uint32_t* flags[kWarpMaxTensors];
   CompactOut out[kWarpMaxTensors];
+  double hopeless;                       // top-p alone, no support wanted: the least share of P for which a second list is tried
 };
 
 // (8 wavefronts per SIMD = four workgroups per compute unit: the decisions of some rows overlap the
@@ -1109,7 +1304,102 @@ __global__ __launch_bounds__(kWarpThreads, 8) void warp_cutoffs_kernel(int V, Wa
   int t = 0;
   while (t + 1 < b.n && (int)blockIdx.x >= b.row_end[t]) ++t;
   const int r = (int)blockIdx.x - (t ? b.row_end[t - 1] : 0);
-  warp_row<DT>(b.z[t], r, V, b.sc[t], b.top_k[t], b.top_p[t], b.cutoff[t], b.flags[t], b.out[t], sh);
+  warp_row<DT>(b.z[t], r, V, b.sc[t], b.top_k[t], b.top_p[t], b.cutoff[t], b.flags[t], b.out[t], b.hopeless, sh);
+}
+
+// Cutoffs of bfloat16 rows that a workgroup holds in its registers, R vectors a lane: one read of the row, the maximum, the
+// normaliser and the counts of its values (ValueBins).  8 x 32000 at P = 0.9, 2500 tokens kept: 10.6 us (27.8 in three sweeps
+// and a sort), the first loads 3, the two looks at the entries 3, the scan of the counters 2.  Bound by arithmetic, about 12
+// operations an entry, where there are more rows than fit at once (1600 x 32000: 44 us, 122 before).  Up to 64 registers, for
+// four rows on a compute unit (with 79, three: 800 x 32000 30.7 us, 29.4 with four).
+template <int R>
+__global__ __launch_bounds__(kWarpThreads, R <= 8 ? 8 : 4) void warp_cutoffs_resident_kernel(int V, WarpBatch b) {
+  __shared__ WarpShared sh;
+  constexpr int nt = kWarpThreads, kWaves = nt / kWave, EPV = Elem<DT_BF16>::per_vec;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  int t = 0;
+  while (t + 1 < b.n && (int)blockIdx.x >= b.row_end[t]) ++t;
+  const int r = (int)blockIdx.x - (t ? b.row_end[t - 1] : 0);
+  const void* row = static_cast<const char*>(b.z[t]) + (size_t)r * V * Elem<DT_BF16>::bytes;
+  const Scale sc = b.sc[t];
+  const float lt = sc.L, top_p = b.top_p[t];
+  const int top_k = b.top_k[t], nvec = V / EPV;
+  const bool use_k = top_k > 0 && top_k < V, use_p = top_p < 1.0f;
+  constexpr uint32_t kNegInf = 0xFF80FF80u;
+  u32x4 q[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    q[j] = u32x4{kNegInf, kNegInf, kNegInf, kNegInf};
+    if (tid + j * nt < nvec) q[j] = load_vec_nt(row, tid + j * nt);
+  }
+  const int tail = nvec * EPV + tid;                       // the entries past the last whole vector
+  const float z_tail = tail < V ? load_elem<DT_BF16>(row, tail) : -INFINITY;
+  clear_bins(sh);
+  float mx = z_tail;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    float f[EPV];
+    unpack<DT_BF16>(q[j], f);
+#pragma unroll
+    for (int e = 0; e < EPV; e += 2) mx = fmaxf(fmaxf(mx, f[e]), f[e + 1]);
+  }
+  mx = wave_max_f32(mx);
+  if (lane == 0) sh.mg.m[0][wave] = mx;
+  __syncthreads();
+  float m = row16_max_all_f32((tid & 15) < kWaves ? sh.mg.m[0][tid & 15] : -INFINITY);
+  m = lane_f32(m, 0);
+  const float c_ref = ref_of(m, lt);
+  ValueBins vb;
+  vb.set(m, V, lt, use_k, top_p);
+  // the exponentials of a vector are added in fp32, the vectors in fp64
+  double s = (double)exp2_fast(__builtin_fmaf(z_tail, lt, -c_ref));
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    // (the vectors stay packed between the two looks at them)
+    asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w));
+    if (tid + j * nt < nvec) {
+      float f[EPV], e[EPV];
+      unpack<DT_BF16>(q[j], f);
+#pragma unroll
+      for (int i = 0; i < EPV; ++i) e[i] = exp2_fast(__builtin_fmaf(f[i], lt, -c_ref));
+      s += (double)(((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])));
+      const float top = fmaxf(fmaxf(fmaxf(f[0], f[1]), fmaxf(f[2], f[3])), fmaxf(fmaxf(f[4], f[5]), fmaxf(f[6], f[7])));
+      if (top >= vb.from) vb.count(sh.steps, q[j], f);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (tail < V) vb.count_one(sh.steps, z_tail);
+  s = wave_sum_f64(s);
+  if (lane == 0) sh.mg.s[0][wave] = s;
+  __syncthreads();
+  MS ms;
+  ms.m = m;
+  ms.s = fold_sums(sh.mg.s[0], kWaves);
+  float cutoff = -INFINITY;
+  uint32_t fl = 0;
+  bool done = true;
+  if (bad_row(ms, lt)) {
+    cutoff = __builtin_nanf("");
+    fl = SV_FLAG_BAD_ROW;
+  } else if (use_k || use_p) {
+    done = cutoff_of_bins(vb, lt, top_k, use_k, top_p, m, ms.s, sh, &cutoff);
+    fl = sh.near_any ? SV_FLAG_NEAR_TIE : 0u;
+  }
+  if (!done) {
+    __syncthreads();
+    if (tid == 0) {
+      const double m_t = (double)m * sc.inv_t;
+      sh.counted = 1;
+      sh.row_s = ms.s;
+      sh.row_Z = ms.s * exp((double)c_ref * kLn2 - sc.tau1 * m_t - m_t);
+    }
+    cut_general_row<DT_BF16>(row, r, V, lt, sc.inv_t, top_k, top_p, m, b.cutoff[t], b.flags[t], nullptr, nullptr, sh);
+    return;
+  }
+  if (tid == 0) {
+    b.cutoff[t][r] = cutoff;
+    if (b.flags[t]) b.flags[t][r] = fl;
+  }
 }
 
 }  // namespace sv
@@ -1153,10 +1443,23 @@ int launch_warp(int n, const void* const* z, const int* rows, int V, int dtype, 
   }
   b.n = n;
   if (total == 0) return SV_OK;
+  b.hopeless = dtype == SV_BF16 && total <= kHopelessRows && total * V <= kHopelessEntries ? 1.0 + 1e-6 : kHopeless;
   hipStream_t st = as_stream(stream);
+  // Rows held in registers: every size for K > 512, for which there are no lists (1600 x 65536, K = 2000: 96 us, 423 before).
+  // For top-p the lists take less of short nuclei once the chip is full: 4000 x 25000, 30 tokens kept, 59.2 with them and 65.9;
+  // 800 x 32000 24.7 and 27.4 (2500 kept: 75.6 and 29.4); 400 x 32000 21.2 and 17.6; 1600 x 24576 of 3 tokens kept 29.6 and
+  // 30.3.  For K up to 512 they are the better way throughout: 200 x 32000, K = 20 10.1 and 16.3.
+  const bool few = V <= 24576 ? total * V <= 40000000 : V <= kResidentMax / 2 && total <= 512;
+  bool resident = !outs && dtype == SV_BF16;
+  for (int t = 0; t < n; ++t) resident = resident && (top_k[t] > kWarpThreads ? V <= kResidentMax : top_k[t] <= 0 && few);
   if (dtype == SV_F32)
     hipLaunchKernelGGL(warp_cutoffs_kernel<DT_F32>, dim3((unsigned)total), dim3(kWarpThreads), 0, st, V, b);
-  else
+  else if (resident) {
+    const dim3 grid((unsigned)total), block(kWarpThreads);
+    if (V <= kResidentMax / 4) hipLaunchKernelGGL(warp_cutoffs_resident_kernel<4>, grid, block, 0, st, V, b);
+    else if (V <= kResidentMax / 2) hipLaunchKernelGGL(warp_cutoffs_resident_kernel<8>, grid, block, 0, st, V, b);
+    else hipLaunchKernelGGL(warp_cutoffs_resident_kernel<16>, grid, block, 0, st, V, b);
+  } else
     hipLaunchKernelGGL(warp_cutoffs_kernel<DT_BF16>, dim3((unsigned)total), dim3(kWarpThreads), 0, st, V, b);
   return launch_status();
 }
