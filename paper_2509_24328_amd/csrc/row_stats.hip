@@ -14,13 +14,14 @@
 // discussed in Sec. 2 of the paper.)
 // A = min(1, P_c(x) / P_d(x)) is a scalar epilogue in fp64.
 //
-// Two kernels (the rule between them stands at launch_stats).  In both, sweep 1 parks what it reads on
+// Three kernels (the rule between them stands at launch_stats).  In the first two, sweep 1 parks what it reads on
 // chip, in registers and in LDS, and only the rest of a pair, if any, is read again, most recent
 // bytes first so that they are still in L2.
 //   row_stats_loop_kernel    workgroups that fill the chip once and walk through the pairs: the places that
 //                            sweep 2 of a pair leaves take the next pair's loads
-//   row_stats_stash_kernel   a workgroup per pair: very short rows, very many pairs of short ones, and few pairs, or a few
-//                            more than compute units, of rows that do not stay on chip
+//   row_stats_stash_kernel   a workgroup per pair: few pairs, or a few more than compute units, of rows that do not stay on
+//                            chip; very many pairs of rows a little too long for the terms kernel; short rows with KL
+//   row_stats_terms_kernel   short rows, without KL: sweep 1 keeps its exponentials in registers, and sweep 2 needs no others
 // Algorithmic HBM traffic: 2 * V * elem_size bytes per pair.
 #include <algorithm>
 #include <type_traits>
@@ -164,8 +165,8 @@ struct PairConsts {
   float zx[2];
 };
 
-// Scalar epilogue of one pair: A, flags and the stores.
-template <bool WITH_KL, bool WARP>
+// Scalar epilogue of one pair: A, flags and the stores.  (SCALED: S is relative to one, not to the head of kappa_d.)
+template <bool WITH_KL, bool WARP, bool SCALED = false>
 __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, const PairConsts& pc, int tok, double S,
                                                double KL, double pa, double p1) {
   const double lse_d = pc.lse[0], lse_c = pc.lse[1];
@@ -187,7 +188,7 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
     S = KL = __builtin_nan("");
   } else {
     // the sums of sweep 2 are relative to the head of kappa_d (MinAcc)
-    const double tail_d = pc.kappa[0] - (double)(float)pc.kappa[0], f_d = exp2(-tail_d);
+    const double tail_d = SCALED ? 0.0 : pc.kappa[0] - (double)(float)pc.kappa[0], f_d = SCALED ? 1.0 : exp2(-tail_d);
     S *= f_d;
     if (WITH_KL) {
       KL *= f_d * kLn2;
@@ -708,6 +709,310 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
   pass(std::true_type(), std::false_type());
 }
 
+// Rows short enough for a lane to keep the terms 2^(z L - c) of sweep 1 in registers instead of the logits: P vector pairs
+// per lane, 512 lanes.  Sweep 2 is then a multiplication, a minimum and an addition per entry,
+//     min(P_d, P_c) = f min(e_d, e_c g),  f = 2^(c_d - C_d) / s_d,  g = 2^((c_c - C_c) - (c_d - C_d)) s_d / s_c
+// where the other kernels unpack both logits and take an exponential: 14 operations per entry pair in all, 19 there.  The
+// references c are whole numbers, so that every power of two is exact, the lane's own at the time of the vector; C and s are
+// the row's.  No logarithm stands between the sweeps: what the results need of a pair is put aside in LDS, and at the
+// end a lane per pair forms the normalisers' logarithms and A.
+// A pass over the places is sweep 2 of a pair, sweep 1 of the next one into the registers that it leaves, and the loads of the one
+// after that: a whole pair is in flight while another one is summed, and one barrier ends the pass.  (ONE: a pair per workgroup.)
+// Bound, for many pairs, by one read of them: 8192 x 32000 bf16 166.5 us = 6.3 TB/s, 202 with a workgroup per pair that takes
+// every exponential twice; for few, by launch, the first loads' latency and the arithmetic of a pair on one compute unit.
+// S against 64 bits, mean of 64 pairs: 2.5e-8 off, 5.4e-8 in the other kernels.
+constexpr int kTermThreads = 512, kTermRecords = 512;
+
+struct TermRecord {
+  double s[2], S;      // sums of the rows relative to the whole-numbered reference, S times the draft's
+  float m[2], zx[2];   // maxima, logits of the drafted token
+  int tok;
+};
+
+__device__ __forceinline__ float whole_ref(float m, const float L) { return __builtin_ceilf(ref_of(m, L)); }
+// (m, s) over the whole-numbered reference, as the other kernels hand it on: relative to c(m)
+__device__ __forceinline__ MS ms_of_whole(float m, double s, const float L) {
+  MS r;
+  r.m = m;
+  r.s = s * exp2((double)(whole_ref(m, L) - ref_of(m, L)));
+  return r;
+}
+
+// A word at a uniform address that nothing writes during the kernel, through the scalar cache: vector loads are waited for in
+// order, and such a word would be waited for with the whole pair that is in flight.
+template <class T>
+__device__ __forceinline__ T load_scalar(const T* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// Several values reduced at once, each in lanes of its own from the first step on: halves of a wavefront are exchanged
+// between two registers (v_permlane32_swap: lanes 0-31 of `a` meet lanes 32-63 of `a`, the same for `b` in the upper half),
+// then rows of 16 lanes.
+struct Halves { uint32_t a, b; };
+__device__ __forceinline__ Halves swap32(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return {r[0], r[1]};
+}
+__device__ __forceinline__ Halves swap16(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  return {r[0], r[1]};
+}
+template <class Swap>
+__device__ __forceinline__ double swap_add(double a, double b, Swap&& swap) {
+  const Halves lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
+  return __hiloint2double(hi.a, lo.a) + __hiloint2double(hi.b, lo.b);
+}
+// Rows 0 to 3 of 16 lanes: sums of a, m, b, m in their lanes 15.
+__device__ __forceinline__ double wave_sum3_f64(double a, double b, double m) {
+  const double ab = swap_add(a, b, swap32), mm = swap_add(m, m, swap32);
+  return row16_sum_f64(swap_add(ab, mm, swap16));
+}
+// Floats as integers of the same order, and back.
+__device__ __forceinline__ int order_key(float f) {
+  const int i = __float_as_int(f);
+  return i ^ ((i >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float from_order_key(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
+template <int CTRL>
+__device__ __forceinline__ int dpp_max_i32(int v) {
+  return max(v, __builtin_amdgcn_update_dpp((int)0x80000000, v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ int row16_max_all_i32(int v) {
+  v = dpp_max_i32<kDppRor1>(v);
+  v = dpp_max_i32<kDppRor2>(v);
+  v = dpp_max_i32<kDppRor4>(v);
+  return dpp_max_i32<kDppRor8>(v);
+}
+// The maximum of a in lanes 0-31, of b in lanes 32-63.
+__device__ __forceinline__ int wave_max2_i32(int a, int b) {
+  const Halves ab = swap32(a, b);
+  const int v = max((int)ab.a, (int)ab.b);
+  const Halves rows = swap16(v, v);
+  return row16_max_all_i32(max((int)rows.a, (int)rows.b));
+}
+
+// Workgroups that fit a compute unit: registers for the terms, references and sums, and for the pair in flight.
+template <int DT, int P, bool ONE>
+constexpr int terms_per_cu() {
+  constexpr int regs = P * (2 * Elem<DT>::per_vec + 2) + (ONE ? 20 : 8 * P + 24);
+  return regs <= 80 ? 3 : regs <= 128 ? 2 : 1;
+}
+
+template <int DT, bool WARP, int P, bool ONE>
+__global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) void row_stats_terms_kernel(StatsArgs a) {
+  constexpr int EPV = Elem<DT>::per_vec, nt = kTermThreads, kWaves = nt / kWave;
+  constexpr int kEnds = DT == DT_F32 ? 4 : 2;          // places that a row may end in or before
+  __shared__ int part_m[2][2][kWaves];                 // [turn][draft, companion][wavefront], ordered keys
+  __shared__ double part_s[2][4][kWaves];              // [turn][draft, minima of the pair before, companion, not used][wavefront]
+  __shared__ TermRecord rec[ONE ? 1 : kTermRecords];
+  int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
+  const int half = lane >> 5;                          // of the wavefront: draft, companion
+  const int pairs = a.B * a.k;
+  int row_bytes = a.V * Elem<DT>::bytes;
+  const Scale sc_d = WARP ? a.sc_d : unit_scale(), sc_c = WARP ? a.sc_c : unit_scale();
+  const float Ld = sc_d.L, Lc = sc_c.L;
+
+  float ed[P][EPV], ec[P][EPV], refd[P], refc[P];      // terms and references of the pair of sweep 2
+  u32x4 qd[P], qc[P];                                  // the pair in flight
+  float G = 0.f, C[2] = {0.f, 0.f};
+
+  // has this wavefront entries at place j?
+  auto busy = [&](int j) { return j < P - kEnds || (wave * kWave + j * nt) * 16 < row_bytes; };
+  // (past the row's last vector, which may start anywhere: that one)
+  using GlobalBytes = const __attribute__((address_space(1))) char*;
+  using GlobalVec = const __attribute__((address_space(1))) u32x4_row*;
+  auto load_place = [&](GlobalBytes row, int j) {
+    const uint32_t at = (tid + j * nt) * 16;
+    return __builtin_nontemporal_load((GlobalVec)(row + (j < P - kEnds ? at : min(at, (uint32_t)row_bytes - 16u))));
+  };
+  // -inf for the entries that a vector shares with the one before it, or has beyond the row
+  auto masked = [&](u32x4 q, int j) {
+    const int n = ((tid + j * nt) * 16 - (row_bytes - 16)) / Elem<DT>::bytes;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if constexpr (DT == DT_F32) {
+        q[w] = n > w ? 0xFF800000u : q[w];
+      } else {
+        q[w] = n > 2 * w ? (q[w] & 0xffff0000u) | 0xFF80u : q[w];
+        q[w] = n > 2 * w + 1 ? (q[w] & 0xffffu) | 0xFF800000u : q[w];
+      }
+    }
+    return q;
+  };
+  // sweep 1 of a vector: its terms, and the lane's running (max, reference, sum)
+  struct Run { float m = -INFINITY, c = kRefFloor, s = 0.f; };
+  auto form_terms = [&](Run& o, const u32x4& q, float (&e)[EPV], float& ref, const float L, const float cut) {
+    float z[EPV];
+    unpack<DT>(q, z);
+    if (WARP) {
+#pragma unroll
+      for (int i = 0; i < EPV; ++i) z[i] = cut_below(z[i], cut);
+    }
+    float mx = o.m;
+#pragma unroll
+    for (int i = 0; i < EPV; i += 2) mx = fmaxf(fmaxf(mx, z[i]), z[i + 1]);
+    const float c = whole_ref(mx, L);
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) e[i] = exp2_fast(__builtin_fmaf(z[i], L, -c));
+    float t[EPV / 2];
+#pragma unroll
+    for (int i = 0; i < EPV / 2; ++i) t[i] = e[i] + e[i + EPV / 2];
+#pragma unroll
+    for (int h = EPV / 4; h >= 1; h /= 2) {
+#pragma unroll
+      for (int i = 0; i < h; ++i) t[i] += t[i + h];
+    }
+    o.s = __builtin_fmaf(o.s, exp2_fast(o.c - c), t[0]);
+    o.m = mx;
+    o.c = ref = c;
+    asm volatile("" : "+v"(o.s));                      // the terms are formed here, not where sweep 2 needs them
+  };
+  // sweep 2 of a vector pair.  (Where g does not fit float32, f underflows, or so nearly that a companion's term beyond the
+  // largest float32 is above any e_d.  The terms are not negative: their bits are ordered as they are.)
+  auto min_terms = [&](int j, float& acc) {
+    const float dd = fmaxf(refd[j] - C[0], -150.f), dc = fmaxf(refc[j] - C[1], -150.f);
+    const float f = exp2_fast(dd), g = fminf(exp2_fast(dc - dd) * G, __FLT_MAX__);
+    float t[EPV];
+#pragma unroll
+    for (int i = 0; i < EPV; ++i) t[i] = __uint_as_float(min(__float_as_uint(ed[j][i]), __float_as_uint(ec[j][i] * g)));
+#pragma unroll
+    for (int h = EPV / 2; h >= 1; h /= 2) {
+#pragma unroll
+      for (int i = 0; i < h; ++i) t[i] += t[i + h];
+    }
+    acc = __builtin_fmaf(f, t[0], acc);
+    asm volatile("" : "+v"(acc));                      // here, not later: the next pair's terms take the registers
+  };
+
+  int next = blockIdx.x, turn = 0, done = 0;           // done: pairs of this workgroup whose sweep 1 is over
+  auto row_at = [&](const void* z, int pair) { return static_cast<const char*>(z) + (size_t)pair * (uint32_t)row_bytes; };
+  auto scalar_row = [&](const void* z, int pair) {     // (a scalar base: the places' offsets are all that lanes add)
+    uintptr_t row = reinterpret_cast<uintptr_t>(row_at(z, pair));
+    asm volatile("" : "+s"(row));
+    return (GlobalBytes)row;
+  };
+  auto load_pair = [&](GlobalBytes rd, GlobalBytes rc, int j) {
+    qd[j] = load_place(rd, j);
+    qc[j] = load_place(rc, j);
+  };
+
+  {
+    const GlobalBytes rd = scalar_row(a.z_d, next), rc = scalar_row(a.z_c, next);
+#pragma unroll
+    for (int j = 0; j < P; ++j) load_pair(rd, rc, j);
+  }
+
+  auto pass = [&](auto has_cur, auto has_more) {
+    constexpr bool CUR = decltype(has_cur)::value, MORE = decltype(has_more)::value;
+    // (nothing derived from these is kept over the passes)
+    asm volatile("" : "+s"(row_bytes));
+    asm volatile("" : "+v"(tid));
+    float cut_d = -INFINITY, cut_c = -INFINITY;
+    if (WARP && a.cut_d) cut_d = load_scalar(a.cut_d + next);
+    if (WARP && a.cut_c) cut_c = load_scalar(a.cut_c + next);
+    // the drafted token's logits, by every lane (a load under a condition would make the waits for the rows coarse)
+    const int tok = load_scalar(a.x + next);
+    const float zx = load_elem<DT>(row_at(half ? a.z_c : a.z_d, next), min(max(tok, 0), a.V - 1));
+    GlobalBytes rd = nullptr, rc = nullptr;            // rows of the pair that is loaded
+    if (MORE) {
+      const int then = min(next + (int)gridDim.x, pairs - 1);
+      rd = scalar_row(a.z_d, then);
+      rc = scalar_row(a.z_c, then);
+    }
+    Run od, oc;
+    float acc = 0.f;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      if (busy(j)) {                                   // (uniform)
+        if (CUR) min_terms(j, acc);
+        if (j >= P - kEnds && (wave * kWave + kWave + j * nt) * 16 > row_bytes) {
+          qd[j] = masked(qd[j], j);
+          qc[j] = masked(qc[j], j);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        form_terms(od, qd[j], ed[j], refd[j], Ld, cut_d);
+        __builtin_amdgcn_sched_barrier(0);
+        form_terms(oc, qc[j], ec[j], refc[j], Lc, cut_c);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (MORE) load_pair(rd, rc, j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int row = lane >> 4, w = lane & 15;
+    const float L = half ? Lc : Ld;
+    {
+      const int key = wave_max2_i32(order_key(od.m), order_key(oc.m));
+      const float ref = whole_ref(from_order_key(key), L);
+      const double sums = wave_sum3_f64((double)od.s * (double)exp2_fast(od.c - lane_f32(ref, 0)),
+                                        (double)oc.s * (double)exp2_fast(oc.c - lane_f32(ref, 32)), (double)acc);
+      if (w == 15) {
+        part_s[turn][row][wave] = sums;
+        part_m[turn][half][wave] = key;
+      }
+    }
+    __syncthreads();
+    // every wavefront folds the partials, a row of 16 lanes each: the draft's, the minima's, the companion's
+    const float mw = from_order_key(part_m[turn][half][w & (kWaves - 1)]);
+    const double sw = w < kWaves ? part_s[turn][row][w & (kWaves - 1)] : 0.0;
+    const float m = row16_max_all_f32(mw), ref = whole_ref(m, L);
+    const double s = row16_sum_f64(row & 1 ? sw : sw * (double)exp2_fast(whole_ref(mw, L) - ref));
+    C[0] = lane_f32(ref, 15);
+    C[1] = lane_f32(ref, 47);
+    {
+      const double s_c = lane_f64(s, 47);
+      double inv = __builtin_amdgcn_rcp(s_c);
+      inv = __builtin_fma(inv, __builtin_fma(-s_c, inv, 1.0), inv);
+      G = (float)(lane_f64(s, 15) * inv);
+    }
+    if (wave == 0 && w == 15) {
+      if (row & 1) {
+        if (CUR) rec[done - 1].S = s;
+      } else {
+        TermRecord& to = rec[done];
+        to.m[half] = m;
+        to.s[half] = s;
+        to.zx[half] = tok < 0 || tok >= a.V ? __builtin_nanf("") : WARP ? cut_below(zx, half ? cut_c : cut_d) : zx;
+        to.tok = tok;
+      }
+    }
+    ++done;
+    turn ^= 1;
+    next += gridDim.x;
+  };
+  if constexpr (ONE) {
+    pass(std::false_type(), std::false_type());
+  } else {
+    // (a workgroup without a second pair asks for the last one all the same)
+    pass(std::false_type(), std::true_type());
+#pragma unroll 1
+    while (next + (int)gridDim.x < pairs) pass(std::true_type(), std::true_type());
+    if (next < pairs) pass(std::true_type(), std::false_type());
+  }
+  float acc = 0.f;
+#pragma unroll
+  for (int j = 0; j < P; ++j)
+    if (busy(j)) min_terms(j, acc);
+  const double t = wave_sum_f64((double)acc);
+  if (lane == 0) part_s[turn][1][wave] = t;
+  __syncthreads();
+  const double S_last = fold_sums(part_s[turn][1], kWaves);
+  // the results, a lane per pair
+  if (tid >= done) return;
+  const TermRecord& r = rec[tid];
+  const int pair = blockIdx.x + tid * gridDim.x;
+  const MS md = ms_of_whole(r.m[0], r.s[0], Ld), mc = ms_of_whole(r.m[1], r.s[1], Lc);
+  PairConsts pc;
+  pc.lse[0] = lse_from_ms(md, sc_d);
+  pc.lse[1] = lse_from_ms(mc, sc_c);
+  pc.kappa[0] = pc.kappa[1] = 0.0;
+  pc.zx[0] = r.zx[0];
+  pc.zx[1] = r.zx[1];
+  a.chain_m[pair] = md.m;
+  a.chain_s[pair] = md.s;
+  stats_epilogue<false, WARP, true>(a, pair, pc, r.tok, (tid == done - 1 ? S_last : r.S) / r.s[0], 0.0, 0.0, 0.0);
+}
+
 // More than 64 KB of dynamic LDS has to be allowed once per kernel and device.
 template <class Kernel>
 static int launch_kernel(Kernel* kernel, bool (&allowed)[64], int groups, int threads, size_t lds_bytes, const StatsArgs& a,
@@ -739,6 +1044,20 @@ static int launch_loop(const StatsArgs& a, hipStream_t st) {
                        Shape::threads, 2 * (size_t)Shape::lds_vecs * 16, a, st);
 }
 
+template <int DT, bool WARP, int P, bool ONLY_ONE = false>
+static int launch_terms(const StatsArgs& a, hipStream_t st) {
+  const int pairs = a.B * a.k;
+  const dim3 threads(kTermThreads);
+  TapScope tap(SV_KERNEL_ROW_STATS, st);
+  if (ONLY_ONE || pairs <= 256 * terms_per_cu<DT, P, true>()) {
+    hipLaunchKernelGGL((row_stats_terms_kernel<DT, WARP, P, true>), dim3(pairs), threads, 0, st, a);
+  } else if constexpr (!ONLY_ONE) {
+    const int fill = 256 * terms_per_cu<DT, P, false>(), groups = std::min(pairs, std::max(fill, (pairs + kTermRecords - 1) / kTermRecords));
+    hipLaunchKernelGGL((row_stats_terms_kernel<DT, WARP, P, false>), dim3(groups), threads, 0, st, a);
+  }
+  return launch_status();
+}
+
 // Which kernel and shape (pairs x entries, bf16 unless said otherwise; us per call in a graph of calls, up to three sets of rows
 // in turn).
 //  * The loop kernel nearly everywhere, with a register share about as long as the row (a workgroup per pair, the better one of
@@ -751,22 +1070,49 @@ static int launch_loop(const StatsArgs& a, hipStream_t st) {
 //    262144 77 / 67; under cutoffs fp32 128 x 152064 52.7 / 48.2.  (Plain fp32 rows gain 5 to 12 % at 96 pairs; at 128 they are
 //    level in turn with themselves and 1.6 us slower in a step, 75.9 / 77.5 with 128 x 128256.)
 //  * many: pairs of short rows have enough to overlap as they are, three to a CU, and the hardware to balance them; the more so
-//    the more arithmetic there is to a byte.  Loop / three: 4096 x 23200 80.7 / 77.1; 8192 x 32800 218 / 197, but 1537 x 32000, which
-//    ends in a nearly empty round, 44.6 / 47.7; under cutoffs 4096 x 48000 187 / 178; fp32, 4096 x 9200 61.0 / 56.0, under cutoffs
-//    69.7 / 58.2, 8192 x 14000 154 / 145, 4096 x 20000 102 / 112.
+//    the more arithmetic there is to a byte.  Loop / three: 8192 x 32800 218 / 197; under cutoffs 4096 x 48000 187 / 178.
 //  * few_more: a few pairs more than CUs, of rows that do not stay on chip: a CU that has two takes longer one after the other than
 //    side by side.  Loop / three / two: 300 x 256512 111 / 105 / 104; under cutoffs 257 x 140000 69.2 / 66.3 / 69.5; fp32, 300 x 30000
 //    22.3 / 19.8 / 22.9, 300 x 50400 32.5 / 32.9 / 29.7, 341 x 58000 38.1 / 41.5 / 36.7.
+//  * Ahead of all of these, without KL, the terms kernel wherever the terms of a pair and the pair in flight fit a lane's
+//    registers (bf16 up to 32768 entries; fp32 14336, 24576 in part), or the terms alone where there is a pair per compute unit
+//    at most (49152; 40960).  The better one of the others / terms, bf16: 64 x 1000 5.1 / 4.3; 64 x 32000 9.4 / 8.5; 512 x 32000
+//    18.4 / 17.8; 2048 x 8192 23.1 / 17.7; 8192 x 16384 114 / 91; 8192 x 32000 202 / 166.5 (6.3 TB/s); under cutoffs 8192 x 32000 231 /
+//    182; 256 x 40960 13.8 / 11.7.  fp32: 64 x 14000 8.1 / 7.1; 2048 x 4096 20.1 / 15.9; 8192 x 10000 113 / 105; 256 x 32000 15.4 /
+//    15.3; under cutoffs 2048 x 20000 59.1 / 55.1.  Where it is not taken: fp32 768 x 16384 19.6 / 20.0, 300 x 20000 15.3 / 16.2, 64 x
+//    49152 13.8 / 14.6, 600 x 1000 7.0 / 7.3.
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr bool kBf16 = DT == DT_BF16;
   constexpr int kCUs = 256, nt = 512;
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
+  if constexpr (!WITH_KL) if (nvec > 0) {
+    const int steps = (a.V + nt * Elem<DT>::per_vec - 1) / (nt * Elem<DT>::per_vec);
+    if constexpr (kBf16) {
+      if (steps <= 2) return launch_terms<DT, WARP, 2>(a, st);
+      if (steps <= 4) return launch_terms<DT, WARP, 4>(a, st);
+      if (steps <= 6) return launch_terms<DT, WARP, 6>(a, st);
+      if (steps <= 8) return launch_terms<DT, WARP, 8>(a, st);
+      if (steps <= 10 && pairs <= kCUs) return launch_terms<DT, WARP, 10, true>(a, st);
+      if (steps <= 12 && pairs <= kCUs) return launch_terms<DT, WARP, 12, true>(a, st);
+    } else {
+      const bool sparse = steps == 1 && pairs > kCUs && pairs <= 3 * kCUs;
+      if (steps <= 4 && !sparse) return launch_terms<DT, WARP, 4>(a, st);
+      if (steps > 4 && (steps <= 7 || (steps <= 8 && (WARP || pairs <= 2 * kCUs || pairs >= 16 * kCUs))))
+        return launch_terms<DT, WARP, 8>(a, st);
+      if (steps > 8 && steps <= 12) {
+        if (pairs <= kCUs) return launch_terms<DT, WARP, 12, true>(a, st);
+        if constexpr (WARP) if (pairs >= 4 * kCUs) return launch_terms<DT, WARP, 12>(a, st);
+      }
+      if (steps > 12 && steps <= 16 && pairs <= kCUs) return launch_terms<DT, WARP, 16, true>(a, st);
+      if (steps > 16 && steps <= 20 && pairs <= kCUs) return launch_terms<DT, WARP, 20, true>(a, st);
+    }
+  }
   const bool one = nvec > (pairs <= kCUs ? 11 * nt : 14 * nt);
   const auto from = [&](int per_cu, int steps) { return pairs >= per_cu * kCUs && nvec <= steps * nt; };
   const bool few = pairs <= (kBf16 || WITH_KL || WARP ? kCUs / 2 : kCUs * 3 / 8) && nvec > 33 * nt;
-  const bool many = kBf16 ? from(6, 7) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
-                          : from(6, WITH_KL || WARP ? 5 : 3) || (WARP ? from(8, 7) || from(12, 9) : !WITH_KL && from(16, 9));
+  const bool many = kBf16 ? (WITH_KL && from(6, 7)) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
+                          : WITH_KL ? from(6, 5) || (WARP && (from(8, 7) || from(12, 9))) : !WARP && from(16, 9);
   const int off_chip = kBf16 ? (WARP ? 16000 : 20000) : (WITH_KL || WARP ? 11 * nt : 14 * nt);
   const bool few_more = pairs > kCUs && pairs <= (kBf16 ? 400 : nvec > 24000 ? 340 : 390) && nvec > off_chip;
   if (nvec <= nt || many || (few_more && (nvec <= 20 * nt || (kBf16 && WARP))))
@@ -778,9 +1124,12 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
   if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 16 : 12, 1>>(a, st);
   if (one) return launch_loop<DT, WITH_KL, WARP, Loop<12, 1>>(a, st);
   if (nvec > 7 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 8 : 6, 2>>(a, st);
-  if (nvec > 5 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<6, 2>>(a, st);
-  if (nvec > 3 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 4 : 2, 2>>(a, st);
-  return launch_loop<DT, WITH_KL, WARP, Loop<2, 2>>(a, st);
+  if constexpr (WITH_KL) {
+    if (nvec > 5 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<6, 2>>(a, st);
+    return launch_loop<DT, WITH_KL, WARP, Loop<2, 2>>(a, st);
+  } else {
+    return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);           // (shorter rows have gone to the terms kernel)
+  }
 }
 
 // Argument checks and launch shared by sv_row_stats and sv_row_stats_warped.
