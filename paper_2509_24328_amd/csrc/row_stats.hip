@@ -713,7 +713,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
 // per lane, 512 lanes.  Sweep 2 is then a multiplication, a minimum and an addition per entry,
 //     min(P_d, P_c) = f min(e_d, e_c g),  f = 2^(c_d - C_d) / s_d,  g = 2^((c_c - C_c) - (c_d - C_d)) s_d / s_c
 // where the other kernels unpack both logits and take an exponential: 14 operations per entry pair in all, 19 there.  The
-// references c are whole numbers, so that every power of two is exact, the lane's own at the time of the vector; C and s are
+// references c are the lane's own at the time of the vector (whole numbers: every power of two is exact); C and s are
 // the row's.  No logarithm stands between the sweeps: what the results need of a pair is put aside in LDS, and at the
 // end a lane per pair forms the normalisers' logarithms and A.
 // A pass over the places is sweep 2 of a pair, sweep 1 of the next one into the registers that it leaves, and the loads of the one
@@ -724,19 +724,10 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
 constexpr int kTermThreads = 512, kTermRecords = 512;
 
 struct TermRecord {
-  double s[2], S;      // sums of the rows relative to the whole-numbered reference, S times the draft's
+  double s[2], S;      // sums of the rows, S times the draft's
   float m[2], zx[2];   // maxima, logits of the drafted token
   int tok;
 };
-
-__device__ __forceinline__ float whole_ref(float m, const float L) { return __builtin_ceilf(ref_of(m, L)); }
-// (m, s) over the whole-numbered reference, as the other kernels hand it on: relative to c(m)
-__device__ __forceinline__ MS ms_of_whole(float m, double s, const float L) {
-  MS r;
-  r.m = m;
-  r.s = s * exp2((double)(whole_ref(m, L) - ref_of(m, L)));
-  return r;
-}
 
 // A word at a uniform address that nothing writes during the kernel, through the scalar cache: vector loads are waited for in
 // order, and such a word would be waited for with the whole pair that is in flight.
@@ -745,24 +736,7 @@ __device__ __forceinline__ T load_scalar(const T* p) {
   return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
 }
 
-// Several values reduced at once, each in lanes of its own from the first step on: halves of a wavefront are exchanged
-// between two registers (v_permlane32_swap: lanes 0-31 of `a` meet lanes 32-63 of `a`, the same for `b` in the upper half),
-// then rows of 16 lanes.
-struct Halves { uint32_t a, b; };
-__device__ __forceinline__ Halves swap32(uint32_t a, uint32_t b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  return {r[0], r[1]};
-}
-__device__ __forceinline__ Halves swap16(uint32_t a, uint32_t b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  return {r[0], r[1]};
-}
-template <class Swap>
-__device__ __forceinline__ double swap_add(double a, double b, Swap&& swap) {
-  const Halves lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
-  return __hiloint2double(hi.a, lo.a) + __hiloint2double(hi.b, lo.b);
-}
-// Rows 0 to 3 of 16 lanes: sums of a, m, b, m in their lanes 15.
+// Sums of a, m, b and m in lanes 15, 31, 47 and 63 (see swap32).
 __device__ __forceinline__ double wave_sum3_f64(double a, double b, double m) {
   const double ab = swap_add(a, b, swap32), mm = swap_add(m, m, swap32);
   return row16_sum_f64(swap_add(ab, mm, swap16));
@@ -841,7 +815,7 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     return q;
   };
   // sweep 1 of a vector: its terms, and the lane's running (max, reference, sum)
-  struct Run { float m = -INFINITY, c = kRefFloor, s = 0.f; };
+  struct Run { float m = -INFINITY, c = kRefFloor; double s = 0.0; };
   auto form_terms = [&](Run& o, const u32x4& q, float (&e)[EPV], float& ref, const float L, const float cut) {
     float z[EPV];
     unpack<DT>(q, z);
@@ -852,18 +826,18 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     float mx = o.m;
 #pragma unroll
     for (int i = 0; i < EPV; i += 2) mx = fmaxf(fmaxf(mx, z[i]), z[i + 1]);
-    const float c = whole_ref(mx, L);
+    const float c = ref_of(mx, L);
 #pragma unroll
     for (int i = 0; i < EPV; ++i) e[i] = exp2_fast(__builtin_fmaf(z[i], L, -c));
-    float t[EPV / 2];
+    float t[EPV];
 #pragma unroll
-    for (int i = 0; i < EPV / 2; ++i) t[i] = e[i] + e[i + EPV / 2];
+    for (int i = 0; i < EPV; ++i) t[i] = e[i];
 #pragma unroll
-    for (int h = EPV / 4; h >= 1; h /= 2) {
+    for (int h = 1; h < EPV; h *= 2) {                 // (the tree of OnlineOf::add: equal vectors have equal sums)
 #pragma unroll
-      for (int i = 0; i < h; ++i) t[i] += t[i + h];
+      for (int i = 0; i < EPV; i += 2 * h) t[i] += t[i + h];
     }
-    o.s = __builtin_fmaf(o.s, exp2_fast(o.c - c), t[0]);
+    o.s = OnlineWide::scaled(o.s, exp2_fast(o.c - c), t[0]);
     o.m = mx;
     o.c = ref = c;
     asm volatile("" : "+v"(o.s));                      // the terms are formed here, not where sweep 2 needs them
@@ -943,9 +917,9 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     const float L = half ? Lc : Ld;
     {
       const int key = wave_max2_i32(order_key(od.m), order_key(oc.m));
-      const float ref = whole_ref(from_order_key(key), L);
-      const double sums = wave_sum3_f64((double)od.s * (double)exp2_fast(od.c - lane_f32(ref, 0)),
-                                        (double)oc.s * (double)exp2_fast(oc.c - lane_f32(ref, 32)), (double)acc);
+      const float ref = ref_of(from_order_key(key), L);
+      const double sums = wave_sum3_f64(od.s * (double)exp2_fast(od.c - lane_f32(ref, 0)),
+                                        oc.s * (double)exp2_fast(oc.c - lane_f32(ref, 32)), (double)acc);
       if (w == 15) {
         part_s[turn][row][wave] = sums;
         part_m[turn][half][wave] = key;
@@ -955,8 +929,8 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     // every wavefront folds the partials, a row of 16 lanes each: the draft's, the minima's, the companion's
     const float mw = from_order_key(part_m[turn][half][w & (kWaves - 1)]);
     const double sw = w < kWaves ? part_s[turn][row][w & (kWaves - 1)] : 0.0;
-    const float m = row16_max_all_f32(mw), ref = whole_ref(m, L);
-    const double s = row16_sum_f64(row & 1 ? sw : sw * (double)exp2_fast(whole_ref(mw, L) - ref));
+    const float m = row16_max_all_f32(mw), ref = ref_of(m, L);
+    const double s = row16_sum_f64(row & 1 ? sw : sw * (double)exp2_fast(ref_of(mw, L) - ref));
     C[0] = lane_f32(ref, 15);
     C[1] = lane_f32(ref, 47);
     {
@@ -1001,7 +975,7 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
   if (tid >= done) return;
   const TermRecord& r = rec[tid];
   const int pair = blockIdx.x + tid * gridDim.x;
-  const MS md = ms_of_whole(r.m[0], r.s[0], Ld), mc = ms_of_whole(r.m[1], r.s[1], Lc);
+  const MS md = {r.m[0], r.s[0]}, mc = {r.m[1], r.s[1]};
   PairConsts pc;
   pc.lse[0] = lse_from_ms(md, sc_d);
   pc.lse[1] = lse_from_ms(mc, sc_c);

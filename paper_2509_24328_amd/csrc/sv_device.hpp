@@ -6,13 +6,18 @@
 //  * Philox-4x32-10 for the speculative-sampling uniforms
 //
 // A row's normaliser is carried as the pair (m, s): m = the row maximum in raw
-// logit units and s = sum_v 2^(z_v * L - c(m)), c(m) = max(fl32(m * L), -2^30),
+// logit units and s = sum_v 2^(z_v * L - c(m)), c(m) = ceil(max(fl32(m * L), -2^30)),
 // where L is log2(e) / T rounded to fp32 (T = sampling temperature of the
 // tensor, 1 unless a warped entry point says otherwise; L32 is the T = 1 value).
 // Because L T / log2(e) = 1 + tau1 with |tau1| < 6e-8 (1.33e-8 for L32) the sum
 // is the soft-max normaliser at a temperature off by that factor; the fp64
 // epilogue removes the first-order effect around the row maximum
 // (lse_from_ms), leaving an error below |tau1| * (H - H_inf) of the row.
+//
+// References are whole numbers, so that every change of reference scales a sum exactly and an entry's term has the same
+// mantissa whatever lane, workgroup or kernel forms it: the normalisers of equal rows differ by the roundings of the additions
+// alone.  (Over c(m) = fl32(m * L) the terms themselves differed by 1e-8 in the mean from lane to lane: a residual of two
+// equal rows, whose normalisers two kernels had formed, was found to have mass.)
 //
 // Range of the logits.  2^(z L - c) is formed with one fused multiply-add, so it
 // is right for any z as long as the part of m * L that fp32 drops from c stays a
@@ -121,23 +126,19 @@ __device__ __forceinline__ void unpack(const u32x4& q, float (&f)[Elem<DT>::per_
 // ---------------------------------------------------------------------------
 // online (max, sum 2^(z L - c)) accumulator, one per lane
 //   Online      fp32 sum
-//   OnlineWide  fp64 sum over a reference that is a whole number, so that raising it scales the sum exactly: nothing in it grows with the
-//               number of entries.  Millions of equal terms, which round the same way in every lane, leave an
+//   OnlineWide  fp64 sum: nothing in it grows with the number of entries.  Millions of equal terms, which round the same way in every lane, leave an
 //               fp32 sum 1.4e-6 off at 2^18 entries and 2e-5 at 2^22.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ float ref_of(float m, const float L = kL32) { return __builtin_ceilf(fmaxf(m * L, kRefFloor)); }
+
 template <class Sum>
 struct OnlineOf {
-  static constexpr bool kWide = sizeof(Sum) == 8;
   float m;   // running maximum (raw units); -inf before the first element
-  float c;   // max(fl32(m * L), kRefFloor), for the wide sum rounded up to a whole number
+  float c;   // c(m)
   Sum s;     // sum of 2^(z*L - c) so far
 
   __device__ __forceinline__ void init() { m = -INFINITY; c = kRefFloor; s = 0; }
 
-  static __device__ __forceinline__ float ref(float mx, const float L) {
-    const float r = fmaxf(mx * L, kRefFloor);
-    return kWide ? __builtin_ceilf(r) : r;
-  }
   static __device__ __forceinline__ float scaled(float s, float scale, float t) { return __builtin_fmaf(s, scale, t); }
   static __device__ __forceinline__ double scaled(double s, float scale, float t) {
     return __builtin_fma(s, (double)scale, (double)t);
@@ -149,7 +150,7 @@ struct OnlineOf {
 #pragma unroll
     for (int j = 0; j + 1 < N; j += 2) mx = fmaxf(fmaxf(mx, z[j]), z[j + 1]);   // v_max3_f32
     if (N & 1) mx = fmaxf(mx, z[N - 1]);
-    const float cn = ref(mx, L);
+    const float cn = ref_of(mx, L);
     const float scale = exp2_fast(c - cn);
     float e[N];
 #pragma unroll
@@ -174,7 +175,7 @@ struct OnlineOf {
 
   __device__ __forceinline__ void add1(float z, const float L = kL32) {
     const float mx = fmaxf(m, z);
-    const float cn = ref(mx, L);
+    const float cn = ref_of(mx, L);
     s = scaled(s, exp2_fast(c - cn), exp2_fast(__builtin_fmaf(z, L, -cn)));
     m = mx;
     c = cn;
@@ -196,8 +197,6 @@ struct MS {
   float m;
   double s;
 };
-
-__device__ __forceinline__ float ref_of(float m, const float L = kL32) { return fmaxf(m * L, kRefFloor); }
 
 // ---------------------------------------------------------------------------
 // Wavefront reductions and scans on the DPP lane network: a step is a register move inside the
@@ -257,6 +256,23 @@ __device__ __forceinline__ float row16_max_all_f32(float v) {
   return dpp_max_f32<kDppRor8, 0xf>(v);
 }
 
+// Several values reduced at once, each in lanes of its own from the first step on: halves of a wavefront are exchanged
+// between two registers (v_permlane32_swap: lanes 0-31 of `a` meet lanes 32-63 of `a`, the same for `b` in the upper half),
+// then rows of 16 lanes.
+struct Halves { uint32_t a, b; };
+__device__ __forceinline__ Halves swap32(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return {r[0], r[1]};
+}
+__device__ __forceinline__ Halves swap16(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  return {r[0], r[1]};
+}
+template <class Swap>
+__device__ __forceinline__ double swap_add(double a, double b, Swap&& swap) {
+  const Halves lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
+  return __hiloint2double(hi.a, lo.a) + __hiloint2double(hi.b, lo.b);
+}
 // Value of one lane (a constant or wavefront-uniform index) in every lane.
 __device__ __forceinline__ double lane_f64(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
