@@ -107,8 +107,8 @@ enum {
   SV_KERNEL_ACCEPT_ESTIMATE = 1,
   SV_KERNEL_SELECT_LENGTH = 2,
   SV_KERNEL_VERIFY_ROWS = 3,    /* first kernel of sv_verify_sample: row normalisers          */
-  SV_KERNEL_VERIFY_MASS = 4,    /* second: accept decision, granule masses of the sampled row  */
-  SV_KERNEL_VERIFY_PICK = 5,    /* third: scan of the granule masses, prefix scan, token       */
+  SV_KERNEL_VERIFY_MASS = 4,    /* second: accept decision, granule masses of the sampled row; of short rows the token too */
+  SV_KERNEL_VERIFY_PICK = 5,    /* third: scan of the granule masses, prefix scan, token (nothing of short rows) */
   SV_KERNEL_COUNT = 6
 };
 

@@ -273,6 +273,11 @@ __device__ __forceinline__ double swap_add(double a, double b, Swap&& swap) {
   const Halves lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
   return __hiloint2double(hi.a, lo.a) + __hiloint2double(hi.b, lo.b);
 }
+// Sums of four values in lanes 15, 31, 47 and 63.
+__device__ __forceinline__ double wave_sum4_f64(double a, double b, double c, double d) {
+  return row16_sum_f64(swap_add(swap_add(a, c, swap32), swap_add(b, d, swap32), swap16));
+}
+
 // Value of one lane (a constant or wavefront-uniform index) in every lane.
 __device__ __forceinline__ double lane_f64(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),

@@ -2,7 +2,7 @@
 // prefix of every sequence (Sec. 4.2 last paragraph of the SV paper; the
 // accept / residual / bonus rule is the standard speculative-sampling one).
 //
-// Three kernels on the caller's stream:
+// Three kernels on the caller's stream, or two where a workgroup can hold a sequence's sampling row (4 instead of 2 and 3):
 //
 //  1. verify_rows_kernel   1..8 workgroups per logit row that the step needs
 //     (target rows 0..gamma_b, draft rows 0..gamma_b-1 of every sequence).
@@ -27,6 +27,9 @@
 //     in order (fp64), locates the granule holding u' * W, weighs its 4096
 //     entries again, 16 consecutive ones per lane in registers, and finds the
 //     token with a prefix scan.
+//
+//  4. verify_draw_kernel   one workgroup per sequence: what 2 and 3 do, with the weights kept in registers
+//     in between.
 //
 // Kernel boundaries carry the cross-workgroup hand-offs (row scalars, plan,
 // chunk masses): device-scope fences inside a kernel were measured to cost far
@@ -720,6 +723,155 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
   SV_PHASE_MARK(5)
 }
 
+// grid (B), rows of up to 4096 J entries: the accept decision, the weights of the sampling row and the token in one
+// kernel.  Lane l of wavefront w holds the weights of entries [512 (w J + j) + 8 l, + 8) for j < J: the 512 entries of a (w, j) are a
+// run, the runs are in order, and once their masses are known the wavefront that holds the token's run finds it
+// among its registers, where the pick kernel reads and weighs a granule again.  Bound by latency (the decision, one trip to
+// memory, two reductions: 8 x 4096 bf16 9.0 us with the row sweep, 12.8 in two kernels) and, on the longest rows, by
+// the arithmetic of a row pair on one compute unit (4 us of 32000 entries).
+template <int DT, bool CUT, bool CHAIN, int THREADS, int J>
+__global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
+  constexpr int EPV = Elem<DT>::per_vec, kEach = 8, kVecs = kEach / EPV, kWaves = THREADS / kWave;
+  constexpr int kRuns = kWaves * J;
+  static_assert(kRuns <= kWave, "a lane for every run");
+  constexpr uint32_t kNegInfWord = (DT == DT_BF16) ? 0xFF80FF80u : 0xFF800000u;
+  __shared__ Plan plan;
+  __shared__ double run_mass[kWave];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (wave == 0) accept_plan<DT, CHAIN>(a, b, tid, true, &plan);
+  if (tid < kWave) run_mass[tid] = 0.0;
+  __syncthreads();
+  const Plan pl = plan;
+  uint32_t flags = pl.flags;
+  if (!pl.target_ok) {
+    if (tid == 0) a.flags[b] = flags | SV_FLAG_BAD_ROW;
+    return;
+  }
+  SampleRow<DT, CUT> sr(a, b, pl);
+  const int V = a.V, groups = (V + kEach - 1) / kEach;
+  float w[J][kEach];
+  auto group_of = [&](int j) { return (wave * J + j) * kWave + lane; };
+  // (a row's last group is its last eight entries: those that belong to the group before are masked out)
+  auto fetch = [&](const void* row, u32x4 (&q)[J][kVecs]) {
+    const u32x4 neg = {kNegInfWord, kNegInfWord, kNegInfWord, kNegInfWord};
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int i = 0; i < kVecs; ++i) {
+        q[j][i] = neg;
+        if (group_of(j) < groups)
+          q[j][i] = load_vec(static_cast<const char*>(row) + (size_t)min(group_of(j) * kEach, V - kEach) * Elem<DT>::bytes, i);
+      }
+    if (V % kEach != 0 && (groups - 1) / (kWave * J) == wave) {             // (uniform)
+      const int twice = kEach - V % kEach;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (group_of(j) == groups - 1) {
+#pragma unroll
+          for (int i = 0; i < kVecs; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              uint32_t z = q[j][i][e];
+              if constexpr (DT == DT_F32) {
+                z = twice > 4 * i + e ? kNegInfWord : z;
+              } else {
+                z = twice > 2 * e ? (z & 0xffff0000u) | 0xFF80u : z;
+                z = twice > 2 * e + 1 ? (z & 0xffffu) | 0xFF800000u : z;
+              }
+              q[j][i][e] = z;
+            }
+        }
+    }
+  };
+  auto weigh = [&](auto small, auto residual) {
+    constexpr bool kSmall = decltype(small)::value, RESID = decltype(residual)::value;
+    u32x4 qt[J][kVecs], qd[J][kVecs];
+    fetch(sr.row_t, qt);
+    if (RESID) fetch(sr.row_d, qd);
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int i = 0; i < kVecs; ++i) {
+        float ft[EPV], fd[EPV];
+        unpack<DT>(qt[j][i], ft);
+        if (RESID) unpack<DT>(qd[j][i], fd);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+          const float wt = sr.template weight_t<kSmall>(ft[e]);
+          w[j][i * EPV + e] = RESID ? sr.template weight_r<kSmall>(wt, fd[e]) : wt;
+        }
+      }
+  };
+  double incl, W;
+  for (;;) {
+    if (sr.small) { if (sr.resid) weigh(std::true_type(), std::true_type()); else weigh(std::true_type(), std::false_type()); }
+    else { if (sr.resid) weigh(std::false_type(), std::true_type()); else weigh(std::false_type(), std::false_type()); }
+    double mine[(J + 3) / 4 * 4] = {};
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+      for (int i = 0; i < kEach; ++i) mine[j] += (double)w[j][i];
+#pragma unroll
+    for (int j = 0; j < J; j += 4) {
+      const double t = wave_sum4_f64(mine[j], mine[j + 1], mine[j + 2], mine[j + 3]);
+      if ((lane & 15) == 15 && j + lane / 16 < J) run_mass[wave * J + j + lane / 16] = t;
+    }
+    __syncthreads();
+    incl = wave_scan_f64(run_mass[lane]);
+    W = lane_f64(incl, kWave - 1);
+    if (!sr.resid || W > 0.0) break;
+    // a residual of any mass is drawn from; only one without mass is not: the target distribution instead
+    sr.resid = false;
+    sr.small = sr.pt.small;
+    flags |= SV_FLAG_RESIDUAL_FALLBACK;
+    __syncthreads();
+  }
+  if (!(isfinite(W) && W > 0.0)) {                     // nothing can be drawn
+    if (tid == 0) a.flags[b] = flags | SV_FLAG_BAD_ROW;
+    return;
+  }
+  const double tau = unit_from_word(pl.random) * W;
+  const double mass = run_mass[lane];
+  const unsigned long long at = __ballot(incl > tau && mass > 0.0), has = __ballot(mass > 0.0);
+  const int run = __builtin_amdgcn_readfirstlane(at ? (int)__builtin_ctzll(at) : 63 - (int)__builtin_clzll(has));
+  if (run / J != wave) return;
+  const double tau_local = tau - lane_f64(incl - mass, run);                // threshold inside the run
+  float mine[kEach];
+#pragma unroll
+  for (int j = 0; j < J; ++j)
+    if (run % J == j) {
+#pragma unroll
+      for (int i = 0; i < kEach; ++i) mine[i] = w[j][i];
+    }
+  double sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < kEach; ++i) sum += (double)mine[i];
+  const double upto = wave_scan_f64(sum);
+  const unsigned long long pass = __ballot(upto > tau_local), any = __ballot(sum > 0.0);
+  // the first lane whose inclusive sum passes the threshold owns the token (rounding between the masses and the scan: the last
+  // lane with weight)
+  if (lane != (pass ? (int)__builtin_ctzll(pass) : 63 - (int)__builtin_clzll(any))) return;
+  double acc = upto - sum, prev = acc, next = acc;
+  int y = -1, last = -1;
+#pragma unroll
+  for (int i = 0; i < kEach; ++i) {
+    const int v = min((run * kWave + lane) * kEach, V - kEach) + i;
+    acc += (double)mine[i];
+    if (mine[i] > 0.f) last = v;
+    if (pass && y < 0 && acc > tau_local) { y = v; next = acc; }
+    if (y < 0) prev = acc;
+  }
+  if (y < 0) {                                         // rounding between the lane's own sum and its place in the scan
+    y = last;
+    flags |= SV_FLAG_NEAR_CDF_EDGE;
+  } else if (fmin(next - tau_local, tau_local - prev) < kCdfEdgeRel * W + kCdfEdgeAbs) {
+    flags |= SV_FLAG_NEAR_CDF_EDGE;
+  }
+  if (y >= 0) a.out_tokens[(size_t)b * (a.k + 1) + pl.n] = y; else flags |= SV_FLAG_BAD_ROW;
+  a.flags[b] = flags;
+}
+
 // Workgroups per row: enough of them to spread the rows evenly over the CUs
 // (1088 rows on 256 CUs leave some CUs a fifth more work than others) and to keep
 // small batches from leaving CUs idle, but never parts shorter than 4096 entries.
@@ -738,6 +890,18 @@ static int rows_split(int rows, int V) {
 // one up to 256 pairs, 0.9 in the mean (from 0.25 for two) up to 512.
 static int wide_groups(int dtype, int granules) { return dtype == DT_F32 || granules == 1 ? 512 : 256; }
 
+// One kernel for decision, masses and token (verify_draw_kernel), or two that spread a sequence over workgroups?  One saves a launch
+// and its loads; a workgroup alone pays for the arithmetic of a long row.  us of the call, two kernels / one: 8 x 4096 bf16
+// 12.8 / 9.0; 512 x 4096 19.4 / 14.9; 8 x 8192 12.8 / 9.7; 2048 x 8192 57.7 / 57.3; 8 x 16384 12.8 / 10.9; 2048 x 16384 104 / 95;
+// fp32, 8 x 16384 13.2 / 11.4, 1024 x 16384 92.3 / 90.0, 2048 x 16384 171.4 / 172.9.  Above, with 1024 lanes to a
+// sequence, for 33 to 512 sequences: 8 x 32000 13.4 / 13.9; 64 x 32000 20.3 / 18.8; 256 x 32000 37.7 / 33.5; 512 x 32000 57.3 /
+// 54.5; 1024 x 32000 94.6 / 96.1; fp32, 256 x 32000 48.1 / 43.8.  (Less than eight entries: two kernels.)
+static bool draws_at_once(int dtype, int B, int V) {
+  if (V < 8 || V > 8 * kGranule) return false;
+  if (V > 4 * kGranule) return B > 32 && B <= 512;
+  return V <= 2 * kGranule || dtype == DT_BF16 || B <= 1024;
+}
+
 template <int DT, bool CUT>
 static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   const int rows = a.B * (a.chained ? a.k + 1 : 2 * a.k + 1);
@@ -747,6 +911,24 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;
   const int C = n_chunks(a.V);
+  if (draws_at_once(DT, a.B, a.V)) {
+    {
+      TapScope tap(SV_KERNEL_VERIFY_MASS, st);
+      auto draw = [&](auto threads, auto runs) {
+        constexpr int T = decltype(threads)::value, J = decltype(runs)::value;
+        if (a.chained) hipLaunchKernelGGL((verify_draw_kernel<DT, CUT, true, T, J>), dim3(a.B), dim3(T), 0, st, a);
+        else hipLaunchKernelGGL((verify_draw_kernel<DT, CUT, false, T, J>), dim3(a.B), dim3(T), 0, st, a);
+      };
+      using std::integral_constant;
+      if (a.V <= kGranule) draw(integral_constant<int, 512>(), integral_constant<int, 1>());
+      else if (a.V <= 2 * kGranule) draw(integral_constant<int, 512>(), integral_constant<int, 2>());
+      else if (a.V > 4 * kGranule) draw(integral_constant<int, 1024>(), integral_constant<int, 4>());
+      else if constexpr (DT == DT_F32) draw(integral_constant<int, 1024>(), integral_constant<int, 2>());
+      else draw(integral_constant<int, 512>(), integral_constant<int, 4>());
+    }
+    TapScope tap(SV_KERNEL_VERIFY_PICK, st);           // (nothing is left to it)
+    return launch_status();
+  }
   {
     TapScope tap(SV_KERNEL_VERIFY_MASS, st);
     auto launch = [&](auto* kernel, int groups, int threads) {
