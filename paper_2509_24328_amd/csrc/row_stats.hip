@@ -20,8 +20,8 @@
 //   row_stats_loop_kernel    workgroups that fill the chip once and walk through the pairs: the places that
 //                            sweep 2 of a pair leaves take the next pair's loads
 //   row_stats_stash_kernel   a workgroup per pair: few pairs, or a few more than compute units, of rows that do not stay on
-//                            chip; very many pairs of rows a little too long for the terms kernel; short rows with KL
-//   row_stats_terms_kernel   short rows, without KL: sweep 1 keeps its exponentials in registers, and sweep 2 needs no others
+//                            chip; very short rows and very many pairs of short ones, with KL or cutoffs
+//   row_stats_terms_kernel   short plain rows: sweep 1 keeps its exponentials in registers, and sweep 2 needs no others
 // Algorithmic HBM traffic: 2 * V * elem_size bytes per pair.
 #include <algorithm>
 #include <type_traits>
@@ -255,7 +255,7 @@ __device__ __forceinline__ void publish_consts(const MergeScratch<2>& mg, int wa
   const MS ms = fold_waves_row16(mg.m[r], mg.s[r], waves, sc.L);
   if (threadIdx.x == kLaneDraft || threadIdx.x == kLaneCompanion) {
     pc.lse[r] = lse_from_ms(ms, sc);
-    pc.kappa[r] = kappa_l32(ms, sc.L);
+    pc.kappa[r] = kappa_l32(ms);
     pc.zx[r] = zx;
     if (r == 0) { a.chain_m[pair] = ms.m; a.chain_s[pair] = ms.s; }
   }
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
 // per lane, 512 lanes.  Sweep 2 is then a multiplication, a minimum and an addition per entry,
 //     min(P_d, P_c) = f min(e_d, e_c g),  f = 2^(c_d - C_d) / s_d,  g = 2^((c_c - C_c) - (c_d - C_d)) s_d / s_c
 // where the other kernels unpack both logits and take an exponential: 14 operations per entry pair in all, 19 there.  The
-// references c are the lane's own at the time of the vector (whole numbers: every power of two is exact); C and s are
+// references c are whole numbers, so that every power of two is exact, the lane's own at the time of the vector; C and s are
 // the row's.  No logarithm stands between the sweeps: what the results need of a pair is put aside in LDS, and at the
 // end a lane per pair forms the normalisers' logarithms and A.
 // A pass over the places is sweep 2 of a pair, sweep 1 of the next one into the registers that it leaves, and the loads of the one
@@ -724,7 +724,7 @@ __global__ __launch_bounds__(Shape::threads, Shape::waves) void row_stats_loop_k
 constexpr int kTermThreads = 512, kTermRecords = 512;
 
 struct TermRecord {
-  double s[2], S;      // sums of the rows, S times the draft's
+  double s[2], S;      // sums of the rows relative to the whole-numbered reference, S times the draft's
   float m[2], zx[2];   // maxima, logits of the drafted token
   int tok;
 };
@@ -772,7 +772,7 @@ constexpr int terms_per_cu() {
   return regs <= 80 ? 3 : regs <= 128 ? 2 : 1;
 }
 
-template <int DT, bool WARP, int P, bool ONE>
+template <int DT, int P, bool ONE>
 __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) void row_stats_terms_kernel(StatsArgs a) {
   constexpr int EPV = Elem<DT>::per_vec, nt = kTermThreads, kWaves = nt / kWave;
   constexpr int kEnds = DT == DT_F32 ? 4 : 2;          // places that a row may end in or before
@@ -784,8 +784,6 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
   const int half = lane >> 5;                          // of the wavefront: draft, companion
   const int pairs = a.B * a.k;
   int row_bytes = a.V * Elem<DT>::bytes;
-  const Scale sc_d = WARP ? a.sc_d : unit_scale(), sc_c = WARP ? a.sc_c : unit_scale();
-  const float Ld = sc_d.L, Lc = sc_c.L;
 
   float ed[P][EPV], ec[P][EPV], refd[P], refc[P];      // terms and references of the pair of sweep 2
   u32x4 qd[P], qc[P];                                  // the pair in flight
@@ -816,19 +814,15 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
   };
   // sweep 1 of a vector: its terms, and the lane's running (max, reference, sum)
   struct Run { float m = -INFINITY, c = kRefFloor; double s = 0.0; };
-  auto form_terms = [&](Run& o, const u32x4& q, float (&e)[EPV], float& ref, const float L, const float cut) {
+  auto form_terms = [&](Run& o, const u32x4& q, float (&e)[EPV], float& ref) {
     float z[EPV];
     unpack<DT>(q, z);
-    if (WARP) {
-#pragma unroll
-      for (int i = 0; i < EPV; ++i) z[i] = cut_below(z[i], cut);
-    }
     float mx = o.m;
 #pragma unroll
     for (int i = 0; i < EPV; i += 2) mx = fmaxf(fmaxf(mx, z[i]), z[i + 1]);
-    const float c = ref_of(mx, L);
+    const float c = whole_ref(mx);
 #pragma unroll
-    for (int i = 0; i < EPV; ++i) e[i] = exp2_fast(__builtin_fmaf(z[i], L, -c));
+    for (int i = 0; i < EPV; ++i) e[i] = exp2_fast(__builtin_fmaf(z[i], kL32, -c));
     float t[EPV];
 #pragma unroll
     for (int i = 0; i < EPV; ++i) t[i] = e[i];
@@ -882,9 +876,6 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     // (nothing derived from these is kept over the passes)
     asm volatile("" : "+s"(row_bytes));
     asm volatile("" : "+v"(tid));
-    float cut_d = -INFINITY, cut_c = -INFINITY;
-    if (WARP && a.cut_d) cut_d = load_scalar(a.cut_d + next);
-    if (WARP && a.cut_c) cut_c = load_scalar(a.cut_c + next);
     // the drafted token's logits, by every lane (a load under a condition would make the waits for the rows coarse)
     const int tok = load_scalar(a.x + next);
     const float zx = load_elem<DT>(row_at(half ? a.z_c : a.z_d, next), min(max(tok, 0), a.V - 1));
@@ -905,19 +896,18 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
           qc[j] = masked(qc[j], j);
         }
         __builtin_amdgcn_sched_barrier(0);
-        form_terms(od, qd[j], ed[j], refd[j], Ld, cut_d);
+        form_terms(od, qd[j], ed[j], refd[j]);
         __builtin_amdgcn_sched_barrier(0);
-        form_terms(oc, qc[j], ec[j], refc[j], Lc, cut_c);
+        form_terms(oc, qc[j], ec[j], refc[j]);
       }
       __builtin_amdgcn_sched_barrier(0);
       if (MORE) load_pair(rd, rc, j);
       __builtin_amdgcn_sched_barrier(0);
     }
     const int row = lane >> 4, w = lane & 15;
-    const float L = half ? Lc : Ld;
     {
       const int key = wave_max2_i32(order_key(od.m), order_key(oc.m));
-      const float ref = ref_of(from_order_key(key), L);
+      const float ref = whole_ref(from_order_key(key));
       const double sums = wave_sum3_f64(od.s * (double)exp2_fast(od.c - lane_f32(ref, 0)),
                                         oc.s * (double)exp2_fast(oc.c - lane_f32(ref, 32)), (double)acc);
       if (w == 15) {
@@ -929,8 +919,8 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
     // every wavefront folds the partials, a row of 16 lanes each: the draft's, the minima's, the companion's
     const float mw = from_order_key(part_m[turn][half][w & (kWaves - 1)]);
     const double sw = w < kWaves ? part_s[turn][row][w & (kWaves - 1)] : 0.0;
-    const float m = row16_max_all_f32(mw), ref = ref_of(m, L);
-    const double s = row16_sum_f64(row & 1 ? sw : sw * (double)exp2_fast(ref_of(mw, L) - ref));
+    const float m = row16_max_all_f32(mw), ref = whole_ref(m);
+    const double s = row16_sum_f64(row & 1 ? sw : sw * (double)exp2_fast(whole_ref(mw) - ref));
     C[0] = lane_f32(ref, 15);
     C[1] = lane_f32(ref, 47);
     {
@@ -946,7 +936,7 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
         TermRecord& to = rec[done];
         to.m[half] = m;
         to.s[half] = s;
-        to.zx[half] = tok < 0 || tok >= a.V ? __builtin_nanf("") : WARP ? cut_below(zx, half ? cut_c : cut_d) : zx;
+        to.zx[half] = tok < 0 || tok >= a.V ? __builtin_nanf("") : zx;
         to.tok = tok;
       }
     }
@@ -975,16 +965,16 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
   if (tid >= done) return;
   const TermRecord& r = rec[tid];
   const int pair = blockIdx.x + tid * gridDim.x;
-  const MS md = {r.m[0], r.s[0]}, mc = {r.m[1], r.s[1]};
+  const MS md = {r.m[0], r.s[0], whole_ref(r.m[0])}, mc = {r.m[1], r.s[1], whole_ref(r.m[1])};
   PairConsts pc;
-  pc.lse[0] = lse_from_ms(md, sc_d);
-  pc.lse[1] = lse_from_ms(mc, sc_c);
+  pc.lse[0] = lse_from_ms(md);
+  pc.lse[1] = lse_from_ms(mc);
   pc.kappa[0] = pc.kappa[1] = 0.0;
   pc.zx[0] = r.zx[0];
   pc.zx[1] = r.zx[1];
   a.chain_m[pair] = md.m;
-  a.chain_s[pair] = md.s;
-  stats_epilogue<false, WARP, true>(a, pair, pc, r.tok, (tid == done - 1 ? S_last : r.S) / r.s[0], 0.0, 0.0, 0.0);
+  a.chain_s[pair] = md.s * exp2((double)(md.ref - ref_of(md.m)));         // (relative to c(m), as the other kernels leave it)
+  stats_epilogue<false, false, true>(a, pair, pc, r.tok, (tid == done - 1 ? S_last : r.S) / r.s[0], 0.0, 0.0, 0.0);
 }
 
 // More than 64 KB of dynamic LDS has to be allowed once per kernel and device.
@@ -1018,16 +1008,16 @@ static int launch_loop(const StatsArgs& a, hipStream_t st) {
                        Shape::threads, 2 * (size_t)Shape::lds_vecs * 16, a, st);
 }
 
-template <int DT, bool WARP, int P, bool ONLY_ONE = false>
+template <int DT, int P, bool ONLY_ONE = false>
 static int launch_terms(const StatsArgs& a, hipStream_t st) {
   const int pairs = a.B * a.k;
   const dim3 threads(kTermThreads);
   TapScope tap(SV_KERNEL_ROW_STATS, st);
   if (ONLY_ONE || pairs <= 256 * terms_per_cu<DT, P, true>()) {
-    hipLaunchKernelGGL((row_stats_terms_kernel<DT, WARP, P, true>), dim3(pairs), threads, 0, st, a);
+    hipLaunchKernelGGL((row_stats_terms_kernel<DT, P, true>), dim3(pairs), threads, 0, st, a);
   } else if constexpr (!ONLY_ONE) {
     const int fill = 256 * terms_per_cu<DT, P, false>(), groups = std::min(pairs, std::max(fill, (pairs + kTermRecords - 1) / kTermRecords));
-    hipLaunchKernelGGL((row_stats_terms_kernel<DT, WARP, P, false>), dim3(groups), threads, 0, st, a);
+    hipLaunchKernelGGL((row_stats_terms_kernel<DT, P, false>), dim3(groups), threads, 0, st, a);
   }
   return launch_status();
 }
@@ -1048,45 +1038,42 @@ static int launch_terms(const StatsArgs& a, hipStream_t st) {
 //  * few_more: a few pairs more than CUs, of rows that do not stay on chip: a CU that has two takes longer one after the other than
 //    side by side.  Loop / three / two: 300 x 256512 111 / 105 / 104; under cutoffs 257 x 140000 69.2 / 66.3 / 69.5; fp32, 300 x 30000
 //    22.3 / 19.8 / 22.9, 300 x 50400 32.5 / 32.9 / 29.7, 341 x 58000 38.1 / 41.5 / 36.7.
-//  * Ahead of all of these, without KL, the terms kernel wherever the terms of a pair and the pair in flight fit a lane's
-//    registers (bf16 up to 32768 entries; fp32 14336, 24576 in part), or the terms alone where there is a pair per compute unit
-//    at most (49152; 40960).  The better one of the others / terms, bf16: 64 x 1000 5.1 / 4.3; 64 x 32000 9.4 / 8.5; 512 x 32000
-//    18.4 / 17.8; 2048 x 8192 23.1 / 17.7; 8192 x 16384 114 / 91; 8192 x 32000 202 / 166.5 (6.3 TB/s); under cutoffs 8192 x 32000 231 /
-//    182; 256 x 40960 13.8 / 11.7.  fp32: 64 x 14000 8.1 / 7.1; 2048 x 4096 20.1 / 15.9; 8192 x 10000 113 / 105; 256 x 32000 15.4 /
-//    15.3; under cutoffs 2048 x 20000 59.1 / 55.1.  Where it is not taken: fp32 768 x 16384 19.6 / 20.0, 300 x 20000 15.3 / 16.2, 64 x
-//    49152 13.8 / 14.6, 600 x 1000 7.0 / 7.3.
+//  * Ahead of all of these, for plain rows (no KL, no warps), the terms kernel wherever the terms of a pair and the pair in flight
+//    fit a lane's registers (bf16 up to 32768 entries; fp32 14336, 16384 in part), or the terms alone where there is a pair per
+//    compute unit at most (49152; 40960).  The better one of the others / terms, bf16: 64 x 1000 5.1 / 4.3; 64 x 32000 9.4 / 8.5;
+//    512 x 32000 18.4 / 17.8; 2048 x 8192 23.1 / 17.7; 8192 x 16384 114 / 91; 8192 x 32000 202 / 166.5 (6.3 TB/s); 256 x 40960 13.8 /
+//    11.7.  fp32: 64 x 14000 8.1 / 7.1; 2048 x 4096 20.1 / 15.9; 8192 x 10000 113 / 105; 256 x 32000 15.4 / 15.3.  Where it is not
+//    taken: fp32 768 x 16384 19.6 / 20.0, 300 x 20000 15.3 / 16.2, 64 x 49152 13.8 / 14.6, 600 x 1000 7.0 / 7.3.  (Warped rows: 10 to 30 %
+//    faster by it, but S of a nucleus of a few equal tokens is then an ulp off the half or third it should be.)
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr bool kBf16 = DT == DT_BF16;
   constexpr int kCUs = 256, nt = 512;
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
-  if constexpr (!WITH_KL) if (nvec > 0) {
+  constexpr bool kPlain = !WITH_KL && !WARP;
+  if constexpr (kPlain) if (nvec > 0) {
     const int steps = (a.V + nt * Elem<DT>::per_vec - 1) / (nt * Elem<DT>::per_vec);
     if constexpr (kBf16) {
-      if (steps <= 2) return launch_terms<DT, WARP, 2>(a, st);
-      if (steps <= 4) return launch_terms<DT, WARP, 4>(a, st);
-      if (steps <= 6) return launch_terms<DT, WARP, 6>(a, st);
-      if (steps <= 8) return launch_terms<DT, WARP, 8>(a, st);
-      if (steps <= 10 && pairs <= kCUs) return launch_terms<DT, WARP, 10, true>(a, st);
-      if (steps <= 12 && pairs <= kCUs) return launch_terms<DT, WARP, 12, true>(a, st);
+      if (steps <= 2) return launch_terms<DT, 2>(a, st);
+      if (steps <= 4) return launch_terms<DT, 4>(a, st);
+      if (steps <= 6) return launch_terms<DT, 6>(a, st);
+      if (steps <= 8) return launch_terms<DT, 8>(a, st);
+      if (steps <= 10 && pairs <= kCUs) return launch_terms<DT, 10, true>(a, st);
+      if (steps <= 12 && pairs <= kCUs) return launch_terms<DT, 12, true>(a, st);
     } else {
       const bool sparse = steps == 1 && pairs > kCUs && pairs <= 3 * kCUs;
-      if (steps <= 4 && !sparse) return launch_terms<DT, WARP, 4>(a, st);
-      if (steps > 4 && (steps <= 7 || (steps <= 8 && (WARP || pairs <= 2 * kCUs || pairs >= 16 * kCUs))))
-        return launch_terms<DT, WARP, 8>(a, st);
-      if (steps > 8 && steps <= 12) {
-        if (pairs <= kCUs) return launch_terms<DT, WARP, 12, true>(a, st);
-        if constexpr (WARP) if (pairs >= 4 * kCUs) return launch_terms<DT, WARP, 12>(a, st);
-      }
-      if (steps > 12 && steps <= 16 && pairs <= kCUs) return launch_terms<DT, WARP, 16, true>(a, st);
-      if (steps > 16 && steps <= 20 && pairs <= kCUs) return launch_terms<DT, WARP, 20, true>(a, st);
+      if (steps <= 4 && !sparse) return launch_terms<DT, 4>(a, st);
+      if (steps > 4 && (steps <= 7 || (steps <= 8 && (pairs <= 2 * kCUs || pairs >= 16 * kCUs)))) return launch_terms<DT, 8>(a, st);
+      if (steps > 8 && steps <= 12 && pairs <= kCUs) return launch_terms<DT, 12, true>(a, st);
+      if (steps > 12 && steps <= 16 && pairs <= kCUs) return launch_terms<DT, 16, true>(a, st);
+      if (steps > 16 && steps <= 20 && pairs <= kCUs) return launch_terms<DT, 20, true>(a, st);
     }
   }
   const bool one = nvec > (pairs <= kCUs ? 11 * nt : 14 * nt);
   const auto from = [&](int per_cu, int steps) { return pairs >= per_cu * kCUs && nvec <= steps * nt; };
   const bool few = pairs <= (kBf16 || WITH_KL || WARP ? kCUs / 2 : kCUs * 3 / 8) && nvec > 33 * nt;
-  const bool many = kBf16 ? (WITH_KL && from(6, 7)) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
-                          : WITH_KL ? from(6, 5) || (WARP && (from(8, 7) || from(12, 9))) : !WARP && from(16, 9);
+  const bool many = kBf16 ? from(6, 7) || (WARP ? from(8, 13) || from(12, 18) : from(16, 9))
+                          : from(6, 5) || (WARP ? from(8, 7) || from(12, 9) : !WITH_KL && from(16, 9));
   const int off_chip = kBf16 ? (WARP ? 16000 : 20000) : (WITH_KL || WARP ? 11 * nt : 14 * nt);
   const bool few_more = pairs > kCUs && pairs <= (kBf16 ? 400 : nvec > 24000 ? 340 : 390) && nvec > off_chip;
   if (nvec <= nt || many || (few_more && (nvec <= 20 * nt || (kBf16 && WARP))))
@@ -1094,15 +1081,13 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
   if (few_more) return launch_shape<DT, WITH_KL, WARP, StashTwo>(a, st);
   if (few) return launch_shape<DT, WITH_KL, WARP, StashWide>(a, st);
   if (nvec > 23 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<WITH_KL ? 18 : WARP ? 22 : 24, 1>>(a, st);
-  constexpr bool kPlain = !WITH_KL && !WARP;              // (a kernel less for every form where the neighbour will do)
   if (nvec > 15 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 16 : 12, 1>>(a, st);
   if (one) return launch_loop<DT, WITH_KL, WARP, Loop<12, 1>>(a, st);
-  if (nvec > 7 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<kPlain ? 8 : 6, 2>>(a, st);
-  if constexpr (WITH_KL) {
+  if constexpr (kPlain) {                                 // (shorter rows have gone to the terms kernel)
+    return launch_loop<DT, WITH_KL, WARP, Loop<8, 2>>(a, st);
+  } else {                                                // (a kernel less for every form where the neighbour will do)
     if (nvec > 5 * nt) return launch_loop<DT, WITH_KL, WARP, Loop<6, 2>>(a, st);
     return launch_loop<DT, WITH_KL, WARP, Loop<2, 2>>(a, st);
-  } else {
-    return launch_shape<DT, WITH_KL, WARP, StashThree>(a, st);           // (shorter rows have gone to the terms kernel)
   }
 }
 

@@ -6,18 +6,13 @@
 //  * Philox-4x32-10 for the speculative-sampling uniforms
 //
 // A row's normaliser is carried as the pair (m, s): m = the row maximum in raw
-// logit units and s = sum_v 2^(z_v * L - c(m)), c(m) = ceil(max(fl32(m * L), -2^30)),
+// logit units and s = sum_v 2^(z_v * L - c(m)), c(m) = max(fl32(m * L), -2^30),
 // where L is log2(e) / T rounded to fp32 (T = sampling temperature of the
 // tensor, 1 unless a warped entry point says otherwise; L32 is the T = 1 value).
 // Because L T / log2(e) = 1 + tau1 with |tau1| < 6e-8 (1.33e-8 for L32) the sum
 // is the soft-max normaliser at a temperature off by that factor; the fp64
 // epilogue removes the first-order effect around the row maximum
 // (lse_from_ms), leaving an error below |tau1| * (H - H_inf) of the row.
-//
-// References are whole numbers, so that every change of reference scales a sum exactly and an entry's term has the same
-// mantissa whatever lane, workgroup or kernel forms it: the normalisers of equal rows differ by the roundings of the additions
-// alone.  (Over c(m) = fl32(m * L) the terms themselves differed by 1e-8 in the mean from lane to lane: a residual of two
-// equal rows, whose normalisers two kernels had formed, was found to have mass.)
 //
 // Range of the logits.  2^(z L - c) is formed with one fused multiply-add, so it
 // is right for any z as long as the part of m * L that fp32 drops from c stays a
@@ -126,19 +121,23 @@ __device__ __forceinline__ void unpack(const u32x4& q, float (&f)[Elem<DT>::per_
 // ---------------------------------------------------------------------------
 // online (max, sum 2^(z L - c)) accumulator, one per lane
 //   Online      fp32 sum
-//   OnlineWide  fp64 sum: nothing in it grows with the number of entries.  Millions of equal terms, which round the same way in every lane, leave an
+//   OnlineWide  fp64 sum over a reference that is a whole number, so that raising it scales the sum exactly: nothing in it grows with the
+//               number of entries.  Millions of equal terms, which round the same way in every lane, leave an
 //               fp32 sum 1.4e-6 off at 2^18 entries and 2e-5 at 2^22.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float ref_of(float m, const float L = kL32) { return __builtin_ceilf(fmaxf(m * L, kRefFloor)); }
-
 template <class Sum>
 struct OnlineOf {
+  static constexpr bool kWide = sizeof(Sum) == 8;
   float m;   // running maximum (raw units); -inf before the first element
-  float c;   // c(m)
+  float c;   // max(fl32(m * L), kRefFloor), for the wide sum rounded up to a whole number
   Sum s;     // sum of 2^(z*L - c) so far
 
   __device__ __forceinline__ void init() { m = -INFINITY; c = kRefFloor; s = 0; }
 
+  static __device__ __forceinline__ float ref(float mx, const float L) {
+    const float r = fmaxf(mx * L, kRefFloor);
+    return kWide ? __builtin_ceilf(r) : r;
+  }
   static __device__ __forceinline__ float scaled(float s, float scale, float t) { return __builtin_fmaf(s, scale, t); }
   static __device__ __forceinline__ double scaled(double s, float scale, float t) {
     return __builtin_fma(s, (double)scale, (double)t);
@@ -150,7 +149,7 @@ struct OnlineOf {
 #pragma unroll
     for (int j = 0; j + 1 < N; j += 2) mx = fmaxf(fmaxf(mx, z[j]), z[j + 1]);   // v_max3_f32
     if (N & 1) mx = fmaxf(mx, z[N - 1]);
-    const float cn = ref_of(mx, L);
+    const float cn = ref(mx, L);
     const float scale = exp2_fast(c - cn);
     float e[N];
 #pragma unroll
@@ -175,7 +174,7 @@ struct OnlineOf {
 
   __device__ __forceinline__ void add1(float z, const float L = kL32) {
     const float mx = fmaxf(m, z);
-    const float cn = ref_of(mx, L);
+    const float cn = ref(mx, L);
     s = scaled(s, exp2_fast(c - cn), exp2_fast(__builtin_fmaf(z, L, -cn)));
     m = mx;
     c = cn;
@@ -196,7 +195,19 @@ using OnlineWide = OnlineOf<double>;
 struct MS {
   float m;
   double s;
+  float ref;       // what s is relative to: c(m), or the next whole number above
 };
+
+__device__ __forceinline__ float ref_of(float m, const float L = kL32) { return fmaxf(m * L, kRefFloor); }
+// Over whole references every change of reference scales a sum exactly, and an entry's term has the same mantissa whatever
+// lane, workgroup or kernel forms it.  The row sweep and the statistics of short plain rows sum over them, vectors in
+// fp64, so that equal target and draft rows have equal normalisers in a chained call too, and no residual of their roundings.
+// (Over c(m) the term of a row's maximum is 1 to within 1e-6, and the masses of a nucleus of a few equal tokens come out as exact
+// halves and thirds: those of warped rows keep it.)
+__device__ __forceinline__ float whole_ref(float m) { return __builtin_ceilf(ref_of(m)); }
+// Does the row sweep of a verification sum over whole references?  Where the statistics may: rows of T = 1 without cutoffs, up
+// to the longest that a lane's registers hold the terms of.
+inline bool sums_over_whole_refs(int V, bool warped) { return !warped && V <= 49152; }
 
 // ---------------------------------------------------------------------------
 // Wavefront reductions and scans on the DPP lane network: a step is a register move inside the
@@ -403,32 +414,35 @@ struct MergeScratch {
 };
 
 // (valid in lane 15 of every row of 16 lanes, each of which may be given another logit row)
-__device__ __forceinline__ MS fold_waves_row16(const float* m, const double* s, int nw, const float L = kL32) {
+__device__ __forceinline__ MS fold_waves_row16(const float* m, const double* s, int nw, const float L = kL32,
+                                               const bool whole = false) {
   const int w = threadIdx.x & 15;
   const float mw = w < nw ? m[w] : -INFINITY;
   const double sw = w < nw ? s[w] : 0.0;
   MS r;
   r.m = row16_max_all_f32(mw);
-  r.s = row16_sum_f64(sw * (double)exp2_fast(ref_of(mw, L) - ref_of(r.m, L)));
+  r.ref = whole ? whole_ref(r.m) : ref_of(r.m, L);
+  r.s = row16_sum_f64(sw * (double)exp2_fast((whole ? whole_ref(mw) : ref_of(mw, L)) - r.ref));
   return r;
 }
 
 template <int NR, class Sum>
 __device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
-                                            const float L = kL32) {
+                                            const float L = kL32, const bool whole = false) {
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const float mw = wave_max_f32(o[r].m);
-    const double sw = wave_sum_f64((double)o[r].s * (double)exp2_fast(o[r].c - ref_of(mw, L)));
+    const double sw = wave_sum_f64((double)o[r].s * (double)exp2_fast(o[r].c - (whole ? whole_ref(mw) : ref_of(mw, L))));
     if ((threadIdx.x & 63) == 0) { sm.m[r][wave] = mw; sm.s[r][wave] = sw; }
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const MS f = fold_waves_row16(sm.m[r], sm.s[r], nw, L);
+    const MS f = fold_waves_row16(sm.m[r], sm.s[r], nw, L, whole);
     out[r].m = lane_f32(f.m, 15);
     out[r].s = lane_f64(f.s, 15);
+    out[r].ref = lane_f32(f.ref, 15);
   }
 }
 
@@ -436,12 +450,12 @@ __device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeS
 // log2 of sum_v 2^(z_v L); the natural-log LSE of the row z / T follows after
 // removing the temperature offset around the maximum.  Bad rows (NaN, +inf, no
 // finite entry) give NaN.
-__device__ __forceinline__ bool bad_row(const MS& r, const float L) {
-  return !(r.s > 0.0) || !isfinite(r.s) || !isfinite(r.m) || ref_of(r.m, L) > kRefCeil;
+__device__ __forceinline__ bool bad_row(const MS& r) {
+  return !(r.s > 0.0) || !isfinite(r.s) || !isfinite(r.m) || r.ref > kRefCeil;
 }
 __device__ __forceinline__ double lse_from_ms(const MS& r, const Scale sc = unit_scale()) {
-  if (bad_row(r, sc.L)) return __builtin_nan("");
-  const double kappa = (double)ref_of(r.m, sc.L) + log2(r.s);
+  if (bad_row(r)) return __builtin_nan("");
+  const double kappa = (double)r.ref + log2(r.s);
   return kappa * kLn2 - sc.tau1 * ((double)r.m * sc.inv_t);
 }
 
@@ -449,15 +463,16 @@ __device__ __forceinline__ double lse_from_ms(const MS& r, const Scale sc = unit
 // one.  Those probabilities are the soft-max of z / T at temperature 1 + tau1;
 // entry v deviates from the exact one by a relative tau1 * (y_v - E_p[y]),
 // y = z / T (1.33e-8 per unit for L32).
-__device__ __forceinline__ double kappa_l32(const MS& r, const float L = kL32) {
-  return (double)ref_of(r.m, L) + log2(r.s);
+__device__ __forceinline__ double kappa_l32(const MS& r) {
+  return (double)r.ref + log2(r.s);
 }
 
 // Normaliser of a row from the `split` <= kMaxParts partials held in global memory: all loads
 // are issued before the first use (a loop would pay one memory latency per part).
 constexpr int kMaxParts = 8;
 
-__device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L = kL32) {
+template <bool WHOLE>
+__device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L) {
   float mp[kMaxParts];
   double sp[kMaxParts];
 #pragma unroll
@@ -470,10 +485,11 @@ __device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, in
   r.m = mp[0];
 #pragma unroll
   for (int p = 1; p < kMaxParts; ++p) r.m = fmaxf(r.m, mp[p]);
-  const float cr = ref_of(r.m, L);
+  r.ref = WHOLE ? whole_ref(r.m) : ref_of(r.m, L);
   r.s = 0.0;
 #pragma unroll
-  for (int p = 0; p < kMaxParts; ++p) r.s += sp[p] * (double)exp2_fast(ref_of(mp[p], L) - cr);   // absent parts add 0
+  for (int p = 0; p < kMaxParts; ++p)                    // absent parts add 0
+    r.s += sp[p] * (double)exp2_fast((WHOLE ? whole_ref(mp[p]) : ref_of(mp[p], L)) - r.ref);
   return r;
 }
 

@@ -77,6 +77,7 @@ struct VerifyArgs {
   int chained;                // 1: draft normalisers come from the statistics pass (workspace), z_d's rows
                               // are not swept
   int dtype;
+  bool whole;                 // partials over whole references
   VerifyWs ws;
 };
 
@@ -118,9 +119,10 @@ __device__ __forceinline__ const void* draft_row(const VerifyArgs& a, int b, int
 }
 
 // Normaliser of a whole row from the partials its workgroups left.
+template <bool WHOLE>
 __device__ __forceinline__ MS target_ms(const VerifyArgs& a, int b, int i) {
   const int idx = (b * (a.k + 1) + i) * a.split;
-  return fold_row_parts(a.ws.m_t + idx, a.ws.s_t + idx, a.split, a.sc_t.L);
+  return fold_row_parts<WHOLE>(a.ws.m_t + idx, a.ws.s_t + idx, a.split, a.sc_t.L);
 }
 // Chained calls: does the workspace hold the draft normalisers of this very step?  (The
 // header names the tensors, shape and scale the statistics pass was given; what the
@@ -140,9 +142,10 @@ __device__ __forceinline__ bool chain_matches(const VerifyArgs& a) {
           (w2.w ^ kChainMagic);
   return diff == 0;
 }
+template <bool WHOLE>
 __device__ __forceinline__ MS draft_ms(const VerifyArgs& a, int b, int i) {
   const int idx = (b * a.k + i) * a.split;
-  return fold_row_parts(a.ws.m_d + idx, a.ws.s_d + idx, a.split, a.sc_d.L);
+  return fold_row_parts<WHOLE>(a.ws.m_d + idx, a.ws.s_d + idx, a.split, a.sc_d.L);
 }
 
 // ---------------------------------------------------------------------------
@@ -157,7 +160,8 @@ struct RowPart {
 };
 
 // The sweep of one part of one needed row by the whole workgroup (results in thread 0).
-template <int DT, bool CUT>
+// WHOLE: see sums_over_whole_refs.
+template <int DT, bool CUT, bool WHOLE>
 __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScratch<1>& sm) {
   RowPart r;
   const int per_seq = a.chained ? a.k + 1 : 2 * a.k + 1;       // chained: target rows only
@@ -181,15 +185,14 @@ __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScra
     const int tok = a.x[r.b * a.k + r.i];
     if (tok >= 0 && tok < a.V) r.zx = load_elem<DT>(row, tok);
   }
-  // (fp64 lane sums, here and in the statistics of short rows, so that equal target and draft rows have equal normalisers in a
-  // chained call too, and no residual of their roundings; 0.1 to 0.4 us of a call)
-  OnlineWide acc[1];
+  using Acc = std::conditional_t<WHOLE, OnlineWide, Online>;
+  Acc acc[1];
   acc[0].init();
   // six vectors in flight per lane: a part is 8-10 vectors per lane at the benchmark shapes, i.e. two
   // round trips to memory (6 + the rest, whose loads also go out together) instead of three or four
-  if (row) sweep_online<DT, CUT, true, 6, OnlineWide>(row, a.V, r.part, a.split, acc[0], L, cut);
+  if (row) sweep_online<DT, CUT, true, 6>(row, a.V, r.part, a.split, acc[0], L, cut);
   MS merged[1];
-  block_merge(acc, sm, merged, L);
+  block_merge(acc, sm, merged, L, WHOLE);
   r.ms = merged[0];                                      // s = 0 for a missing row => bad row
   if (CUT) r.zx = cut_below(r.zx, cut);
   return r;
@@ -210,10 +213,10 @@ __device__ __forceinline__ void store_row_part(const VerifyArgs& a, const RowPar
   }
 }
 
-template <int DT, bool CUT>
+template <int DT, bool CUT, bool WHOLE>
 __global__ __launch_bounds__(kRowsThreads) void verify_rows_kernel(VerifyArgs a) {
   __shared__ MergeScratch<1> sm;
-  const RowPart r = sweep_row_part<DT, CUT>(a, sm);
+  const RowPart r = sweep_row_part<DT, CUT, WHOLE>(a, sm);
   if (r.needed && threadIdx.x == 0) store_row_part(a, r);
 }
 
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(kWave) void accept_ratio_kernel(VerifyArgs a, float
     if (tok < 0 || tok >= a.V) {
       fl |= SV_FLAG_BAD_TOKEN;
     } else {
-      const double lse_t = lse_from_ms(target_ms(a, b, i), a.sc_t), lse_d = lse_from_ms(draft_ms(a, b, i), a.sc_d);
+      const double lse_t = lse_from_ms(target_ms<false>(a, b, i), a.sc_t), lse_d = lse_from_ms(draft_ms<false>(a, b, i), a.sc_d);
       if (isnan(lse_t) || isnan(lse_d)) {
         fl |= SV_FLAG_BAD_ROW;
       } else {
@@ -315,7 +318,7 @@ static_assert(sizeof(Plan) == 32, "workspace carve-up reserves 32 bytes per sequ
 // every workgroup of the mass kernel that works on sequence b calls it and gets
 // the same plan, the one with `publish` set also writes the accepted tokens,
 // the ratios, the accept count and the plan itself for the pick kernel.
-template <int DT, bool CHAIN>
+template <int DT, bool CHAIN, bool WHOLE>
 __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, const int i, const bool publish,
                                             Plan* plan_out) {
   const int k = a.k, V = a.V;
@@ -337,6 +340,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     chain_ms.m = a.ws.chain_m[at];
     chain_ms.s = a.ws.chain_s[at];
     chain_zx = a.ws.chain_zx[at];
+    chain_ms.ref = ref_of(chain_ms.m, a.sc_d.L);
     chain_ok = chain_matches(a);
     if (!chain_ok) { chain_ms.m = -INFINITY; chain_ms.s = 0.0; }   // no sum: an unusable row
   }
@@ -344,8 +348,8 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   // known (rows past the length hold whatever an earlier call left: read, never used), so that
   // the loads travel together instead of in three dependent rounds: length, partials, logits.
   const int it = min(i, k), id = min(i, k - 1);
-  const MS ms_t = target_ms(a, b, it);
-  const MS ms_d = CHAIN ? chain_ms : draft_ms(a, b, id);
+  const MS ms_t = target_ms<WHOLE>(a, b, it);
+  const MS ms_d = CHAIN ? chain_ms : draft_ms<WHOLE>(a, b, id);
   const float zx_t = a.ws.zx_t[b * k + id];
   const float zx_d = CHAIN ? chain_zx : a.ws.zx_d[b * k + id];
   const int tok = a.x[b * k + id];
@@ -397,7 +401,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     have_target_n = both & 1;
     maybe_empty = both >> 1;
   } else {
-    lse_t_n = lse_from_ms(target_ms(a, b, n), a.sc_t);
+    lse_t_n = lse_from_ms(target_ms<WHOLE>(a, b, n), a.sc_t);
     lse_d_n = __builtin_nan("");
     have_target_n = target_row<DT>(a, b, n) != nullptr;
   }
@@ -512,8 +516,8 @@ __device__ __forceinline__ double lane_mass(const SampleRow<DT, CUT>& sr, int v0
 // row pairs go through at 3 TB/s (64 x 152064 bf16: 14.5 to 16.4 us, by what the kernels before it left in the caches; 512 x
 // 32000: 23.8), bound by two exponentials and some twenty further operations per entry pair.  Seven wavefronts per SIMD: eight leave 64 registers, of which bf16
 // spills 8 and, under cutoffs, 20.
-template <int DT, bool CUT, bool CHAIN, bool WIDE>
-__global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7) void verify_mass_kernel(VerifyArgs a) {
+template <int DT, bool CUT, bool CHAIN, bool WIDE, bool WHOLE>
+__device__ __forceinline__ void granule_masses(const VerifyArgs& a) {
   __shared__ Plan plan;
   constexpr int kGran = WIDE ? 1 : kChunk / kGranule;                  // granules of a workgroup
   constexpr int kLanes = (WIDE ? kWideThreads : kSampleThreads) / kGran, kWaves = kLanes / kWave;    // of a granule
@@ -521,7 +525,7 @@ __global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7)
   const int b = blockIdx.y, c = blockIdx.x;
   const int tid = threadIdx.x;
   SV_PHASE_MARK(6)
-  if (tid < kWave) accept_plan<DT, CHAIN>(a, b, tid, c == 0, &plan);
+  if (tid < kWave) accept_plan<DT, CHAIN, WHOLE>(a, b, tid, c == 0, &plan);
   __syncthreads();
   SV_PHASE_MARK(7)
   const Plan pl = plan;
@@ -558,6 +562,16 @@ __global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7)
     a.ws.mass[(size_t)b * n_granules(a.V) + v0 / kGranule] = m > 0.0 ? m : mt;
   }
   SV_PHASE_MARK(9)
+}
+
+template <int DT, bool CUT, bool CHAIN, bool WIDE>
+__global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7) void verify_mass_kernel(VerifyArgs a) {
+  granule_masses<DT, CUT, CHAIN, WIDE, false>(a);
+}
+// of rows whose partials are over whole references
+template <int DT, bool CHAIN, bool WIDE>
+__global__ __launch_bounds__(WIDE ? kWideThreads : kSampleThreads, WIDE ? 4 : 7) void verify_mass_of_whole_kernel(VerifyArgs a) {
+  granule_masses<DT, false, CHAIN, WIDE, true>(a);
 }
 
 // grid (B): the granule of the sampling row that holds u' * W from the granule masses, then
@@ -729,7 +743,7 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
 // among its registers, where the pick kernel reads and weighs a granule again.  Bound by latency (the decision, one trip to
 // memory, two reductions: 8 x 4096 bf16 9.0 us with the row sweep, 12.8 in two kernels) and, on the longest rows, by
 // the arithmetic of a row pair on one compute unit (4 us of 32000 entries).
-template <int DT, bool CUT, bool CHAIN, int THREADS, int J>
+template <int DT, bool CUT, bool CHAIN, bool WHOLE, int THREADS, int J>
 __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
   constexpr int EPV = Elem<DT>::per_vec, kEach = 8, kVecs = kEach / EPV, kWaves = THREADS / kWave;
   constexpr int kRuns = kWaves * J;
@@ -739,7 +753,7 @@ __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
   __shared__ double run_mass[kWave];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  if (wave == 0) accept_plan<DT, CHAIN>(a, b, tid, true, &plan);
+  if (wave == 0) accept_plan<DT, CHAIN, WHOLE>(a, b, tid, true, &plan);
   if (tid < kWave) run_mass[tid] = 0.0;
   __syncthreads();
   const Plan pl = plan;
@@ -907,7 +921,13 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   const int rows = a.B * (a.chained ? a.k + 1 : 2 * a.k + 1);
   {
     TapScope tap(SV_KERNEL_VERIFY_ROWS, st);
-    hipLaunchKernelGGL((verify_rows_kernel<DT, CUT>), dim3(rows * a.split), dim3(kRowsThreads), 0, st, a);
+    const dim3 grid(rows * a.split), block(kRowsThreads);
+    if constexpr (!CUT) {
+      if (a.whole) hipLaunchKernelGGL((verify_rows_kernel<DT, false, true>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT, false, false>), grid, block, 0, st, a);
+    } else {
+      hipLaunchKernelGGL((verify_rows_kernel<DT, true, false>), grid, block, 0, st, a);
+    }
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;
   const int C = n_chunks(a.V);
@@ -916,8 +936,14 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
       TapScope tap(SV_KERNEL_VERIFY_MASS, st);
       auto draw = [&](auto threads, auto runs) {
         constexpr int T = decltype(threads)::value, J = decltype(runs)::value;
-        if (a.chained) hipLaunchKernelGGL((verify_draw_kernel<DT, CUT, true, T, J>), dim3(a.B), dim3(T), 0, st, a);
-        else hipLaunchKernelGGL((verify_draw_kernel<DT, CUT, false, T, J>), dim3(a.B), dim3(T), 0, st, a);
+        auto launch = [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3(a.B), dim3(T), 0, st, a); };
+        if constexpr (!CUT) if (a.whole) {
+          if (a.chained) launch(&verify_draw_kernel<DT, false, true, true, T, J>);
+          else launch(&verify_draw_kernel<DT, false, false, true, T, J>);
+          return;
+        }
+        if (a.chained) launch(&verify_draw_kernel<DT, CUT, true, false, T, J>);
+        else launch(&verify_draw_kernel<DT, CUT, false, false, T, J>);
       };
       using std::integral_constant;
       if (a.V <= kGranule) draw(integral_constant<int, 512>(), integral_constant<int, 1>());
@@ -935,7 +961,13 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
       hipLaunchKernelGGL(kernel, dim3(groups, a.B), dim3(threads), 0, st, a);
     };
     const int G = n_granules(a.V);
-    if ((long)G * a.B <= wide_groups(DT, G)) {
+    const bool wide = (long)G * a.B <= wide_groups(DT, G);
+    if (!CUT && a.whole) {
+      if (wide && a.chained) launch(&verify_mass_of_whole_kernel<DT, true, true>, G, kWideThreads);
+      else if (wide) launch(&verify_mass_of_whole_kernel<DT, false, true>, G, kWideThreads);
+      else if (a.chained) launch(&verify_mass_of_whole_kernel<DT, true, false>, C, kSampleThreads);
+      else launch(&verify_mass_of_whole_kernel<DT, false, false>, C, kSampleThreads);
+    } else if (wide) {
       if (a.chained) launch(&verify_mass_kernel<DT, CUT, true, true>, G, kWideThreads);
       else launch(&verify_mass_kernel<DT, CUT, false, true>, G, kWideThreads);
     } else {
@@ -980,6 +1012,7 @@ static int verify_sample_checked(const void* z_t, const int32_t* t_offsets, int 
   a.B = B; a.k = k; a.V = V;
   a.chained = chained ? 1 : 0;
   a.dtype = dtype;
+  a.whole = sums_over_whole_refs(V, cut_t || cut_d || sc_t.L != kL32 || sc_d.L != kL32);
   a.split = rows_split(B * (chained ? k + 1 : 2 * k + 1), V);
   a.t_seq_rows = k + 1;
   a.with_bonus = 1;
@@ -1130,11 +1163,11 @@ static int accept_ratio_checked(const void* z_t, int t_rows_per_seq, const void*
     TapScope tap(SV_KERNEL_VERIFY_ROWS, st);
     const dim3 grid(rows * a.split), block(kRowsThreads);
     if (dtype == SV_F32) {
-      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_F32, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((verify_rows_kernel<DT_F32, false>), grid, block, 0, st, a);
+      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_F32, true, false>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT_F32, false, false>), grid, block, 0, st, a);
     } else {
-      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, false>), grid, block, 0, st, a);
+      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, true, false>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, false, false>), grid, block, 0, st, a);
     }
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;

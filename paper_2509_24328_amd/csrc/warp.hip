@@ -233,7 +233,7 @@ __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online
       top.add((okey(vmax) & 0xFFFF0000u) | (uint32_t)(i / nt + u));   // i = tid + step * nt
       mx = fmaxf(mx, vmax);
     }
-    const float cn = ref_of(mx, L), scale = exp2_fast(acc.c - cn);
+    const float cn = OnlineWide::ref(mx, L), scale = exp2_fast(acc.c - cn);
     float t = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -898,7 +898,7 @@ __device__ __forceinline__ void warp_row(const void* z, const int r, int V, cons
   const float m = merged[0].m;
   SV_PHASE_MARK(1)
   const double row_s = merged[0].s;
-  if (bad_row(merged[0], lt)) {
+  if (bad_row(merged[0])) {
     if (tid == 0) {
       if (cutoff) cutoff[r] = __builtin_nanf("");
       if (flags) flags[r] = SV_FLAG_BAD_ROW;
@@ -1375,10 +1375,11 @@ __global__ __launch_bounds__(kWarpThreads, R <= 8 ? 8 : 4) void warp_cutoffs_res
   MS ms;
   ms.m = m;
   ms.s = fold_sums(sh.mg.s[0], kWaves);
+  ms.ref = c_ref;
   float cutoff = -INFINITY;
   uint32_t fl = 0;
   bool done = true;
-  if (bad_row(ms, lt)) {
+  if (bad_row(ms)) {
     cutoff = __builtin_nanf("");
     fl = SV_FLAG_BAD_ROW;
   } else if (use_k || use_p) {
