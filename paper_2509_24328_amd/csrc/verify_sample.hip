@@ -743,8 +743,10 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
 // among its registers, where the pick kernel reads and weighs a granule again.  Bound by latency (the decision, one trip to
 // memory, two reductions: 8 x 4096 bf16 9.0 us with the row sweep, 12.8 in two kernels) and, on the longest rows, by
 // the arithmetic of a row pair on one compute unit (4 us of 32000 entries).
-template <int DT, bool CUT, bool CHAIN, bool WHOLE, int THREADS, int J>
-__global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
+// G < J: the runs of a wavefront are weighed G at a time and the token's run once more; two workgroups of 1024 lanes then fit a
+// compute unit, for more sequences than there are of these.
+template <int DT, bool CUT, bool CHAIN, bool WHOLE, int THREADS, int J, int G>
+__global__ __launch_bounds__(THREADS, G < J ? 8 : 4) void verify_draw_kernel(VerifyArgs a) {
   constexpr int EPV = Elem<DT>::per_vec, kEach = 8, kVecs = kEach / EPV, kWaves = THREADS / kWave;
   constexpr int kRuns = kWaves * J;
   static_assert(kRuns <= kWave, "a lane for every run");
@@ -764,24 +766,25 @@ __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
   }
   SampleRow<DT, CUT> sr(a, b, pl);
   const int V = a.V, groups = (V + kEach - 1) / kEach;
-  float w[J][kEach];
-  auto group_of = [&](int j) { return (wave * J + j) * kWave + lane; };
+  float w[G][kEach];                                   // weights of runs [first, first + G)
   // (a row's last group is its last eight entries: those that belong to the group before are masked out)
-  auto fetch = [&](const void* row, u32x4 (&q)[J][kVecs]) {
+  auto fetch = [&](const void* row, int first, u32x4 (&q)[G][kVecs]) {
     const u32x4 neg = {kNegInfWord, kNegInfWord, kNegInfWord, kNegInfWord};
 #pragma unroll
-    for (int j = 0; j < J; ++j)
+    for (int j = 0; j < G; ++j) {
+      const int group = (first + j) * kWave + lane;
 #pragma unroll
       for (int i = 0; i < kVecs; ++i) {
         q[j][i] = neg;
-        if (group_of(j) < groups)
-          q[j][i] = load_vec(static_cast<const char*>(row) + (size_t)min(group_of(j) * kEach, V - kEach) * Elem<DT>::bytes, i);
+        if (group < groups) q[j][i] = load_vec(static_cast<const char*>(row) + (size_t)min(group * kEach, V - kEach) * Elem<DT>::bytes, i);
       }
-    if (V % kEach != 0 && (groups - 1) / (kWave * J) == wave) {             // (uniform)
+    }
+    const int ends = (groups - 1) / kWave;             // the run that the row ends in
+    if (V % kEach != 0 && ends >= first && ends < first + G) {              // (uniform)
       const int twice = kEach - V % kEach;
 #pragma unroll
-      for (int j = 0; j < J; ++j)
-        if (group_of(j) == groups - 1) {
+      for (int j = 0; j < G; ++j)
+        if ((first + j) * kWave + lane == groups - 1) {
 #pragma unroll
           for (int i = 0; i < kVecs; ++i)
 #pragma unroll
@@ -798,13 +801,13 @@ __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
         }
     }
   };
-  auto weigh = [&](auto small, auto residual) {
+  auto weigh_as = [&](auto small, auto residual, int first) {
     constexpr bool kSmall = decltype(small)::value, RESID = decltype(residual)::value;
-    u32x4 qt[J][kVecs], qd[J][kVecs];
-    fetch(sr.row_t, qt);
-    if (RESID) fetch(sr.row_d, qd);
+    u32x4 qt[G][kVecs], qd[G][kVecs];
+    fetch(sr.row_t, first, qt);
+    if (RESID) fetch(sr.row_d, first, qd);
 #pragma unroll
-    for (int j = 0; j < J; ++j)
+    for (int j = 0; j < G; ++j)
 #pragma unroll
       for (int i = 0; i < kVecs; ++i) {
         float ft[EPV], fd[EPV];
@@ -817,19 +820,25 @@ __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
         }
       }
   };
+  auto weigh = [&](int first) {
+    if (sr.small) { if (sr.resid) weigh_as(std::true_type(), std::true_type(), first); else weigh_as(std::true_type(), std::false_type(), first); }
+    else { if (sr.resid) weigh_as(std::false_type(), std::true_type(), first); else weigh_as(std::false_type(), std::false_type(), first); }
+  };
   double incl, W;
   for (;;) {
-    if (sr.small) { if (sr.resid) weigh(std::true_type(), std::true_type()); else weigh(std::true_type(), std::false_type()); }
-    else { if (sr.resid) weigh(std::false_type(), std::true_type()); else weigh(std::false_type(), std::false_type()); }
-    double mine[(J + 3) / 4 * 4] = {};
+#pragma unroll 1
+    for (int j0 = 0; j0 < J; j0 += G) {
+      weigh(wave * J + j0);
+      double mine[(G + 3) / 4 * 4] = {};
 #pragma unroll
-    for (int j = 0; j < J; ++j)
+      for (int j = 0; j < G; ++j)
 #pragma unroll
-      for (int i = 0; i < kEach; ++i) mine[j] += (double)w[j][i];
+        for (int i = 0; i < kEach; ++i) mine[j] += (double)w[j][i];
 #pragma unroll
-    for (int j = 0; j < J; j += 4) {
-      const double t = wave_sum4_f64(mine[j], mine[j + 1], mine[j + 2], mine[j + 3]);
-      if ((lane & 15) == 15 && j + lane / 16 < J) run_mass[wave * J + j + lane / 16] = t;
+      for (int j = 0; j < G; j += 4) {
+        const double t = wave_sum4_f64(mine[j], mine[j + 1], mine[j + 2], mine[j + 3]);
+        if ((lane & 15) == 15 && j + lane / 16 < G) run_mass[wave * J + j0 + j + lane / 16] = t;
+      }
     }
     __syncthreads();
     incl = wave_scan_f64(run_mass[lane]);
@@ -851,10 +860,11 @@ __global__ __launch_bounds__(THREADS, 4) void verify_draw_kernel(VerifyArgs a) {
   const int run = __builtin_amdgcn_readfirstlane(at ? (int)__builtin_ctzll(at) : 63 - (int)__builtin_clzll(has));
   if (run / J != wave) return;
   const double tau_local = tau - lane_f64(incl - mass, run);                // threshold inside the run
+  if (G < J) weigh(run / G * G);
   float mine[kEach];
 #pragma unroll
-  for (int j = 0; j < J; ++j)
-    if (run % J == j) {
+  for (int j = 0; j < G; ++j)
+    if (run % G == j) {
 #pragma unroll
       for (int i = 0; i < kEach; ++i) mine[i] = w[j][i];
     }
@@ -908,11 +918,13 @@ static int wide_groups(int dtype, int granules) { return dtype == DT_F32 || gran
 // and its loads; a workgroup alone pays for the arithmetic of a long row.  us of the call, two kernels / one: 8 x 4096 bf16
 // 12.8 / 9.0; 512 x 4096 19.4 / 14.9; 8 x 8192 12.8 / 9.7; 2048 x 8192 57.7 / 57.3; 8 x 16384 12.8 / 10.9; 2048 x 16384 104 / 95;
 // fp32, 8 x 16384 13.2 / 11.4, 1024 x 16384 92.3 / 90.0, 2048 x 16384 171.4 / 172.9.  Above, with 1024 lanes to a
-// sequence, for 33 to 512 sequences: 8 x 32000 13.4 / 13.9; 64 x 32000 20.3 / 18.8; 256 x 32000 37.7 / 33.5; 512 x 32000 57.3 /
-// 54.5; 1024 x 32000 94.6 / 96.1; fp32, 256 x 32000 48.1 / 43.8.  (Less than eight entries: two kernels.)
+// sequence, from 33 sequences on: 8 x 32000 13.4 / 13.9; 64 x 32000 20.2 / 18.6; 256 x 32000 38.1 / 33.7; then two sequences to a
+// compute unit: 300 x 24000 36.5 / 37.2; 512 x 32000 57.3 / 52.3 (one to a compute unit, which keeps its weights: 54.5); 1024 x 32000
+// 96.9 / 93.5; 2048 x 24000 136.7 / 142.8; fp32, 256 x 32000 48.4 / 44.1; 2048 x 32000 299.8 / 284.8.  (Less than eight entries: two
+// kernels.)
 static bool draws_at_once(int dtype, int B, int V) {
   if (V < 8 || V > 8 * kGranule) return false;
-  if (V > 4 * kGranule) return B > 32 && B <= 512;
+  if (V > 4 * kGranule) return B > 32 && (B <= 256 || (B >= 384 && B <= (dtype == DT_BF16 ? 1024 : 4096)));
   return V <= 2 * kGranule || dtype == DT_BF16 || B <= 1024;
 }
 
@@ -934,23 +946,28 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
   if (draws_at_once(DT, a.B, a.V)) {
     {
       TapScope tap(SV_KERNEL_VERIFY_MASS, st);
-      auto draw = [&](auto threads, auto runs) {
-        constexpr int T = decltype(threads)::value, J = decltype(runs)::value;
+      auto draw = [&](auto threads, auto runs, auto at_once) {
+        constexpr int T = decltype(threads)::value, J = decltype(runs)::value, G = decltype(at_once)::value;
         auto launch = [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3(a.B), dim3(T), 0, st, a); };
         if constexpr (!CUT) if (a.whole) {
-          if (a.chained) launch(&verify_draw_kernel<DT, false, true, true, T, J>);
-          else launch(&verify_draw_kernel<DT, false, false, true, T, J>);
+          if (a.chained) launch(&verify_draw_kernel<DT, false, true, true, T, J, G>);
+          else launch(&verify_draw_kernel<DT, false, false, true, T, J, G>);
           return;
         }
-        if (a.chained) launch(&verify_draw_kernel<DT, CUT, true, false, T, J>);
-        else launch(&verify_draw_kernel<DT, CUT, false, false, T, J>);
+        if (a.chained) launch(&verify_draw_kernel<DT, CUT, true, false, T, J, G>);
+        else launch(&verify_draw_kernel<DT, CUT, false, false, T, J, G>);
       };
-      using std::integral_constant;
-      if (a.V <= kGranule) draw(integral_constant<int, 512>(), integral_constant<int, 1>());
-      else if (a.V <= 2 * kGranule) draw(integral_constant<int, 512>(), integral_constant<int, 2>());
-      else if (a.V > 4 * kGranule) draw(integral_constant<int, 1024>(), integral_constant<int, 4>());
-      else if constexpr (DT == DT_F32) draw(integral_constant<int, 1024>(), integral_constant<int, 2>());
-      else draw(integral_constant<int, 512>(), integral_constant<int, 4>());
+      using One = std::integral_constant<int, 1>;
+      using Two = std::integral_constant<int, 2>;
+      using Four = std::integral_constant<int, 4>;
+      using Lanes512 = std::integral_constant<int, 512>;
+      using Lanes1024 = std::integral_constant<int, 1024>;
+      if (a.V <= kGranule) draw(Lanes512(), One(), One());
+      else if (a.V <= 2 * kGranule) draw(Lanes512(), Two(), Two());
+      else if (a.V > 4 * kGranule && a.B > 256) draw(Lanes1024(), Four(), One());
+      else if (a.V > 4 * kGranule) draw(Lanes1024(), Four(), Four());
+      else if constexpr (DT == DT_F32) draw(Lanes1024(), Two(), Two());
+      else draw(Lanes512(), Four(), Four());
     }
     TapScope tap(SV_KERNEL_VERIFY_PICK, st);           // (nothing is left to it)
     return launch_status();

@@ -13,7 +13,7 @@ import harness as H
 pytestmark = pytest.mark.gpu
 
 SIZES = [(7, 3), (8, 3), (9, 40), (15, 5), (511, 9), (513, 9), (4095, 12), (4096, 33), (4097, 12), (8191, 9), (8192, 5), (8193, 40),
-         (16383, 6), (16384, 6), (16385, 32), (16385, 33), (20003, 34), (32767, 33), (32768, 34), (32769, 33), (1003, 513), (17001, 513)]
+         (16383, 6), (16384, 6), (16385, 32), (16385, 33), (20003, 34), (32767, 33), (32768, 34), (32769, 33), (1003, 513), (17001, 383), (17001, 384), (16391, 513)]
 
 
 @pytest.mark.parametrize("chained", [False, True])
