@@ -205,9 +205,13 @@ __device__ __forceinline__ float ref_of(float m, const float L = kL32) { return 
 // (Over c(m) the term of a row's maximum is 1 to within 1e-6, and the masses of a nucleus of a few equal tokens come out as exact
 // halves and thirds: those of warped rows keep it.)
 __device__ __forceinline__ float whole_ref(float m) { return __builtin_ceilf(ref_of(m)); }
-// Does the row sweep of a verification sum over whole references?  Where the statistics may: rows of T = 1 without cutoffs, up
-// to the longest that a lane's registers hold the terms of.
-inline bool sums_over_whole_refs(int V, bool warped) { return !warped && V <= 49152; }
+// Does the row sweep of a verification sum over whole references?  Where the statistics of as many pairs do (launch_stats): rows of
+// T = 1 without cutoffs, up to the longest that a lane's registers hold the terms of, longer ones up to a pair per compute unit.
+// (Elsewhere the fp64 sums would cost 0.3 to 0.5 us of a call and bring nothing.)
+inline bool sums_over_whole_refs(int dtype, long long pairs, int V, bool warped) {
+  const bool bf16 = dtype == DT_BF16;
+  return !warped && (V <= (bf16 ? 32768 : 16384) || (V <= (bf16 ? 49152 : 40960) && pairs <= 256));
+}
 
 // ---------------------------------------------------------------------------
 // Wavefront reductions and scans on the DPP lane network: a step is a register move inside the

@@ -1029,7 +1029,7 @@ static int verify_sample_checked(const void* z_t, const int32_t* t_offsets, int 
   a.B = B; a.k = k; a.V = V;
   a.chained = chained ? 1 : 0;
   a.dtype = dtype;
-  a.whole = sums_over_whole_refs(V, cut_t || cut_d || sc_t.L != kL32 || sc_d.L != kL32);
+  a.whole = sums_over_whole_refs(dtype, (long long)B * k, V, cut_t || cut_d || sc_t.L != kL32 || sc_d.L != kL32);
   a.split = rows_split(B * (chained ? k + 1 : 2 * k + 1), V);
   a.t_seq_rows = k + 1;
   a.with_bonus = 1;
