@@ -165,8 +165,9 @@ struct PairConsts {
   float zx[2];
 };
 
-// Scalar epilogue of one pair: A, flags and the stores.  (SCALED: S is relative to one, not to the head of kappa_d.)
-template <bool WITH_KL, bool WARP, bool SCALED = false>
+// Scalar epilogue of one pair: A, flags and the stores.  (TERMS: S is relative to one, not to the head of kappa_d, and the
+// normalisers' sums to whole references.)
+template <bool WITH_KL, bool WARP, bool TERMS = false>
 __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, const PairConsts& pc, int tok, double S,
                                                double KL, double pa, double p1) {
   const double lse_d = pc.lse[0], lse_c = pc.lse[1];
@@ -180,7 +181,7 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
     h.cut_d = WARP ? reinterpret_cast<uint64_t>(a.cut_d) : 0;
     h.B = a.B; h.k = a.k; h.V = a.V; h.dtype = a.dtype;
     h.scale_bits = __float_as_uint(WARP ? a.sc_d.L : kL32);
-    h.magic = kChainMagic;
+    h.magic = kChainMagic | (TERMS ? kChainWhole : 0u);
     *a.chain = h;
   }
   double H_d = __builtin_nan("");
@@ -188,7 +189,7 @@ __device__ __forceinline__ void stats_epilogue(const StatsArgs& a, int pair, con
     S = KL = __builtin_nan("");
   } else {
     // the sums of sweep 2 are relative to the head of kappa_d (MinAcc)
-    const double tail_d = SCALED ? 0.0 : pc.kappa[0] - (double)(float)pc.kappa[0], f_d = SCALED ? 1.0 : exp2(-tail_d);
+    const double tail_d = TERMS ? 0.0 : pc.kappa[0] - (double)(float)pc.kappa[0], f_d = TERMS ? 1.0 : exp2(-tail_d);
     S *= f_d;
     if (WITH_KL) {
       KL *= f_d * kLn2;
@@ -973,7 +974,7 @@ __global__ __launch_bounds__(kTermThreads, (2 * terms_per_cu<DT, P, ONE>())) voi
   pc.zx[0] = r.zx[0];
   pc.zx[1] = r.zx[1];
   a.chain_m[pair] = md.m;
-  a.chain_s[pair] = md.s * exp2((double)(md.ref - ref_of(md.m)));         // (relative to c(m), as the other kernels leave it)
+  a.chain_s[pair] = md.s;
   stats_epilogue<false, false, true>(a, pair, pc, r.tok, (tid == done - 1 ? S_last : r.S) / r.s[0], 0.0, 0.0, 0.0);
 }
 
@@ -1051,7 +1052,7 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr int kCUs = 256, nt = 512;
   const int pairs = a.B * a.k, nvec = a.V / Elem<DT>::per_vec;
   constexpr bool kPlain = !WITH_KL && !WARP;
-  if constexpr (kPlain) if (nvec > 0) {
+  if constexpr (kPlain) if (nvec > 0 && sums_over_whole_refs(DT, pairs, a.V, false)) {
     const int steps = (a.V + nt * Elem<DT>::per_vec - 1) / (nt * Elem<DT>::per_vec);
     if constexpr (kBf16) {
       if (steps <= 2) return launch_terms<DT, 2>(a, st);

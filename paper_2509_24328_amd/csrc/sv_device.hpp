@@ -124,19 +124,27 @@ __device__ __forceinline__ void unpack(const u32x4& q, float (&f)[Elem<DT>::per_
 //   OnlineWide  fp64 sum over a reference that is a whole number, so that raising it scales the sum exactly: nothing in it grows with the
 //               number of entries.  Millions of equal terms, which round the same way in every lane, leave an
 //               fp32 sum 1.4e-6 off at 2^18 entries and 2e-5 at 2^22.
+//   OnlineEither  fp64 sum over a whole number or over c(m), as the workspace's header says
 // ---------------------------------------------------------------------------
-template <class Sum>
+// What the header's magic has added to it where the sums that the statistics left are over whole references.
+constexpr uint32_t kChainWhole = 0x80000000u;
+enum Refs { kOverMax, kOverWhole, kAsChained };          // sums over c(m), over the next whole number, as the header says
+
+template <class Sum, bool EITHER = false>
 struct OnlineOf {
   static constexpr bool kWide = sizeof(Sum) == 8;
   float m;   // running maximum (raw units); -inf before the first element
   float c;   // max(fl32(m * L), kRefFloor), for the wide sum rounded up to a whole number
   Sum s;     // sum of 2^(z*L - c) so far
+  uint32_t magic = 0;    // EITHER: the header's
 
   __device__ __forceinline__ void init() { m = -INFINITY; c = kRefFloor; s = 0; }
 
-  static __device__ __forceinline__ float ref(float mx, const float L) {
+  __device__ __forceinline__ float ref(float mx, const float L) const {
     const float r = fmaxf(mx * L, kRefFloor);
-    return kWide ? __builtin_ceilf(r) : r;
+    uint32_t w = magic;
+    if (EITHER) asm volatile("" : "+s"(w));            // (looked at ahead of the sweep it would hold up the first loads)
+    return kWide && (!EITHER || (w & kChainWhole)) ? __builtin_ceilf(r) : r;
   }
   static __device__ __forceinline__ float scaled(float s, float scale, float t) { return __builtin_fmaf(s, scale, t); }
   static __device__ __forceinline__ double scaled(double s, float scale, float t) {
@@ -190,6 +198,7 @@ struct OnlineOf {
 };
 using Online = OnlineOf<float>;
 using OnlineWide = OnlineOf<double>;
+using OnlineEither = OnlineOf<double, true>;
 
 // A row's normaliser: exact maximum m and fp64 sum s relative to c(m).
 struct MS {
@@ -199,13 +208,16 @@ struct MS {
 };
 
 __device__ __forceinline__ float ref_of(float m, const float L = kL32) { return fmaxf(m * L, kRefFloor); }
-// Over whole references every change of reference scales a sum exactly, and an entry's term has the same mantissa whatever
-// lane, workgroup or kernel forms it.  The row sweep and the statistics of short plain rows sum over them, vectors in
-// fp64, so that equal target and draft rows have equal normalisers in a chained call too, and no residual of their roundings.
+// Over whole references every change of reference scales a sum exactly, and with fp64 sums of vectors a lane's, wavefront's or
+// workgroup's share does not depend on who forms it; of an entry's term, only the last bit of its exponent depends on the
+// reference of its lane.
+// A chained call sums the target as the statistics summed the draft (ChainHeader::magic): equal rows of a few tokens in lanes
+// of their own have equal normalisers then, and no residual of their roundings.  A target over whole numbers beside a
+// draft over c(m) would have one: of equal rows of three tokens two in five.
 // (Over c(m) the term of a row's maximum is 1 to within 1e-6, and the masses of a nucleus of a few equal tokens come out as exact
 // halves and thirds: those of warped rows keep it.)
 __device__ __forceinline__ float whole_ref(float m) { return __builtin_ceilf(ref_of(m)); }
-// Does the row sweep of a verification sum over whole references?  Where the statistics of as many pairs do (launch_stats): rows of
+// Where the statistics may sum over whole references (launch_stats goes by it; the row sweep of independent calls too): rows of
 // T = 1 without cutoffs, up to the longest that a lane's registers hold the terms of, longer ones up to a pair per compute unit.
 // (Elsewhere the fp64 sums would cost 0.3 to 0.5 us of a call and bring nothing.)
 inline bool sums_over_whole_refs(int dtype, long long pairs, int V, bool warped) {
@@ -430,8 +442,8 @@ __device__ __forceinline__ MS fold_waves_row16(const float* m, const double* s, 
   return r;
 }
 
-template <int NR, class Sum>
-__device__ __forceinline__ void block_merge(const OnlineOf<Sum> (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
+template <int NR, class Acc>
+__device__ __forceinline__ void block_merge(const Acc (&o)[NR], MergeScratch<NR>& sm, MS (&out)[NR],
                                             const float L = kL32, const bool whole = false) {
   const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
@@ -475,8 +487,8 @@ __device__ __forceinline__ double kappa_l32(const MS& r) {
 // are issued before the first use (a loop would pay one memory latency per part).
 constexpr int kMaxParts = 8;
 
-template <bool WHOLE>
-__device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L) {
+template <Refs REFS>
+__device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L, uint32_t magic) {
   float mp[kMaxParts];
   double sp[kMaxParts];
 #pragma unroll
@@ -489,11 +501,12 @@ __device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, in
   r.m = mp[0];
 #pragma unroll
   for (int p = 1; p < kMaxParts; ++p) r.m = fmaxf(r.m, mp[p]);
-  r.ref = WHOLE ? whole_ref(r.m) : ref_of(r.m, L);
+  const bool whole = REFS == kOverWhole || (REFS == kAsChained && (magic & kChainWhole));
+  r.ref = whole ? whole_ref(r.m) : ref_of(r.m, L);
   r.s = 0.0;
 #pragma unroll
   for (int p = 0; p < kMaxParts; ++p)                    // absent parts add 0
-    r.s += sp[p] * (double)exp2_fast((WHOLE ? whole_ref(mp[p]) : ref_of(mp[p], L)) - r.ref);
+    r.s += sp[p] * (double)exp2_fast((whole ? whole_ref(mp[p]) : ref_of(mp[p], L)) - r.ref);
   return r;
 }
 
@@ -502,12 +515,12 @@ __device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, in
 // workgroup.  Parts are contiguous runs of whole 16-byte vectors (the last one
 // also takes the scalar tail).
 // ---------------------------------------------------------------------------
-// NT: the row is not read again soon (non-temporal loads).  U: vectors in flight per lane.
+// NT: the row is not read again soon (non-temporal loads).  U: vectors in flight per lane.  threads: of the workgroup, if known.
 template <int DT, bool CUT = false, bool NT = true, int U = 4, class Acc = Online>
 __device__ __forceinline__ void sweep_online(const void* row, int V, int part, int split, Acc& acc,
-                                             const float L = kL32, const float cut = -INFINITY) {
+                                             const float L = kL32, const float cut = -INFINITY, const int threads = 0) {
   constexpr int EPV = Elem<DT>::per_vec;
-  const int tid = threadIdx.x, nt = blockDim.x;
+  const int tid = threadIdx.x, nt = threads ? threads : blockDim.x;
   auto add_vec = [&](const u32x4& q) {
     float f[EPV];
     unpack<DT>(q, f);

@@ -40,13 +40,13 @@ struct alignas(16) ChainHeader {
   uint64_t z_d, x, cut_d;    // device addresses the statistics pass was given (cut_d: 0 without warps)
   int32_t B, k, V, dtype;
   uint32_t scale_bits;       // bit pattern of the draft's exponent scale fl32(log2(e) / T)
-  uint32_t magic;
+  uint32_t magic;            // kChainMagic; with kChainWhole: chain_s is not relative to c(m), but to the next whole number
 };
 constexpr uint32_t kChainMagic = 0x53564348u;
 
 // Workspace carve-up for sv_verify_sample.  All offsets are multiples of 256.
 struct VerifyWs {
-  double* s_t;        // [B*(k+1)*kMaxSplit] partial sums relative to c(m) of each target row
+  double* s_t;        // [B*(k+1)*kMaxSplit] partial sums of each target row, relative to c(m) or to the next whole number
   double* s_d;        // [B*k*kMaxSplit]     same for draft rows
   float* m_t;         // [B*(k+1)*kMaxSplit] partial maxima
   float* m_d;         // [B*k*kMaxSplit]
@@ -57,7 +57,7 @@ struct VerifyWs {
   Plan* plan;          // [B] per-sequence sampling plan (verify_sample.hip)
   // written by sv_row_stats, read by sv_verify_sample_chained
   ChainHeader* chain;  // [1]
-  double* chain_s;     // [B*k] sum relative to c(m) of each whole draft row
+  double* chain_s;     // [B*k] sum of each whole draft row, relative to what the header's magic says
   float* chain_m;      // [B*k] maximum of each draft row
   float* chain_zx;     // [B*k] draft logit of the drafted token (NaN: token out of range)
   size_t bytes;

@@ -77,7 +77,7 @@ struct VerifyArgs {
   int chained;                // 1: draft normalisers come from the statistics pass (workspace), z_d's rows
                               // are not swept
   int dtype;
-  bool whole;                 // partials over whole references
+  bool whole;                 // partials over whole references; chained: where those of the statistics are
   VerifyWs ws;
 };
 
@@ -119,33 +119,30 @@ __device__ __forceinline__ const void* draft_row(const VerifyArgs& a, int b, int
 }
 
 // Normaliser of a whole row from the partials its workgroups left.
-template <bool WHOLE>
-__device__ __forceinline__ MS target_ms(const VerifyArgs& a, int b, int i) {
+template <Refs REFS>
+__device__ __forceinline__ MS target_ms(const VerifyArgs& a, int b, int i, const uint32_t magic = 0) {
   const int idx = (b * (a.k + 1) + i) * a.split;
-  return fold_row_parts<WHOLE>(a.ws.m_t + idx, a.ws.s_t + idx, a.split, a.sc_t.L);
+  return fold_row_parts<REFS>(a.ws.m_t + idx, a.ws.s_t + idx, a.split, a.sc_t.L, magic);
 }
 // Chained calls: does the workspace hold the draft normalisers of this very step?  (The
 // header names the tensors, shape and scale the statistics pass was given; what the
 // tensors contain is the caller's business.)
-__device__ __forceinline__ bool chain_matches(const VerifyArgs& a) {
-  // the whole header in three 128-bit loads, compared without short-circuit: field-by-field
-  // loads inside a chain of && become as many dependent trips to memory
-  static_assert(sizeof(ChainHeader) == 48, "three 16-byte words");
-  const u32x4* w = reinterpret_cast<const u32x4*>(a.ws.chain);
-  const u32x4 w0 = w[0], w1 = w[1], w2 = w[2];
+// REFS: whether sums over either kind of reference will do.
+template <Refs REFS>
+__device__ __forceinline__ bool chain_matches(const VerifyArgs& a, const u32x4& w0, const u32x4& w1, const u32x4& w2) {
   const uint64_t zd = reinterpret_cast<uint64_t>(a.z_d), x = reinterpret_cast<uint64_t>(a.x),
                  cd = reinterpret_cast<uint64_t>(a.cut_d);
   uint32_t diff = (w0.x ^ (uint32_t)zd) | (w0.y ^ (uint32_t)(zd >> 32)) | (w0.z ^ (uint32_t)x) |
                   (w0.w ^ (uint32_t)(x >> 32));
   diff |= (w1.x ^ (uint32_t)cd) | (w1.y ^ (uint32_t)(cd >> 32)) | (w1.z ^ (uint32_t)a.B) | (w1.w ^ (uint32_t)a.k);
   diff |= (w2.x ^ (uint32_t)a.V) | (w2.y ^ (uint32_t)a.dtype) | (w2.z ^ __float_as_uint(a.sc_d.L)) |
-          (w2.w ^ kChainMagic);
+          ((REFS == kAsChained ? w2.w & ~kChainWhole : w2.w) ^ kChainMagic);
   return diff == 0;
 }
-template <bool WHOLE>
+template <Refs REFS>
 __device__ __forceinline__ MS draft_ms(const VerifyArgs& a, int b, int i) {
   const int idx = (b * a.k + i) * a.split;
-  return fold_row_parts<WHOLE>(a.ws.m_d + idx, a.ws.s_d + idx, a.split, a.sc_d.L);
+  return fold_row_parts<REFS>(a.ws.m_d + idx, a.ws.s_d + idx, a.split, a.sc_d.L, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -160,8 +157,7 @@ struct RowPart {
 };
 
 // The sweep of one part of one needed row by the whole workgroup (results in thread 0).
-// WHOLE: see sums_over_whole_refs.
-template <int DT, bool CUT, bool WHOLE>
+template <int DT, bool CUT, Refs REFS>
 __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScratch<1>& sm) {
   RowPart r;
   const int per_seq = a.chained ? a.k + 1 : 2 * a.k + 1;       // chained: target rows only
@@ -185,14 +181,16 @@ __device__ __forceinline__ RowPart sweep_row_part(const VerifyArgs& a, MergeScra
     const int tok = a.x[r.b * a.k + r.i];
     if (tok >= 0 && tok < a.V) r.zx = load_elem<DT>(row, tok);
   }
-  using Acc = std::conditional_t<WHOLE, OnlineWide, Online>;
-  Acc acc[1];
+  std::conditional_t<REFS == kOverMax, Online, std::conditional_t<REFS == kOverWhole, OnlineWide, OnlineEither>> acc[1];
   acc[0].init();
+  // (one sweep for both kinds of reference, and the header's word under way with the first vectors: two copies of the
+  //  sweep and a branch made a chained call 0.3 to 0.5 us longer)
+  if (REFS == kAsChained) acc[0].magic = a.ws.chain->magic;
   // six vectors in flight per lane: a part is 8-10 vectors per lane at the benchmark shapes, i.e. two
   // round trips to memory (6 + the rest, whose loads also go out together) instead of three or four
-  if (row) sweep_online<DT, CUT, true, 6>(row, a.V, r.part, a.split, acc[0], L, cut);
+  if (row) sweep_online<DT, CUT, true, 6>(row, a.V, r.part, a.split, acc[0], L, cut, kRowsThreads);
   MS merged[1];
-  block_merge(acc, sm, merged, L, WHOLE);
+  block_merge(acc, sm, merged, L, REFS == kOverWhole || (REFS == kAsChained && (acc[0].magic & kChainWhole)));
   r.ms = merged[0];                                      // s = 0 for a missing row => bad row
   if (CUT) r.zx = cut_below(r.zx, cut);
   return r;
@@ -213,10 +211,10 @@ __device__ __forceinline__ void store_row_part(const VerifyArgs& a, const RowPar
   }
 }
 
-template <int DT, bool CUT, bool WHOLE>
+template <int DT, bool CUT, Refs REFS>
 __global__ __launch_bounds__(kRowsThreads) void verify_rows_kernel(VerifyArgs a) {
   __shared__ MergeScratch<1> sm;
-  const RowPart r = sweep_row_part<DT, CUT, WHOLE>(a, sm);
+  const RowPart r = sweep_row_part<DT, CUT, REFS>(a, sm);
   if (r.needed && threadIdx.x == 0) store_row_part(a, r);
 }
 
@@ -287,7 +285,7 @@ __global__ __launch_bounds__(kWave) void accept_ratio_kernel(VerifyArgs a, float
     if (tok < 0 || tok >= a.V) {
       fl |= SV_FLAG_BAD_TOKEN;
     } else {
-      const double lse_t = lse_from_ms(target_ms<false>(a, b, i), a.sc_t), lse_d = lse_from_ms(draft_ms<false>(a, b, i), a.sc_d);
+      const double lse_t = lse_from_ms(target_ms<kOverMax>(a, b, i), a.sc_t), lse_d = lse_from_ms(draft_ms<kOverMax>(a, b, i), a.sc_d);
       if (isnan(lse_t) || isnan(lse_d)) {
         fl |= SV_FLAG_BAD_ROW;
       } else {
@@ -332,28 +330,38 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   bool have_target = false;
   // chained: everything the statistics pass left goes into flight at once, before any branch
   // (three dependent round trips to memory otherwise: header, normaliser, logit)
-  bool chain_ok = true;
-  MS chain_ms;
+  constexpr Refs REFS = !WHOLE ? kOverMax : CHAIN ? kAsChained : kOverWhole;
+  MS ms_d;
+  u32x4 w0 = {}, w1 = {}, w2 = {};
   float chain_zx = 0.f;
   if (CHAIN) {
     const int at = b * k + min(i, k - 1);
-    chain_ms.m = a.ws.chain_m[at];
-    chain_ms.s = a.ws.chain_s[at];
+    ms_d.m = a.ws.chain_m[at];
+    ms_d.s = a.ws.chain_s[at];
     chain_zx = a.ws.chain_zx[at];
-    chain_ms.ref = ref_of(chain_ms.m, a.sc_d.L);
-    chain_ok = chain_matches(a);
-    if (!chain_ok) { chain_ms.m = -INFINITY; chain_ms.s = 0.0; }   // no sum: an unusable row
+    // (the whole header in three 128-bit loads, compared without short-circuit: field-by-field
+    // loads inside a chain of && become as many dependent trips to memory)
+    static_assert(sizeof(ChainHeader) == 48, "three 16-byte words");
+    const u32x4* w = reinterpret_cast<const u32x4*>(a.ws.chain);
+    w0 = w[0]; w1 = w[1]; w2 = w[2];
   }
   // Everything the decision may need is asked for here, for every lane and before the length is
   // known (rows past the length hold whatever an earlier call left: read, never used), so that
   // the loads travel together instead of in three dependent rounds: length, partials, logits.
   const int it = min(i, k), id = min(i, k - 1);
-  const MS ms_t = target_ms<WHOLE>(a, b, it);
-  const MS ms_d = CHAIN ? chain_ms : draft_ms<WHOLE>(a, b, id);
   const float zx_t = a.ws.zx_t[b * k + id];
   const float zx_d = CHAIN ? chain_zx : a.ws.zx_d[b * k + id];
   const int tok = a.x[b * k + id];
   const bool target_there = target_index(a, b, it) >= 0;
+  const MS ms_t = target_ms<REFS>(a, b, it, w2.w);
+  bool chain_ok = true;
+  if (CHAIN) {
+    ms_d.ref = REFS == kAsChained && (w2.w & kChainWhole) ? whole_ref(ms_d.m) : ref_of(ms_d.m, a.sc_d.L);
+    chain_ok = chain_matches<REFS>(a, w0, w1, w2);
+    if (!chain_ok) { ms_d.m = -INFINITY; ms_d.s = 0.0; }             // no sum: an unusable row
+  } else {
+    ms_d = draft_ms<REFS>(a, b, id);
+  }
   if (i <= g) {                                   // target rows 0..g (row g: bonus position)
     have_target = target_there;
     lse_t = lse_from_ms(ms_t, a.sc_t);
@@ -401,7 +409,7 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
     have_target_n = both & 1;
     maybe_empty = both >> 1;
   } else {
-    lse_t_n = lse_from_ms(target_ms<WHOLE>(a, b, n), a.sc_t);
+    lse_t_n = lse_from_ms(target_ms<REFS>(a, b, n, REFS == kAsChained ? a.ws.chain->magic : 0), a.sc_t);
     lse_d_n = __builtin_nan("");
     have_target_n = target_row<DT>(a, b, n) != nullptr;
   }
@@ -935,10 +943,11 @@ static int launch_verify(const VerifyArgs& a, hipStream_t st) {
     TapScope tap(SV_KERNEL_VERIFY_ROWS, st);
     const dim3 grid(rows * a.split), block(kRowsThreads);
     if constexpr (!CUT) {
-      if (a.whole) hipLaunchKernelGGL((verify_rows_kernel<DT, false, true>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((verify_rows_kernel<DT, false, false>), grid, block, 0, st, a);
+      if (a.whole && a.chained) hipLaunchKernelGGL((verify_rows_kernel<DT, false, kAsChained>), grid, block, 0, st, a);
+      else if (a.whole) hipLaunchKernelGGL((verify_rows_kernel<DT, false, kOverWhole>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT, false, kOverMax>), grid, block, 0, st, a);
     } else {
-      hipLaunchKernelGGL((verify_rows_kernel<DT, true, false>), grid, block, 0, st, a);
+      hipLaunchKernelGGL((verify_rows_kernel<DT, true, kOverMax>), grid, block, 0, st, a);
     }
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;
@@ -1180,11 +1189,11 @@ static int accept_ratio_checked(const void* z_t, int t_rows_per_seq, const void*
     TapScope tap(SV_KERNEL_VERIFY_ROWS, st);
     const dim3 grid(rows * a.split), block(kRowsThreads);
     if (dtype == SV_F32) {
-      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_F32, true, false>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((verify_rows_kernel<DT_F32, false, false>), grid, block, 0, st, a);
+      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_F32, true, kOverMax>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT_F32, false, kOverMax>), grid, block, 0, st, a);
     } else {
-      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, true, false>), grid, block, 0, st, a);
-      else hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, false, false>), grid, block, 0, st, a);
+      if (cut) hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, true, kOverMax>), grid, block, 0, st, a);
+      else hipLaunchKernelGGL((verify_rows_kernel<DT_BF16, false, kOverMax>), grid, block, 0, st, a);
     }
   }
   if (launch_status() != SV_OK) return SV_ERR_LAUNCH;

@@ -233,7 +233,7 @@ __device__ __forceinline__ void sweep_online_top4(const void* row, int V, Online
       top.add((okey(vmax) & 0xFFFF0000u) | (uint32_t)(i / nt + u));   // i = tid + step * nt
       mx = fmaxf(mx, vmax);
     }
-    const float cn = OnlineWide::ref(mx, L), scale = exp2_fast(acc.c - cn);
+    const float cn = acc.ref(mx, L), scale = exp2_fast(acc.c - cn);
     float t = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
