@@ -132,7 +132,7 @@ enum Refs { kOverMax, kOverWhole, kAsChained };          // sums over c(m), over
 
 template <class Sum, bool EITHER = false>
 struct OnlineOf {
-  static constexpr bool kWide = sizeof(Sum) == 8;
+  static constexpr bool kWide = sizeof(Sum) == 8, kEither = EITHER;
   float m;   // running maximum (raw units); -inf before the first element
   float c;   // max(fl32(m * L), kRefFloor), for the wide sum rounded up to a whole number
   Sum s;     // sum of 2^(z*L - c) so far
@@ -184,6 +184,8 @@ struct OnlineOf {
     const float mx = fmaxf(m, z);
     const float cn = ref(mx, L);
     s = scaled(s, exp2_fast(c - cn), exp2_fast(__builtin_fmaf(z, L, -cn)));
+    // (over c(m) the sum of an entry past the last vector and of its lane's vector is rounded as in the fp32 sums it is compared with)
+    if (EITHER && !(magic & kChainWhole)) s = (Sum)(float)s;
     m = mx;
     c = cn;
   }
@@ -552,11 +554,27 @@ __device__ __forceinline__ void sweep_online(const void* row, int V, int part, i
     for (int u = 0; u < U - 1; ++u)
       if (i + u * nt < end) add_vec(q[u]);
   }
-  if (part == split - 1)
+  if (part == split - 1) {
+    if constexpr (Acc::kEither) {
+      // The statistics over whole references add the entries past the last whole vector as one: a vector that shares
+      // its first entries with the one before it.
+      if ((acc.magic & kChainWhole) && nvec > 0) {
+        const int rest = V - nvec * EPV;
+        if (rest != 0 && (nvec - part * per - tid) % nt == 0) {
+          float f[EPV];
+          unpack<DT>(load_vec(static_cast<const char*>(row) + (size_t)(V - EPV) * Elem<DT>::bytes, 0), f);
+#pragma unroll
+          for (int j = 0; j < EPV; ++j) f[j] = j < EPV - rest ? -INFINITY : f[j];
+          acc.add(f, L);
+        }
+        return;
+      }
+    }
     for (int v = nvec * EPV + tid; v < V; v += nt) {
       const float z = load_elem<DT>(row, v);
       acc.add1(CUT ? cut_below(z, cut) : z, L);
     }
+  }
 }
 
 // ---------------------------------------------------------------------------

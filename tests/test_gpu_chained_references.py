@@ -75,3 +75,17 @@ def test_equal_rows_have_no_residual_where_plain_statistics_keep_c_of_m(V, dtype
 @pytest.mark.parametrize("n", [3, 20])
 def test_equal_rows_of_more_tokens_have_no_residual_after_plain_statistics(V, dtype, B, n):
     _assert_no_residual(*_equal_rows(V, dtype, B, 1, n), "plain")
+
+
+# the entries past a row's last whole vector, as the statistics add them: rows whose only tokens are these
+@pytest.mark.parametrize("form", ["plain", "kl"])
+@pytest.mark.parametrize("V,dtype,n", [(4103, "bf16", 2), (4103, "bf16", 7), (4097, "bf16", 2), (9, "bf16", 2), (15, "bf16", 7), (32007, "bf16", 5), (4099, "f32", 2),
+                                       (4099, "f32", 3), (7, "f32", 3), (30001, "f32", 2)])
+def test_equal_rows_of_tokens_past_the_last_vector_have_no_residual(V, dtype, n, form):
+    g = np.random.default_rng(V + n)
+    B = 96
+    z_t = torch.full((B, 2, V), float("-inf"))
+    z_t[:, :, V - n:] = torch.from_numpy(g.normal(0.0, 2.0, (B, 1, n)).astype(np.float32))
+    z_t = z_t.to(torch.float32 if dtype == "f32" else torch.bfloat16).cuda()
+    x = torch.zeros((B, 1), dtype=torch.int32, device="cuda")
+    _assert_no_residual(z_t, z_t[:, :1].contiguous(), x, form)
