@@ -479,11 +479,12 @@ __device__ __forceinline__ bool list_nucleus_step(const void* row, int V, float 
 // m - T ln(V / (1 - P)) for top-p, or 2^-32 of the top entry's mass where a K has to be found) lie within 32 octaves of
 // either sign, 128 values each, so 8192 counters hold one value each - but for those under 2^-31 of the largest magnitude,
 // which share a counter with zero; a cutoff there, or below the lowest counter, is left to the other ways.  The counts in
-// descending order of the value, times one exponential per counter, are all that top-k and top-p ask about: no further
+// descending order of the value, times fp64 masses of the values, are all that top-k and top-p ask about: no further
 // sweep, list or sort, and no order that sums depend on.
-// Cutoffs of 200 rows at P = 0.9, us, lists and steps of the exponent / counts from cache / counts of rows in registers:
-// 32000 entries, 2500 tokens kept 48.9 / 23.0 / 13.9, 40 kept 21.4 / 15.6 / 13.3; 128256, 8000 kept 79.8 / 40.5; K = 2000 and P =
-// 0.95 at 32000 (radix levels before) 59.5 / 22.6 / 14.9, at 128256 166 / 38.
+// Cutoffs of 200 rows at P = 0.9, us, lists and steps of the exponent / counts: 32000 entries (held in registers), 2800 tokens
+// kept 35.7 / 12.5, 36 kept 26.7 / 12.4; 128256 (from cache), 8500 kept 80.1 / 35.8; K = 2000 and P = 0.95 at 32000 (radix levels
+// before) 59.4 / 14.2, at 128256 166 / 34.8.  (With an fp32 exponential per counter, 3e-7 off in the exponent: 13.2, 13.1, 39.7, 15.5,
+// 37.8.)
 struct ValueBins {
   uint32_t base, top;                                      // magnitudes (15 bits) of the lowest and highest counter of a sign
   float from;                                              // the lowest value that is counted
@@ -522,8 +523,9 @@ struct ValueBins {
       if (f[2 * i + 1] >= from) atomicAdd(reinterpret_cast<uint32_t*>(b + (both >> 16)), 1u);
     }
   }
+  __device__ __forceinline__ int place(float v) const { return places(__float_as_uint(v)).y; }       // (a bfloat16 value is the upper half)
   __device__ __forceinline__ void count_one(uint32_t* bins, float v) const {
-    if (v >= from) atomicAdd(&bins[slot_of(places(__float_as_uint(v)).y)], 1u);        // (a bfloat16 value is the upper half)
+    if (v >= from) atomicAdd(&bins[slot_of(place(v))], 1u);
   }
   // The value of a counter (of those that share one: the largest magnitude).
   __device__ __forceinline__ bool shared(int place) const { return place == kSteps / 2 || place == kSteps / 2 - 1; }
@@ -540,39 +542,29 @@ __device__ __forceinline__ void clear_bins(WarpShared& sh) {
   if (threadIdx.x == 0) sh.near_any = 0;
 }
 
-// The cutoff from the counts of a row's values in sh.steps (complete: a barrier lies between).  Called by all threads.
-// False: the counters do not tell.
-__device__ __forceinline__ bool cutoff_of_bins(const ValueBins& vb, float lt, int top_k, bool use_k, float top_p, float m,
-                                               double row_s, WarpShared& sh, float* cutoff) {
+// The cutoff from the counts of a row's values in sh.steps (complete: a barrier lies between); row_Z is the sum of
+// exp((z - m) / T) over the row.  Called by all threads.  False: the counters do not tell.
+__device__ __forceinline__ bool cutoff_of_bins(const ValueBins& vb, double inv_t, int top_k, bool use_k, float top_p, float m,
+                                               double row_Z, WarpShared& sh, float* cutoff) {
   constexpr int kRun = kSteps / kWarpThreads, kWaves = kWarpThreads / kWave;
   static_assert(kRun == 16, "slot_of pads one word per lane's run");
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const bool use_p = top_p < 1.0f;
-  const float c_ref = ref_of(m, lt);
   const int last = kSteps - 1 - tid * kRun;                // this lane's counters: last, last - 1, ..., in descending order
-  // (read again where they are needed again: sixteen registers fewer, and four workgroups fit a compute unit)
   const uint32_t* run_end = sh.steps + ValueBins::slot_of(last - (kRun - 1));
-  auto count_of = [&](int j) { return run_end[kRun - 1 - j]; };
-  // (a run's values are all of one sign)
-  const uint32_t first_bits = __float_as_uint(vb.value(last)), next_bits = last < kSteps / 2 ? 1u << 16 : ~0u << 16;
-  float e[kRun];                                           // the mass of one entry
-  auto mass_of = [&](uint32_t c, int j) { return (double)c * (double)e[j]; };
+  // The values of a lane's counters are equally spaced (they share sign and exponent), so their masses are a power series: two
+  // exponentials for sixteen of them.  The counters above m are empty, and what they would weigh can be infinite.
   int n_mine = 0;
+  uint32_t c[kRun];
+#pragma unroll
+  for (int j = 0; j < kRun; ++j) { c[j] = run_end[kRun - 1 - j]; n_mine += (int)c[j]; }
   double m_mine = 0.0;
+  if (use_p && __ballot(n_mine != 0)) {                    // (a nucleus lies in the counters of one or two wavefronts)
+    const int above = min(max(last - vb.place(m), 0), kRun - 1);
+    const double ratio = exp(((double)vb.value(last - 1) - (double)vb.value(last)) * inv_t);
 #pragma unroll
-  for (int j0 = 0; j0 < kRun; j0 += 4) {
-    uint32_t c[4], any = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { c[j] = count_of(j0 + j); any |= c[j]; n_mine += (int)c[j]; e[j0 + j] = 0.f; }
-    if (__ballot(any != 0)) {                              // (a nucleus lies in the counters of one or two wavefronts)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float w = exp2_fast(__builtin_fmaf(__uint_as_float(first_bits + (uint32_t)(j0 + j) * next_bits), lt, -c_ref));
-        e[j0 + j] = c[j] ? w : 0.f;                        // (infinite for counters far above the row)
-        m_mine += mass_of(c[j], j0 + j);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int j = kRun - 1; j >= 0; --j) m_mine = j >= above ? __builtin_fma(m_mine, ratio, (double)c[j]) : m_mine;
+    m_mine = n_mine ? m_mine * exp(((double)vb.value(last - above) - (double)m) * inv_t) : 0.0;
   }
   const double m_incl = wave_scan_f64(m_mine);
   const int n_incl = wave_scan_i32(n_mine);
@@ -583,20 +575,25 @@ __device__ __forceinline__ bool cutoff_of_bins(const ValueBins& vb, float lt, in
 #pragma unroll
   for (int w = 0; w < kWaves; ++w)
     if (w < wave) { before += sh.wave_m[w]; n_before += sh.wave_c[w]; }
-  double total = row_s;
+  // The sixteen counters of one of the wavefront's lanes, a lane for each: place, entries, entries and mass up to it.
+  struct Stretch { int place; uint32_t c; double n, run; };
+  auto stretch_of = [&](int owner) {
+    Stretch t;
+    t.place = kSteps - 1 - (wave * kWave + owner) * kRun - (lane & (kRun - 1));
+    t.c = lane < kRun ? sh.steps[ValueBins::slot_of(t.place)] : 0;
+    t.n = lane_f64(n_before, owner) + (double)wave_scan_i32((int)t.c);
+    const double mass = t.c ? exp(((double)vb.value(t.place) - (double)m) * inv_t) : 0.0;      // (of one entry)
+    t.run = lane_f64(before, owner) + wave_scan_f64((double)t.c * mass);
+    return t;
+  };
+  double total = row_Z;
   int at_k = 0;                                            // counter of the K-th largest value
   if (use_k) {
-    if (n_before < (double)top_k && n_before + (double)n_mine >= (double)top_k) {
-      double n = n_before, run = before;
-#pragma unroll
-      for (int j = 0; j < kRun; ++j) {
-        if (n < (double)top_k) {
-          const uint32_t c = count_of(j);
-          n += (double)c;
-          run += mass_of(c, j);
-          if (n >= (double)top_k) { sh.last_reach = last - j; sh.sel_mass_above = run; }
-        }
-      }
+    const unsigned long long owner = __ballot(n_before < (double)top_k && n_before + (double)n_mine >= (double)top_k);
+    if (owner) {
+      const Stretch t = stretch_of((int)__builtin_ctzll(owner));
+      const unsigned long long reach = __ballot(t.n >= (double)top_k);
+      if (lane == (int)__builtin_ctzll(reach)) { sh.last_reach = t.place; sh.sel_mass_above = t.run; }
     }
     __syncthreads();
     at_k = sh.last_reach;
@@ -606,17 +603,13 @@ __device__ __forceinline__ bool cutoff_of_bins(const ValueBins& vb, float lt, in
   }
   // The end of the first group of equal values whose running mass reaches P; ends up to it that lie close to P.
   const double want = (double)top_p * total, tie = kNearTie * total;
-  if (n_mine && before < want && before + m_mine >= want - tie) {
-    double run = before;
-#pragma unroll
-    for (int j = 0; j < kRun; ++j) {
-      const uint32_t c = count_of(j);
-      if (c && run < want) {
-        run += mass_of(c, j);
-        if (fabs(run - want) < tie) sh.near_any = 1;
-        if (run >= want) sh.first_reach = last - j;
-      }
-    }
+  unsigned long long owners = __ballot(n_mine && before < want && before + m_mine >= want - tie);
+  for (; owners; owners &= owners - 1) {
+    const Stretch t = stretch_of((int)__builtin_ctzll(owners));
+    const unsigned long long reach = __ballot(t.c != 0 && t.run >= want);
+    const int first = reach ? (int)__builtin_ctzll(reach) : kRun;
+    if (t.c != 0 && lane <= first && fabs(t.run - want) < tie) sh.near_any = 1;
+    if (lane == first && reach) sh.first_reach = t.place;
   }
   __syncthreads();
   const int at = sh.first_reach;
@@ -742,7 +735,7 @@ __device__ __forceinline__ float general_cutoff(const void* row, int V, float lt
       if (nvec * EPV + tid < V) vb.count_one(sh.steps, load_elem<DT>(row, nvec * EPV + tid));
       __syncthreads();
       float cutoff;
-      const bool told = cutoff_of_bins(vb, lt, top_k, use_k, top_p, m, sh.row_s, sh, &cutoff);
+      const bool told = cutoff_of_bins(vb, inv_t, top_k, use_k, top_p, m, sh.row_Z, sh, &cutoff);
       if (told) {
         if (tid == 0) sh.near_tie = sh.near_any;
         return cutoff;
@@ -1308,7 +1301,7 @@ __global__ __launch_bounds__(kWarpThreads, 8) void warp_cutoffs_kernel(int V, Wa
 }
 
 // Cutoffs of bfloat16 rows that a workgroup holds in its registers, R vectors a lane: one read of the row, the maximum, the
-// normaliser and the counts of its values (ValueBins).  8 x 32000 at P = 0.9, 2500 tokens kept: 10.6 us (27.8 in three sweeps
+// normaliser and the counts of its values (ValueBins).  8 x 32000 at P = 0.9, 2700 tokens kept: 9.9 us (28.6 in three sweeps
 // and a sort), the first loads 3, the two looks at the entries 3, the scan of the counters 2.  Bound by arithmetic, about 12
 // operations an entry, where there are more rows than fit at once (1600 x 32000: 44 us, 122 before).  Up to 64 registers, for
 // four rows on a compute unit (with 79, three: 800 x 32000 30.7 us, 29.4 with four).
@@ -1379,20 +1372,20 @@ __global__ __launch_bounds__(kWarpThreads, R <= 8 ? 8 : 4) void warp_cutoffs_res
   float cutoff = -INFINITY;
   uint32_t fl = 0;
   bool done = true;
+  const double m_t = (double)m * sc.inv_t, row_Z = ms.s * exp((double)c_ref * kLn2 - sc.tau1 * m_t - m_t);
   if (bad_row(ms)) {
     cutoff = __builtin_nanf("");
     fl = SV_FLAG_BAD_ROW;
   } else if (use_k || use_p) {
-    done = cutoff_of_bins(vb, lt, top_k, use_k, top_p, m, ms.s, sh, &cutoff);
+    done = cutoff_of_bins(vb, sc.inv_t, top_k, use_k, top_p, m, row_Z, sh, &cutoff);
     fl = sh.near_any ? SV_FLAG_NEAR_TIE : 0u;
   }
   if (!done) {
     __syncthreads();
     if (tid == 0) {
-      const double m_t = (double)m * sc.inv_t;
       sh.counted = 1;
       sh.row_s = ms.s;
-      sh.row_Z = ms.s * exp((double)c_ref * kLn2 - sc.tau1 * m_t - m_t);
+      sh.row_Z = row_Z;
     }
     cut_general_row<DT_BF16>(row, r, V, lt, sc.inv_t, top_k, top_p, m, b.cutoff[t], b.flags[t], nullptr, nullptr, sh);
     return;

@@ -52,3 +52,26 @@ def test_both_sides_of_the_line_agree(V, rows):
         near = (out[0][1] | out[1][1]) != 0
         assert ((out[0][0] == out[1][0]) | near).all()
         assert int(near.sum()) <= rows // 20
+
+
+# One value and 65534 equal ones, 10.6 to 11.6 T below it, about as heavy together; one entry out of the K largest.  P lies 2 to
+# 4 % inside or outside the band of a near tie around the top value's share, and the fp32 exponent's rounding
+# of the lower value, up to 5e-7 of its mass, is 4 to 10 % of that band: the masses have to be better than fp32.
+EDGE = [(1.4409691095352173, 31.875, 15.625, 0.54656982421875, False), (1.4184449911117554, 24.375, 8.4375, 0.5363317728042603, False),
+        (0.7103328704833984, 29.0, 21.0, 0.5428975224494934, True), (0.6587724089622498, 36.5, 29.0, 0.5730973482131958, True),
+        (1.4334756135940552, 27.125, 11.4375, 0.46340182423591614, True), (0.7185483574867249, 16.625, 8.6875, 0.4890678822994232, True),
+        (0.7185483574867249, 16.625, 8.6875, 0.4890618920326233, False), (1.4334756135940552, 27.125, 11.4375, 0.46340784430503845, False)]
+
+
+@pytest.mark.parametrize("V", [65536, 65600])                 # held in registers, read again from cache
+@pytest.mark.parametrize("T,top,low,Pp,near", EDGE)
+def test_masses_of_the_counters_are_not_rounded_to_fp32(V, T, top, low, Pp, near):
+    share = 1.0 / (1.0 + 65534 * np.exp((low - top) / T))
+    assert (abs(share - Pp) < 3e-6) == near and abs(abs(share - Pp) - 3e-6) > 6e-8
+    z = torch.full((1, V), -1e4)
+    z[0, V - 65534:] = low
+    z[0, 0] = top
+    cut, fl = torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    H.sv().sv_warp_cutoffs(z.to(torch.bfloat16).cuda(), T, 65535, Pp, cut, fl)
+    assert float(cut[0]) == (top if share >= Pp else low)
+    assert bool(int(fl[0]) & 2) == near
