@@ -38,6 +38,7 @@
 // downstream can work on a few dozen entries per row instead of V.
 #include "sv_device.hpp"
 #include "sv_host.hpp"
+#include "warp_rules.hpp"
 
 // Phase marks: empty in the library; a profiling build may define
 // SV_PHASE_MARK(n) to record a clock at the boundaries of the kernel's phases.
@@ -47,12 +48,10 @@
 
 namespace sv {
 
-constexpr int kWarpThreads = 512;
 constexpr int kBins = 2048;
 constexpr int kCand = 2048;          // capacity of the candidate list
 constexpr int kSteps = 8192;         // counters of list_nucleus_step
 constexpr int kGuessRank = 384;      // top-p alone: tau = this rank among the lane maxima
-constexpr int kResidentMax = 16 * kWarpThreads * Elem<DT_BF16>::per_vec;   // entries of a row that a workgroup holds
 constexpr double kNearTie = 3e-6;    // flagged band of a top-p decision
 
 __device__ __forceinline__ uint32_t okey(float f) {            // ascending order-preserving key
@@ -862,9 +861,13 @@ constexpr int kNucleusRank2 = 256;
 // 32000 fp32 entries at P = 0.9, us with 0.6 / 0.8 / 1.0 (always a list first: 59): 3600 tokens kept 57 / 42 / 43, 310 kept
 // 54 / 38 / 39, 39 kept 29 / 30 / 35, 12 kept 26 / 26 / 30; 800 of 128256: 1140 kept 187 / 187 / 172, 98 kept 108 / 100 / 158, 41
 // kept 86 / 88 / 127.
-// The counts of a bfloat16 row's values cost less than that list, where the row comes from cache: with 0.8 / 1.0, 200 x
-// 128256 66.8 / 38.4 (600 kept) and 34.9 / 29.1 (30 kept), 800 x 32000 56.4 / 50.5 and 24.7 / 21.2; but 1600 x 128256, where
-// it comes from memory, 115 / 144 (120 kept), 800 x 152064 91 / 98.
+// The counts of a bfloat16 row's values cost less than that list where a row's latency counts, and more where the rows' bytes do: a
+// second list reads a few vectors again, the counts the whole row.  0.8 / 1.0, us, at 8500, 650, 85 to 107, 21 and 5 tokens kept
+// (of 65536 half as many): 200 x 128256 45.8 / 36.2, 66.1 / 35.7, 45.8 / 36.0, 38.8 / 34.3, 27.6 / 25.2; 1024 x 65536 77.3 / 68.0, 70.6 / 65.9, 53.2 /
+// 54.2, 47.8 / 43.0, 40.1 / 35.1; 600 x 128256 84.5 / 80.8, 101 / 79.3, 70.3 / 72.7, 66.5 / 59.0, 52.9 / 46.8; 800 x 128256 107 / 106, 119 / 104, 80.9 /
+// 94.6, 74.5 / 67.7, 60.1 / 54.2; 800 x 152064 123 / 123, 139 / 121, 90.9 / 111, 86.1 / 84.2, 70.1 / 65.0; 1600 x 65536 108 / 106, 104 / 103, 76.7 /
+// 86.1, 62.3 / 59.1, 53.4 / 48.3; 1600 x 128256 188 / 188, 199 / 187, 130 / 164, 105 / 116, 96.8 / 85.4.  The line lies where the most that
+// either loses is the same, 15 to 17 %, which is at 100 M entries of at most a round of rows (four to a compute unit).
 constexpr double kHopeless = 0.8;
 // (bfloat16 rows beside one another, and their entries, up to which a list has to promise all of P)
 constexpr long long kHopelessRows = 1024, kHopelessEntries = 105000000;
@@ -1303,8 +1306,8 @@ __global__ __launch_bounds__(kWarpThreads, 8) void warp_cutoffs_kernel(int V, Wa
 // Cutoffs of bfloat16 rows that a workgroup holds in its registers, R vectors a lane: one read of the row, the maximum, the
 // normaliser and the counts of its values (ValueBins).  8 x 32000 at P = 0.9, 2700 tokens kept: 9.9 us (28.6 in three sweeps
 // and a sort), the first loads 3, the two looks at the entries 3, the scan of the counters 2.  Bound by arithmetic, about 12
-// operations an entry, where there are more rows than fit at once (1600 x 32000: 44 us, 122 before).  Up to 64 registers, for
-// four rows on a compute unit (with 79, three: 800 x 32000 30.7 us, 29.4 with four).
+// operations an entry, where there are more rows than fit at once (1600 x 32000: 43.4 us, 71.2 by lists).  Up to 64 registers, for
+// four rows on a compute unit (with 79, three: 800 x 32000 30.7 us, 29.4 with four, when this was chosen).
 template <int R>
 __global__ __launch_bounds__(kWarpThreads, R <= 8 ? 8 : 4) void warp_cutoffs_resident_kernel(int V, WarpBatch b) {
   __shared__ WarpShared sh;
@@ -1439,13 +1442,7 @@ int launch_warp(int n, const void* const* z, const int* rows, int V, int dtype, 
   if (total == 0) return SV_OK;
   b.hopeless = dtype == SV_BF16 && total <= kHopelessRows && total * V <= kHopelessEntries ? 1.0 + 1e-6 : kHopeless;
   hipStream_t st = as_stream(stream);
-  // Rows held in registers: every size for K > 512, for which there are no lists (1600 x 65536, K = 2000: 96 us, 423 before).
-  // For top-p the lists take less of short nuclei once the chip is full: 4000 x 25000, 30 tokens kept, 59.2 with them and 65.9;
-  // 800 x 32000 24.7 and 27.4 (2500 kept: 75.6 and 29.4); 400 x 32000 21.2 and 17.6; 1600 x 24576 of 3 tokens kept 29.6 and
-  // 30.3.  For K up to 512 they are the better way throughout: 200 x 32000, K = 20 10.1 and 16.3.
-  const bool few = V <= 24576 ? total * V <= 40000000 : V <= kResidentMax / 2 && total <= 512;
-  bool resident = !outs && dtype == SV_BF16;
-  for (int t = 0; t < n; ++t) resident = resident && (top_k[t] > kWarpThreads ? V <= kResidentMax : top_k[t] <= 0 && few);
+  const bool resident = !outs && dtype == SV_BF16 && rows_in_registers(total, V, n, top_k);
   if (dtype == SV_F32)
     hipLaunchKernelGGL(warp_cutoffs_kernel<DT_F32>, dim3((unsigned)total), dim3(kWarpThreads), 0, st, V, b);
   else if (resident) {
