@@ -767,10 +767,12 @@ __device__ __forceinline__ int wave_max2_i32(int a, int b) {
 }
 
 // Workgroups that fit a compute unit: registers for the terms, references and sums, and for the pair in flight.
+// (Four bf16 places would need four registers more than two workgroups have: spilled, 2048 x 14000 27.5 us, 513 x 16384 13.1; one to a
+// compute unit 25.0 and 11.8, level from 4096 pairs on.)
 template <int DT, int P, bool ONE>
 constexpr int terms_per_cu() {
   constexpr int regs = P * (2 * Elem<DT>::per_vec + 2) + (ONE ? 20 : 8 * P + 24);
-  return regs <= 80 ? 3 : regs <= 128 ? 2 : 1;
+  return regs <= 80 ? 3 : regs < 128 ? 2 : 1;
 }
 
 template <int DT, int P, bool ONE>
@@ -1043,9 +1045,11 @@ static int launch_terms(const StatsArgs& a, hipStream_t st) {
 //    fit a lane's registers (bf16 up to 32768 entries; fp32 14336, 16384 in part), or the terms alone where there is a pair per
 //    compute unit at most (49152; 40960).  The better one of the others / terms, bf16: 64 x 1000 5.1 / 4.3; 64 x 32000 9.4 / 8.5;
 //    512 x 32000 18.4 / 17.8; 2048 x 8192 23.1 / 17.7; 8192 x 16384 114 / 91; 8192 x 32000 202 / 166.5 (6.3 TB/s); 256 x 40960 13.8 /
-//    11.7.  fp32: 64 x 14000 8.1 / 7.1; 2048 x 4096 20.1 / 15.9; 8192 x 10000 113 / 105; 256 x 32000 15.4 / 15.3.  Where it is not
-//    taken: fp32 768 x 16384 19.6 / 20.0, 300 x 20000 15.3 / 16.2, 64 x 49152 13.8 / 14.6, 600 x 1000 7.0 / 7.3.  (Warped rows: 10 to 30 %
-//    faster by it, but S of a nucleus of a few equal tokens is then an ulp off the half or third it should be.)
+//    11.7.  fp32: 64 x 14000 8.1 / 7.1; 2048 x 4096 20.1 / 15.9; 8192 x 10000 113 / 105; of 12, 16 and 20 places, the terms alone: 4 x
+//    17000 6.6 / 6.2, 64 x 18000 8.9 / 8.1, 4 x 24000 7.5 / 7.4, 256 x 24000 11.9 / 11.7, 4 x 32000 9.2 / 9.0, 32 x 30000 11.1 / 10.3, 128 x
+//    40000 13.9 / 13.4, level at 256 x 32000 and 2 x 32768.  Where it is not taken: fp32 768 x 16384 19.6 / 20.0, 300 x 20000 15.3 / 16.2,
+//    64 x 49152 13.8 / 14.6, 600 x 1000 7.0 / 7.3.  Three bf16 places / four: 513 x 12000 9.7 / 11.1, 2048 x 10000 19.5 / 21.0, 8192 x 8200 59.0 /
+//    62.9.  (Warped rows would be 10 to 30 % faster by it, in other bits: sv_device.hpp, whole_ref.)
 template <int DT, bool WITH_KL, bool WARP>
 static int launch_stats(const StatsArgs& a, hipStream_t st) {
   constexpr bool kBf16 = DT == DT_BF16;
@@ -1056,6 +1060,7 @@ static int launch_stats(const StatsArgs& a, hipStream_t st) {
     const int steps = (a.V + nt * Elem<DT>::per_vec - 1) / (nt * Elem<DT>::per_vec);
     if constexpr (kBf16) {
       if (steps <= 2) return launch_terms<DT, 2>(a, st);
+      if (steps <= 3) return launch_terms<DT, 3>(a, st);
       if (steps <= 4) return launch_terms<DT, 4>(a, st);
       if (steps <= 6) return launch_terms<DT, 6>(a, st);
       if (steps <= 8) return launch_terms<DT, 8>(a, st);

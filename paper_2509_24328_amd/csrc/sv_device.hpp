@@ -216,8 +216,9 @@ __device__ __forceinline__ float ref_of(float m, const float L = kL32) { return 
 // A chained call sums the target as the statistics summed the draft (ChainHeader::magic): equal rows of a few tokens in lanes
 // of their own have equal normalisers then, and no residual of their roundings.  A target over whole numbers beside a
 // draft over c(m) would have one: of equal rows of three tokens two in five.
-// (Over c(m) the term of a row's maximum is 1 to within 1e-6, and the masses of a nucleus of a few equal tokens come out as exact
-// halves and thirds: those of warped rows keep it.)
+// (Warped rows keep c(m).  The S of their nuclei of a few equal tokens is a half or a third, an ulp off in half of the rows over c(m) and
+// in a tenth of them over whole references, and a half is an edge of the acceptance estimate: the other form would move
+// estimates either way, in 22 of 60 steps of 32 x 8 x 128256.)
 __device__ __forceinline__ float whole_ref(float m) { return __builtin_ceilf(ref_of(m)); }
 // Where the statistics may sum over whole references (launch_stats goes by it; the row sweep of independent calls too): rows of
 // T = 1 without cutoffs, up to the longest that a lane's registers hold the terms of, longer ones up to a pair per compute unit.

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 ROWS = [(8, "bf16"), (9, "bf16"), (511, "bf16"), (513, "bf16")]
 ROWS += [(p * 4096 + d, "bf16") for p in (1, 2, 4, 6, 8) for d in (-7, 0, 1)] + [(7 * 4096 + 520, "bf16"), (10 * 4096, "bf16"),
                                                                               (10 * 4096 + 1, "bf16"), (12 * 4096, "bf16"), (12 * 4096 + 3, "bf16")]
+ROWS += [(3 * 4096 + d, "bf16") for d in (-7, 0, 1)]
 ROWS += [(4, "f32"), (5, "f32"), (255, "f32")]
 ROWS += [(p * 2048 + d, "f32") for p in (1, 2, 4, 7, 8, 12) for d in (-3, 0, 1)] + [(16 * 2048 + 1, "f32"), (20 * 2048, "f32"), (20 * 2048 + 1, "f32")]
 
