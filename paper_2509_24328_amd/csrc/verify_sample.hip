@@ -752,7 +752,8 @@ __global__ __launch_bounds__(kPickThreads) void verify_pick_kernel(VerifyArgs a)
 // memory, two reductions: 8 x 4096 bf16 9.0 us with the row sweep, 12.8 in two kernels) and, on the longest rows, by
 // the arithmetic of a row pair on one compute unit (4 us of 32000 entries).
 // G < J: the runs of a wavefront are weighed G at a time and the token's run once more; two workgroups of 1024 lanes then fit a
-// compute unit, for more sequences than there are of these.
+// compute unit, for more sequences than there are of these.  (They leave 78 scalar registers, of which 12 to 27 are spilled to
+// vector registers, ahead of the weights' loops and behind them.)
 template <int DT, bool CUT, bool CHAIN, bool WHOLE, int THREADS, int J, int G>
 __global__ __launch_bounds__(THREADS, G < J ? 8 : 4) void verify_draw_kernel(VerifyArgs a) {
   constexpr int EPV = Elem<DT>::per_vec, kEach = 8, kVecs = kEach / EPV, kWaves = THREADS / kWave;
@@ -923,17 +924,30 @@ static int rows_split(int rows, int V) {
 static int wide_groups(int dtype, int granules) { return dtype == DT_F32 || granules == 1 ? 512 : 256; }
 
 // One kernel for decision, masses and token (verify_draw_kernel), or two that spread a sequence over workgroups?  One saves a launch
-// and its loads; a workgroup alone pays for the arithmetic of a long row.  us of the call, two kernels / one: 8 x 4096 bf16
-// 12.8 / 9.0; 512 x 4096 19.4 / 14.9; 8 x 8192 12.8 / 9.7; 2048 x 8192 57.7 / 57.3; 8 x 16384 12.8 / 10.9; 2048 x 16384 104 / 95;
-// fp32, 8 x 16384 13.2 / 11.4, 1024 x 16384 92.3 / 90.0, 2048 x 16384 171.4 / 172.9.  Above, with 1024 lanes to a
-// sequence, from 33 sequences on: 8 x 32000 13.4 / 13.9; 64 x 32000 20.2 / 18.6; 256 x 32000 38.1 / 33.7; then two sequences to a
-// compute unit: 300 x 24000 36.5 / 37.2; 512 x 32000 57.3 / 52.3 (one to a compute unit, which keeps its weights: 54.5); 1024 x 32000
-// 96.9 / 93.5; 2048 x 24000 136.7 / 142.8; fp32, 256 x 32000 48.4 / 44.1; 2048 x 32000 299.8 / 284.8.  (Less than eight entries: two
-// kernels.)
+// and its loads; but a workgroup alone pays for the arithmetic of a long row, and it weighs as many runs as it has wavefronts
+// whatever the row's length, which counts once the sequences are many.  us of the call, two kernels / one, by sequences:
+//  * up to 4096 entries: bf16 256 x 1000 14.6 / 9.7; 2048 x 1000 29.8 / 29.0; 4096 x 1000 48.3 / 51.0; 16384 x 64 138 / 175; 2048 x 4096 35.4 /
+//    32.3, 4096 58.2 / 56.8, 8192 102 / 107; fp32, 2048 x 1000 30.7 / 29.1, 4096 49.6 / 50.8; 4096 x 2000 53.8 / 53.1, 8192 94.3 / 99.7; 16384 x
+//    4096 269 / 227
+//  * up to 8192: bf16 8 x 8192 12.8 / 9.7; 1024 x 5000 24.9 / 23.3, 1280 29.5 / 29.5, 1536 31.4 / 32.7, 8192 111 / 143; 1536 x 8192 37.9 / 37.7,
+//    2048 46.9 / 48.1, 8192 130 / 155; fp32, 4096 x 5000 83.7 / 82.7, 8192 151 / 158; 16384 x 8192 406 / 379
+//  * up to 16384: bf16 8 x 16384 12.9 / 10.8; 256 21.0 / 15.6; 2048 67.1 / 65.1, 3000 90.3 / 91.9, 4096 114 / 117; fp32, 8 x 16384 13.1 / 11.1,
+//    1024 57.2 / 55.1, 1200 64.7 / 65.1, 4096 188 / 201
+//  * up to 32768 with 1024 lanes to a sequence: bf16 32 x 17000 15.1 / 14.7, 32 x 24000 15.0 / 15.2, 32 x 32768 15.2 / 15.7; 40 x 32000 17.2 / 16.5,
+//    256 37.8 / 32.9; fp32, 1 x 4 x 17000 12.3 / 12.5; 2 x 4 x 17000 13.0 / 12.6; 8 x 32000 14.1 / 13.8; 256 48.3 / 42.9
+//  * from 257 sequences on of these two to a compute unit (one to a compute unit, which keeps its weights: 512 x 32000 54.5): bf16 300 x
+//    17000 27.7 / 28.3, 512 43.6 / 41.4, 640 35.6 / 38.3, 1024 51.8 / 55.8; 300 x 32000 35.5 / 34.2, 512 55.6 / 50.8, 1024 77.0 / 75.8, 2048 127 / 129;
+//    fp32, 300 x 24000 36.1 / 34.7, 1024 91.9 / 86.8, 4096 258 / 240; 4096 x 17000 237 / 243
+// (Less than eight entries: two kernels.)
 static bool draws_at_once(int dtype, int B, int V) {
+  const bool bf16 = dtype == DT_BF16;
   if (V < 8 || V > 8 * kGranule) return false;
-  if (V > 4 * kGranule) return B > 32 && (B <= 256 || (B >= 384 && B <= (dtype == DT_BF16 ? 1024 : 4096)));
-  return V <= 2 * kGranule || dtype == DT_BF16 || B <= 1024;
+  if (V <= kGranule) return B <= (V <= kGranule / 2 ? 2048 : bf16 ? 4096 : 65535);
+  if (V <= 2 * kGranule) return B <= (bf16 ? 1280 : V <= 3 * kGranule / 2 ? 4096 : 65535);
+  if (V <= 4 * kGranule) return B <= (bf16 ? 2048 : 1024);
+  if (!bf16) return B > 1 && B <= 4096;
+  if (V > 6 * kGranule) return B > 32 && B <= 1024;
+  return B > 32 && B <= 512 && (B <= 256 || B >= 384);
 }
 
 template <int DT, bool CUT>

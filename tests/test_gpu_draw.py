@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 
 SIZES = [(7, 3), (8, 3), (9, 40), (15, 5), (511, 9), (513, 9), (4095, 12), (4096, 33), (4097, 12), (8191, 9), (8192, 5), (8193, 40),
          (16383, 6), (16384, 6), (16385, 32), (16385, 33), (20003, 34), (32767, 33), (32768, 34), (32769, 33), (1003, 513), (17001, 383), (17001, 384), (16391, 513)]
+# the most sequences that a length is drawn at once for, and one more
+SIZES += [(2001, 2048), (2001, 2049), (4097, 1280), (4097, 1281), (17001, 1), (17001, 2), (17001, 256), (17001, 257), (25001, 257), (9001, 1025)]
 
 
 @pytest.mark.parametrize("chained", [False, True])
