@@ -11,7 +11,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include "warp_rules.hpp"
 int main() {
-  const int rows[] = {1, 200, 512, 513, 800, 1627, 4000, 70000}, sizes[] = {1, 8, 400, 513, 4096, 24576, 24577, 32768, 32769, 65536, 65537, 152064};
+  const int rows[] = {1, 200, 512, 513, 800, 1627, 4000, 70000}, sizes[] = {1, 8, 64, 65, 400, 513, 4096, 24576, 24577, 32768, 32769, 65536, 65537, 152064};
   for (int r : rows)
     for (int V : sizes) {
       const int off[] = {0, -1, V, V + 1, 1 << 30};
@@ -20,6 +20,7 @@ int main() {
         const int mixed[] = {0, k};
         if (sv::rows_in_registers(r, V, 2, mixed) != sv::rows_in_registers(r, V, 1, off)) { std::printf("%d x %d, K = 0 and %d\n", r, V, k); return 1; }
       }
+      if (V <= 64 && sv::rows_in_registers(r, V, 1, off)) { std::printf("%d x %d, a list for one wavefront\n", r, V); return 1; }
       const int deep = 513, list = 512;
       if (V > deep && sv::rows_in_registers(r, V, 1, &deep) != (V <= 65536)) { std::printf("%d x %d, deep\n", r, V); return 1; }
       if (V > list && sv::rows_in_registers(r, V, 1, &list)) { std::printf("%d x %d, list\n", r, V); return 1; }
