@@ -1,6 +1,6 @@
-"""sv_verify_sample on both sides of the line between the mass pass's two workgroup shapes (512 pairs of a sequence and
-a granule of 4096 entries, 256 in bfloat16 with several granules to a row): what one more sequence turns over must leave the others' results where they are, and
-both agree with the oracle."""
+"""sv_verify_sample on both sides of the lines between its ways to a token: the mass pass's two workgroup shapes (512 pairs of a
+sequence and a granule of 4096 entries, 256 in bfloat16 with several granules to a row), and the one kernel that draws short rows at once.  What
+one more sequence turns over must leave the others' results where they are, and both agree with the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -41,8 +41,15 @@ def _verify(cfg, B, chained, warped=False):
     return tok.cpu().numpy(), n.cpu().numpy(), fl.cpu().numpy()
 
 
-@pytest.mark.parametrize("B,V,dtype", [(512, 4096, "bf16"), (512, 4001, "f32"), (256, 4097, "bf16"), (170, 8200, "f32"), (64, 32000, "bf16"),
-                                       (128, 4097, "bf16"), (85, 8200, "bf16"), (32, 32000, "bf16")])
+# (the mass pass: a granule to a workgroup, two, or what the one becomes with one sequence more)
+MASS = [(28, 36000, "bf16"), (56, 36000, "f32"), (512, 7, "bf16"), (512, 7, "f32")]
+# (one kernel on both sides, and on one side only)
+DRAW = [(512, 4096, "bf16"), (512, 4001, "f32"), (256, 4097, "bf16"), (170, 8200, "f32"), (64, 32000, "bf16"),
+                                       (128, 4097, "bf16"), (85, 8200, "bf16"), (32, 32000, "bf16"), (40, 17001, "bf16"), (40, 17001, "f32"), (400, 17001, "bf16"), (256, 17001, "f32"), (2048, 1999, "bf16"),
+        (1280, 4099, "bf16"), (1024, 8201, "f32"), (512, 17001, "bf16")]
+
+
+@pytest.mark.parametrize("B,V,dtype", MASS + DRAW)
 @pytest.mark.parametrize("chained", [False, True])
 @pytest.mark.parametrize("warped", [False, True])
 def test_mass_pass_shapes_agree(B, V, dtype, chained, warped):

@@ -60,10 +60,15 @@ def test_residual_without_mass(V, dtype):
     assert V < 9000 or len(seen) > 1
 
 
+# long rows, and more sequences of short ones than are drawn at once
+LARGE = [(33000, "f32", 60), (36001, "bf16", 30), (9001, "f32", 1032), (5000, "bf16", 1284)]
+
+
 @pytest.mark.parametrize("chained", [False, True])
-@pytest.mark.parametrize("V,dtype,B", [(4097, "f32", 260), (8193, "bf16", 130), (12305, "bf16", 90), (9001, "f32", 180)])
+@pytest.mark.parametrize("V,dtype,B", [(4097, "f32", 260), (8193, "bf16", 130), (12305, "bf16", 90), (9001, "f32", 180)] + LARGE)
 def test_residual_without_mass_in_large_batches(V, dtype, B, chained):
-    """More than 512 (bfloat16: 256) pairs of a sequence and a granule: a workgroup of the mass pass takes two granules.
+    """More than 512 (bfloat16: 256) pairs of a sequence and a granule: a workgroup of the mass pass takes two granules
+    where short rows are not drawn at once, LARGE, and one kernel does it all where they are.
     Every third sequence has a residual, in one granule only."""
     n = 6                                                # a few different sequences, in turn
     cfg = svgen.make_config(1, seed=V + 3, B=n, k=1, V=V, dtype=dtype)
@@ -130,9 +135,10 @@ def test_residual_without_mass_under_cutoffs(V, dtype, chained):
 
 @pytest.mark.parametrize("chained", [False, True])
 @pytest.mark.parametrize("V,dtype,B", [(4097, torch.float32, 260), (8193, torch.bfloat16, 130), (12290, torch.bfloat16, 90),
-                                       (9001, torch.float32, 180)])
+                                       (9001, torch.float32, 180)]
+                         + [(V, torch.float32 if d == "f32" else torch.bfloat16, B) for V, d, B in LARGE])
 def test_residual_without_mass_under_cutoffs_in_large_batches(V, dtype, B, chained):
-    """The same where a workgroup takes two granules, the last of them alone in its chunk or with a partner."""
+    """The same where a workgroup takes two granules, the last of them alone in its chunk or with a partner (LARGE), and in one kernel."""
     _check_nuclei(V, dtype, B, chained, range(1))
 
 

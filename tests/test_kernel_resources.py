@@ -44,6 +44,14 @@ def test_the_mass_pass_of_large_batches_spills_nothing(tmp_path):
         cut, chained, wide = (m == "1" for m in re.search(r"Lb(\d)ELb(\d)ELb(\d)E", n).groups())
         if not chained:
             assert k["SGPRs"] == 0, (n, k)
+    # the other kernels of the sampling stage: what they spill, and no more.  The draw that weighs its runs one at a time leaves 78
+    # scalar registers, two workgroups of 1024 lanes to a compute unit.
+    for n, k in kernels.items():
+        if "verify_mass_of_whole_kernel" in n:
+            chained, wide = (m == "1" for m in re.search(r"Lb(\d)ELb(\d)E", n).groups())
+            assert k["SGPRs"] <= (20 if chained and not wide else 0), (n, k)
+        if "verify_draw_kernel" in n:
+            assert k["SGPRs"] <= (28 if "Li1024ELi4ELi1E" in n else 0), (n, k)
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no compiler")
