@@ -490,26 +490,30 @@ __device__ __forceinline__ double kappa_l32(const MS& r) {
 // are issued before the first use (a loop would pay one memory latency per part).
 constexpr int kMaxParts = 8;
 
-template <Refs REFS>
-__device__ __forceinline__ MS fold_row_parts(const float* m, const double* s, int split, const float L, uint32_t magic) {
-  float mp[kMaxParts];
-  double sp[kMaxParts];
+struct RowParts {
+  float m[kMaxParts];
+  double s[kMaxParts];
+  __device__ __forceinline__ void load(const float* mp, const double* sp, int split) {
 #pragma unroll
-  for (int p = 0; p < kMaxParts; ++p) {
-    const bool on = p < split;
-    mp[p] = on ? m[p] : -INFINITY;
-    sp[p] = on ? s[p] : 0.0;
+    for (int p = 0; p < kMaxParts; ++p) {
+      const bool on = p < split;
+      m[p] = on ? mp[p] : -INFINITY;
+      s[p] = on ? sp[p] : 0.0;
+    }
   }
+};
+template <Refs REFS>
+__device__ __forceinline__ MS fold_row_parts(const RowParts& t, const float L, uint32_t magic) {
   MS r;
-  r.m = mp[0];
+  r.m = t.m[0];
 #pragma unroll
-  for (int p = 1; p < kMaxParts; ++p) r.m = fmaxf(r.m, mp[p]);
+  for (int p = 1; p < kMaxParts; ++p) r.m = fmaxf(r.m, t.m[p]);
   const bool whole = REFS == kOverWhole || (REFS == kAsChained && (magic & kChainWhole));
   r.ref = whole ? whole_ref(r.m) : ref_of(r.m, L);
   r.s = 0.0;
 #pragma unroll
   for (int p = 0; p < kMaxParts; ++p)                    // absent parts add 0
-    r.s += sp[p] * (double)exp2_fast((whole ? whole_ref(mp[p]) : ref_of(mp[p], L)) - r.ref);
+    r.s += t.s[p] * (double)exp2_fast((whole ? whole_ref(t.m[p]) : ref_of(t.m[p], L)) - r.ref);
   return r;
 }
 

@@ -119,10 +119,15 @@ __device__ __forceinline__ const void* draft_row(const VerifyArgs& a, int b, int
 }
 
 // Normaliser of a whole row from the partials its workgroups left.
+__device__ __forceinline__ RowParts target_parts(const VerifyArgs& a, int b, int i) {
+  const int idx = (b * (a.k + 1) + i) * a.split;
+  RowParts t;
+  t.load(a.ws.m_t + idx, a.ws.s_t + idx, a.split);
+  return t;
+}
 template <Refs REFS>
 __device__ __forceinline__ MS target_ms(const VerifyArgs& a, int b, int i, const uint32_t magic = 0) {
-  const int idx = (b * (a.k + 1) + i) * a.split;
-  return fold_row_parts<REFS>(a.ws.m_t + idx, a.ws.s_t + idx, a.split, a.sc_t.L, magic);
+  return fold_row_parts<REFS>(target_parts(a, b, i), a.sc_t.L, magic);
 }
 // Chained calls: does the workspace hold the draft normalisers of this very step?  (The
 // header names the tensors, shape and scale the statistics pass was given; what the
@@ -142,7 +147,9 @@ __device__ __forceinline__ bool chain_matches(const VerifyArgs& a, const u32x4& 
 template <Refs REFS>
 __device__ __forceinline__ MS draft_ms(const VerifyArgs& a, int b, int i) {
   const int idx = (b * a.k + i) * a.split;
-  return fold_row_parts<REFS>(a.ws.m_d + idx, a.ws.s_d + idx, a.split, a.sc_d.L, 0);
+  RowParts t;
+  t.load(a.ws.m_d + idx, a.ws.s_d + idx, a.split);
+  return fold_row_parts<REFS>(t, a.sc_d.L, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -349,11 +356,12 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   // known (rows past the length hold whatever an earlier call left: read, never used), so that
   // the loads travel together instead of in three dependent rounds: length, partials, logits.
   const int it = min(i, k), id = min(i, k - 1);
+  const RowParts parts_t = target_parts(a, b, it);
   const float zx_t = a.ws.zx_t[b * k + id];
   const float zx_d = CHAIN ? chain_zx : a.ws.zx_d[b * k + id];
   const int tok = a.x[b * k + id];
   const bool target_there = target_index(a, b, it) >= 0;
-  const MS ms_t = target_ms<REFS>(a, b, it, w2.w);
+  const MS ms_t = fold_row_parts<REFS>(parts_t, a.sc_t.L, w2.w);
   bool chain_ok = true;
   if (CHAIN) {
     ms_d.ref = REFS == kAsChained && (w2.w & kChainWhole) ? whole_ref(ms_d.m) : ref_of(ms_d.m, a.sc_d.L);
