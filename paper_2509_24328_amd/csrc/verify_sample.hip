@@ -132,8 +132,6 @@ __device__ __forceinline__ MS target_ms(const VerifyArgs& a, int b, int i, const
 // Chained calls: does the workspace hold the draft normalisers of this very step?  (The
 // header names the tensors, shape and scale the statistics pass was given; what the
 // tensors contain is the caller's business.)
-// REFS: whether sums over either kind of reference will do.
-template <Refs REFS>
 __device__ __forceinline__ bool chain_matches(const VerifyArgs& a, const u32x4& w0, const u32x4& w1, const u32x4& w2) {
   const uint64_t zd = reinterpret_cast<uint64_t>(a.z_d), x = reinterpret_cast<uint64_t>(a.x),
                  cd = reinterpret_cast<uint64_t>(a.cut_d);
@@ -141,7 +139,7 @@ __device__ __forceinline__ bool chain_matches(const VerifyArgs& a, const u32x4& 
                   (w0.w ^ (uint32_t)(x >> 32));
   diff |= (w1.x ^ (uint32_t)cd) | (w1.y ^ (uint32_t)(cd >> 32)) | (w1.z ^ (uint32_t)a.B) | (w1.w ^ (uint32_t)a.k);
   diff |= (w2.x ^ (uint32_t)a.V) | (w2.y ^ (uint32_t)a.dtype) | (w2.z ^ __float_as_uint(a.sc_d.L)) |
-          ((REFS == kAsChained ? w2.w & ~kChainWhole : w2.w) ^ kChainMagic);
+          ((w2.w & ~kChainWhole) ^ kChainMagic);
   return diff == 0;
 }
 template <Refs REFS>
@@ -364,8 +362,9 @@ __device__ __forceinline__ void accept_plan(const VerifyArgs& a, const int b, co
   const MS ms_t = fold_row_parts<REFS>(parts_t, a.sc_t.L, w2.w);
   bool chain_ok = true;
   if (CHAIN) {
-    ms_d.ref = REFS == kAsChained && (w2.w & kChainWhole) ? whole_ref(ms_d.m) : ref_of(ms_d.m, a.sc_d.L);
-    chain_ok = chain_matches<REFS>(a, w0, w1, w2);
+    // (after plain statistics a target that alone is warped is summed over c(m) all the same)
+    ms_d.ref = w2.w & kChainWhole ? whole_ref(ms_d.m) : ref_of(ms_d.m, a.sc_d.L);
+    chain_ok = chain_matches(a, w0, w1, w2);
     if (!chain_ok) { ms_d.m = -INFINITY; ms_d.s = 0.0; }             // no sum: an unusable row
   } else {
     ms_d = draft_ms<REFS>(a, b, id);

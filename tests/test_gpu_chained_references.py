@@ -89,3 +89,35 @@ def test_equal_rows_of_tokens_past_the_last_vector_have_no_residual(V, dtype, n,
     z_t = z_t.to(torch.float32 if dtype == "f32" else torch.bfloat16).cuda()
     x = torch.zeros((B, 1), dtype=torch.int32, device="cuda")
     _assert_no_residual(z_t, z_t[:, :1].contiguous(), x, form)
+
+
+# the draft as it is, the target warped: the statistics' sum is over whole references, the target's over c(m)
+@pytest.mark.parametrize("cutoffs", [False, True])
+@pytest.mark.parametrize("V,dtype,B", [(4096, "bf16", 8), (32000, "bf16", 40), (30001, "f32", 8), (16391, "bf16", 270)])
+def test_a_warped_target_after_plain_statistics(V, dtype, B, cutoffs):
+    import svgen
+    P, k, T = H.sv(), 3, float(np.float32(0.7))
+    cfg = svgen.make_config(1, seed=V, B=B, k=k, V=V, dtype=dtype)
+    z_t, z_d, x = (cfg[n].cuda() for n in ("z_t", "z_d", "x"))
+    f32 = lambda *s: torch.empty(s, dtype=torch.float32, device="cuda")
+    i32 = lambda *s: torch.full(s, -5, dtype=torch.int32, device="cuda")
+    cut_t = None
+    if cutoffs:
+        cut_t = f32(B, k + 1)
+        P.sv_warp_cutoffs(z_t, T, 40, 1.0, cut_t)
+    ws = P.alloc_workspace(B, k, V, P.binding._dtype_tag(z_d))
+    out = []
+    for chained in (True, False):
+        o = dict(tokens=i32(B, k + 1), n=i32(B), flags=i32(B), ratio=f32(B, k))
+        if chained:
+            P.sv_row_stats(z_d, z_d, x, f32(B, k), f32(B, k), f32(B, k), f32(B, k), None, None, ws)
+        (P.sv_verify_sample_warped_chained if chained else P.sv_verify_sample_warped)(
+            z_t, None, z_d, x, None, T, cut_t, 1.0, None, 5, 2, o["tokens"], o["n"], o["flags"], o["ratio"], ws)
+        out.append({n: v.cpu().numpy() for n, v in o.items()})
+    a, b = out
+    assert not (a["flags"] & P.binding.FLAG_NO_CHAIN).any()
+    near = ((a["flags"] | b["flags"]) & (O.FLAG_NEAR_TIE | O.FLAG_NEAR_CDF_EDGE)) != 0
+    for n in ("tokens", "n"):
+        np.testing.assert_array_equal(a[n][~near], b[n][~near])
+    np.testing.assert_allclose(a["ratio"][~near], b["ratio"][~near], rtol=1e-5)
+    assert near.mean() <= 4e-6 * V + 0.1
