@@ -202,7 +202,7 @@ using Online = OnlineOf<float>;
 using OnlineWide = OnlineOf<double>;
 using OnlineEither = OnlineOf<double, true>;
 
-// A row's normaliser: exact maximum m and fp64 sum s relative to c(m).
+// A row's normaliser: exact maximum m and fp64 sum s relative to 2^ref.
 struct MS {
   float m;
   double s;
